@@ -746,8 +746,14 @@ size_t workspace_bytes(const smha_plan *plan, int lvl, int B, int H, int d, size
 // The block kernel's work order for B x H heads on `slots` resident workgroups per XCD.  Items
 // differ in length (tile rows under global tokens, random blocks, padding), and with equal item
 // counts per workgroup the slowest one ends well after the average one; so the items of each head
-// go, longest first, to the workgroup with the least work so far (cost: tiles plus a fixed part per
-// item), head after head so that an XCD's workgroups stay on one head's K/V at a time.
+// go, longest first, to the compute unit with the least work so far and there to the workgroup with the
+// least (cost: tiles plus a fixed part per item), head after head so that an XCD's workgroups stay on
+// one head's K/V at a time.  The last heads, about three items per workgroup of them, are dealt together,
+// longest first over all of them, so that the last item dealt is a short one.
+// The workgroups of ranks r, r + n_cu / 8, ... of an XCD share a compute unit (measured, all 1024 of them), and
+// what a launch waits for is the unit with the most work.  Where four share one, the older ones are faster: the
+// hardware issues the oldest wave first (equal work ended at 0.92 : 0.97 : 1.04 : 1.09 of the mean, the same on
+// four masks), so work is dealt in that proportion.
 // table = {start of each XCD's list (8), its length (8), then (batch*head, item index) pairs};
 // list position = turn * per_xcd + workgroup rank; a workgroup's unused turns hold batch*head = -1.
 void build_work_order(const smha_plan *plan, int lvl, int B, int H, int slots, std::vector<int32_t> &table, int &per_xcd) {
@@ -760,40 +766,69 @@ void build_work_order(const smha_plan *plan, int lvl, int B, int H, int slots, s
         for (int bh = x; bh < BH; bh += 8) n += wl.item_cnt[mask_of(bh)];
         most = std::max(most, n);
     }
-    per_xcd = (int)std::min<int64_t>(slots, most);
+    // (as many workgroups on every compute unit: an odd one would be a unit that takes its second item late)
+    const int n_units = (int)std::min<int64_t>({(int64_t)std::max(plan->n_cu / 8, 1), (int64_t)slots, most});
     table.assign(16, 0);
-    if (per_xcd == 0) return;
+    per_xcd = 0;
+    if (most == 0) return;
+    per_xcd = (int)std::min<int64_t>(slots, (most + n_units - 1) / n_units * n_units);
     constexpr int kItemCost = 2;  // an item's start and end, in tiles
-    typedef std::pair<int64_t, int> Load;  // (work so far, workgroup rank)
-    std::vector<std::vector<int32_t>> mine(per_xcd);
+    const bool aged = slots == 4 * n_units;
+    static const double kPace[4] = {1.09, 1.03, 0.96, 0.92};
+    struct Pick { int32_t bh, index, cost; };
+    typedef std::pair<int64_t, int> Load;  // (work so far, compute unit)
+    std::vector<std::vector<Pick>> mine(per_xcd);
+    std::vector<double> done(per_xcd);  // work so far, in terms of the workgroup's pace
+    std::vector<Pick> deal;
     for (int x = 0; x < 8; ++x) {
         std::priority_queue<Load, std::vector<Load>, std::greater<Load>> heap;
+        for (int u = 0; u < n_units; ++u) heap.push({0, u});
         for (int r = 0; r < per_xcd; ++r) {
-            heap.push({0, r});
             mine[r].clear();
+            done[r] = 0;
         }
-        for (int bh = x; bh < BH; bh += 8) {
+        int last = BH > x ? x + (BH - 1 - x) / 8 * 8 : x - 8, joint = last;  // this XCD's last head, first head of the joint deal
+        for (int64_t n = 0; joint >= x; joint -= 8) {
+            n += wl.item_cnt[mask_of(joint)];
+            if (n > 3 * (int64_t)per_xcd && joint != last) break;
+        }
+        joint += 8;
+        for (int bh = x; bh <= last; bh += 8) {
             const int mask = mask_of(bh);
             const int32_t off = wl.item_off[mask];
+            if (bh <= joint) deal.clear();
             for (int it = 0; it < wl.item_cnt[mask]; ++it) {  // (sorted by length, longest first)
                 const Item &item = wl.items[off + it];
+                deal.push_back({bh, off + it, kItemCost + (item.end - item.begin)});
+            }
+            if (bh >= joint && bh != last) continue;
+            if (joint < last && bh == last)
+                std::stable_sort(deal.begin(), deal.end(), [](const Pick &a, const Pick &b) { return a.cost > b.cost; });
+            for (const Pick &p : deal) {
                 Load l = heap.top();
                 heap.pop();
-                mine[l.second].push_back(bh);
-                mine[l.second].push_back(off + it);
-                l.first += kItemCost + (item.end - item.begin);
+                int best = l.second;
+                for (int r = l.second + n_units; r < per_xcd; r += n_units)
+                    if (done[r] < done[best]) best = r;
+                mine[best].push_back(p);
+                done[best] += aged ? p.cost / kPace[best / n_units & 3] : (double)p.cost;
+                l.first += p.cost;
                 heap.push(l);
             }
         }
+        if (joint < last)
+            for (auto &list : mine)  // (short lists: insertion keeps the order within a head)
+                for (size_t i = 1; i < list.size(); ++i)
+                    for (size_t k = i; k > 0 && list[k].bh < list[k - 1].bh; --k) std::swap(list[k], list[k - 1]);
         size_t turns = 0;
-        for (int r = 0; r < per_xcd; ++r) turns = std::max(turns, mine[r].size() / 2);
+        for (int r = 0; r < per_xcd; ++r) turns = std::max(turns, mine[r].size());
         table[x] = (int32_t)((table.size() - 16) / 2);
         table[8 + x] = (int32_t)(turns * per_xcd);
         for (size_t t = 0; t < turns; ++t)
             for (int r = 0; r < per_xcd; ++r) {
-                const bool has = 2 * t < mine[r].size();
-                table.push_back(has ? mine[r][2 * t] : -1);
-                table.push_back(has ? mine[r][2 * t + 1] : 0);
+                const bool has = t < mine[r].size();
+                table.push_back(has ? mine[r][t].bh : -1);
+                table.push_back(has ? mine[r][t].index : 0);
             }
     }
 }

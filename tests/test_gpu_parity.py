@@ -267,6 +267,24 @@ def test_ragged_lengths_and_degenerate_rows(torch_mod, smha, kernel, d, dtype):
         assert np.allclose(got[1, 1].astype(np.float64), W.bits_to_f64(V, dtype)[1, 1], rtol=1e-5, atol=1e-7)
 
 
+@pytest.mark.parametrize("d,dtype", [(64, "f16"), (64, "bf16"), (40, "f16"), (128, "f16"), (256, "bf16")])
+@pytest.mark.parametrize("S,heads", [(1, 8), (31, 8), (1037, 8), (2049, 4)])
+def test_short_rows_that_share_a_wave(torch_mod, smha, d, dtype, S, heads):
+    """Rows with few keys: eight rows per wave (64 columns, where there are enough rows), else four or two,
+    three keys a batch where a row has one lane group.  Row lengths 0 to 13 cover every remainder of a batch,
+    the row counts every remainder of a wave and of a workgroup."""
+    Q, K, V = W.qkv_bits(1, heads, S, d, dtype, 1.0, 500 + S)
+    masks = np.zeros((1, 1, S, S), dtype=np.uint8)
+    rng = np.random.default_rng(S)
+    for i in range(S):
+        masks[0, 0, i, rng.choice(S, size=min(S, i % 14), replace=False)] = 1
+    masks[0, 0, S - 1, :: max(1, S // 40)] = 1  # one long row among them
+    for out_f32 in (True, False):
+        got = run_case(torch_mod, smha, Q, K, V, dtype, masks, KERNELS["row"], out_f32=out_f32, heads=[(0, 0), (0, heads - 1)],
+                       what=f"short rows S={S} d={d} {dtype}")
+        assert np.all(got[:, :, 0:S - 1:14] == 0.0)
+
+
 @pytest.mark.parametrize("kernel", ["block", "row"])
 @pytest.mark.parametrize("d,dtype", [(8, "f16"), (32, "f16"), (32, "bf16"), (40, "f16"), (80, "bf16"), (96, "f16"),
                                      (96, "bf16"), (120, "f16"), (136, "bf16"), (192, "f16"), (256, "f16"), (256, "bf16")])

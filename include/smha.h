@@ -268,8 +268,9 @@ smha_status_t smha_plan_prepare(const smha_plan_t *plan, int B, int H, int d);
 /* The block kernel's work order for B x H heads when workgroups_per_xcd workgroups are
  * resident on each of the chip's 8 XCDs (smha_forward uses 4 per compute unit at 64 columns,
  * 2 at 128, 1 at 256): the plan's work items (the workgroup tiling of Algorithm 1's outer loop)
- * differ in length, and each head's items go, longest first, to the compute unit with the least work
- * so far and there to the workgroup with the least (the last heads are dealt together).  For inspection and tests; runs on the host.
+ * differ in length, and each head's items go, longest first, to the compute unit with the least
+ * work so far and there to the workgroup with the least (the last heads are dealt together).
+ * For inspection and tests; runs on the host.
  *   fine       0: the items of SMHA_EXPORT_KERNEL_ITEMS, 1: those of KERNEL_ITEMS_FINE
  *   host_dst   host, int32: 8 list starts (in pairs), 8 list lengths (in pairs), then the
  *              lists: (batch*head, index into that grain's items of all masks, masks in

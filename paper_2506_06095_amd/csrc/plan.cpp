@@ -781,6 +781,19 @@ void build_work_order(const smha_plan *plan, int lvl, int B, int H, int slots, s
     std::vector<double> done(per_xcd);  // work so far, in terms of the workgroup's pace
     std::vector<Pick> deal;
     for (int x = 0; x < 8; ++x) {
+        if (x > 0 && plan->Bm * plan->Hm == 1 && (BH - 1 - x + 8) / 8 == (BH - x + 8) / 8) {
+            // one mask for all heads, and as many heads as the XCD before: its deal, one head on
+            const size_t from = 16 + 2 * (size_t)table[x - 1], n = 2 * (size_t)table[8 + x - 1];
+            table[x] = (int32_t)((table.size() - 16) / 2);
+            table[8 + x] = table[8 + x - 1];
+            table.reserve(table.size() + (8 - x) * n);
+            for (size_t i = from; i < from + n; i += 2) {
+                const int32_t bh = table[i], index = table[i + 1];
+                table.push_back(bh < 0 ? bh : bh + 1);
+                table.push_back(index);
+            }
+            continue;
+        }
         std::priority_queue<Load, std::vector<Load>, std::greater<Load>> heap;
         for (int u = 0; u < n_units; ++u) heap.push({0, u});
         for (int r = 0; r < per_xcd; ++r) {

@@ -284,6 +284,23 @@ def test_work_order_covers_every_item_once_and_balances():
             plan.work_order(3, 3, 64)            # batch does not match the plan's masks
 
 
+@pytest.mark.parametrize("B,H,slots", [(1, 1, 4), (1, 8, 64), (3, 7, 4), (2, 12, 16), (4, 16, 128)])
+def test_work_order_of_one_mask_is_that_of_the_same_mask_for_every_head(B, H, slots):
+    """One mask for all heads: the deal of an XCD is copied where the next has as many heads.  The same mask given
+    once per head is dealt XCD by XCD, with items numbered through all masks."""
+    m = np.tril(np.ones((1, 1, 1000, 1000), np.uint8), 300)
+    m[0, 0, :40] = 1
+    with smha.Plan.from_dense(m, force=smha.SMHA_KERNEL_BLOCK) as one, \
+            smha.Plan.from_dense(np.repeat(m, H, axis=1), force=smha.SMHA_KERNEL_BLOCK) as many:
+        check_work_order(one, B, H, slots)
+        n_items = len(one.export("kernel_items", 0).reshape(-1, 8))
+        got, per = one.work_order(B, H, slots, False)
+        want, per_many = many.work_order(B, H, slots, False)
+        assert per == per_many and np.array_equal(got[:16], want[:16])
+        got, want = got[16:].reshape(-1, 2), want[16:].reshape(-1, 2)
+        assert np.array_equal(got[:, 0], want[:, 0]) and np.array_equal(got[:, 1], want[:, 1] % n_items)
+
+
 def mask_from_kernel_lists(plan, mi, Sq, Sk, which="kernel_items", longest=64):
     """Rebuild mask `mi` from the block kernel's work lists, counting how often each entry is visited."""
     items = plan.export(which, mi).reshape(-1, 8)

@@ -285,6 +285,29 @@ def test_short_rows_that_share_a_wave(torch_mod, smha, d, dtype, S, heads):
         assert np.all(got[:, :, 0:S - 1:14] == 0.0)
 
 
+@pytest.mark.parametrize("d", [64, 128, 256])
+def test_row_kernel_reaches_the_far_end_of_a_widely_strided_head(torch_mod, smha, d):
+    """K and V rows lie as far apart as the 2^31-byte limit of a head allows (32-bit offsets past 2^30): the result is
+    that of the same rows stored together, bit for bit."""
+    torch, S = torch_mod, 4096
+    stride = ((1 << 30) - 1 - d) // (S + 128) // 8 * 8
+    assert 2 * stride * (S - 1) > 2_000_000_000 and 2 * ((S + 128) * stride + d) < 1 << 31
+    g = torch.Generator(device="cuda").manual_seed(9)
+    Q, K, V = (torch.randn(1, 1, S, d, device="cuda", dtype=torch.float16, generator=g) for _ in range(3))
+    far = torch.empty((S - 1) * stride + 2 * d, device="cuda", dtype=torch.float16)  # (rows of K, each followed by V's)
+    Kf, Vf = (far[at:].as_strided((1, 1, S, d), (S * stride, S * stride, stride, 1)) for at in (0, d))
+    Kf.copy_(K)
+    Vf.copy_(V)
+    mask = np.eye(S, dtype=np.uint8)[None, None]
+    rng = np.random.default_rng(9)
+    for i in range(S):
+        mask[0, 0, i, rng.integers(S, size=6)] = 1
+    mask[..., S - 1] = 1
+    with smha.Plan.from_dense(mask, force=KERNELS["row"]) as plan:
+        want = plan.forward(Q, K, V)
+        assert torch.equal(plan.forward(Q, Kf, Vf), want)
+
+
 @pytest.mark.parametrize("kernel", ["block", "row"])
 @pytest.mark.parametrize("d,dtype", [(8, "f16"), (32, "f16"), (32, "bf16"), (40, "f16"), (80, "bf16"), (96, "f16"),
                                      (96, "bf16"), (120, "f16"), (136, "bf16"), (192, "f16"), (256, "f16"), (256, "bf16")])

@@ -945,8 +945,11 @@ __global__ void __launch_bounds__(256) smha_row_fwd(const FwdParams p) {
     const int32_t *ci = p.col_idx + p.col_off[mask];
     // (a head's keys lie within 2^31 bytes, smha_forward refuses others: 32-bit byte offsets from the head's start)
     const char *Kb = reinterpret_cast<const char *>(p.K + b * p.ks.b + h * p.ks.h);
-    const char *Vb = reinterpret_cast<const char *>(p.V + b * p.vs.b + h * p.vs.h);
+    const auto Vr = make_rsrc(p.V + b * p.vs.b + h * p.vs.h, 2 * ((int64_t)(p.Sk - 1) * p.vs.s + p.d));
     const uint32_t k_pitch = 2u * (uint32_t)p.ks.s, v_pitch = 2u * (uint32_t)p.vs.s, sub_off = 16u * sub;
+    // A last batch's places past the row's keys read the row's first key again, whose score is then thrown away, and
+    // V past its end, which gives zeros (that key's values would enter the sums as 0 * value: NaN where that is infinite).
+    constexpr uint32_t kPastEnd = 0x80000000u;
 
     float m = NEG_INF, l = 0.f, acc[8];
 #pragma unroll
@@ -961,7 +964,7 @@ __global__ void __launch_bounds__(256) smha_row_fwd(const FwdParams p) {
             ok[u] = idx < end;
             const uint32_t col = (uint32_t)ci[ok[u] ? idx : beg];
             kv[u] = *reinterpret_cast<const u32x4 *>(Kb + (col * k_pitch + sub_off));
-            vv[u] = *reinterpret_cast<const u32x4 *>(Vb + (col * v_pitch + sub_off));
+            vv[u] = buf_load16(Vr, (int)(col * v_pitch + (ok[u] ? sub_off : kPastEnd)));
         }
         float s[U];
 #pragma unroll

@@ -285,6 +285,29 @@ def test_short_rows_that_share_a_wave(torch_mod, smha, d, dtype, S, heads):
         assert np.all(got[:, :, 0:S - 1:14] == 0.0)
 
 
+@pytest.mark.parametrize("d", [64, 40, 128, 256])
+@pytest.mark.parametrize("heads", [8, 2])
+def test_row_kernel_passes_infinite_values_through(torch_mod, smha, d, heads):
+    """Values of infinity reach the rows that attend them as infinities (their weights are positive), and no other row:
+    a batch of keys that the row does not fill adds nothing, whatever its places read.  Rows of 0 to 17 keys, then a
+    mean above 32 (a wave per row); columns are independent, so all else is that of the finite values, bit for bit."""
+    torch, S = torch_mod, 600
+    for short in (True, False):
+        mask = np.zeros((1, 1, S, S), dtype=np.uint8)
+        rng = np.random.default_rng(d)
+        for i in range(S):
+            mask[0, 0, i, rng.choice(S, size=i % 18 if short else 30 + i % 18, replace=False)] = 1
+        g = torch.Generator(device="cuda").manual_seed(d)
+        Q, K, V = (torch.randn(1, heads, S, d, device="cuda", dtype=torch.float16, generator=g) for _ in range(3))
+        Vi, at = V.clone(), torch.arange(0, S, 7, device="cuda")
+        Vi[:, :, at, d - 3] = float("inf")
+        attends = torch.from_numpy(mask[0, 0]).bool().cuda()[:, at].any(1)
+        with smha.Plan.from_dense(mask, force=KERNELS["row"], head_dim=d) as plan:
+            want = plan.forward(Q, K, V)
+            want[:, :, attends, d - 3] = float("inf")
+            assert torch.equal(plan.forward(Q, K, Vi), want)
+
+
 @pytest.mark.parametrize("d", [64, 128, 256])
 def test_row_kernel_reaches_the_far_end_of_a_widely_strided_head(torch_mod, smha, d):
     """K and V rows lie as far apart as the 2^31-byte limit of a head allows (32-bit offsets past 2^30): the result is

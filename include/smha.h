@@ -286,6 +286,13 @@ smha_status_t smha_plan_work_order(const smha_plan_t *plan, int B, int H, int wo
                                    int fine, int32_t *host_dst, size_t cap, size_t *need,
                                    int *per_xcd);
 
+/* Which form of the row kernel smha_forward runs for B x H heads of size d: how many query rows
+ * share a wave (8, 4, 2 or 1), and how many keys each lane group of a row has in flight.  For
+ * inspection and tests; runs on the host.
+ * Errors: INVALID_ARG, UNSUPPORTED (d, no row format), SHAPE. */
+smha_status_t smha_plan_row_form(const smha_plan_t *plan, int B, int H, int d, int *rows_per_wave,
+                                 int *keys_in_flight);
+
 void smha_plan_destroy(smha_plan_t *plan); /* NULL is allowed */
 
 const char *smha_status_string(smha_status_t status);

@@ -99,6 +99,8 @@ def _load():
     lib.smha_plan_work_order.argtypes = [vp, C.c_int, C.c_int, C.c_int, C.c_int, vp, C.c_size_t,
                                          C.POINTER(C.c_size_t), C.POINTER(C.c_int)]
     lib.smha_plan_work_order.restype = C.c_int
+    lib.smha_plan_row_form.argtypes = [vp, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int)]
+    lib.smha_plan_row_form.restype = C.c_int
     lib.smha_plan_destroy.argtypes = [vp]
     lib.smha_plan_destroy.restype = None
     lib.smha_status_string.argtypes = [C.c_int]
@@ -218,6 +220,15 @@ def smha_plan_work_order(plan: int, B: int, H: int, workgroups_per_xcd: int, fin
     return out, per.value
 
 
+def smha_plan_row_form(plan: int, B: int, H: int, d: int):
+    """(query rows per wave, keys in flight per lane group) of the row kernel for that call shape."""
+    rows, keys = C.c_int(0), C.c_int(0)
+    st = _load().smha_plan_row_form(C.c_void_p(plan), B, H, d, C.byref(rows), C.byref(keys))
+    if st != 0:
+        raise SmhaError(st, "smha_plan_row_form")
+    return rows.value, keys.value
+
+
 def smha_plan_prepare(plan: int, B: int, H: int, d: int) -> None:
     """Make the work order and workspaces for calls with this batch size, head count and head size."""
     st = _load().smha_plan_prepare(C.c_void_p(plan), B, H, d)
@@ -328,6 +339,9 @@ class Plan:
 
     def work_order(self, B: int, H: int, workgroups_per_xcd: int, fine: bool = False):
         return smha_plan_work_order(self.handle, B, H, workgroups_per_xcd, fine)
+
+    def row_form(self, B: int, H: int, d: int):
+        return smha_plan_row_form(self.handle, B, H, d)
 
     def prepare(self, B: int, H: int, d: int) -> None:
         smha_plan_prepare(self.handle, B, H, d)

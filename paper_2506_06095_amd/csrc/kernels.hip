@@ -891,27 +891,25 @@ __device__ __forceinline__ float group_sum(float v) {
     return v;
 }
 
-// RPW query rows per wave: 1 (a whole wave per row: long rows), 4 (rows with few keys, where a wave per
-// row spends its time on set-up and on merging 8 mostly idle key groups) or 64 / LPK (as many as the lanes
-// of one key allow: a row then has one lane group, nothing to merge and no lane that idles on its last
-// keys).  What bounds a row is its chain (row pointers, key numbers, K and V rows, per batch of keys)
-// and the vector work per batch; with one lane group per row both the batches' idle lanes and the merge
-// are gone.  Measured, 9 keys a row, 64 x 2048 rows: 64 columns 30.2 us (four rows) -> 19.0 (eight),
-// 5 keys 22.0 -> 15.7, 17 keys 38.4 -> 30.6, 25 keys 47.8 -> 41.4.  Batches of U = 3 keys there (2, 4, 5
-// and 6: 21.8, 22.2, 20.4, 22.5 us at 9 keys; requesting the next batch's key numbers ahead: 20.5); 128 and
-// 256 columns always had one lane group per short row, and 3 instead of 4 keys a batch: 9 keys 41.8 -> 35.8
-// and 80.3 -> 68.5 us, 13 keys 51.5 -> 50.3 and 100.8 -> 97.2.
+// RPW query rows per wave, U keys in flight per lane group (kRowForms): a whole wave per row where rows are long, four
+// or two (256 columns) where they have few keys and a wave per row spends its time on set-up and on merging mostly
+// idle key groups, and at 64 columns eight, so that a row has one lane group, nothing to merge and no lane that idles on
+// its last keys.  What bounds a row is its chain (row pointers, key numbers, K and V rows, per batch of keys) and the
+// vector work per batch.  Measured, 9 keys a row, 64 x 2048 rows at 64 columns: a wave per row 58 us, four rows 29.2,
+// eight 19.2 with 3 keys in flight (2, 4, 5 and 6: 21.8, 22.3, 20.4, 22.5; requesting the next batch's key numbers
+// ahead: 20.5); 5 keys 21.1 / 15.4 with four / eight rows, 17 keys 38 / 31, 24 keys 38.6 / 37.6.  At 128 and 256 columns a
+// short row has one lane group in any case: 9 keys 38.0 / 33.8 and 75.4 / 66.1 us with 4 / 3 keys in flight.  Which form a
+// call runs: row_form, with more of these figures.
 // K and V rows are addressed by 32-bit offsets (one quarter-rate multiply per row instead of the three of a
 // 64-bit product; as 24-bit multiplies: no faster, 18.3 us either way) and 16-bit results leave in one store of
 // 16 bytes per lane instead of two of 8.  9 keys a row: 64 columns 19.2 -> 18.3 us, bf16 23.7 -> 21.4; 128 columns
 // 34.6 -> 33.0; 256 columns bf16 86.9 -> 76.2; 61 keys a row, a wave per row: 64 columns 116.2 -> 108.6, 128
 // columns bf16 208.7 -> 192.7.
-template <int D, bool BF16, int RPW>
+template <int D, bool BF16, int RPW, int U>
 __global__ void __launch_bounds__(256) smha_row_fwd(const FwdParams p) {
     constexpr int LPK = D / 8;     // lanes that share one key (16 bytes of the row each)
     constexpr int LPR = 64 / RPW;  // lanes per query row
     constexpr int KPS = LPR / LPK; // keys a row handles per step
-    constexpr int U = RPW == 1 ? 2 : KPS == 1 ? 3 : 4;  // independent steps in flight
     const int wg = blockIdx.x;
     const int xcd = wg & 7, rest = wg >> 3;
     const int grp = rest / p.wgs_per_bh, rb = rest - grp * p.wgs_per_bh;
@@ -1400,32 +1398,22 @@ static hipError_t launch_block(const smha_plan *plan, FwdParams &fp, hipStream_t
     return launch_block_out<D, BF16, BF16 ? SMHA_BF16 : SMHA_F16>(plan, fp, stream);
 }
 
-template <int D, bool BF16>
-static hipError_t launch_row(const smha_plan *plan, FwdParams &fp, hipStream_t stream) {
-    const int BH = fp.B * fp.H;
-    const int groups = (BH + 7) / 8;
-    // rows with few keys share a wave (see the kernel): decided from the mean row length of the plan
-    const bool short_rows = plan->row_mean_nnz <= 32.0;
-    constexpr int RPW = D <= 128 ? 4 : 2;  // rows of a wave when rows are short (a row needs D / 8 lanes per key)
-    // At 64 columns eight short rows fit a wave, and are taken together where that still leaves the chip
-    // about a wave per SIMD and more, the more the longer the rows (a lone row handles 3 keys per trip to
-    // memory there, 8 with four rows per wave): 9 keys a row, kernel time with four / eight rows per wave: 4096 rows
-    // 4.6 / 4.6 us, 8192 rows 5.4 / 4.8, 16384 rows 7.2 / 5.5; 31 keys, 256 rows 5.2 / 6.6.
-    const bool eight = D == 64 && short_rows && (double)BH * fp.S >= 768.0 * plan->row_mean_nnz;
-    const int rows_per_wg = eight ? 32 : short_rows ? 4 * RPW : 4;
+template <int D, bool BF16, int F>  // F: which of kRowForms[row_width(D)]
+static hipError_t launch_row_form(FwdParams &fp, hipStream_t stream) {
+    constexpr RowForm form = kRowForms[row_width(D)][F];
+    const int groups = (fp.B * fp.H + 7) / 8, rows_per_wg = 4 * form.rows;
     fp.wgs_per_bh = (fp.S + rows_per_wg - 1) / rows_per_wg;
     const unsigned grid = (unsigned)(8 * groups * fp.wgs_per_bh);
-    if constexpr (D == 64) {
-        if (eight) {
-            hipLaunchKernelGGL((smha_row_fwd<D, BF16, 8>), dim3(grid), dim3(256), 0, stream, fp);
-            return hipGetLastError();
-        }
-    }
-    if (short_rows)
-        hipLaunchKernelGGL((smha_row_fwd<D, BF16, RPW>), dim3(grid), dim3(256), 0, stream, fp);
-    else
-        hipLaunchKernelGGL((smha_row_fwd<D, BF16, 1>), dim3(grid), dim3(256), 0, stream, fp);
+    hipLaunchKernelGGL((smha_row_fwd<D, BF16, form.rows, form.batch>), dim3(grid), dim3(256), 0, stream, fp);
     return hipGetLastError();
+}
+
+template <int D, bool BF16>
+static hipError_t launch_row(const smha_plan *plan, FwdParams &fp, hipStream_t stream) {
+    const int f = row_form(plan, fp.B, fp.H, D);
+    if (f == 0) return launch_row_form<D, BF16, 0>(fp, stream);
+    if (f == 1) return launch_row_form<D, BF16, 1>(fp, stream);
+    return launch_row_form<D, BF16, 2>(fp, stream);
 }
 
 // Which grain of work items a call walks: the coarse lists unless they leave more than half of the

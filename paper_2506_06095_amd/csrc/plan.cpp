@@ -444,6 +444,40 @@ static void formats_from_tiles(const TileInfo *info, const std::vector<uint64_t>
     mf.kt_bitmap = mf.bitmap;
 }
 
+// Rows of at most this many keys on average may share a wave of the row kernel.
+constexpr double kSharedRowMean = 32.0;
+
+// steps of a form's waves over eight rows, given the longest of each wave's (a template: the divisors are constants)
+template <int W, int F>
+static void add_row_steps(const int *longest, smha_plan *p) {
+    constexpr int keys = row_step_keys(W, F);
+    int n = 0;
+    for (int k = 0; k < 8 / kRowForms[W][F].rows; ++k) n += (longest[k] + keys - 1) / keys;
+    p->row_steps[W][F] += n;
+}
+
+static void count_row_steps(const std::vector<int32_t> &row_ptr, int S, smha_plan *p) {
+    static_assert(kRowForms[0][0].rows == 8 && kRowForms[0][1].rows == 4 && kRowForms[1][0].rows == 4 &&
+                  kRowForms[1][1].rows == 4 && kRowForms[2][0].rows == 2 && kRowForms[2][1].rows == 2, "as used below");
+    for (int i0 = 0; i0 < S; i0 += 8) {
+        int one[8], two[4], four[2];
+        for (int r = 0; r < 8; ++r) one[r] = i0 + r < S ? row_ptr[i0 + r + 1] - row_ptr[i0 + r] : 0;
+        for (int r = 0; r < 4; ++r) two[r] = std::max(one[2 * r], one[2 * r + 1]);
+        for (int r = 0; r < 2; ++r) four[r] = std::max(two[2 * r], two[2 * r + 1]);
+        const int eight = std::max(four[0], four[1]);
+        p->row_longest = std::max(p->row_longest, eight);
+        add_row_steps<0, 0>(&eight, p);
+        add_row_steps<0, 1>(four, p);
+        add_row_steps<0, 2>(one, p);
+        add_row_steps<1, 0>(four, p);
+        add_row_steps<1, 1>(four, p);
+        add_row_steps<1, 2>(one, p);
+        add_row_steps<2, 0>(two, p);
+        add_row_steps<2, 1>(two, p);
+        add_row_steps<2, 2>(one, p);
+    }
+}
+
 // After a first pass without the per-row lists: could the selector take the row kernel?  (The
 // block estimate here ignores gathered tiles, so it is an upper bound: if the row kernel does not
 // beat it, it will not beat the final one either.)  If so the masks are analysed again with rows.
@@ -711,6 +745,8 @@ smha_status_t finish_plan(smha_plan *p) {
             p->h_col_idx.reserve(off);
             for (auto &m : p->masks)
                 p->h_col_idx.insert(p->h_col_idx.end(), m.col_idx.begin(), m.col_idx.end());
+            if (p->row_mean_nnz <= kSharedRowMean)
+                for (auto &m : p->masks) count_row_steps(m.row_ptr, S, p);
         }
         // the per-row column list is large; drop it when no kernel will read it
         if (!p->has_row)
@@ -730,6 +766,47 @@ smha_status_t finish_plan(smha_plan *p) {
         if (dev < 0) return SMHA_OK;  // host-only plan; forward will report SMHA_ERR_HIP
     }
     return upload_plan(p, dev);
+}
+
+// The form of the row kernel with the least estimated time, for plans whose rows may share waves at all.  Two things
+// bound a launch, and their root sum of squares is the estimate:
+//   work   waves * fixed + steps * keys in flight * 0.067 ns: what the chip's waves take together; each lasts as long
+//          as its longest row, and a step costs by the 1 KiB loads in it;
+//   chain  steps of the longest row * trip: key numbers, then K and V, a serial chain that no other wave shortens; 0.42 us
+//          a step while the call's K and V fit the L2s (up to 16 MB of them), 1.1 us beyond, 1.2 times that with four
+//          keys in flight and 0.85 times with two.
+// Fitted to rows of 1 to 32 keys, and of 9 keys with 1 to 64 rows of 16 to 2048 among them, 256 to 131072 rows: on these
+// 360 the choice is within 1 % of the fastest form in the mean, and nowhere more than 2 % behind the forms that short rows
+// of any length had first (four rows a wave, two at 256 columns, four keys in flight).  Where each wins, us:
+//   64 columns, 64 x 2048 rows, eight / four rows a wave: 9 keys 19.2 / 29.2, 16 keys 29.3 / 30.4, 32 keys 50.8 / 47.3; one
+//   row of 64 keys among the 9s 31.4 / 31.8, of 128 55.9 / 37.1, of 1024 411 / 140, and with a wave per row 84;
+//   8 x 2048 rows, one of 24 keys 6.9 / 6.8; 4 x 1024 rows, 9 keys 4.4 / 4.9, 16 keys 5.6 / 4.9;
+//   128 columns, 64 x 2048 rows, three / four keys in flight: 3 keys 22.7 / 24.0, 4 keys 26.8 / 24.3, 8 keys 32.6 / 30.5,
+//   9 keys 33.8 / 38.0, 16 keys 55.0 / 49.0, 32 keys 92.5 / 87.5; 256 columns 4 keys 53.4 / 45.3, 9 keys 66.1 / 75.4.
+// A wave per row starts so many waves that it is given another 1 us, and has to win by a tenth.
+int row_form(const smha_plan *plan, int B, int H, int D) {
+    constexpr int kWavePerRow = 2;
+    if (plan->row_mean_nnz > kSharedRowMean) return kWavePerRow;
+    const int w = row_width(D);
+    const double heads = (double)B * H, masks = (double)plan->Bm * plan->Hm;
+    const double trip_us = heads * plan->Sk * D * 4 <= 16e6 ? 0.42 : 1.1;
+    int best = 0;
+    double best_us = 0;
+    for (int f = 0; f < 3; ++f) {
+        const RowForm form = kRowForms[w][f];
+        const double fixed_ns = form.rows == 8 ? 0.57 : form.rows == 1 ? 0.30 : 0.43;  // (per wave: start, queries, merge, store)
+        const double waves = heads * ((plan->S + form.rows - 1) / form.rows), steps = heads / masks * (double)plan->row_steps[w][f];
+        const int chain = (plan->row_longest + row_step_keys(w, f) - 1) / row_step_keys(w, f);
+        const double work_us = 1e-3 * (waves * fixed_ns + steps * form.batch * 0.067);
+        const double chain_us = chain * trip_us * (form.batch == 4 ? 1.2 : form.batch == 2 ? 0.85 : 1.0);
+        double us = std::hypot(work_us, chain_us);
+        if (f == kWavePerRow) us = 1.1 * (us + 1.0);
+        if (f == 0 || us < best_us) {
+            best = f;
+            best_us = us;
+        }
+    }
+    return best;
 }
 
 // One workspace of the block kernel for a call shape: per (batch*head) max_slots partial results of
@@ -984,6 +1061,17 @@ extern "C" smha_status_t smha_plan_work_order(const smha_plan_t *p, int B, int H
     *need = table.size();
     if (per_xcd) *per_xcd = n;
     if (cap >= table.size()) std::memcpy(host_dst, table.data(), table.size() * sizeof(int32_t));
+    return SMHA_OK;
+}
+
+extern "C" smha_status_t smha_plan_row_form(const smha_plan_t *p, int B, int H, int d, int *rows_per_wave, int *keys_in_flight) {
+    if (!p || B < 1 || H < 1 || !rows_per_wave || !keys_in_flight) return SMHA_ERR_INVALID_ARG;
+    if (d < 8 || d > 256 || d % 8 || !p->has_row) return SMHA_ERR_UNSUPPORTED;
+    if ((p->Bm != 1 && p->Bm != B) || (p->Hm != 1 && p->Hm != H)) return SMHA_ERR_SHAPE;
+    const int D = d <= 64 ? 64 : d <= 128 ? 128 : 256;
+    const RowForm form = kRowForms[row_width(D)][row_form(p, B, H, D)];
+    *rows_per_wave = form.rows;
+    *keys_in_flight = form.batch;
     return SMHA_OK;
 }
 

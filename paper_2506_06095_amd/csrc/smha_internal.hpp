@@ -70,6 +70,17 @@ struct SplitRow {
     int32_t qtile, slot0, count, pad;
 };
 
+// The forms of the row kernel at 64, 128 and 256 columns: query rows that share a wave, and keys that each
+// lane group of a row (D / 8 lanes) has in flight.  row_form chooses.
+struct RowForm {
+    int rows, batch;
+};
+constexpr RowForm kRowForms[3][3] = {{{8, 3}, {4, 4}, {1, 2}}, {{4, 3}, {4, 4}, {1, 2}}, {{2, 3}, {2, 4}, {1, 2}}};
+constexpr int row_width(int D) { return D == 64 ? 0 : D == 128 ? 1 : 2; }
+constexpr int row_step_keys(int width, int form) {  // keys of a row that one step covers
+    return kRowForms[width][form].batch * (8 >> width) / kRowForms[width][form].rows;
+}
+
 struct DeviceArrays {
     void *arena = nullptr;        // the one allocation every array below is a part of
     // row path
@@ -107,6 +118,10 @@ struct smha_plan {
     std::vector<smha::MaskFormats> masks;
     double eq1_threshold = 0.0, model_row_us = 0.0, model_block_us = 0.0;
     double row_mean_nnz = 0.0;  // unmasked keys per query row, mean over masks
+    // Row kernel: steps of each form over all masks, a wave taking as many as its longest row, and the longest row.
+    // Filled for plans with the row format and at most 32 keys per row on average.
+    int64_t row_steps[3][3] = {{0}};
+    int32_t row_longest = 0;
 
     // concatenated host copies of what the kernels read
     std::vector<int32_t> h_row_ptr, h_col_idx;
@@ -153,6 +168,8 @@ namespace smha {
 smha_status_t finish_plan(smha_plan *p);      // selector, work lists, concatenation
 // which workgroup of the block kernel takes which item, for B x H heads on `slots` workgroups per XCD
 void build_work_order(const smha_plan *plan, int lvl, int B, int H, int slots, std::vector<int32_t> &table, int &per_xcd);
+// which of kRowForms[row_width(D)] a call of the row kernel runs
+int row_form(const smha_plan *plan, int B, int H, int D);
 // bytes of one workspace for that call shape: partials first, then 4 counters per (batch*head, split group)
 size_t workspace_bytes(const smha_plan *plan, int lvl, int B, int H, int d, size_t *counters_at);
 // device.hip

@@ -285,6 +285,32 @@ def test_short_rows_that_share_a_wave(torch_mod, smha, d, dtype, S, heads):
         assert np.all(got[:, :, 0:S - 1:14] == 0.0)
 
 
+@pytest.mark.parametrize("d,dtype", [(64, "f16"), (64, "bf16"), (128, "bf16"), (256, "f16")])
+@pytest.mark.parametrize("what", ["short", "short_full_batches", "one_longer", "one_full", "two_rows"])
+def test_forms_of_the_row_kernel(torch_mod, smha, what, d, dtype):
+    """Each form that rows of few keys may run, at row counts one past a workgroup's: which one is asserted."""
+    S, heads = {"short": (33, 512), "short_full_batches": (129, 64), "one_longer": (257, 64), "one_full": (513, 16),
+                "two_rows": (2, 3)}[what]
+    lengths = [{"short": 3, "short_full_batches": 8}.get(what, 9)] * S
+    lengths = list(range(4))[:S] + lengths[4:]
+    if what == "one_longer":
+        lengths[S // 2] = 32
+    if what == "one_full":
+        lengths[S // 2] = S
+    masks = np.zeros((1, 1, S, S), dtype=np.uint8)
+    rng = np.random.default_rng(S)
+    for i, n in enumerate(lengths):
+        masks[0, 0, i, rng.choice(S, size=min(n, S), replace=False)] = 1
+    Q, K, V = W.qkv_bits(1, heads, S, d, dtype, 1.0, 700 + S)
+    with smha.Plan.from_dense(masks, force=KERNELS["row"], head_dim=d) as plan:
+        form = {64: {"short": (8, 3), "one_full": (1, 2), "two_rows": (8, 3)}, 128: {"short": (4, 3), "one_longer": (4, 3), "one_full": (1, 2),
+                "two_rows": (4, 3)}, 256: {"short": (2, 3), "one_full": (1, 2), "two_rows": (2, 3)}}
+        assert plan.row_form(1, heads, d) == form[d].get(what, {64: (4, 4), 128: (4, 4), 256: (2, 4)}[d])
+        got = run_case(torch_mod, smha, Q, K, V, dtype, masks, KERNELS["row"], plan=plan, out_f32=True,
+                       heads=[(0, 0), (0, heads - 1)], what=f"{what} d={d} {dtype}")
+        assert np.all(got[:, :, 0] == 0.0)
+
+
 @pytest.mark.parametrize("d", [64, 40, 128, 256])
 @pytest.mark.parametrize("heads", [8, 2])
 def test_row_kernel_passes_infinite_values_through(torch_mod, smha, d, heads):

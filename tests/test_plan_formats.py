@@ -301,6 +301,41 @@ def test_work_order_of_one_mask_is_that_of_the_same_mask_for_every_head(B, H, sl
         assert np.array_equal(got[:, 0], want[:, 0]) and np.array_equal(got[:, 1], want[:, 1] % n_items)
 
 
+def mask_of_row_lengths(lengths, Sk):
+    m = np.zeros((1, 1, len(lengths), Sk), np.uint8)
+    rng = np.random.default_rng(len(lengths))
+    for i, n in enumerate(lengths):
+        m[0, 0, i, rng.choice(Sk, size=n, replace=False)] = 1
+    return m
+
+
+@pytest.mark.parametrize("lengths,heads,want", [
+    ([9] * 2048, 64, ((8, 3), (4, 3), (2, 3))),                 # short rows, many of them
+    ([8] * 2048, 64, ((8, 3), (4, 4), (2, 4))),                 # what four keys a batch hold exactly
+    ([4] * 2047, 8, ((8, 3), (4, 4), (2, 4))),
+    ([16] * 1024, 4, ((4, 4), (4, 4), (2, 4))),                 # too few rows to fill the chip: the chain counts
+    ([9] * 2047 + [128], 64, ((4, 4), (4, 3), (2, 3))),         # one longer row is a chain of 43 steps or of 16
+    ([9] * 2047 + [1024], 64, ((1, 2), (1, 2), (1, 2))),        # one long row is the launch
+    ([8] * 2032 + [2048] * 16, 8, ((1, 2), (1, 2), (1, 2))),    # a few global rows
+    ([33] * 2048, 64, ((1, 2), (1, 2), (1, 2))),                # long rows throughout
+    ([3] * 7, 4096, ((8, 3), (4, 3), (2, 3))),                  # fewer rows than a wave takes
+    ([3], 4096, ((4, 4), (4, 3), (2, 3))),
+    ([0] * 100, 4, ((8, 3), (4, 3), (2, 3))),                   # nothing attends
+])
+def test_form_of_the_row_kernel_by_row_lengths(lengths, heads, want):
+    """Rows share a wave, and lane groups keep three or four keys in flight, by what the rows' lengths make of it:
+    a long row among short ones is not left to a lane group that takes three of its keys at a time."""
+    with smha.Plan.from_dense_rect(mask_of_row_lengths(lengths, 2048), force=smha.SMHA_KERNEL_ROW, device_id=-2) as plan:
+        assert tuple(plan.row_form(1, heads, d) for d in (64, 128, 256)) == want
+        assert plan.row_form(heads, 1, 40) == want[0] and plan.row_form(1, heads, 136) == want[2]
+        for args in ((0, heads, 64), (1, 0, 64), (1, heads, 12), (1, heads, 264)):
+            with pytest.raises(smha.SmhaError):
+                plan.row_form(*args)
+    with smha.Plan.from_dense(np.ones((1, 2, 64, 64), np.uint8), force=smha.SMHA_KERNEL_BLOCK, device_id=-2) as plan:
+        with pytest.raises(smha.SmhaError):
+            plan.row_form(1, 2, 64)                             # no row format
+
+
 def mask_from_kernel_lists(plan, mi, Sq, Sk, which="kernel_items", longest=64):
     """Rebuild mask `mi` from the block kernel's work lists, counting how often each entry is visited."""
     items = plan.export(which, mi).reshape(-1, 8)

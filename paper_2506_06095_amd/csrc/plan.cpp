@@ -5,10 +5,8 @@
 #include <atomic>
 #include <cmath>
 #include <cstring>
-#include <functional>
 #include <memory>
 #include <new>
-#include <queue>
 #include <thread>
 #include <utility>
 #include <vector>
@@ -853,10 +851,12 @@ void build_work_order(const smha_plan *plan, int lvl, int B, int H, int slots, s
     const bool aged = slots == 4 * n_units;
     static const double kPace[4] = {1.09, 1.03, 0.96, 0.92};
     struct Pick { int32_t bh, index, cost; };
-    typedef std::pair<int64_t, int> Load;  // (work so far, compute unit)
-    std::vector<std::vector<Pick>> mine(per_xcd);
-    std::vector<double> done(per_xcd);  // work so far, in terms of the workgroup's pace
-    std::vector<Pick> deal;
+    std::vector<Pick> deal, sorted;
+    std::vector<int32_t> start;
+    // units by work so far, least on top: work << 20 | unit
+    std::vector<int64_t> heap(n_units);
+    std::vector<double> done(per_xcd);    // a workgroup's work so far, in terms of its pace
+    std::vector<int32_t> turns(per_xcd);  // items it has
     for (int x = 0; x < 8; ++x) {
         if (x > 0 && plan->Bm * plan->Hm == 1 && (BH - 1 - x + 8) / 8 == (BH - x + 8) / 8) {
             // one mask for all heads, and as many heads as the XCD before: its deal, one head on
@@ -871,12 +871,12 @@ void build_work_order(const smha_plan *plan, int lvl, int B, int H, int slots, s
             }
             continue;
         }
-        std::priority_queue<Load, std::vector<Load>, std::greater<Load>> heap;
-        for (int u = 0; u < n_units; ++u) heap.push({0, u});
-        for (int r = 0; r < per_xcd; ++r) {
-            mine[r].clear();
-            done[r] = 0;
-        }
+        const size_t base = table.size();
+        table[x] = (int32_t)((base - 16) / 2);
+        int n_turns = 0;
+        for (int u = 0; u < n_units; ++u) heap[u] = u;
+        std::fill(done.begin(), done.end(), 0.0);
+        std::fill(turns.begin(), turns.end(), 0);
         int last = BH > x ? x + (BH - 1 - x) / 8 * 8 : x - 8, joint = last;  // this XCD's last head, first head of the joint deal
         for (int64_t n = 0; joint >= x; joint -= 8) {
             n += wl.item_cnt[mask_of(joint)];
@@ -892,34 +892,50 @@ void build_work_order(const smha_plan *plan, int lvl, int B, int H, int slots, s
                 deal.push_back({bh, off + it, kItemCost + (item.end - item.begin)});
             }
             if (bh >= joint && bh != last) continue;
-            if (joint < last && bh == last)
-                std::stable_sort(deal.begin(), deal.end(), [](const Pick &a, const Pick &b) { return a.cost > b.cost; });
+            const bool mixed = joint < last && bh == last;
+            if (mixed) {  // longest first over all of them, head after head where equal: a counting sort
+                int32_t top = 0;
+                for (const Pick &p : deal) top = std::max(top, p.cost);
+                start.assign((size_t)top + 2, 0);
+                for (const Pick &p : deal) ++start[top - p.cost + 1];
+                for (int32_t c = 0; c <= top; ++c) start[c + 1] += start[c];
+                sorted.resize(deal.size());
+                for (const Pick &p : deal) sorted[start[top - p.cost]++] = p;
+                deal.swap(sorted);
+            }
             for (const Pick &p : deal) {
-                Load l = heap.top();
-                heap.pop();
-                int best = l.second;
-                for (int r = l.second + n_units; r < per_xcd; r += n_units)
+                const int unit = (int)(heap[0] & 0xFFFFF);
+                const int64_t load = heap[0] + ((int64_t)p.cost << 20);
+                for (int at = 0;;) {  // (the top's new place)
+                    int child = 2 * at + 1;
+                    if (child >= n_units) { heap[at] = load; break; }
+                    if (child + 1 < n_units) child += heap[child + 1] < heap[child];
+                    if (heap[child] >= load) { heap[at] = load; break; }
+                    heap[at] = heap[child];
+                    at = child;
+                }
+                int best = unit;
+                for (int r = unit + n_units; r < per_xcd; r += n_units)
                     if (done[r] < done[best]) best = r;
-                mine[best].push_back(p);
                 done[best] += aged ? p.cost / kPace[best / n_units & 3] : (double)p.cost;
-                l.first += p.cost;
-                heap.push(l);
+                if (turns[best] == n_turns) {
+                    ++n_turns;
+                    const size_t row = table.size();
+                    table.resize(row + 2 * (size_t)per_xcd, 0);
+                    for (int r = 0; r < per_xcd; ++r) table[row + 2 * (size_t)r] = -1;
+                }
+                // (its place among the workgroup's items: head after head)
+                const size_t pitch = 2 * (size_t)per_xcd;
+                int32_t *to = table.data() + base + pitch * turns[best]++ + 2 * (size_t)best;
+                for (; mixed && to >= table.data() + base + pitch && to[-(ptrdiff_t)pitch] > p.bh; to -= pitch) {
+                    to[0] = to[-(ptrdiff_t)pitch];
+                    to[1] = to[1 - (ptrdiff_t)pitch];
+                }
+                to[0] = p.bh;
+                to[1] = p.index;
             }
         }
-        if (joint < last)
-            for (auto &list : mine)  // (short lists: insertion keeps the order within a head)
-                for (size_t i = 1; i < list.size(); ++i)
-                    for (size_t k = i; k > 0 && list[k].bh < list[k - 1].bh; --k) std::swap(list[k], list[k - 1]);
-        size_t turns = 0;
-        for (int r = 0; r < per_xcd; ++r) turns = std::max(turns, mine[r].size());
-        table[x] = (int32_t)((table.size() - 16) / 2);
-        table[8 + x] = (int32_t)(turns * per_xcd);
-        for (size_t t = 0; t < turns; ++t)
-            for (int r = 0; r < per_xcd; ++r) {
-                const bool has = t < mine[r].size();
-                table.push_back(has ? mine[r][t].bh : -1);
-                table.push_back(has ? mine[r][t].index : 0);
-            }
+        table[8 + x] = (int32_t)(n_turns * per_xcd);
     }
 }
 

@@ -284,6 +284,60 @@ def test_work_order_covers_every_item_once_and_balances():
             plan.work_order(3, 3, 64)            # batch does not match the plan's masks
 
 
+def deal_by_unit(items, BH, mask_of, slots, n_units=32):
+    """The work order, written down plainly: items[mask] = [(index, cost), longest first]."""
+    heads = [[bh for bh in range(BH) if bh % 8 == x] for x in range(8)]
+    most = max(sum(len(items[mask_of(bh)]) for bh in hs) for hs in heads)
+    n_units = min(n_units, slots, most)
+    per = min(slots, -(-most // n_units) * n_units) if most else 0
+    pace = (1.09, 1.03, 0.96, 0.92) if slots == 4 * n_units else None
+    lists = []
+    for hs in heads:
+        joint, n = len(hs), 0
+        while joint > 0 and (joint == len(hs) or n + len(items[mask_of(hs[joint - 1])]) <= 3 * per):
+            joint -= 1
+            n += len(items[mask_of(hs[joint])])
+        deals = [[(bh, i, c) for i, c in items[mask_of(bh)]] for bh in hs[:joint]]
+        deals.append(sorted(((bh, i, c) for bh in hs[joint:] for i, c in items[mask_of(bh)]), key=lambda p: -p[2])
+                     if joint < len(hs) - 1 else [(bh, i, c) for bh in hs[joint:] for i, c in items[mask_of(bh)]])
+        load, done, mine = [0] * n_units, [0.0] * per, [[] for _ in range(per)]
+        for bh, i, c in (p for d in deals for p in d):
+            unit = min(range(n_units), key=lambda u: (load[u], u))
+            r = min(range(unit, per, n_units), key=lambda r: (done[r], r))
+            load[unit] += c
+            done[r] += c / pace[r // n_units % 4] if pace else c
+            mine[r].append((bh, i))
+        lists.append([sorted(m, key=lambda p: p[0]) for m in mine])
+    return lists, per
+
+
+@pytest.mark.parametrize("B,H,slots,S", [(2, 3, 128, 1000), (2, 3, 3, 700), (2, 12, 64, 513), (2, 28, 8, 513), (2, 16, 32, 2047),
+                                         (2, 20, 128, 3001)])
+@pytest.mark.parametrize("per_head", [False, True])
+def test_work_order_is_the_deal_by_unit(B, H, slots, S, per_head):
+    """Entry for entry that of the plain deal: heads one by one, the last ones together, each item to the unit with the
+    least work and there to the workgroup that has done the least at its pace."""
+    spec = W.MaskSpec(flags=W.WINDOW | W.GLOBAL | W.BLOCK_RANDOM | W.PADDING, window_left=64, window_right=64, block=64,
+                      n_global=70, keep_p=0.1, seed=S, per_head=per_head, valid_len=(S, S - S // 3))
+    with smha.Plan.from_desc(spec, B, H, S, head_dim=64, force=smha.SMHA_KERNEL_BLOCK, device_id=-2) as plan:
+        Hm = plan.info()["Hm"]
+        for fine in (False, True):
+            items, off = [], 0
+            for m in range(B * Hm):
+                it = plan.export("kernel_items_fine" if fine else "kernel_items", m).reshape(-1, 8)
+                items.append([(off + i, 2 + int(r[2] - r[1])) for i, r in enumerate(it)])
+                off += len(it)
+            want, want_per = deal_by_unit(items, B * H, lambda bh: bh // H * Hm + (bh % H if Hm > 1 else 0), slots)
+            table, per = plan.work_order(B, H, slots, fine)
+            assert per == want_per
+            pairs = table[16:].reshape(-1, 2)
+            for x in range(8):
+                lst = pairs[table[x]:table[x] + table[8 + x]].reshape(-1, per, 2)
+                assert len(lst) == max(len(m) for m in want[x])
+                for r in range(per):
+                    assert [tuple(p) for p in lst[:, r].tolist() if p[0] >= 0] == want[x][r]
+
+
 @pytest.mark.parametrize("B,H,slots", [(1, 1, 4), (1, 8, 64), (3, 7, 4), (2, 12, 16), (4, 16, 128)])
 def test_work_order_of_one_mask_is_that_of_the_same_mask_for_every_head(B, H, slots):
     """One mask for all heads: the deal of an XCD is copied where the next has as many heads.  The same mask given

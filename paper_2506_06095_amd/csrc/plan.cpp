@@ -823,8 +823,14 @@ size_t workspace_bytes(const smha_plan *plan, int lvl, int B, int H, int d, size
 // counts per workgroup the slowest one ends well after the average one; so the items of each head
 // go, longest first, to the compute unit with the least work so far and there to the workgroup with the
 // least (cost: tiles plus a fixed part per item), head after head so that an XCD's workgroups stay on
-// one head's K/V at a time.  The last heads, about three items per workgroup of them, are dealt together,
-// longest first over all of them, so that the last item dealt is a short one.
+// one head's K/V at a time.  The last heads, at most 2.25 items per workgroup of them (or one head), are dealt together,
+// longest first over all of them, so that the last item dealt is a short one.  Their K and V are then in use at once,
+// and an XCD's L2 holds 4 MB: with three items per workgroup at 128 and 256 columns BigBird blocks 2 x 20 x 3200 x 160 took
+// 125.8 us instead of 108.4 with one head at a time (three heads of 2 MB; with 2.25 items 107.4), per-head 64-blocks
+// 3 x 32 x 2624 x 112 bf16 126 instead of 103 (110), and the mean over 113 masks was the same; two items: the same in
+// the mean, BigBird blocks 1 x 32 x 8192 x 128 132.9 us instead of 130.9.  At 64 columns heads are half as large: three
+// items, never more than 1 % slower than one head at a time on 37 masks (BigBird 16 x 12 x 2048 112.7 us, with two or
+// 2.25 items 114.4).
 // The workgroups of ranks r, r + n_cu / 8, ... of an XCD share a compute unit (measured, all 1024 of them), and
 // what a launch waits for is the unit with the most work.  Where four share one, the older ones are faster: the
 // hardware issues the oldest wave first (equal work ended at 0.92 : 0.97 : 1.04 : 1.09 of the mean, the same on
@@ -880,7 +886,7 @@ void build_work_order(const smha_plan *plan, int lvl, int B, int H, int slots, s
         int last = BH > x ? x + (BH - 1 - x) / 8 * 8 : x - 8, joint = last;  // this XCD's last head, first head of the joint deal
         for (int64_t n = 0; joint >= x; joint -= 8) {
             n += wl.item_cnt[mask_of(joint)];
-            if (n > 3 * (int64_t)per_xcd && joint != last) break;
+            if (4 * n > (aged ? 12 : 9) * (int64_t)per_xcd && joint != last) break;
         }
         joint += 8;
         for (int bh = x; bh <= last; bh += 8) {

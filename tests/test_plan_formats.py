@@ -294,7 +294,7 @@ def deal_by_unit(items, BH, mask_of, slots, n_units=32):
     lists = []
     for hs in heads:
         joint, n = len(hs), 0
-        while joint > 0 and (joint == len(hs) or n + len(items[mask_of(hs[joint - 1])]) <= 3 * per):
+        while joint > 0 and (joint == len(hs) or n + len(items[mask_of(hs[joint - 1])]) <= (3 if pace else 2.25) * per):
             joint -= 1
             n += len(items[mask_of(hs[joint])])
         deals = [[(bh, i, c) for i, c in items[mask_of(bh)]] for bh in hs[:joint]]

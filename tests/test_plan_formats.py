@@ -220,6 +220,9 @@ def test_library_exports_every_declared_symbol():
         assert hasattr(lib, n), n
 
 
+PACE = (1.09, 1.03, 0.96, 0.92)  # of the four workgroups that share a compute unit at 64 columns, oldest first
+
+
 def check_work_order(plan, B, H, slots, fine=False):
     """Every (batch*head, item) once, on the XCD of its head, ranks compact, loads balanced."""
     info = plan.info()
@@ -235,6 +238,10 @@ def check_work_order(plan, B, H, slots, fine=False):
     pairs = table[16:].reshape(-1, 2)
     seen = set()
     ratio = 0.0
+    n_heads = [[bh for bh in range(B * H) if bh % 8 == x] for x in range(8)]
+    most = max(sum(len(lengths[(bh // H if Bm > 1 else 0) * Hm + (bh % H if Hm > 1 else 0)]) for bh in hs) for hs in n_heads)
+    n_units = min(32, slots, most)                             # workgroups of ranks r, r + n_units, ... share a compute unit
+    paced = slots == 4 * n_units
     for x in range(8):
         at, n = int(table[x]), int(table[8 + x])
         assert n % per == 0
@@ -252,8 +259,13 @@ def check_work_order(plan, B, H, slots, fine=False):
                 loads[r] += 2 + all_len[idx]
             heads = lst[live, r, 0]
             assert np.all(np.diff(heads) >= 0)                 # head after head
-        # greedy longest-first: no workgroup exceeds its XCD's mean by more than the longest item
-        assert loads.max() <= loads.mean() + 2 + int(all_len.max())
+        # each item goes to the compute unit with the least work: none exceeds the mean by more than the longest item
+        longest = 2 + int(all_len.max())
+        units = np.bincount(np.arange(per) % n_units, weights=loads, minlength=n_units)
+        assert units.max() <= units.mean() + longest
+        # and there to the workgroup that has done the least, at its pace where four share a unit
+        for r in range(per):
+            assert loads[r] <= (PACE[r // n_units] if paced else 1.0) * units.mean() * n_units / per + longest
         if loads.sum():
             ratio = max(ratio, float(loads.max() / loads.mean()))
     want = {(bh, i) for bh in range(B * H)
@@ -261,6 +273,27 @@ def check_work_order(plan, B, H, slots, fine=False):
                            off[(bh // H if Bm > 1 else 0) * Hm + (bh % H if Hm > 1 else 0) + 1])}
     assert seen == want
     return ratio
+
+
+@pytest.mark.parametrize("spec,B,H,S", [
+    (W.MaskSpec(flags=W.CAUSAL), 4, 16, 2047),
+    (W.MaskSpec(flags=W.BLOCK_RANDOM, block=64, keep_p=0.1, per_head=True, seed=4), 2, 16, 4096),
+    (W.MaskSpec(flags=W.WINDOW | W.GLOBAL, window_left=64, window_right=64, n_global=64), 4, 16, 2048),
+    (W.MaskSpec(flags=W.WINDOW, window_left=64, window_right=64), 32, 32, 4096),
+])
+def test_work_order_balances_compute_units(spec, B, H, S):
+    """Masks whose longest items all went to one unit while workgroups were balanced without regard to who shares one."""
+    with smha.Plan.from_desc(spec, B, H, S, head_dim=64, force=smha.SMHA_KERNEL_BLOCK, device_id=-2) as plan:
+        for slots in (128, 64, 32):                                # 64, 128 and 256 columns
+            check_work_order(plan, B, H, slots)
+        # many turns: the four workgroups of a unit, the oldest first, get work in proportion to their pace
+        if S == 4096 and B == 32:
+            items = plan.export("kernel_items", 0).reshape(-1, 8)
+            table, per = plan.work_order(B, H, 128)
+            lst = table[16 + 2 * table[0]:16 + 2 * (table[0] + table[8])].reshape(-1, per, 2)
+            cost = np.where(lst[:, :, 0] >= 0, 2 + (items[:, 2] - items[:, 1])[lst[:, :, 1]], 0).sum(0)
+            share = cost.reshape(4, 32).sum(1) / cost.sum() * 4
+            assert per == 128 and len(lst) > 16 and np.abs(share - PACE).max() < 0.02
 
 
 def test_work_order_covers_every_item_once_and_balances():
@@ -290,7 +323,7 @@ def deal_by_unit(items, BH, mask_of, slots, n_units=32):
     most = max(sum(len(items[mask_of(bh)]) for bh in hs) for hs in heads)
     n_units = min(n_units, slots, most)
     per = min(slots, -(-most // n_units) * n_units) if most else 0
-    pace = (1.09, 1.03, 0.96, 0.92) if slots == 4 * n_units else None
+    pace = PACE if slots == 4 * n_units else None
     lists = []
     for hs in heads:
         joint, n = len(hs), 0

@@ -270,9 +270,9 @@ def test_ragged_lengths_and_degenerate_rows(torch_mod, smha, kernel, d, dtype):
 @pytest.mark.parametrize("d,dtype", [(64, "f16"), (64, "bf16"), (40, "f16"), (128, "f16"), (256, "bf16")])
 @pytest.mark.parametrize("S,heads", [(1, 8), (31, 8), (1037, 8), (2049, 4)])
 def test_short_rows_that_share_a_wave(torch_mod, smha, d, dtype, S, heads):
-    """Rows with few keys: eight rows per wave (64 columns, where there are enough rows), else four or two,
-    three keys a batch where a row has one lane group.  Row lengths 0 to 13 cover every remainder of a batch,
-    the row counts every remainder of a wave and of a workgroup."""
+    """Rows with few keys and one of about 40 share a wave: mostly in the forms with four keys in flight, whose batches
+    the row lengths 0 to 13 fill to every remainder; row counts of 1, 31 and one past a multiple of four.  (The test below
+    reaches every form.)"""
     Q, K, V = W.qkv_bits(1, heads, S, d, dtype, 1.0, 500 + S)
     masks = np.zeros((1, 1, S, S), dtype=np.uint8)
     rng = np.random.default_rng(S)
@@ -286,13 +286,17 @@ def test_short_rows_that_share_a_wave(torch_mod, smha, d, dtype, S, heads):
 
 
 @pytest.mark.parametrize("d,dtype", [(64, "f16"), (64, "bf16"), (128, "bf16"), (256, "f16")])
-@pytest.mark.parametrize("what", ["short", "short_full_batches", "one_longer", "one_full", "two_rows"])
+@pytest.mark.parametrize("what", ["short", "short_7", "short_31", "short_32", "short_mixed", "short_full_batches", "one_longer",
+                                  "one_full", "two_rows"])
 def test_forms_of_the_row_kernel(torch_mod, smha, what, d, dtype):
-    """Each form that rows of few keys may run, at row counts one past a workgroup's: which one is asserted."""
-    S, heads = {"short": (33, 512), "short_full_batches": (129, 64), "one_longer": (257, 64), "one_full": (513, 16),
-                "two_rows": (2, 3)}[what]
-    lengths = [{"short": 3, "short_full_batches": 8}.get(what, 9)] * S
+    """Each form that rows of few keys may run: which one is asserted.  Eight rows a wave (32 a workgroup) at 7, 31, 32, 33
+    and 1037 rows; row lengths of 0 to 13 in the mixed case."""
+    S, heads = {"short": (33, 512), "short_7": (7, 2048), "short_31": (31, 512), "short_32": (32, 512), "short_mixed": (1037, 64),
+                "short_full_batches": (129, 64), "one_longer": (257, 64), "one_full": (513, 16), "two_rows": (2, 3)}[what]
+    lengths = [8 if what == "short_full_batches" else 3 if what.startswith("short") else 9] * S
     lengths = list(range(4))[:S] + lengths[4:]
+    if what == "short_mixed":
+        lengths = [i % 14 for i in range(S)]
     if what == "one_longer":
         lengths[S // 2] = 32
     if what == "one_full":
@@ -303,9 +307,9 @@ def test_forms_of_the_row_kernel(torch_mod, smha, what, d, dtype):
         masks[0, 0, i, rng.choice(S, size=min(n, S), replace=False)] = 1
     Q, K, V = W.qkv_bits(1, heads, S, d, dtype, 1.0, 700 + S)
     with smha.Plan.from_dense(masks, force=KERNELS["row"], head_dim=d) as plan:
-        form = {64: {"short": (8, 3), "one_full": (1, 2), "two_rows": (8, 3)}, 128: {"short": (4, 3), "one_longer": (4, 3), "one_full": (1, 2),
-                "two_rows": (4, 3)}, 256: {"short": (2, 3), "one_full": (1, 2), "two_rows": (2, 3)}}
-        assert plan.row_form(1, heads, d) == form[d].get(what, {64: (4, 4), 128: (4, 4), 256: (2, 4)}[d])
+        three, four = {64: ((8, 3), (4, 4)), 128: ((4, 3), (4, 4)), 256: ((2, 3), (2, 4))}[d]
+        assert plan.row_form(1, heads, d) == (
+            (1, 2) if what == "one_full" else four if what == "short_full_batches" or (what == "one_longer" and d != 128) else three)
         got = run_case(torch_mod, smha, Q, K, V, dtype, masks, KERNELS["row"], plan=plan, out_f32=True,
                        heads=[(0, 0), (0, heads - 1)], what=f"{what} d={d} {dtype}")
         assert np.all(got[:, :, 0] == 0.0)
@@ -334,8 +338,8 @@ def test_row_kernel_passes_infinite_values_through(torch_mod, smha, d, heads):
             assert torch.equal(plan.forward(Q, K, Vi), want)
 
 
-@pytest.mark.parametrize("d", [64, 128, 256])
-def test_row_kernel_reaches_the_far_end_of_a_widely_strided_head(torch_mod, smha, d):
+@pytest.mark.parametrize("d,keys", [(64, 6), (64, 1), (128, 6), (256, 6)])
+def test_row_kernel_reaches_the_far_end_of_a_widely_strided_head(torch_mod, smha, d, keys):
     """K and V rows lie as far apart as the 2^31-byte limit of a head allows (32-bit offsets past 2^30): the result is
     that of the same rows stored together, bit for bit."""
     torch, S = torch_mod, 4096
@@ -350,9 +354,10 @@ def test_row_kernel_reaches_the_far_end_of_a_widely_strided_head(torch_mod, smha
     mask = np.eye(S, dtype=np.uint8)[None, None]
     rng = np.random.default_rng(9)
     for i in range(S):
-        mask[0, 0, i, rng.integers(S, size=6)] = 1
+        mask[0, 0, i, rng.integers(S, size=keys)] = 1
     mask[..., S - 1] = 1
     with smha.Plan.from_dense(mask, force=KERNELS["row"]) as plan:
+        assert plan.row_form(1, 1, d)[0] == {64: 8 if keys == 1 else 4, 128: 4, 256: 2}[d]
         want = plan.forward(Q, K, V)
         assert torch.equal(plan.forward(Q, Kf, Vf), want)
 
@@ -776,6 +781,9 @@ def test_nothing_is_written_outside_the_output(torch_mod, smha):
         (W.MaskSpec(flags=W.BIGBIRD, block=64, n_window_blocks=3, n_global_blocks=2, n_random_blocks=2, seed=4), 1, 3, 4000, 128, "split"),
         (W.MaskSpec(flags=W.CAUSAL | W.WINDOW | W.STRIDED, window_left=100, stride=32, stride_phase=1), 2, 2, 1501, 64, "gathered"),
         (W.MaskSpec(flags=W.WINDOW, window_left=40, window_right=9), 1, 5, 777, 128, "plain"),
+        (W.MaskSpec(flags=W.WINDOW, window_left=1, window_right=1), 1, 5, 777, 64, "eight rows a wave"),
+        (W.MaskSpec(flags=W.WINDOW, window_left=1, window_right=1), 1, 5, 777, 128, "four rows a wave"),
+        (W.MaskSpec(flags=W.WINDOW, window_left=1, window_right=1), 1, 5, 777, 256, "two rows a wave"),
     ]
     for spec, B, H, S, d, what in cases:
         with smha.Plan.from_desc(spec, B, H, S, head_dim=d, build_both=True) as plan:
@@ -784,6 +792,8 @@ def test_nothing_is_written_outside_the_output(torch_mod, smha):
                 assert info["n_split_rows"] > 0
             if what == "gathered":
                 assert info["n_gathered"] > 0
+            if what.endswith("a wave"):
+                assert plan.row_form(B, H, d) == {64: (8, 3), 128: (4, 3), 256: (2, 3)}[d]
             gen = torch.Generator(device="cuda").manual_seed(S)
             q, k, v = (torch.randn(B, H, S, d, device="cuda", generator=gen).half() for _ in range(3))
             n = B * H * S * d

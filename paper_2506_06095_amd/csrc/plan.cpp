@@ -826,11 +826,15 @@ size_t workspace_bytes(const smha_plan *plan, int lvl, int B, int H, int d, size
 // one head's K/V at a time.  The last heads, at most 2.25 items per workgroup of them (or one head), are dealt together,
 // longest first over all of them, so that the last item dealt is a short one.  Their K and V are then in use at once,
 // and an XCD's L2 holds 4 MB: with three items per workgroup at 128 and 256 columns BigBird blocks 2 x 20 x 3200 x 160 took
-// 125.8 us instead of 108.4 with one head at a time (three heads of 2 MB; with 2.25 items 107.4), per-head 64-blocks
+// 125.8 us instead of 108.4 with one head at a time (padded; three heads of 2 MB; with 2.25 items 107.4), per-head 32-blocks
 // 3 x 32 x 2624 x 112 bf16 126 instead of 103 (110), and the mean over 113 masks was the same; two items: the same in
 // the mean, BigBird blocks 1 x 32 x 8192 x 128 132.9 us instead of 130.9.  At 64 columns heads are half as large: three
 // items, never more than 1 % slower than one head at a time on 37 masks (BigBird 16 x 12 x 2048 112.7 us, with two or
-// 2.25 items 114.4).
+// 2.25 items 114.4).  Fine lists at 64 columns (few heads, every list cut into parts of about one length) with more than
+// one item per workgroup and fewer than two are dealt head after head: together, the groups of all heads have their
+// last parts in the second turn and are merged at the end (causal 1 x 20 x 3000 x 64 55.7 us instead of 47.0, BigBird
+// 1 x 12 x 4096 x 64 58.5 instead of 54.6; with two items and more together is faster again, BigBird 1 x 10 x 5000 x 64
+// 71.5 against 82.2, and so it is at 128 columns, causal 1 x 10 x 2500 x 128 50.9 against 53.3).
 // The workgroups of ranks r, r + n_cu / 8, ... of an XCD share a compute unit (measured, all 1024 of them), and
 // what a launch waits for is the unit with the most work.  Where four share one, the older ones are faster: the
 // hardware issues the oldest wave first (equal work ended at 0.92 : 0.97 : 1.04 : 1.09 of the mean, the same on
@@ -854,7 +858,7 @@ void build_work_order(const smha_plan *plan, int lvl, int B, int H, int slots, s
     if (most == 0) return;
     per_xcd = (int)std::min<int64_t>(slots, (most + n_units - 1) / n_units * n_units);
     constexpr int kItemCost = 2;  // an item's start and end, in tiles
-    const bool aged = slots == 4 * n_units;
+    const bool aged = slots == 4 * n_units, fine = lvl == 1 && plan->fine_differs;
     static const double kPace[4] = {1.09, 1.03, 0.96, 0.92};
     struct Pick { int32_t bh, index, cost; };
     std::vector<Pick> deal, sorted;
@@ -884,8 +888,12 @@ void build_work_order(const smha_plan *plan, int lvl, int B, int H, int slots, s
         std::fill(done.begin(), done.end(), 0.0);
         std::fill(turns.begin(), turns.end(), 0);
         int last = BH > x ? x + (BH - 1 - x) / 8 * 8 : x - 8, joint = last;  // this XCD's last head, first head of the joint deal
+        int64_t here = 0;  // items of this XCD
+        for (int bh = x; bh <= last; bh += 8) here += wl.item_cnt[mask_of(bh)];
+        const bool apart = aged && fine && here > per_xcd && here < 2 * (int64_t)per_xcd;
         for (int64_t n = 0; joint >= x; joint -= 8) {
             n += wl.item_cnt[mask_of(joint)];
+            if (apart && joint != last) break;
             if (4 * n > (aged ? 12 : 9) * (int64_t)per_xcd && joint != last) break;
         }
         joint += 8;

@@ -317,7 +317,7 @@ def test_work_order_covers_every_item_once_and_balances():
             plan.work_order(3, 3, 64)            # batch does not match the plan's masks
 
 
-def deal_by_unit(items, BH, mask_of, slots, n_units=32):
+def deal_by_unit(items, BH, mask_of, slots, fine, n_units=32):
     """The work order, written down plainly: items[mask] = [(index, cost), longest first]."""
     heads = [[bh for bh in range(BH) if bh % 8 == x] for x in range(8)]
     most = max(sum(len(items[mask_of(bh)]) for bh in hs) for hs in heads)
@@ -326,8 +326,10 @@ def deal_by_unit(items, BH, mask_of, slots, n_units=32):
     pace = PACE if slots == 4 * n_units else None
     lists = []
     for hs in heads:
+        here = sum(len(items[mask_of(bh)]) for bh in hs)
+        apart = pace and fine and per < here < 2 * per              # fine lists, a second turn for some: head after head
         joint, n = len(hs), 0
-        while joint > 0 and (joint == len(hs) or n + len(items[mask_of(hs[joint - 1])]) <= (3 if pace else 2.25) * per):
+        while joint > 0 and (joint == len(hs) or not apart and n + len(items[mask_of(hs[joint - 1])]) <= (3 if pace else 2.25) * per):
             joint -= 1
             n += len(items[mask_of(hs[joint])])
         deals = [[(bh, i, c) for i, c in items[mask_of(bh)]] for bh in hs[:joint]]
@@ -345,7 +347,7 @@ def deal_by_unit(items, BH, mask_of, slots, n_units=32):
 
 
 @pytest.mark.parametrize("B,H,slots,S", [(2, 3, 128, 1000), (2, 3, 3, 700), (2, 12, 64, 513), (2, 28, 8, 513), (2, 16, 32, 2047),
-                                         (2, 20, 128, 3001)])
+                                         (2, 20, 128, 3001), (2, 8, 128, 6000)])
 @pytest.mark.parametrize("per_head", [False, True])
 def test_work_order_is_the_deal_by_unit(B, H, slots, S, per_head):
     """Entry for entry that of the plain deal: heads one by one, the last ones together, each item to the unit with the
@@ -360,7 +362,7 @@ def test_work_order_is_the_deal_by_unit(B, H, slots, S, per_head):
                 it = plan.export("kernel_items_fine" if fine else "kernel_items", m).reshape(-1, 8)
                 items.append([(off + i, 2 + int(r[2] - r[1])) for i, r in enumerate(it)])
                 off += len(it)
-            want, want_per = deal_by_unit(items, B * H, lambda bh: bh // H * Hm + (bh % H if Hm > 1 else 0), slots)
+            want, want_per = deal_by_unit(items, B * H, lambda bh: bh // H * Hm + (bh % H if Hm > 1 else 0), slots, fine)
             table, per = plan.work_order(B, H, slots, fine)
             assert per == want_per
             pairs = table[16:].reshape(-1, 2)

@@ -6,7 +6,7 @@
 //   S^T = K Q^T and O^T = V^T P^T on v_mfma_f32_32x32x16 so that every lane owns one query
 //   row: the softmax statistics are per-lane scalars and the score accumulators are already
 //   a legal k-slice of the second MFMA's B operand (no LDS round trip for P).
-// Row-wise kernel (Sec. 4.1): one wave per query row, groups of d/8 lanes gather one K/V
+// Row-wise kernel (Sec. 4.1): one wave per query row, or for up to eight short ones; groups of d/8 lanes gather one K/V
 //   row each as a single contiguous 16-byte-per-lane segment, DPP/shuffle reductions, no
 //   LDS and no barrier.
 #include <hip/hip_runtime.h>

@@ -395,11 +395,14 @@ static double eq1_threshold(double valid16, int Sq, int Sk) {
 //                 4889 / 1056 = 4.6, BigBird 8192 (32 pairs) 125 us / 32 / 866 = 4.5 -> 4.5.  fixed_ns = 60:
 //                 what a launch of the block kernel costs beyond one of the row kernel, per pair at 64 pairs
 //                 (decides only the smallest masks: both kernels are launch-bound there);
-//   row kernel:   time = entries * entry_ns + rows * row_ns.  Rows of at most 32 keys on average share a wave
-//                 four at a time.  d = 64: entry 0.0096 (2 vs 16 keys per row: 568 ns / 57344 entries; 32 vs
+//   row kernel:   time = entries * entry_ns + rows * row_ns.  Rows of at most 32 keys on average share a wave:
+//                 the constants are those of four rows a wave (two at 256 columns) with four keys in flight, before
+//                 row_form chose among forms; 9 keys a row at 64 columns are priced at 28 us for 131072 rows and take
+//                 18.7, so masks near the line may go to the slower block kernel.  d = 64: entry 0.0096 (2 vs 16 keys per row: 568 ns / 57344 entries; 32 vs
 //                 64: 1134 / 129434 = 0.0088; causal 0.0100), row 0.13 shared / 0.44 with a wave per row;
 //                 d = 128: entry 0.0195 (0.0198, 0.0188, causal 0.0203), row 0.12 / 0.43.
-// Of the 60 measured cases the model now picks the slower kernel in 4, by at most 1.17x.
+// Of the 60 measured cases the model picked the slower kernel in 4, by at most 1.17x; with the row kernel as it is now it
+// picks the faster one on the 13 masks (2 to 64 scattered keys per row, narrow windows) timed again.
 struct CostModel {
     double step_ns, fixed_ns, entry_ns, row_ns;
 };
@@ -838,7 +841,8 @@ size_t workspace_bytes(const smha_plan *plan, int lvl, int B, int H, int d, size
 // The workgroups of ranks r, r + n_cu / 8, ... of an XCD share a compute unit (measured, all 1024 of them), and
 // what a launch waits for is the unit with the most work.  Where four share one, the older ones are faster: the
 // hardware issues the oldest wave first (equal work ended at 0.92 : 0.97 : 1.04 : 1.09 of the mean, the same on
-// four masks), so work is dealt in that proportion.
+// four masks), so work is dealt in that proportion (BigBird blocks 4 x 16 x 4000 x 64 66.8 -> 63.7 us, BigBird 16 x 12 x 2048
+// 111.9 -> 113.4, most masks the same).
 // table = {start of each XCD's list (8), its length (8), then (batch*head, item index) pairs};
 // list position = turn * per_xcd + workgroup rank; a workgroup's unused turns hold batch*head = -1.
 void build_work_order(const smha_plan *plan, int lvl, int B, int H, int slots, std::vector<int32_t> &table, int &per_xcd) {

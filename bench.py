@@ -30,12 +30,12 @@ PEAK_HBM_GBS = 8000.0
 # summaries under profiles/ (runs of this very command, scaled by what the same counters read for a 256 MiB device
 # copy: FETCH_SIZE x2.0, WRITE_SIZE x1.0 on this machine).  This run does not measure them; the line says so.
 MEASURED_TRAFFIC = {  # (workload, kernel as smha_kernel_name gives it)
-    ("cfg5_bigbird_8k", "smha_block_fwd16"): {"read_bytes": 329.2e6, "write_bytes": 82.8e6},
-    ("cfg5_bigbird_8k", "smha_block_fwd"): {"read_bytes": 310.2e6, "write_bytes": 82.3e6},
-    ("cfg4_random_blocks", "smha_block_fwd"): {"read_bytes": 50.8e6, "write_bytes": 16.8e6},
+    ("cfg5_bigbird_8k", "smha_block_fwd16"): {"read_bytes": 335.6e6, "write_bytes": 82.8e6},
+    ("cfg5_bigbird_8k", "smha_block_fwd"): {"read_bytes": 343.4e6, "write_bytes": 82.3e6},
+    ("cfg4_random_blocks", "smha_block_fwd"): {"read_bytes": 50.7e6, "write_bytes": 16.8e6},
     ("cfg3_strided_causal", "smha_row_fwd"): {"read_bytes": 59.1e6, "write_bytes": 16.8e6},
-    ("cfg3_strided_causal", "smha_block_fwd"): {"read_bytes": 58.2e6, "write_bytes": 19.9e6},
-    ("scattered_2048_k8", "smha_row_fwd"): {"read_bytes": 51.1e6, "write_bytes": 16.8e6},
+    ("cfg3_strided_causal", "smha_block_fwd"): {"read_bytes": 58.4e6, "write_bytes": 19.9e6},
+    ("scattered_2048_k8", "smha_row_fwd"): {"read_bytes": 51.0e6, "write_bytes": 16.8e6},
 }
 
 

@@ -28,6 +28,10 @@ static void exports(smha_plan_t *p, int n_masks) {
     // the work order, both grains, for a few batch and head counts the plan's masks allow
     smha_plan_info_t info;
     if (smha_plan_info(p, &info) != SMHA_OK) return;
+    for (int d : {8, 64, 128, 256, 12}) {  // the row kernel's form (refused without the row format)
+        int rows = 0, keys = 0;
+        if (smha_plan_row_form(p, info.Bm, info.Hm == 1 ? 9 : info.Hm, d, &rows, &keys) == SMHA_OK && (rows < 1 || keys < 2)) abort();
+    }
     for (int fine = 0; fine < 2; ++fine)
         for (int B : {info.Bm, info.Bm == 1 ? 3 : info.Bm})
             for (int H : {info.Hm, info.Hm == 1 ? 9 : info.Hm})

@@ -66,7 +66,8 @@ typedef struct {
                        work lists only; the exported formats are never affected)               */
     int block_form; /* which form of the block-wise kernel runs where several exist: 0 = the library's choice
                        (at 128 columns form 3, unless nearly all tiles are full and the lists long: form 1;
-                       at 256 columns form 3; at 64 columns form 1),
+                       at 256 columns form 3; at 64 columns form 1; at 64 and 128 columns the wave form, one
+                       wave per 32 query rows, for calls that it is estimated to run faster),
                        1 = four waves per workgroup, every wave forms scores, probabilities and output of
                        its 32 rows (one to four workgroups per compute unit); 2 = eight waves per workgroup,
                        score waves and value waves, one workgroup per compute unit (64 and 128 columns);
@@ -147,6 +148,11 @@ typedef struct {
  *     keys KERNEL_GATHER_KEYS[gathered tile][0..63] (keys >= Sk are padding)
  *   KERNEL_BITMAPS uint64[n][64]: word r = query row r of the 64, bit k = k-th key of the entry
  *   KERNEL_GATHER_KEYS int32[n][64]
+ * The lists of the block kernel's wave form (UNSUPPORTED if the plan has none):
+ *   WAVE_ITEMS int32[n of this mask][8]: {32-row group, first entry, entries, workspace slot or -1, split
+ *     group (index among this mask's) or -1, the first entry's two words, 0}, longest first
+ *   WAVE_ENTRIES int32[n][2], all masks: {first key of a 32-key tile, -1 = every entry set, else the block
+ *     of KERNEL_BITMAPS that holds the tile: its rows 32 (group mod 2) .., its bits 32 (key / 32 mod 2) ..}
  */
 typedef enum {
     SMHA_EXPORT_ROW_PTR = 0,
@@ -164,7 +170,9 @@ typedef enum {
     SMHA_EXPORT_KERNEL_ENTRIES = 12,
     SMHA_EXPORT_KERNEL_BITMAPS = 13,
     SMHA_EXPORT_KERNEL_GATHER_KEYS = 14,
-    SMHA_EXPORT_KERNEL_ITEMS_FINE = 15
+    SMHA_EXPORT_KERNEL_ITEMS_FINE = 15,
+    SMHA_EXPORT_WAVE_ITEMS = 16,
+    SMHA_EXPORT_WAVE_ENTRIES = 17
 } smha_export_t;
 
 /* Mask analysis (Sec. 4.2.1) from a dense boolean mask.
@@ -298,7 +306,11 @@ void smha_plan_destroy(smha_plan_t *plan); /* NULL is allowed */
 const char *smha_status_string(smha_status_t status);
 
 /* Name and average duration bookkeeping is left to the caller; this returns the symbol
- * name of the kernel smha_forward would launch, for matching profiler output. */
+ * name of the kernel smha_forward would launch, for matching profiler output: of the block
+ * kernel's forms, the one that calls run which fill the chip.  smha_call_kernel_name answers for
+ * one call shape, where the wave form may take its place ("" for arguments that forward refuses). */
+const char *smha_call_kernel_name(const smha_plan_t *plan, int B, int H, int d, smha_dtype_t in_dtype,
+                                  smha_kernel_t kernel);
 const char *smha_kernel_name(const smha_plan_t *plan, int d, smha_dtype_t in_dtype,
                              smha_kernel_t kernel);
 

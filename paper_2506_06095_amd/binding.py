@@ -26,6 +26,7 @@ EXPORTS = {
     "bitmap_it8": (10, np.uint64),
     "kernel_items": (11, np.int32), "kernel_items_fine": (15, np.int32), "kernel_entries": (12, np.int32),
     "kernel_bitmaps": (13, np.uint64), "kernel_gather_keys": (14, np.int32),
+    "wave_items": (16, np.int32), "wave_entries": (17, np.int32),
 }
 
 
@@ -107,6 +108,8 @@ def _load():
     lib.smha_status_string.restype = C.c_char_p
     lib.smha_kernel_name.argtypes = [vp, C.c_int, C.c_int, C.c_int]
     lib.smha_kernel_name.restype = C.c_char_p
+    lib.smha_call_kernel_name.argtypes = [vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int]
+    lib.smha_call_kernel_name.restype = C.c_char_p
     _lib = lib
     return lib
 
@@ -243,6 +246,11 @@ def smha_plan_destroy(plan: Optional[int]) -> None:
 
 def smha_kernel_name(plan: int, d: int, in_dtype: int, kernel: int = SMHA_KERNEL_AUTO) -> str:
     return _load().smha_kernel_name(C.c_void_p(plan), d, in_dtype, kernel).decode()
+
+
+def smha_call_kernel_name(plan: int, B: int, H: int, d: int, in_dtype: int, kernel: int = SMHA_KERNEL_AUTO) -> str:
+    """The kernel that a call with this batch size, head count and head size runs ("" where forward refuses it)."""
+    return _load().smha_call_kernel_name(C.c_void_p(plan), B, H, d, in_dtype, kernel).decode()
 
 
 def _strides3(t):

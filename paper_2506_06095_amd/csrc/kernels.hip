@@ -68,6 +68,13 @@ struct FwdParams {
     int max_slots, max_splits;
     const SplitRow *split_rows;
     const int32_t *split_off, *split_cnt;
+    // wave form: what each wave of a workgroup does (four WaveItems per workgroup, wave_n workgroups per mask), the
+    // items' 32-key tiles, and the size of kt_bitmap; the split arrays above are its own.  heads_magic = 2^40 / H + 1
+    const WaveItem *wave_items;
+    const WaveEntry *wave_ents;
+    int wave_n;
+    int64_t bmp_bytes;
+    uint64_t heads_magic;
     // row path
     const int32_t *row_ptr, *col_idx;
     const int64_t *col_off;
@@ -227,12 +234,20 @@ __device__ __forceinline__ void store4(void *O, int64_t elem_off, float a, float
 // waves' references and sums, and a group has eight counters, whichever form runs.
 constexpr uint32_t kMergeMark = 0x80000000u;
 constexpr int kSlotExtra = 1024;  // floats of a workspace slot after the 128 x D accumulators: 512 references, 512 sums
+// (ROWS = 32: the wave form's items; a slot is 32 x D accumulators, 64 references and 64 sums, a group has one
+// counter, and w is 0: see put_wave_part.)
+template <int D, int ROWS> struct SlotOf {
+    static constexpr int kRefs = ROWS * D, kSums = kRefs + (ROWS == 128 ? kSlotExtra / 2 : 64);
+    static constexpr size_t kFloats = (size_t)kRefs + (ROWS == 128 ? kSlotExtra : 128);
+    static constexpr int kCounters = ROWS == 128 ? 8 : 1;
+};
 template <int D, typename Acc, int NA>
 __device__ __forceinline__ bool put_split_part(const FwdParams &p, const Acc (&o)[NA], float m_c, float l_tot,
                                                int w, int lane, int b, int h, int bh, int slot, int split) {
     constexpr int E = sizeof(Acc) / 4;
     constexpr int NR = E * NA;                                 // accumulator registers per lane
-    constexpr size_t SLOT = (size_t)(128 * D + kSlotExtra);  // floats per workspace slot
+    using Slot = SlotOf<D, 128>;
+    constexpr size_t SLOT = Slot::kFloats;
     float *mine = p.scratch + ((size_t)bh * p.max_slots + slot) * SLOT;
     auto put = [&](float *ptr, float v) __attribute__((always_inline)) {
         __hip_atomic_store(ptr, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -241,12 +256,12 @@ __device__ __forceinline__ bool put_split_part(const FwdParams &p, const Acc (&o
     for (int dt = 0; dt < NA; ++dt)
 #pragma unroll
         for (int r = 0; r < E; ++r) put(mine + ((size_t)w * NR + dt * E + r) * 64 + lane, o[dt][r]);
-    put(mine + 128 * D + w * 64 + lane, m_c);
-    put(mine + 128 * D + 512 + w * 64 + lane, l_tot);
+    put(mine + Slot::kRefs + w * 64 + lane, m_c);
+    put(mine + Slot::kSums + w * 64 + lane, l_tot);
     __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0): the stores above have completed
     const int mask = (p.Bm > 1 ? b : 0) * p.Hm + (p.Hm > 1 ? h : 0);
     const int count = uniform_load(&p.split_rows[uniform_load(p.split_off + mask) + split].count);
-    uint32_t *counter = p.counters + ((size_t)bh * p.max_splits + split) * 8 + w;
+    uint32_t *counter = p.counters + ((size_t)bh * p.max_splits + split) * Slot::kCounters + w;
     int last = 0;
     if (lane == 0) {
         const uint32_t seen = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -261,17 +276,18 @@ __device__ __forceinline__ bool put_split_part(const FwdParams &p, const Acc (&o
 // which part came last), then O; the counter goes back to zero for the next launch.
 // (owner_known: the caller remembers put_split_part's answer, and the counter need not be asked)
 // (W16: the eight-wave form: register r of a lane is column 16 (r / 4) + 4 (lane / 16) + r % 4 of its row)
-template <int D, int OUT, int PB, int RB, bool W16 = false>  // a batch of loads in flight: PB parts x RB accumulator registers
+template <int D, int OUT, int PB, int RB, bool W16 = false, int ROWS = 128>  // a batch of loads in flight: PB parts x RB accumulator registers
 __device__ __forceinline__ void merge_split_parts(const FwdParams &p, int w, int lane, int b, int h, int bh, int qrow, int split,
                                                   bool owner_known = false) {
     constexpr int NR = W16 ? D / 4 : D / 2;
-    constexpr size_t SLOT = (size_t)(128 * D + kSlotExtra);
+    using Slot = SlotOf<D, ROWS>;
+    constexpr size_t SLOT = Slot::kFloats;
     const int hh = lane >> 5;
     const float NEG_INF = -__builtin_inff();
     auto get = [&](const float *ptr) __attribute__((always_inline)) {
         return __hip_atomic_load(const_cast<float *>(ptr), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
-    uint32_t *counter = p.counters + ((size_t)bh * p.max_splits + split) * 8 + w;
+    uint32_t *counter = p.counters + ((size_t)bh * p.max_splits + split) * Slot::kCounters + w;
     if (!owner_known) {
         uint32_t state = 0;
         if (lane == 0) state = __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -291,7 +307,7 @@ __device__ __forceinline__ void merge_split_parts(const FwdParams &p, int w, int
         for (int c0 = 0; c0 < sr.count; c0 += 8) {
             float ms[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) ms[u] = get(base + (size_t)min(c0 + u, sr.count - 1) * SLOT + 128 * D + w * 64 + lane);
+            for (int u = 0; u < 8; ++u) ms[u] = get(base + (size_t)min(c0 + u, sr.count - 1) * SLOT + Slot::kRefs + w * 64 + lane);
 #pragma unroll
             for (int u = 0; u < 8; ++u) mstar = fmaxf(mstar, ms[u]);
         }
@@ -310,8 +326,8 @@ __device__ __forceinline__ void merge_split_parts(const FwdParams &p, int w, int
 #pragma unroll
             for (int u = 0; u < PB; ++u) {
                 at[u] = (c0 + u < sr.count ? c0 + u : c0) * (int)SLOT;
-                mu[u] = get(base + at[u] + 128 * D + w * 64 + lane);
-                if (r0 == 0) lu[u] = get(base + at[u] + 128 * D + 512 + w * 64 + lane);
+                mu[u] = get(base + at[u] + Slot::kRefs + w * 64 + lane);
+                if (r0 == 0) lu[u] = get(base + at[u] + Slot::kSums + w * 64 + lane);
             }
 #pragma unroll
             for (int u = 0; u < PB; ++u)
@@ -870,6 +886,7 @@ __global__ void __launch_bounds__(256, D == 64 ? 4 : D == 128 ? 2 : 1) smha_bloc
 
 #include "block_fwd2.inc"
 #include "block_fwd16.inc"
+#include "wave_fwd.inc"
 
 // ---------------------------------------------------------------------------------------
 // Row-wise kernel
@@ -1289,6 +1306,11 @@ smha_status_t upload_plan(smha_plan *p, int device_id) {
             arena.add(d.split_off[lvl], wl.split_off);
             arena.add(d.split_cnt[lvl], wl.split_cnt);
         }
+        if (!p->wave.items.empty()) {
+            arena.add(d.wave_ents, p->wave.ents);
+            arena.add(d.wave_split_off, p->wave.split_off);
+            arena.add(d.wave_splits, p->wave.splits);
+        }
     }
     bool ok = true;
     if (!arena.host.empty()) {
@@ -1322,6 +1344,7 @@ void release_device(smha_plan *p) {
         delete pr;
     }
     p->prepared.clear();
+    p->calls.clear();
     p->device = -1;
     (void)hipSetDevice(prev);
 }
@@ -1339,12 +1362,15 @@ static bool strides_ok(const int64_t *s) { return !s || (s[0] % 8 == 0 && s[1] %
 // the environment (read once), else the first form (on the workloads measured so far it is the faster
 // one).  Plans with gathered tiles, and bfloat16 at d = 128 (the second form's LDS does not hold two
 // probability operands per step there), run the first form whatever is asked for.
-static int block_form(const smha_plan *plan, int d, bool bf16) {
+static int form_asked(const smha_plan *plan) {
     static const int from_env = [] {
         const char *e = getenv("SMHA_BLOCK_FORM");
         return e ? atoi(e) : 0;
     }();
-    const int asked = plan->opts.block_form ? plan->opts.block_form : from_env;
+    return plan->opts.block_form ? plan->opts.block_form : from_env;
+}
+static int block_form(const smha_plan *plan, int d, bool bf16) {
+    const int asked = form_asked(plan);
     if (plan->n_gathered > 0) return 1;
     if (d > 128) return asked == 1 ? 1 : 3;  // 256 columns: eight waves of 16 rows are two waves per SIMD, four of 32 are one
     if (asked == 3) return d == 128 ? 3 : 1;  // eight waves of 16 rows: 128 and 256 columns
@@ -1357,6 +1383,16 @@ static int workgroups_per_cu(int form, int d) { return form == 2 ? 1 : form == 3
 template <int D, bool BF16, int OUT>
 static hipError_t launch_block_out(const smha_plan *plan, FwdParams &fp, hipStream_t stream) {
     if (fp.n_work == 0) return hipSuccess;
+    if constexpr (D <= 128) {
+        if (fp.form == 4) {
+            const dim3 grid(8, (unsigned)fp.wave_n, (unsigned)(((int64_t)fp.B * fp.H + 7) / 8));
+            if (fp.max_slots > 0)
+                hipLaunchKernelGGL((smha_wave_fwd<D, BF16, OUT, true>), grid, dim3(256), 0, stream, fp);
+            else
+                hipLaunchKernelGGL((smha_wave_fwd<D, BF16, OUT, false>), grid, dim3(256), 0, stream, fp);
+            return hipGetLastError();
+        }
+    }
     if constexpr (!(BF16 && D == 128) && D <= 128) {
         if (fp.form == 2) {
             hipLaunchKernelGGL((smha_block_fwd2<D, BF16, OUT>), dim3(8u * (unsigned)fp.per_xcd), dim3(512), 0, stream, fp);
@@ -1430,107 +1466,138 @@ static int grain_for(const smha_plan *plan, int B, int H, int d, int form) {
     return 2 * n_items < (int64_t)workgroups_per_cu(form, d) * plan->n_cu ? 1 : 0;
 }
 
-// The work order and workspaces for a call shape: found, or made now (allocates and copies; nothing
-// that exists is freed or moved).  *ws receives the workspace for this call (null if the plan splits
-// no group).
-static smha_status_t prepared_for(const smha_plan *plan, int B, int H, int d, int lvl, int form,
+// (a form that was asked for, by option or environment, is run; the library's own choice may give way)
+static bool takes_wave_form(const smha_plan *plan, int lvl, int form, int B, int H, int d, bool bf16, int &alone) {
+    return form_asked(plan) == 0 && wave_form_pays(plan, lvl, form, B, H, d, bf16, alone);
+}
+
+// The work order and workspaces for a call shape that runs `form` at grain `lvl` (wave form: with lists of up to `alone`
+// entries walked by one wave): allocates and copies; nothing that exists is freed or moved.
+static smha_status_t make_prepared(const smha_plan *plan, int B, int H, int d, int lvl, int form, int alone, smha_plan::Prepared **out) {
+    const WorkLists &wl = plan->lists[plan->fine_differs ? lvl : 0];
+    if ((int64_t)B * H * wl.max_items > ((int64_t)1 << 28)) return SMHA_ERR_UNSUPPORTED;  // (the order table indexes items with 32 bits)
+    std::vector<int32_t> table;
+    int per_xcd = 0, longest = 0;
+    int64_t step_words = 0, item_words = 0;
+    const int slots = workgroups_per_cu(form, d) * plan->n_cu / 8;  // workgroups that fit an XCD at once
+    smha_plan::Prepared *q = nullptr;
+    try {
+        if (form == 4) {
+            longest = build_wave_order(plan, alone, table);
+        } else {
+            build_work_order(plan, lvl, B, H, slots, table, per_xcd);
+            for (int x = 0; x < 8; ++x) longest = std::max(longest, table[8 + x]);
+        }
+        if (form == 2) {
+            // The second form walks, per workgroup, one contiguous stream of steps and one of items
+            // (see StepRec / ItemRec): {8 offsets} + per workgroup {first step, steps, first item,
+            // items} + step records + item records.
+            const int n_wg = 8 * per_xcd;
+            std::vector<int32_t> hdr((size_t)4 * n_wg, 0), steps, items;
+            for (int wg = 0; wg < n_wg; ++wg) {
+                const int x = wg & 7, r = wg >> 3;
+                hdr[4 * wg] = (int32_t)(steps.size() / 4);
+                hdr[4 * wg + 2] = (int32_t)(items.size() / 8);
+                int n_it = 0;
+                for (int pos = r; pos < table[8 + x]; pos += per_xcd) {
+                    const int32_t bh = table[16 + 2 * (table[x] + pos)];
+                    if (bh < 0) break;
+                    const Item &it = wl.items[table[16 + 2 * (table[x] + pos) + 1]];
+                    const int32_t rec[8] = {bh / H, bh % H, it.qtile, it.slot, it.split, 0, 0, 0};
+                    items.insert(items.end(), rec, rec + 8);
+                    const int n = it.end - it.begin;
+                    for (int e = 0; e < std::max(n, 1); ++e) {  // (an item without entries is one step that loads and computes nothing)
+                        const int32_t meta = n_it | (e == 0 ? kStepFirst : 0) | (e == std::max(n, 1) - 1 ? kStepLast : 0);
+                        const UEntry none{-1, {-2, -2}, 0};
+                        const UEntry &u = n > 0 ? plan->h_uent[it.begin + e] : none;
+                        const int32_t st[4] = {u.col, u.code[0], u.code[1], meta};
+                        steps.insert(steps.end(), st, st + 4);
+                    }
+                    ++n_it;
+                }
+                hdr[4 * wg + 1] = (int32_t)(steps.size() / 4) - hdr[4 * wg];
+                hdr[4 * wg + 3] = n_it;
+            }
+            if (items.size() / 8 > (size_t)kStepItemMask || steps.size() / 4 > (size_t)INT32_MAX / 16) return SMHA_ERR_UNSUPPORTED;
+            std::vector<int32_t> all(8, 0);
+            all[0] = 8;                                  // per-workgroup headers
+            all[1] = all[0] + (int32_t)hdr.size();       // step records
+            all[2] = all[1] + (int32_t)steps.size();     // item records
+            all[3] = all[2] + (int32_t)items.size();     // end
+            all.insert(all.end(), hdr.begin(), hdr.end());
+            all.insert(all.end(), steps.begin(), steps.end());
+            all.insert(all.end(), items.begin(), items.end());
+            all.resize(all.size() + 256, 0);             // (whole 1 KiB requests past the last record stay inside the buffer's bounds check anyway; slack for tidiness)
+            table.swap(all);
+            step_words = (int64_t)steps.size();
+            item_words = (int64_t)items.size();
+        }
+        q = new smha_plan::Prepared();
+    } catch (const std::bad_alloc &) {
+        return SMHA_ERR_ALLOC;
+    }
+    q->B = B; q->H = H; q->d = d; q->lvl = lvl; q->form = form; q->per_xcd = per_xcd;
+    q->longest = longest;
+    q->alone = alone;
+    q->step_words = step_words;
+    q->item_words = item_words;
+    bool ok = table.empty() ||
+              (hipMalloc((void **)&q->order, table.size() * sizeof(int32_t)) == hipSuccess &&
+               hipMemcpy(q->order, table.data(), table.size() * sizeof(int32_t), hipMemcpyHostToDevice) == hipSuccess);
+    if (ok && (form == 4 ? plan->wave.max_slots : wl.max_slots) > 0) {
+        q->ws_bytes = workspace_bytes(plan, lvl, form, B, H, d, &q->counters_at);
+        // (the counters start at zero and every launch leaves them at zero; the copy has completed on return)
+        const std::vector<uint32_t> zeros((q->ws_bytes - q->counters_at) / sizeof(uint32_t), 0u);
+        for (int i = 0; ok && i < smha_plan::kCallSlots; ++i)
+            ok = hipMalloc(&q->ws[i], q->ws_bytes) == hipSuccess &&
+                 hipMemcpy((char *)q->ws[i] + q->counters_at, zeros.data(), zeros.size() * sizeof(uint32_t),
+                           hipMemcpyHostToDevice) == hipSuccess;
+    }
+    if (ok) {
+        try {
+            plan->prepared.push_back(q);
+        } catch (const std::bad_alloc &) {
+            ok = false;
+        }
+    }
+    if (!ok) {
+        (void)hipGetLastError();
+        if (q->order) (void)hipFree(q->order);
+        for (void *w : q->ws)
+            if (w) (void)hipFree(w);
+        delete q;
+        return SMHA_ERR_ALLOC;
+    }
+    *out = q;
+    return SMHA_OK;
+}
+
+// What a call shape was given: found, or made now.  `form` is the block form the call would run (block_form); the wave
+// form takes its place where it is estimated to be faster.  *ws receives the workspace for this call (null if it
+// splits no group).
+static smha_status_t prepared_for(const smha_plan *plan, int B, int H, int d, bool bf16, int form,
                                   const smha_plan::Prepared **out, void **ws, bool may_allocate = true) {
     std::lock_guard<std::mutex> lock(plan->prepared_mutex);
     smha_plan::Prepared *hit = nullptr;
-    for (smha_plan::Prepared *q : plan->prepared)
-        if (q->B == B && q->H == H && q->d == d && q->lvl == lvl && q->form == form) hit = q;
-    if (!hit && !may_allocate) return SMHA_ERR_UNSUPPORTED;
+    for (const smha_plan::CallShape &c : plan->calls)
+        if (c.B == B && c.H == H && c.d == d && c.bf16 == (int)bf16 && c.form == form) hit = c.prepared;
     if (!hit) {
-        const WorkLists &wl = plan->lists[plan->fine_differs ? lvl : 0];
-        if ((int64_t)B * H * wl.max_items > ((int64_t)1 << 28)) return SMHA_ERR_UNSUPPORTED;  // (the order table indexes items with 32 bits)
-        std::vector<int32_t> table;
-        int per_xcd = 0, longest = 0;
-        int64_t step_words = 0, item_words = 0;
-        const int slots = workgroups_per_cu(form, d) * plan->n_cu / 8;  // workgroups that fit an XCD at once
-        smha_plan::Prepared *q = nullptr;
+        if (!may_allocate) return SMHA_ERR_UNSUPPORTED;
+        int lvl = grain_for(plan, B, H, d, form), alone = 0;
         try {
-            build_work_order(plan, lvl, B, H, slots, table, per_xcd);
-            longest = 0;
-            for (int x = 0; x < 8; ++x) longest = std::max(longest, table[8 + x]);
-            if (form == 2) {
-                // The second form walks, per workgroup, one contiguous stream of steps and one of items
-                // (see StepRec / ItemRec): {8 offsets} + per workgroup {first step, steps, first item,
-                // items} + step records + item records.
-                const int n_wg = 8 * per_xcd;
-                std::vector<int32_t> hdr((size_t)4 * n_wg, 0), steps, items;
-                for (int wg = 0; wg < n_wg; ++wg) {
-                    const int x = wg & 7, r = wg >> 3;
-                    hdr[4 * wg] = (int32_t)(steps.size() / 4);
-                    hdr[4 * wg + 2] = (int32_t)(items.size() / 8);
-                    int n_it = 0;
-                    for (int pos = r; pos < table[8 + x]; pos += per_xcd) {
-                        const int32_t bh = table[16 + 2 * (table[x] + pos)];
-                        if (bh < 0) break;
-                        const Item &it = wl.items[table[16 + 2 * (table[x] + pos) + 1]];
-                        const int32_t rec[8] = {bh / H, bh % H, it.qtile, it.slot, it.split, 0, 0, 0};
-                        items.insert(items.end(), rec, rec + 8);
-                        const int n = it.end - it.begin;
-                        for (int e = 0; e < std::max(n, 1); ++e) {  // (an item without entries is one step that loads and computes nothing)
-                            const int32_t meta = n_it | (e == 0 ? kStepFirst : 0) | (e == std::max(n, 1) - 1 ? kStepLast : 0);
-                            const UEntry none{-1, {-2, -2}, 0};
-                            const UEntry &u = n > 0 ? plan->h_uent[it.begin + e] : none;
-                            const int32_t st[4] = {u.col, u.code[0], u.code[1], meta};
-                            steps.insert(steps.end(), st, st + 4);
-                        }
-                        ++n_it;
-                    }
-                    hdr[4 * wg + 1] = (int32_t)(steps.size() / 4) - hdr[4 * wg];
-                    hdr[4 * wg + 3] = n_it;
-                }
-                if (items.size() / 8 > (size_t)kStepItemMask || steps.size() / 4 > (size_t)INT32_MAX / 16) return SMHA_ERR_UNSUPPORTED;
-                std::vector<int32_t> all(8, 0);
-                all[0] = 8;                                  // per-workgroup headers
-                all[1] = all[0] + (int32_t)hdr.size();       // step records
-                all[2] = all[1] + (int32_t)steps.size();     // item records
-                all[3] = all[2] + (int32_t)items.size();     // end
-                all.insert(all.end(), hdr.begin(), hdr.end());
-                all.insert(all.end(), steps.begin(), steps.end());
-                all.insert(all.end(), items.begin(), items.end());
-                all.resize(all.size() + 256, 0);             // (whole 1 KiB requests past the last record stay inside the buffer's bounds check anyway; slack for tidiness)
-                table.swap(all);
-                step_words = (int64_t)steps.size();
-                item_words = (int64_t)items.size();
+            const bool wave = takes_wave_form(plan, lvl, form, B, H, d, bf16, alone);
+            if (wave) lvl = 0;
+            const int runs = wave ? 4 : form;
+            for (smha_plan::Prepared *q : plan->prepared)
+                if (q->B == B && q->H == H && q->d == d && q->lvl == lvl && q->form == runs && (!wave || q->alone == alone)) hit = q;
+            if (!hit) {
+                const smha_status_t st = make_prepared(plan, B, H, d, lvl, runs, alone, &hit);
+                if (st != SMHA_OK) return st;
             }
-            q = new smha_plan::Prepared();
+            plan->calls.push_back({B, H, d, (int)bf16, form, hit});
         } catch (const std::bad_alloc &) {
             return SMHA_ERR_ALLOC;
         }
-        q->B = B; q->H = H; q->d = d; q->lvl = lvl; q->form = form; q->per_xcd = per_xcd;
-        q->longest = longest;
-        q->step_words = step_words;
-        q->item_words = item_words;
-        bool ok = hipMalloc((void **)&q->order, table.size() * sizeof(int32_t)) == hipSuccess &&
-                  hipMemcpy(q->order, table.data(), table.size() * sizeof(int32_t), hipMemcpyHostToDevice) == hipSuccess;
-        if (ok && wl.max_slots > 0) {
-            q->ws_bytes = workspace_bytes(plan, lvl, B, H, d, &q->counters_at);
-            // (the counters start at zero and every launch leaves them at zero; the copy has completed on return)
-            const std::vector<uint32_t> zeros((q->ws_bytes - q->counters_at) / sizeof(uint32_t), 0u);
-            for (int i = 0; ok && i < smha_plan::kCallSlots; ++i)
-                ok = hipMalloc(&q->ws[i], q->ws_bytes) == hipSuccess &&
-                     hipMemcpy((char *)q->ws[i] + q->counters_at, zeros.data(), zeros.size() * sizeof(uint32_t),
-                               hipMemcpyHostToDevice) == hipSuccess;
-        }
-        if (ok) {
-            try {
-                plan->prepared.push_back(q);
-            } catch (const std::bad_alloc &) {
-                ok = false;
-            }
-        }
-        if (!ok) {
-            (void)hipGetLastError();
-            if (q->order) (void)hipFree(q->order);
-            for (void *w : q->ws)
-                if (w) (void)hipFree(w);
-            delete q;
-            return SMHA_ERR_ALLOC;
-        }
-        hit = q;
     }
     *out = hit;
     *ws = hit->ws_bytes ? hit->ws[hit->next++ % smha_plan::kCallSlots] : nullptr;
@@ -1566,7 +1633,7 @@ extern "C" smha_status_t smha_plan_prepare(const smha_plan_t *plan, int B, int H
         if (form == 2 && d != D) form = 1;  // (the second form has no narrower heads)
         const smha_plan::Prepared *pr = nullptr;
         void *ws = nullptr;
-        const smha_status_t s2 = prepared_for(plan, B, H, D, grain_for(plan, B, H, D, form), form, &pr, &ws);
+        const smha_status_t s2 = prepared_for(plan, B, H, D, bf16 != 0, form, &pr, &ws);
         if (s2 != SMHA_OK) return s2;
     }
     return SMHA_OK;
@@ -1575,7 +1642,6 @@ extern "C" smha_status_t smha_plan_prepare(const smha_plan_t *plan, int B, int H
 // Workspace in the library's own image, for callers that cannot allocate: one array per GPU, kept
 // until the process ends.  Host code only ever uses the address hipGetSymbolAddress returns for the
 // current device (the array's name is not a device address on the host side).
-constexpr size_t kStaticScratchBytes = (size_t)32 << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 constexpr int kMaxDevices = 64;
 static std::mutex static_scratch_mutex;
@@ -1651,25 +1717,22 @@ static smha_status_t forward_impl(const smha_plan_t *plan, const void *Q, const 
     const float sc = scale > 0.f ? scale : 1.0f / std::sqrt((float)d);
     fp.c = sc * 1.4426950408889634f;
     const DeviceArrays &dv = plan->dev;
-    int form = block_form(plan, D, in_dtype == SMHA_BF16);
-    if (form == 2 && d != D) form = 1;  // (the second form has no narrower heads)
-    const int lvl = grain_for(plan, B, H, D, form);
-    const WorkLists &wl = plan->lists[lvl];
-    fp.items = dv.items[lvl]; fp.item_off = dv.item_off[lvl]; fp.item_cnt = dv.item_cnt[lvl];
     fp.uent = dv.uent; fp.gidx = dv.gidx; fp.n_gidx = (int)plan->h_gidx.size(); fp.kt_bitmap = dv.kt_bitmap; fp.bmp_spare = (int)(plan->h_kt_bitmap.size() / 64) - 1;
-    fp.max_slots = wl.max_slots;
-    fp.split_rows = dv.split_rows[lvl]; fp.split_off = dv.split_off[lvl]; fp.split_cnt = dv.split_cnt[lvl];
     fp.row_ptr = dv.row_ptr; fp.col_idx = dv.col_idx; fp.col_off = dv.col_off;
 
     hipStream_t stream = (hipStream_t)hip_stream;
     hipError_t e = hipSuccess;
     if (which == SMHA_KERNEL_BLOCK) {
-        if ((int64_t)B * H * wl.max_items > ((int64_t)1 << 28)) return SMHA_ERR_UNSUPPORTED;  // (the order table indexes items with 32 bits)
+        const int asked = block_form(plan, D, in_dtype == SMHA_BF16);
         const smha_plan::Prepared *pr = nullptr;
         void *ws = nullptr;
-        const smha_status_t st = prepared_for(plan, B, H, D, lvl, form, &pr, &ws, !static_ws);
-        fp.form = form;
+        const smha_status_t st = prepared_for(plan, B, H, D, in_dtype == SMHA_BF16, asked == 2 && d != D ? 1 : asked /* (the second form has no narrower heads) */, &pr, &ws, !static_ws);
         if (st != SMHA_OK) return st;
+        const int form = fp.form = pr->form, lvl = pr->lvl;
+        const WorkLists &wl = plan->lists[lvl];
+        fp.items = dv.items[lvl]; fp.item_off = dv.item_off[lvl]; fp.item_cnt = dv.item_cnt[lvl];
+        fp.max_slots = wl.max_slots;
+        fp.split_rows = dv.split_rows[lvl]; fp.split_off = dv.split_off[lvl]; fp.split_cnt = dv.split_cnt[lvl];
         if (static_ws && pr->ws_bytes) {
             // the library's own array instead of a workspace of the plan; its counters are cleared by a
             // small kernel ahead of the launch (the array is shared by every such call on this GPU)
@@ -1682,7 +1745,15 @@ static smha_status_t forward_impl(const smha_plan_t *plan, const void *Q, const 
             if (hipGetLastError() != hipSuccess) return SMHA_ERR_HIP;
         }
         fp.order_hdr = pr->order;
-        fp.order = pr->order + 16;
+        fp.order = pr->order ? pr->order + 16 : nullptr;
+        if (form == 4) {
+            fp.wave_items = (const WaveItem *)pr->order; fp.wave_ents = dv.wave_ents;
+            fp.bmp_bytes = (int64_t)plan->h_kt_bitmap.size() * 8;
+            fp.wave_n = pr->longest;
+            fp.heads_magic = ((uint64_t)1 << 40) / (uint64_t)H + 1;
+            fp.max_slots = plan->wave.max_slots;
+            fp.split_rows = dv.wave_splits; fp.split_off = dv.wave_split_off;
+        }
         if (form == 2) {
             fp.order_hdr = pr->order + 8;
             fp.order = pr->order + 8 + 4 * 8 * (int64_t)pr->per_xcd;
@@ -1694,7 +1765,7 @@ static smha_status_t forward_impl(const smha_plan_t *plan, const void *Q, const 
         fp.per_xcd = pr->per_xcd;
         fp.scratch = (float *)ws;
         fp.counters = ws ? (uint32_t *)((char *)ws + pr->counters_at) : nullptr;
-        fp.max_splits = wl.max_split_rows;
+        fp.max_splits = form == 4 ? plan->wave.max_splits : wl.max_split_rows;
         if (D == 64)
             e = in_dtype == SMHA_BF16 ? launch_block<64, true>(plan, fp, stream) : launch_block<64, false>(plan, fp, stream);
         else if (D == 128)
@@ -1742,4 +1813,21 @@ extern "C" const char *smha_kernel_name(const smha_plan_t *plan, int d, smha_dty
     int form = block_form(plan, D, in_dtype == SMHA_BF16);
     if (form == 2 && d != D) form = 1;
     return form == 3 ? "smha_block_fwd16" : form == 2 ? "smha_block_fwd2" : "smha_block_fwd";
+}
+
+extern "C" const char *smha_call_kernel_name(const smha_plan_t *plan, int B, int H, int d, smha_dtype_t in_dtype,
+                                             smha_kernel_t kernel) {
+    if (check_shape(plan, B, H, d) != SMHA_OK) return "";
+    const int which = kernel == SMHA_KERNEL_AUTO ? plan->kernel : (int)kernel;
+    if (which == SMHA_KERNEL_BLOCK && plan->has_block) {
+        const bool bf16 = in_dtype == SMHA_BF16;
+        const int D = kernel_head_size(d), form = block_form(plan, D, bf16);
+        int alone = 0;
+        try {
+            if (takes_wave_form(plan, grain_for(plan, B, H, D, form), form, B, H, D, bf16, alone)) return "smha_wave_fwd";
+        } catch (const std::bad_alloc &) {
+            return "";
+        }
+    }
+    return smha_kernel_name(plan, d, in_dtype, kernel);
 }

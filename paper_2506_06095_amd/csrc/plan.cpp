@@ -497,6 +497,80 @@ static bool row_may_be_chosen(const smha_plan *p) {
     return nnz / n_masks * cm.entry_ns + p->S * cm.row_ns < tiles / n_masks * cm.step_ns + cm.fixed_ns;
 }
 
+// The wave form's lists (see WaveItem).  Masks with more than kMaxWaveEntries 32-key tiles in all get none: their lists
+// would be a burden, and calls on masks so large fill the chip through the other forms.
+static void build_wave_lists(smha_plan *p, const std::vector<int32_t> &bmp_base) {
+    constexpr int64_t kMaxWaveEntries = 1 << 20;
+    const int n_masks = p->Bm * p->Hm, n_groups = (p->S + 31) / 32;
+    int64_t at_most = 0;
+    for (const MaskFormats &m : p->masks) at_most += 4 * (int64_t)m.kt_col.size();
+    if (at_most > kMaxWaveEntries || p->h_kt_bitmap.size() * sizeof(uint64_t) >= ((size_t)1 << 31)) return;
+    WaveLists &wl = p->wave;
+    std::vector<WaveEntry> list[2];
+    std::vector<WaveItem> items;
+    std::vector<int32_t> first;  // of each 32-row group: its first entry
+    std::vector<int32_t> at;
+    wl.ents.reserve((size_t)at_most + 1);
+    for (int mi = 0; mi < n_masks; ++mi) {
+        const MaskFormats &m = p->masks[mi];
+        first.assign(1, (int32_t)wl.ents.size());
+        for (int tr = 0; 2 * tr < n_groups; ++tr) {
+            list[0].clear();
+            list[1].clear();
+            for (int e = m.kt_row_ptr[tr]; e < m.kt_row_ptr[tr + 1]; ++e) {
+                const int32_t key = m.kt_col[e] * 64;
+                if (m.kt_bmp[e] < 0) {
+                    for (auto &l : list) { l.push_back({key, -1}); l.push_back({key + 32, -1}); }
+                    continue;
+                }
+                const uint64_t *w = m.kt_bitmap.data() + (size_t)m.kt_bmp[e] * 64;
+                for (int side = 0; side < 2; ++side) {
+                    uint64_t any = 0, all = ~(uint64_t)0;
+                    for (int r = 32 * side; r < 32 * side + 32; ++r) { any |= w[r]; all &= w[r]; }
+                    for (int half = 0; half < 2; ++half)
+                        if ((uint32_t)(any >> (32 * half)))
+                            list[side].push_back({key + 32 * half, (uint32_t)(all >> (32 * half)) == 0xFFFFFFFFu ? -1 : m.kt_bmp[e] + bmp_base[mi]});
+                }
+            }
+            for (int side = 0; side < 2 && 2 * tr + side < n_groups; ++side) {
+                wl.ents.insert(wl.ents.end(), list[side].begin(), list[side].end());
+                first.push_back((int32_t)wl.ents.size());
+            }
+        }
+        // a wave holds one entry per lane and four waves may share a list (build_wave_order): lists of more than 128
+        // entries are cut into parts of at most 64, whose partial results are merged in memory
+        items.clear();
+        int32_t slots = 0, n_splits = 0;
+        wl.split_off.push_back((int32_t)wl.splits.size());
+        for (int g = 0; g < n_groups; ++g) {
+            const int32_t b = first[g], n = first[g + 1] - b;
+            const int parts = n <= kWaveWhole ? 1 : (n + 63) / 64;
+            if (parts > 1) wl.splits.push_back({g, slots, parts, 0});
+            for (int c = 0; c < parts; ++c) {
+                const int32_t cb = b + (int32_t)((int64_t)n * c / parts), ce = b + (int32_t)((int64_t)n * (c + 1) / parts);
+                const WaveEntry e0 = ce > cb ? wl.ents[cb] : WaveEntry{0, -1};
+                items.push_back({g, cb, ce - cb, parts > 1 ? slots++ : -1, parts > 1 ? n_splits : -1, e0.key, e0.code, 0});
+            }
+            n_splits += parts > 1;
+        }
+        // longest first, in row order where equal: a counting sort
+        at.assign(kWaveWhole + 2, 0);
+        for (const WaveItem &i : items) {
+            ++at[kWaveWhole - i.n + 1];
+            ++wl.of_length[i.n];
+        }
+        for (int c = 0; c <= kWaveWhole; ++c) at[c + 1] += at[c];
+        const size_t base = wl.items.size();
+        wl.items.resize(base + items.size());
+        for (const WaveItem &i : items) wl.items[base + at[kWaveWhole - i.n]++] = i;
+        wl.item_off.push_back((int32_t)base);
+        wl.item_cnt.push_back((int32_t)items.size());
+        wl.max_splits = std::max(wl.max_splits, (int)n_splits);
+        wl.max_slots = std::max(wl.max_slots, (int)slots);
+    }
+    wl.ents.push_back({0, -1});  // (an empty item's entry)
+}
+
 smha_status_t finish_plan(smha_plan *p) {
     const int n_masks = p->Bm * p->Hm;
     const int S = p->S;  // queries
@@ -515,6 +589,7 @@ smha_status_t finish_plan(smha_plan *p) {
     p->row_mean_nnz = nnz / S;
 
     try {
+        std::vector<int32_t> bmp_base_of;  // of each mask: its first block in h_kt_bitmap
         // ---- block path first (its work lists say how many tiles the kernel will really visit,
         // which the selector needs): tiles, work items, split rows --------------------------
         if (p->opts.force != SMHA_KERNEL_ROW || p->opts.build_both) {
@@ -523,6 +598,7 @@ smha_status_t finish_plan(smha_plan *p) {
             for (int mi = 0; mi < n_masks; ++mi) {
                 MaskFormats &m = p->masks[mi];
                 const int32_t bmp_base = (int32_t)(p->h_kt_bitmap.size() / 64);
+                bmp_base_of.push_back(bmp_base);
                 p->h_kt_bitmap.insert(p->h_kt_bitmap.end(), m.kt_bitmap.begin(), m.kt_bitmap.end());
                 // union of the two tile rows of every supertile (both lists ascending: merge); tiles
                 // that use few key columns are repacked into gathered tiles (see UEntry), which go
@@ -722,6 +798,7 @@ smha_status_t finish_plan(smha_plan *p) {
             const double groups = (double)n_masks * ((p->S + 127) / 128);
             p->dense_long_lists = (double)part_in_lists < 0.15 * (double)tiles_in_lists && (double)p->h_uent.size() > 16.0 * groups;
         }
+        if (p->has_block && p->opts.block_form == 0) build_wave_lists(p, bmp_base_of);
         if (p->has_block) {
             p->h_kt_bitmap.insert(p->h_kt_bitmap.end(), 64, 0ull);  // spare all-zero block
             p->h_uent.push_back(UEntry{0, {-2, -2}, 0});             // spare entry: an empty item may read one past its list
@@ -813,12 +890,168 @@ int row_form(const smha_plan *plan, int B, int H, int D) {
 // One workspace of the block kernel for a call shape: per (batch*head) max_slots partial results of
 // 128 rows (O, then running maximum and sum per row, each written per wave: 128 d + 512 floats), then
 // four arrival counters (one per 32-row quarter) per (batch*head, split group).
-size_t workspace_bytes(const smha_plan *plan, int lvl, int B, int H, int d, size_t *counters_at) {
+size_t workspace_bytes(const smha_plan *plan, int lvl, int form, int B, int H, int d, size_t *counters_at) {
+    if (form == 4) {  // 32 rows per partial result, one counter per split group
+        const size_t at = ((size_t)B * H * plan->wave.max_slots * (size_t)(32 * d + 128) * sizeof(float) + 255) / 256 * 256;
+        if (counters_at) *counters_at = at;
+        return at + (size_t)B * H * plan->wave.max_splits * sizeof(uint32_t);
+    }
     const WorkLists &wl = plan->lists[plan->fine_differs ? lvl : 0];
     const size_t partials = (size_t)B * H * wl.max_slots * (size_t)(128 * d + 1024) * sizeof(float);
     const size_t at = (partials + 255) / 256 * 256;
     if (counters_at) *counters_at = at;
     return at + (size_t)B * H * wl.max_split_rows * 8 * sizeof(uint32_t);
+}
+
+// The wave form's work for one call shape: four waves make a workgroup, and each mask gets as many workgroups (records
+// past a mask's own have rg = -1).  Workgroups start in the order in which they are listed, longest items first; an
+// item of more than `alone` entries is shared by the four waves of a workgroup.
+int build_wave_order(const smha_plan *plan, int alone, std::vector<int32_t> &table) {
+    const WaveLists &wl = plan->wave;
+    const int n_masks = plan->Bm * plan->Hm;
+    std::vector<size_t> waves(n_masks, 0);
+    size_t most = 0;
+    for (int mi = 0; mi < n_masks; ++mi) {
+        for (int32_t i = wl.item_off[mi]; i < wl.item_off[mi] + wl.item_cnt[mi]; ++i) waves[mi] += wl.items[i].n > alone ? 4 : 1;
+        most = std::max(most, (waves[mi] + 3) / 4);
+    }
+    static_assert(sizeof(WaveItem) == 32, "eight words a record");
+    table.resize(most * n_masks * 32);
+    for (int mi = 0; mi < n_masks; ++mi) {
+        WaveItem *to = reinterpret_cast<WaveItem *>(table.data()) + most * 4 * mi, *const end = to + most * 4;
+        for (int32_t i = wl.item_off[mi]; i < wl.item_off[mi] + wl.item_cnt[mi]; ++i) {
+            const WaveItem &it = wl.items[i];
+            if (it.n <= alone) {
+                *to++ = it;
+                continue;
+            }
+            for (int w = 0; w < 4; ++w) {
+                const int at = it.n * w / 4;
+                const WaveEntry &e = wl.ents[it.begin + at];
+                *to++ = WaveItem{it.rg, it.begin + at, it.n * (w + 1) / 4 - at, it.slot, it.split, e.key, e.code, 1};
+            }
+        }
+        for (; to < end; ++to) *to = WaveItem{-1, 0, 0, -1, -1, 0, -1, 0};
+    }
+    return (int)most;
+}
+
+// Estimated time of a call through the wave form, with the longest list that one wave walks alone chosen for it (`alone`).
+// Two things bound a launch, and the root of the sum of their p-th powers is the estimate: what the chip's waves take
+// together (each its start and end, and its steps; at 128 columns, where only eight waves fit a compute unit, a
+// workgroup holds its place as long as its longest wave), and the longest wave's chain of steps, which is slower the
+// fuller the chip is.  A list shared by four waves is a chain of a quarter, but four starts and a merge.
+// Constants fitted to 201 calls (all kinds of masks, 128 to 8192 queries, 2 to 300 heads, each with 12 limits): 6 % mean
+// error at 64 columns, 7 % at 128; the limit chosen is 2 % behind the best one in the mean.  Where sharing matters, us with
+// the longest list alone / shared: Longformer 8 x 12 x 512 x 64 14.1 / 8.8, window 1 x 2 x 1772 x 32 7.2 / 4.4.
+static double wave_time_us(const smha_plan *plan, int B, int H, int D, bool bf16, int &alone) {
+    const WaveLists &wl = plan->wave;
+    const double per_mask = 1.0 / (plan->Bm * plan->Hm), heads = (double)B * H;
+    const bool wide = D > 64;
+    const double slots = (wide ? 8.0 : 16.0) * plan->n_cu, bf16_cost = bf16 ? 1.15 : 1.0;
+    double best = 0;
+    alone = 0;
+    for (int limit : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64}) {
+        // a mask's workgroups, longest items first: those that one item fills, then four items each
+        double teams = 0, solos = 0, steps = 0, held = 0, left = 0;
+        int chain = 0;
+        for (int n = kWaveWhole; n >= 0; --n) {
+            double k = per_mask * wl.of_length[n];
+            if (k == 0) continue;
+            steps += k * n;
+            if (n > limit) {
+                teams += k;
+                held += 4 * k * ((n + 3) / 4);
+                chain = std::max(chain, (n + 3) / 4);
+                continue;
+            }
+            chain = std::max(chain, n);
+            solos += k;
+            const double filled = std::min(k, left);  // places in a workgroup that a longer item opened
+            left -= filled;
+            k -= filled;
+            const double opened = std::ceil(k / 4 - 1e-9);
+            held += 4 * opened * n;
+            left += 4 * opened - k;
+        }
+        const double waves = heads * (4 * teams + solos), groups = heads * (teams + std::ceil(solos / 4));
+        const double uneven = groups > plan->n_cu ? std::ceil(groups / plan->n_cu) * plan->n_cu / groups - 1 : 0;
+        const double work_us = wide ? 1e-3 * (waves * 1.52 + heads * (0.05 * steps + 0.95 * held) * 0.693) * (1 + 0.35 * uneven)
+                                    : 1e-3 * (waves * 0.755 + heads * steps * 0.372);
+        const double fill = std::min(1.0, waves / slots);
+        const double chain_us = chain * (wide ? 0.692 + 0.143 * fill : 0.487 + 0.207 * fill);
+        const double power = wide ? 3.3 : 2.25;
+        const double us = std::pow(std::pow(work_us, power) + std::pow(chain_us, power), 1 / power);
+        if (alone == 0 || us < best) {
+            best = us;
+            alone = limit;
+        }
+    }
+    return (wide ? 3.7 : 3.25) + best * bf16_cost;
+}
+
+// Estimated time of a call through one of the other two forms (1: four waves of 32 rows, 3: eight of 16), the same way:
+// the busiest compute unit's work and the longest workgroup's chain, in steps plus 2 per item (see build_work_order).
+// Fitted to the same calls: 8 to 9 % mean error.
+static double block_time_us(const smha_plan *plan, int lvl, int form, int B, int H, int D, bool bf16) {
+    const WorkLists &wl = plan->lists[plan->fine_differs ? lvl : 0];
+    const int BH = B * H, n_masks = plan->Bm * plan->Hm;
+    double total = 0, items = 0, longest = 0;
+    std::vector<double> cost(n_masks, 0.0);
+    for (int mi = 0; mi < n_masks; ++mi) {
+        for (int it = 0; it < wl.item_cnt[mi]; ++it) {
+            const Item &i = wl.items[wl.item_off[mi] + it];
+            cost[mi] += 2 + i.end - i.begin;
+            longest = std::max(longest, 2.0 + i.end - i.begin);
+        }
+    }
+    for (int x = 0; x < std::min(8, BH); ++x) {  // the busiest XCD
+        double t = 0, n = 0;
+        if (n_masks == 1) {
+            const int heads = (BH - x + 7) / 8;
+            t = heads * cost[0];
+            n = (double)heads * wl.item_cnt[0];
+        } else {
+            for (int bh = x; bh < BH; bh += 8) {
+                const int mi = (plan->Bm > 1 ? bh / H : 0) * plan->Hm + (plan->Hm > 1 ? bh % H : 0);
+                t += cost[mi];
+                n += wl.item_cnt[mi];
+            }
+        }
+        total = std::max(total, t);
+        items = std::max(items, n);
+    }
+    const double units = std::max(plan->n_cu / 8, 1);
+    const double slots = units * (D == 64 ? 4 : D == 128 ? 2 : 1);
+    const double unit = items > units ? std::max(longest, total / units + 0.35 * total / items) : longest;
+    const double group = std::max(longest, total / std::max(1.0, std::min(slots, items)));
+    int64_t tiles = 0, part = 0;
+    for (const MaskFormats &m : plan->masks) {
+        tiles += (int64_t)m.kt_col.size();
+        part += (int64_t)(m.kt_bitmap.size() / 64);
+    }
+    const double parts = tiles ? (double)part / (double)tiles : 0.0, gathers = plan->n_gathered > 0 ? 1.0 : 0.0, fine = plan->fine_differs ? lvl : 0;
+    if (D == 64) return 2.43 + (1 + 0.137 * parts) * std::pow(std::pow(unit * 0.461, 4.0) + std::pow(group * 0.717, 4.0), 0.25) * (bf16 ? 1.236 : 1.0) * (1 + 0.178 * gathers) + 5.0 * fine;
+    if (form == 1) return 3.9 + (1 - 0.16 * parts) * std::max(unit * 0.962, group * 1.121) * (bf16 ? 1.017 : 1.0) * (1 + 0.337 * gathers) + 5.9 * fine;
+    return 3.0 + (unit * 0.9 + group * 0.148) * (bf16 ? 1.086 : 1.0) + 4.5 * fine;
+}
+
+// The wave form wins where tiles are filled poorly (BigBird with random 32-blocks 16 x 12 x 2048 x 64: 112 us, 66 with
+// the wave form) and where a call has too few 128-row groups to fill the chip (fresh mask 1 x 4 x 1037 x 64: 8.9 / 4.6;
+// causal 9 x 2 x 1088 x 128: 26.2 / 14.4); it loses where tiles are full and rows many (causal 16 x 12 x 4096 x 128: 870 /
+// 1176), because every K and V tile is loaded once per 32 rows.  It has to win by 5 %, and by 20 % on masks of
+// full tiles, where the estimates are farther off: with these margins no one of the 201 calls is more than 2 % slower
+// than without the form, the mean is 0.73, and the best choice for each would be 0.71.
+bool wave_form_pays(const smha_plan *plan, int lvl, int form, int B, int H, int D, bool bf16, int &alone) {
+    if (plan->wave.items.empty() || D > 128 || H > 65535 || (int64_t)B * H > (1 << 19)) return false;
+    if (workspace_bytes(plan, 0, 4, B, H, D, nullptr) > kStaticScratchBytes) return false;  // (smha_forward_static takes what it took)
+    int64_t tiles = 0, part = 0;
+    for (const MaskFormats &m : plan->masks) {
+        tiles += (int64_t)m.kt_col.size();
+        part += (int64_t)(m.kt_bitmap.size() / 64);
+    }
+    const double margin = 10 * part > tiles ? 0.95 : 0.8;
+    return wave_time_us(plan, B, H, D, bf16, alone) < margin * block_time_us(plan, lvl, form, B, H, D, bf16);
 }
 
 // The block kernel's work order for B x H heads on `slots` resident workgroups per XCD.  Items
@@ -1191,6 +1424,13 @@ extern "C" smha_status_t smha_plan_export(const smha_plan_t *p, int mask_index, 
             src = wl.items.data() + wl.item_off[mask_index];
             bytes = (size_t)wl.item_cnt[mask_index] * sizeof(Item); break;
         }
+        case SMHA_EXPORT_WAVE_ITEMS:
+            if (p->wave.items.empty()) return SMHA_ERR_UNSUPPORTED;
+            src = p->wave.items.data() + p->wave.item_off[mask_index];
+            bytes = (size_t)p->wave.item_cnt[mask_index] * sizeof(WaveItem); break;
+        case SMHA_EXPORT_WAVE_ENTRIES:
+            if (p->wave.items.empty()) return SMHA_ERR_UNSUPPORTED;
+            src = p->wave.ents.data(); bytes = (p->wave.ents.size() - 1) * sizeof(WaveEntry); break;  // (without the spare entry)
         default: return SMHA_ERR_INVALID_ARG;
     }
     *need = bytes;

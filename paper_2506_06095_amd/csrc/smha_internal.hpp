@@ -70,6 +70,18 @@ struct SplitRow {
     int32_t qtile, slot0, count, pad;
 };
 
+// The wave form of the block kernel (wave_fwd.inc): an item is 32 query rows (group `rg`) and n of the 32-key tiles in
+// which any of them has a key, entries begin ..; slot and split as in Item, with one SplitRow and one counter per
+// 32-row group.  key0 / code0 repeat the first entry.  team: the workgroup's four waves hold a quarter each of one item's
+// list and merge in LDS (set in a call shape's order only).  An entry's code is -1 where all 32 x 32 scores are kept, else
+// the block of kt_bitmap that holds the tile (its rows 32 (rg & 1) .., bits 32 ((key / 32) & 1) ..).
+struct WaveItem {
+    int32_t rg, begin, n, slot, split, key0, code0, team;
+};
+struct WaveEntry {
+    int32_t key, code;
+};
+
 // The forms of the row kernel at 64, 128 and 256 columns: query rows that share a wave, and keys that each
 // lane group of a row (D / 8 lanes) has in flight.  row_form chooses.
 struct RowForm {
@@ -96,6 +108,10 @@ struct DeviceArrays {
     int32_t *item_off[2] = {nullptr, nullptr}, *item_cnt[2] = {nullptr, nullptr};      // [n_masks]
     SplitRow *split_rows[2] = {nullptr, nullptr};
     int32_t *split_off[2] = {nullptr, nullptr}, *split_cnt[2] = {nullptr, nullptr};    // [n_masks]
+    // the wave form's (WaveLists)
+    WaveEntry *wave_ents = nullptr;
+    int32_t *wave_split_off = nullptr;                                                 // [n_masks]
+    SplitRow *wave_splits = nullptr;
 };
 
 // The block kernel's work items for every mask of a plan: each 128-row group's list of steps, whole
@@ -106,6 +122,17 @@ struct WorkLists {
     std::vector<SplitRow> split_rows;
     std::vector<int32_t> split_off, split_cnt;
     int max_items = 0, max_split_rows = 0, max_slots = 0;
+};
+
+// The wave form's work items of every mask, longest first; none where the form is ruled out.
+constexpr int kWaveWhole = 128;  // longest list that is not cut
+struct WaveLists {
+    std::vector<WaveItem> items;
+    std::vector<WaveEntry> ents;
+    std::vector<int32_t> item_off, item_cnt, split_off;
+    std::vector<SplitRow> splits;
+    int max_splits = 0, max_slots = 0;
+    int32_t of_length[kWaveWhole + 1] = {0};  // items by entries, over all masks
 };
 
 }  // namespace smha
@@ -133,6 +160,7 @@ struct smha_plan {
     // keep the chip busy); [1]: every list cut to at most 16 steps (latency: with few heads the
     // longest list is the whole launch).  smha_forward picks by how many items the call has.
     smha::WorkLists lists[2];
+    smha::WaveLists wave;
     bool fine_differs = false;  // false: [1] is empty and [0] serves both
     // Tiles almost all full and lists long (dense causal and the like): at 128 columns such plans run the
     // block kernel's first form; all others its third form, whose waves skip at 16 rows x 32 keys.
@@ -152,26 +180,40 @@ struct smha_plan {
     static constexpr int kCallSlots = 4;
     struct Prepared {
         int B = 0, H = 0, d = 0, lvl = 0, form = 1, per_xcd = 0, longest = 0;  // form: which block kernel the order is for
+        int alone = 0;  // wave form (4): see build_wave_order
         int32_t *order = nullptr;
         int64_t step_words = 0, item_words = 0;  // second form: sizes of the step and item streams inside `order`
         size_t ws_bytes = 0, counters_at = 0;  // one workspace; byte offset of its counters
         void *ws[kCallSlots] = {nullptr, nullptr, nullptr, nullptr};
         unsigned next = 0;
     };
+    // which of them serves a call: decided once per shape, input type and block form (the first or third) it would run
+    // otherwise
+    struct CallShape {
+        int B, H, d, bf16, form;
+        Prepared *prepared;
+    };
     mutable std::mutex prepared_mutex;
     mutable std::vector<Prepared *> prepared;
+    mutable std::vector<CallShape> calls;
 };
 
 namespace smha {
+
+constexpr size_t kStaticScratchBytes = (size_t)32 << 20;  // smha_forward_static's workspace
 
 // plan.cpp
 smha_status_t finish_plan(smha_plan *p);      // selector, work lists, concatenation
 // which workgroup of the block kernel takes which item, for B x H heads on `slots` workgroups per XCD
 void build_work_order(const smha_plan *plan, int lvl, int B, int H, int slots, std::vector<int32_t> &table, int &per_xcd);
+// whether a call shape runs the wave form rather than `form` at grain `lvl`; alone: see build_wave_order
+bool wave_form_pays(const smha_plan *plan, int lvl, int form, int B, int H, int D, bool bf16, int &alone);
+// the wave form's workgroups: four WaveItems each, as many per mask (the result); see WaveItem
+int build_wave_order(const smha_plan *plan, int alone, std::vector<int32_t> &table);
 // which of kRowForms[row_width(D)] a call of the row kernel runs
 int row_form(const smha_plan *plan, int B, int H, int D);
 // bytes of one workspace for that call shape: partials first, then 4 counters per (batch*head, split group)
-size_t workspace_bytes(const smha_plan *plan, int lvl, int B, int H, int d, size_t *counters_at);
+size_t workspace_bytes(const smha_plan *plan, int lvl, int form, int B, int H, int d, size_t *counters_at);
 // device.hip
 smha_status_t upload_plan(smha_plan *p, int device_id);
 void release_device(smha_plan *p);

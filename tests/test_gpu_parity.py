@@ -895,3 +895,58 @@ def test_plan_that_holds_only_the_row_format(torch_mod, smha):
         q = to_dev(torch_mod, Q, "f16")
         with pytest.raises(smha.SmhaError):
             plan.forward(q, q, q, kernel=smha.SMHA_KERNEL_BLOCK)
+
+
+def wave_form_masks(name, B, H):
+    """Masks at the edges of the wave form: lists of no, one and many entries, rows and keys that fill no 32-key tile."""
+    rng = np.random.default_rng(len(name))
+    if name == "one_key":                               # one entry a list at most, most groups empty
+        m = np.zeros((1, 1, 97, 33), bool)
+        m[0, 0, 64, 32] = m[0, 0, 96, 0] = True
+    elif name == "ragged":                              # a last tile of one key, a last group of one row
+        m = rng.random((B, H, 161, 225)) < 0.3
+        m[0, 0, 32:64] = False
+        m[0, 0, 64:96] = True
+    elif name == "shared":                              # lists of 1 to 128 entries: walked alone and by four waves
+        i, j = np.arange(4096 - 300, 4096)[:, None], np.arange(4096)[None]
+        m = ((j <= i) & ((i < 3860) | (i - j < 40) | (j % 1024 == 3)))[None, None]
+    elif name == "cut":                                 # 129 entries and more: parts merged in memory
+        m = np.zeros((1, 1, 70, 6000), bool)
+        m[..., :33, :] = True
+        m[..., 33:64, ::7] = True
+        m[..., 64:, 5000:] = True
+    else:                                               # "blocks": full and partial 32 x 32 sub-tiles, one mask per head
+        m = np.stack([np.kron(rng.random((20, 20)) < 0.15, np.ones((32, 32), bool))[:610, :610] for _ in range(H)])[None]
+        m |= np.abs(np.arange(610)[:, None] - np.arange(610)[None]) < 3
+    return m.astype(np.uint8)
+
+
+@pytest.mark.parametrize("name", ["one_key", "ragged", "shared", "cut", "blocks"])
+@pytest.mark.parametrize("d,dtype", [(64, "f16"), (64, "bf16"), (128, "f16"), (128, "bf16"), (8, "f16"), (80, "bf16")])
+def test_wave_form(torch_mod, smha, name, d, dtype):
+    """The wave form beside the first (and at 128 columns the third) form of the block kernel, all against the oracle;
+    strided tensors, so that a read or store past a row's end would meet its neighbours.  Three heads: the heads that
+    are left over are dealt over all XCDs; nine: one full round and one left over."""
+    torch = torch_mod
+    for B, H in ((1, 3), (3, 3)):
+        masks = wave_form_masks(name, B, H)
+        if B > 1 and name in ("shared", "cut"):
+            continue
+        Sq, Sk = masks.shape[2:]
+        Q = W.qkv_bits(B, H, Sq, d, dtype, 1.0, 901)[0]
+        _, K, V = W.qkv_bits(B, H, Sk, d, dtype, 1.0, 902)
+        ref = oracle.masked_attention(Q, K, V, dtype, masks)
+        q, k, v = (to_dev(torch, x, dtype).transpose(1, 2).contiguous().transpose(1, 2) for x in (Q, K, V))
+        make = smha.Plan.from_dense if Sq == Sk else smha.Plan.from_dense_rect
+        for form in (0, 1, 3) if d > 64 else (0, 1):
+            with make(masks, head_dim=d, force=smha.SMHA_KERNEL_BLOCK, block_form=form) as plan:
+                kernel = smha.smha_call_kernel_name(plan.handle, B, H, d, smha.SMHA_F16 if dtype == "f16" else smha.SMHA_BF16)
+                assert (kernel == "smha_wave_fwd") == (form == 0), kernel
+                for f32 in (False, True):
+                    out = torch.full((B, Sq, H, d), float("nan"), device="cuda", dtype=torch.float32 if f32 else q.dtype).transpose(1, 2)
+                    plan.forward(q, k, v, out=out)
+                    first = out.float().cpu().numpy()
+                    check(first, ref, f"{name} {B}x{H} d={d} {dtype} form={form} f32={f32}", bf16_out=dtype == "bf16" and not f32)
+                    for _ in range(3):                  # (the merge's counters are back at zero, its order is fixed)
+                        plan.forward(q, k, v, out=out)
+                    assert np.array_equal(out.float().cpu().numpy(), first)

@@ -575,3 +575,73 @@ def test_which_form_of_the_block_kernel_a_plan_runs():
             assert got == want, (spec, S, d, extra, got, want)
     with smha.Plan.from_desc(c5.mask, 1, 2, 8192, head_dim=128, device_id=-2, force=smha.SMHA_KERNEL_ROW) as plan:
         assert smha.smha_kernel_name(plan.handle, 128, smha.SMHA_F16) == "smha_row_fwd"
+
+
+def wave_masks(name, rng):
+    if name == "ragged":          # rows and keys that fill no tile, one empty row group, one row group of a single key
+        m = rng.random((1, 2, 131, 997)) < 0.02
+        m[0, 0, 32:64] = False
+        m[0, 1, :32] = False
+        m[0, 1, 5, 900] = True
+    elif name == "one_row":
+        m = np.ones((1, 1, 1, 33), bool)
+    elif name == "long":          # lists of 128 entries (whole), 129 and 190 (cut), beside short ones
+        m = np.zeros((1, 1, 160, 6080), bool)
+        m[..., :32, :4096] = True
+        m[..., 40, :4097] = True
+        m[..., 64:96, :] = True
+        m[..., 96:, 17::640] = True
+    else:                         # blocks, a band, global tokens; another mask per batch entry
+        i, j = np.arange(700)[:, None], np.arange(700)[None]
+        m = np.stack([np.kron(rng.random((22, 22)) < 0.1, np.ones((32, 32), bool))[:700, :700] | (np.abs(i - j) < 20) | (j < 5 + 9 * b)
+                      for b in range(2)])[:, None]
+    return m.astype(np.uint8)
+
+
+@pytest.mark.parametrize("name", ["ragged", "one_row", "long", "mixed"])
+def test_wave_lists_cover_each_unmasked_entry_once(name):
+    """The wave form's items rebuild the mask; long lists are cut into parts of at most 64 entries with slots of their own."""
+    masks = wave_masks(name, np.random.default_rng(3))
+    make = smha.Plan.from_dense if masks.shape[2] == masks.shape[3] else smha.Plan.from_dense_rect
+    with make(masks, device_id=-2, force=smha.SMHA_KERNEL_BLOCK) as plan:
+        ents, bmp = plan.export("wave_entries").reshape(-1, 2), plan.export("kernel_bitmaps").reshape(-1, 64)
+        for mi in range(masks.shape[0] * masks.shape[1]):
+            mask = masks.reshape(-1, *masks.shape[2:])[mi]
+            items = plan.export("wave_items", mi).reshape(-1, 8)
+            assert np.all(np.diff(items[:, 2]) <= 0) and items[0, 2] <= 128                 # longest first
+            assert sorted(set(items[:, 0])) == list(range((mask.shape[0] + 31) // 32))      # every row group, empty ones too
+            cut = items[items[:, 3] >= 0]
+            assert sorted(cut[:, 3]) == list(range(len(cut))) and (len(cut) == 0 or cut[:, 2].max() <= 64)
+            for g in set(cut[:, 0]):
+                assert len(set(cut[cut[:, 0] == g, 4])) == 1 and (items[:, 0] == g).sum() == (cut[:, 0] == g).sum() > 1
+            cnt = np.zeros((mask.shape[0] + 32, mask.shape[1] + 64), np.int32)
+            for rg, begin, n, slot, split, key0, code0, team in items:
+                assert n == 0 or (key0, code0) == tuple(ents[begin])
+                for key, code in ents[begin:begin + n]:
+                    if code < 0:
+                        bits = np.ones((32, 32), np.int32)
+                    else:
+                        words = bmp[code][32 * (rg % 2):32 * (rg % 2) + 32] >> np.uint64(key % 64)
+                        bits = ((words[:, None] >> np.arange(32, dtype=np.uint64)) & np.uint64(1)).astype(np.int32)
+                    assert bits.any()
+                    cnt[32 * rg:32 * rg + 32, key:key + 32] += bits
+            assert np.array_equal(cnt[:mask.shape[0], :mask.shape[1]], mask) and cnt.sum() == mask.sum()
+    with make(masks, device_id=-2, force=smha.SMHA_KERNEL_BLOCK, block_form=1) as plan:
+        with pytest.raises(smha.SmhaError):
+            plan.export("wave_items")                                                       # a form was asked for
+
+
+def test_which_calls_take_the_wave_form():
+    bert, causal = W.table2_spec("bigbird"), W.MaskSpec(flags=W.CAUSAL)
+    blocks = W.MaskSpec(flags=W.BIGBIRD, block=64, n_window_blocks=3, n_global_blocks=2, n_random_blocks=3, seed=5)
+    for spec, B, H, S, d, opts, want in [
+            (bert, 16, 12, 2048, 64, {}, "smha_wave_fwd"),                  # poorly filled tiles
+            (bert, 16, 12, 2048, 64, {"block_form": 1}, "smha_block_fwd"),  # asked for
+            (bert, 1, 2, 2048, 256, {}, "smha_block_fwd16"),                # 256 columns never
+            (causal, 1, 2, 512, 64, {}, "smha_wave_fwd"),                   # too few 128-row groups
+            (causal, 16, 12, 4096, 64, {}, "smha_block_fwd"), (causal, 16, 12, 4096, 128, {}, "smha_block_fwd"),
+            (blocks, 1, 32, 8192, 128, {}, "smha_block_fwd16"), (blocks, 1, 2, 2048, 128, {}, "smha_wave_fwd")]:
+        with smha.Plan.from_desc(spec, B, H, S, head_dim=d, device_id=-2, force=smha.SMHA_KERNEL_BLOCK, **opts) as plan:
+            for dtype in (smha.SMHA_F16, smha.SMHA_BF16):
+                assert smha.smha_call_kernel_name(plan.handle, B, H, d, dtype) == want, (B, H, S, d, opts, dtype)
+            assert smha.smha_call_kernel_name(plan.handle, B, H, 12, smha.SMHA_F16) == ""

@@ -294,6 +294,13 @@ smha_status_t smha_plan_work_order(const smha_plan_t *plan, int B, int H, int wo
                                    int fine, int32_t *host_dst, size_t cap, size_t *need,
                                    int *per_xcd);
 
+/* The order that smha_forward's block kernel walks: as smha_plan_work_order, but heads that are left over when
+ * B * H is no multiple of 8 are not kept on one XCD each (batch*head mod 8): their items are dealt over all
+ * XCDs, each such head over a stretch of them.  The same arguments, table and errors. */
+smha_status_t smha_plan_call_order(const smha_plan_t *plan, int B, int H, int workgroups_per_xcd,
+                                   int fine, int32_t *host_dst, size_t cap, size_t *need,
+                                   int *per_xcd);
+
 /* Which form of the row kernel smha_forward runs for B x H heads of size d: how many query rows
  * share a wave (8, 4, 2 or 1), and how many keys each lane group of a row has in flight.  For
  * inspection and tests; runs on the host.

@@ -97,9 +97,9 @@ def _load():
     lib.smha_forward_static.restype = C.c_int
     lib.smha_plan_prepare.argtypes = [vp, C.c_int, C.c_int, C.c_int]
     lib.smha_plan_prepare.restype = C.c_int
-    lib.smha_plan_work_order.argtypes = [vp, C.c_int, C.c_int, C.c_int, C.c_int, vp, C.c_size_t,
+    lib.smha_plan_work_order.argtypes = lib.smha_plan_call_order.argtypes = [vp, C.c_int, C.c_int, C.c_int, C.c_int, vp, C.c_size_t,
                                          C.POINTER(C.c_size_t), C.POINTER(C.c_int)]
-    lib.smha_plan_work_order.restype = C.c_int
+    lib.smha_plan_work_order.restype = lib.smha_plan_call_order.restype = C.c_int
     lib.smha_plan_row_form.argtypes = [vp, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int)]
     lib.smha_plan_row_form.restype = C.c_int
     lib.smha_plan_destroy.argtypes = [vp]
@@ -207,19 +207,21 @@ def smha_plan_export(plan: int, which: str, mask_index: int = 0) -> np.ndarray:
     return out
 
 
-def smha_plan_work_order(plan: int, B: int, H: int, workgroups_per_xcd: int, fine: bool = False):
-    """(table, per_xcd): int32 table = 8 list starts, 8 list lengths, then (batch*head, item) pairs."""
-    lib = _load()
+def smha_plan_work_order(plan: int, B: int, H: int, workgroups_per_xcd: int, fine: bool = False, spread: bool = False):
+    """(table, per_xcd): int32 table = 8 list starts, 8 list lengths, then (batch*head, item) pairs.  spread: as
+    smha_forward deals (smha_plan_call_order), left-over heads over all XCDs."""
+    entry = "smha_plan_call_order" if spread else "smha_plan_work_order"
+    order = getattr(_load(), entry)
     need, per = C.c_size_t(0), C.c_int(0)
-    st = lib.smha_plan_work_order(C.c_void_p(plan), B, H, workgroups_per_xcd, int(fine), None, 0, C.byref(need),
+    st = order(C.c_void_p(plan), B, H, workgroups_per_xcd, int(fine), None, 0, C.byref(need),
                                   C.byref(per))
     if st != 0:
-        raise SmhaError(st, "smha_plan_work_order")
+        raise SmhaError(st, entry)
     out = np.empty(need.value, dtype=np.int32)
-    st = lib.smha_plan_work_order(C.c_void_p(plan), B, H, workgroups_per_xcd, int(fine),
+    st = order(C.c_void_p(plan), B, H, workgroups_per_xcd, int(fine),
                                   C.c_void_p(out.ctypes.data), need.value, C.byref(need), C.byref(per))
     if st != 0:
-        raise SmhaError(st, "smha_plan_work_order")
+        raise SmhaError(st, entry)
     return out, per.value
 
 
@@ -345,8 +347,8 @@ class Plan:
     def export(self, which: str, mask_index: int = 0) -> np.ndarray:
         return smha_plan_export(self.handle, which, mask_index)
 
-    def work_order(self, B: int, H: int, workgroups_per_xcd: int, fine: bool = False):
-        return smha_plan_work_order(self.handle, B, H, workgroups_per_xcd, fine)
+    def work_order(self, B: int, H: int, workgroups_per_xcd: int, fine: bool = False, spread: bool = False):
+        return smha_plan_work_order(self.handle, B, H, workgroups_per_xcd, fine, spread)
 
     def row_form(self, B: int, H: int, d: int):
         return smha_plan_row_form(self.handle, B, H, d)

@@ -44,8 +44,8 @@ struct FwdParams {
     // block path
     const Item *items;
     const int32_t *item_off, *item_cnt;
-    // work order of the block kernel: for each XCD x a list of (batch*head, item index) pairs of the
-    // heads with batch*head mod 8 = x; the workgroup of rank r on that XCD (of gridDim.x / 8) takes
+    // work order of the block kernel: for each XCD x a list of (batch*head, item index) pairs (see
+    // build_work_order); the workgroup of rank r on that XCD (of gridDim.x / 8) takes
     // positions r, r + gridDim.x / 8, ... until the list ends or a pair with batch*head < 0 comes up.
     // order_hdr = {start of each XCD's list (8), length (8)}
     const int32_t *order, *order_hdr;
@@ -1485,7 +1485,7 @@ static smha_status_t make_prepared(const smha_plan *plan, int B, int H, int d, i
         if (form == 4) {
             longest = build_wave_order(plan, alone, table);
         } else {
-            build_work_order(plan, lvl, B, H, slots, table, per_xcd);
+            build_work_order(plan, lvl, B, H, slots, true, table, per_xcd);
             for (int x = 0; x < 8; ++x) longest = std::max(longest, table[8 + x]);
         }
         if (form == 2) {

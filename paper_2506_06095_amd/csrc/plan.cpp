@@ -1076,16 +1076,45 @@ bool wave_form_pays(const smha_plan *plan, int lvl, int form, int B, int H, int 
 // hardware issues the oldest wave first (equal work ended at 0.92 : 0.97 : 1.04 : 1.09 of the mean, the same on
 // four masks), so work is dealt in that proportion (BigBird blocks 4 x 16 x 4000 x 64 66.8 -> 63.7 us, BigBird 16 x 12 x 2048
 // 111.9 -> 113.4, most masks the same).
+// spread: heads that are left over when their number is no multiple of 8 (all of them, if there are fewer) are not given
+// to one XCD each but dealt over all: the eight XCDs stand in a row, each left-over head takes the same stretch of them
+// (one or a few, so that its K and V come to few L2s), and its items go, longest first, to the XCD in that stretch with
+// the least of them so far.  Without it 12 heads are two for four XCDs and one for the others: causal
+// 5 x 12 x 3313 x 80 bf16 228.6 us, spread 214.9, BigBird blocks 3 x 12 x 4928 x 160 179.7 and 161.2, per-head 64-blocks
+// 3 x 12 x 3712 x 96 61.3 and 55.9; 60 such calls 0.98 in the mean, none more than 2 % slower.
 // table = {start of each XCD's list (8), its length (8), then (batch*head, item index) pairs};
 // list position = turn * per_xcd + workgroup rank; a workgroup's unused turns hold batch*head = -1.
-void build_work_order(const smha_plan *plan, int lvl, int B, int H, int slots, std::vector<int32_t> &table, int &per_xcd) {
+void build_work_order(const smha_plan *plan, int lvl, int B, int H, int slots, bool spread, std::vector<int32_t> &table, int &per_xcd) {
     const WorkLists &wl = plan->lists[plan->fine_differs ? lvl : 0];
     const int BH = B * H;
     auto mask_of = [&](int bh) { return (plan->Bm > 1 ? bh / H : 0) * plan->Hm + (plan->Hm > 1 ? bh % H : 0); };
+    constexpr int kItemCost = 2;  // an item's start and end, in tiles
+    // what each XCD gets of each head: all items, or those listed in `some`
+    struct Share { int32_t bh; std::vector<int32_t> some; };
+    std::vector<Share> shares[8];
+    const int left_over = spread ? BH % 8 : 0, whole = BH - left_over;
+    for (int x = 0; x < 8; ++x)
+        for (int bh = x; bh < whole; bh += 8) shares[x].push_back({bh, {}});
+    int64_t dealt[8] = {0};
+    for (int l = 0; l < left_over; ++l) {
+        const int mask = mask_of(whole + l), first = 8 * l / left_over, last = (8 * (l + 1) - 1) / left_over;
+        for (int x = first; x <= last; ++x) shares[x].push_back({whole + l, {}});
+        for (int32_t it = 0; it < wl.item_cnt[mask]; ++it) {
+            const Item &item = wl.items[wl.item_off[mask] + it];
+            int to = first;
+            for (int x = first + 1; x <= last; ++x)
+                if (dealt[x] < dealt[to]) to = x;
+            dealt[to] += kItemCost + (item.end - item.begin);
+            shares[to].back().some.push_back(it);
+        }
+        for (int x = first; x <= last; ++x)
+            if (shares[x].back().some.empty()) shares[x].pop_back();
+    }
+    auto count = [&](const Share &s) { return s.some.empty() ? (int64_t)wl.item_cnt[mask_of(s.bh)] : (int64_t)s.some.size(); };
     int64_t most = 0;  // items of the busiest XCD
     for (int x = 0; x < 8; ++x) {
         int64_t n = 0;
-        for (int bh = x; bh < BH; bh += 8) n += wl.item_cnt[mask_of(bh)];
+        for (const Share &s : shares[x]) n += count(s);
         most = std::max(most, n);
     }
     // (as many workgroups on every compute unit: an odd one would be a unit that takes its second item late)
@@ -1094,7 +1123,6 @@ void build_work_order(const smha_plan *plan, int lvl, int B, int H, int slots, s
     per_xcd = 0;
     if (most == 0) return;
     per_xcd = (int)std::min<int64_t>(slots, (most + n_units - 1) / n_units * n_units);
-    constexpr int kItemCost = 2;  // an item's start and end, in tiles
     const bool aged = slots == 4 * n_units, fine = lvl == 1 && plan->fine_differs;
     static const double kPace[4] = {1.09, 1.03, 0.96, 0.92};
     struct Pick { int32_t bh, index, cost; };
@@ -1105,7 +1133,7 @@ void build_work_order(const smha_plan *plan, int lvl, int B, int H, int slots, s
     std::vector<double> done(per_xcd);    // a workgroup's work so far, in terms of its pace
     std::vector<int32_t> turns(per_xcd);  // items it has
     for (int x = 0; x < 8; ++x) {
-        if (x > 0 && plan->Bm * plan->Hm == 1 && (BH - 1 - x + 8) / 8 == (BH - x + 8) / 8) {
+        if (x > 0 && left_over == 0 && plan->Bm * plan->Hm == 1 && (BH - 1 - x + 8) / 8 == (BH - x + 8) / 8) {
             // one mask for all heads, and as many heads as the XCD before: its deal, one head on
             const size_t from = 16 + 2 * (size_t)table[x - 1], n = 2 * (size_t)table[8 + x - 1];
             table[x] = (int32_t)((table.size() - 16) / 2);
@@ -1124,26 +1152,30 @@ void build_work_order(const smha_plan *plan, int lvl, int B, int H, int slots, s
         for (int u = 0; u < n_units; ++u) heap[u] = u;
         std::fill(done.begin(), done.end(), 0.0);
         std::fill(turns.begin(), turns.end(), 0);
-        int last = BH > x ? x + (BH - 1 - x) / 8 * 8 : x - 8, joint = last;  // this XCD's last head, first head of the joint deal
-        int64_t here = 0;  // items of this XCD
-        for (int bh = x; bh <= last; bh += 8) here += wl.item_cnt[mask_of(bh)];
+        const std::vector<Share> &mine = shares[x];
+        const int last = (int)mine.size() - 1;  // this XCD's last head
+        int joint = last;                       // first head of the joint deal
+        int64_t here = 0;                       // items of this XCD
+        for (const Share &s : mine) here += count(s);
         const bool apart = aged && fine && here > per_xcd && here < 2 * (int64_t)per_xcd;
-        for (int64_t n = 0; joint >= x; joint -= 8) {
-            n += wl.item_cnt[mask_of(joint)];
+        for (int64_t n = 0; joint >= 0; --joint) {
+            n += count(mine[joint]);
             if (apart && joint != last) break;
             if (4 * n > (aged ? 12 : 9) * (int64_t)per_xcd && joint != last) break;
         }
-        joint += 8;
-        for (int bh = x; bh <= last; bh += 8) {
-            const int mask = mask_of(bh);
-            const int32_t off = wl.item_off[mask];
-            if (bh <= joint) deal.clear();
-            for (int it = 0; it < wl.item_cnt[mask]; ++it) {  // (sorted by length, longest first)
+        ++joint;
+        for (int i = 0; i <= last; ++i) {
+            const int32_t bh = mine[i].bh;
+            const int32_t off = wl.item_off[mask_of(bh)];
+            if (i <= joint) deal.clear();
+            const int64_t n = count(mine[i]);
+            for (int64_t k = 0; k < n; ++k) {  // (sorted by length, longest first)
+                const int32_t it = mine[i].some.empty() ? (int32_t)k : mine[i].some[k];
                 const Item &item = wl.items[off + it];
                 deal.push_back({bh, off + it, kItemCost + (item.end - item.begin)});
             }
-            if (bh >= joint && bh != last) continue;
-            const bool mixed = joint < last && bh == last;
+            if (i >= joint && i != last) continue;
+            const bool mixed = joint < last && i == last;
             if (mixed) {  // longest first over all of them, head after head where equal: a counting sort
                 int32_t top = 0;
                 for (const Pick &p : deal) top = std::max(top, p.cost);
@@ -1315,8 +1347,8 @@ extern "C" smha_status_t smha_plan_from_desc(const smha_mask_desc_t *desc, int B
     }
 }
 
-extern "C" smha_status_t smha_plan_work_order(const smha_plan_t *p, int B, int H, int workgroups_per_xcd, int fine,
-                                              int32_t *host_dst, size_t cap, size_t *need, int *per_xcd) {
+static smha_status_t export_order(const smha_plan_t *p, int B, int H, int workgroups_per_xcd, int fine, bool spread,
+                                  int32_t *host_dst, size_t cap, size_t *need, int *per_xcd) {
     if (!p || !need || B < 1 || H < 1 || workgroups_per_xcd < 1 || fine < 0 || fine > 1) return SMHA_ERR_INVALID_ARG;
     if (cap > 0 && !host_dst) return SMHA_ERR_INVALID_ARG;
     if ((p->Bm != 1 && p->Bm != B) || (p->Hm != 1 && p->Hm != H)) return SMHA_ERR_SHAPE;
@@ -1324,11 +1356,21 @@ extern "C" smha_status_t smha_plan_work_order(const smha_plan_t *p, int B, int H
     if ((int64_t)B * H > (1 << 24)) return SMHA_ERR_UNSUPPORTED;
     std::vector<int32_t> table;
     int n = 0;
-    try { build_work_order(p, fine, B, H, workgroups_per_xcd, table, n); } catch (const std::bad_alloc &) { return SMHA_ERR_ALLOC; }
+    try { build_work_order(p, fine, B, H, workgroups_per_xcd, spread, table, n); } catch (const std::bad_alloc &) { return SMHA_ERR_ALLOC; }
     *need = table.size();
     if (per_xcd) *per_xcd = n;
     if (cap >= table.size()) std::memcpy(host_dst, table.data(), table.size() * sizeof(int32_t));
     return SMHA_OK;
+}
+
+extern "C" smha_status_t smha_plan_work_order(const smha_plan_t *p, int B, int H, int workgroups_per_xcd, int fine,
+                                              int32_t *host_dst, size_t cap, size_t *need, int *per_xcd) {
+    return export_order(p, B, H, workgroups_per_xcd, fine, false, host_dst, cap, need, per_xcd);
+}
+
+extern "C" smha_status_t smha_plan_call_order(const smha_plan_t *p, int B, int H, int workgroups_per_xcd, int fine,
+                                              int32_t *host_dst, size_t cap, size_t *need, int *per_xcd) {
+    return export_order(p, B, H, workgroups_per_xcd, fine, true, host_dst, cap, need, per_xcd);
 }
 
 extern "C" smha_status_t smha_plan_row_form(const smha_plan_t *p, int B, int H, int d, int *rows_per_wave, int *keys_in_flight) {

@@ -205,7 +205,7 @@ constexpr size_t kStaticScratchBytes = (size_t)32 << 20;  // smha_forward_static
 // plan.cpp
 smha_status_t finish_plan(smha_plan *p);      // selector, work lists, concatenation
 // which workgroup of the block kernel takes which item, for B x H heads on `slots` workgroups per XCD
-void build_work_order(const smha_plan *plan, int lvl, int B, int H, int slots, std::vector<int32_t> &table, int &per_xcd);
+void build_work_order(const smha_plan *plan, int lvl, int B, int H, int slots, bool spread, std::vector<int32_t> &table, int &per_xcd);
 // whether a call shape runs the wave form rather than `form` at grain `lvl`; alone: see build_wave_order
 bool wave_form_pays(const smha_plan *plan, int lvl, int form, int B, int H, int D, bool bf16, int &alone);
 // the wave form's workgroups: four WaveItems each, as many per mask (the result); see WaveItem

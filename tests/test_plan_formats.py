@@ -390,6 +390,42 @@ def test_work_order_of_one_mask_is_that_of_the_same_mask_for_every_head(B, H, sl
         assert np.array_equal(got[:, 0], want[:, 0]) and np.array_equal(got[:, 1], want[:, 1] % n_items)
 
 
+@pytest.mark.parametrize("B,H,per_head", [(1, 1, False), (1, 3, True), (3, 4, False), (5, 3, True), (2, 8, True), (1, 23, False)])
+def test_order_of_a_call_spreads_left_over_heads(B, H, per_head):
+    """Whole rounds of eight heads stay on their XCDs; what is left over is dealt evenly, each head over one stretch."""
+    spec = W.MaskSpec(flags=W.BLOCK_RANDOM, block=64, keep_p=0.2, per_head=per_head, seed=9)
+    left = B * H // 8 * 8
+    with smha.Plan.from_desc(spec, B, H, 3000, force=smha.SMHA_KERNEL_BLOCK, device_id=-2) as plan:
+        items = [plan.export("kernel_items", m).reshape(-1, 8) for m in range(H if per_head else 1)]
+        off = np.cumsum([0] + [len(i) for i in items])
+        cost = np.concatenate([2 + i[:, 2] - i[:, 1] for i in items])
+        for slots in (128, 3):
+            table, per = plan.work_order(B, H, slots, spread=True)
+            pairs, seen, load, xcds = table[16:].reshape(-1, 2), set(), np.zeros(8, int), {}
+            for x in range(8):
+                lst = pairs[table[x]:table[x] + table[8 + x]].reshape(-1, per, 2)
+                for r in range(per):
+                    live = lst[:, r, 0] >= 0
+                    assert not np.any(live[1:] & ~live[:-1])           # a rank's unused turns are its last ones
+                    for bh, idx in lst[live, r]:
+                        mask = bh % H if per_head else 0
+                        assert off[mask] <= idx < off[mask + 1] and (bh, idx) not in seen
+                        seen.add((int(bh), int(idx)))
+                        if bh < left:
+                            assert bh % 8 == x
+                        else:
+                            load[x] += cost[idx]
+                            xcds.setdefault(bh, set()).add(x)
+            assert len(seen) == sum(len(items[bh % H if per_head else 0]) for bh in range(B * H))
+            if left < B * H:
+                n = B * H - left
+                assert load.max() <= 1.35 * load.mean() + cost.max()
+                for k, bh in enumerate(range(left, B * H)):
+                    assert xcds[bh] <= set(range(8 * k // n, -(-8 * (k + 1) // n)))
+            else:
+                assert np.array_equal(table, plan.work_order(B, H, slots)[0])
+
+
 def mask_of_row_lengths(lengths, Sk):
     m = np.zeros((1, 1, len(lengths), Sk), np.uint8)
     rng = np.random.default_rng(len(lengths))

@@ -69,12 +69,14 @@ struct FwdParams {
     const SplitRow *split_rows;
     const int32_t *split_off, *split_cnt;
     // wave form: what each wave of a workgroup does (four WaveItems per workgroup, wave_n workgroups per mask), the
-    // items' 32-key tiles, and the size of kt_bitmap; the split arrays above are its own.  heads_magic = 2^40 / H + 1
+    // items' 32-key tiles, and the size of kt_bitmap; the split arrays above are its own.  wave_heads: heads an XCD
+    // takes at a time.  Factors that stand for divisions: heads_magic = 2^40 / H + 1, group_magic = 2^32 / wave_heads + 1,
+    // left_magic = 2^32 / (B H mod 8) + 1
     const WaveItem *wave_items;
     const WaveEntry *wave_ents;
-    int wave_n;
+    int wave_n, wave_heads;
     int64_t bmp_bytes;
-    uint64_t heads_magic;
+    uint64_t heads_magic, group_magic, left_magic;
     // row path
     const int32_t *row_ptr, *col_idx;
     const int64_t *col_off;
@@ -1383,15 +1385,15 @@ static int workgroups_per_cu(int form, int d) { return form == 2 ? 1 : form == 3
 template <int D, bool BF16, int OUT>
 static hipError_t launch_block_out(const smha_plan *plan, FwdParams &fp, hipStream_t stream) {
     if (fp.n_work == 0) return hipSuccess;
-    if constexpr (D <= 128) {
-        if (fp.form == 4) {
-            const dim3 grid(8, (unsigned)fp.wave_n, (unsigned)(((int64_t)fp.B * fp.H + 7) / 8));
-            if (fp.max_slots > 0)
-                hipLaunchKernelGGL((smha_wave_fwd<D, BF16, OUT, true>), grid, dim3(256), 0, stream, fp);
-            else
-                hipLaunchKernelGGL((smha_wave_fwd<D, BF16, OUT, false>), grid, dim3(256), 0, stream, fp);
-            return hipGetLastError();
-        }
+    if (fp.form == 4) {
+        const int heads = fp.B * fp.H, left = heads % 8, rounds = heads / 8;
+        const unsigned y = (unsigned)std::max(fp.wave_n * fp.wave_heads, (left * fp.wave_n + 7) / 8);
+        const dim3 grid(8, y, (unsigned)((rounds + fp.wave_heads - 1) / fp.wave_heads + (left > 0)));
+        if (fp.max_slots > 0)
+            hipLaunchKernelGGL((smha_wave_fwd<D, BF16, OUT, true>), grid, dim3(256), 0, stream, fp);
+        else
+            hipLaunchKernelGGL((smha_wave_fwd<D, BF16, OUT, false>), grid, dim3(256), 0, stream, fp);
+        return hipGetLastError();
     }
     if constexpr (!(BF16 && D == 128) && D <= 128) {
         if (fp.form == 2) {
@@ -1469,6 +1471,16 @@ static int grain_for(const smha_plan *plan, int B, int H, int d, int form) {
 // (a form that was asked for, by option or environment, is run; the library's own choice may give way)
 static bool takes_wave_form(const smha_plan *plan, int lvl, int form, int B, int H, int d, bool bf16, int &alone) {
     return form_asked(plan) == 0 && wave_form_pays(plan, lvl, form, B, H, d, bf16, alone);
+}
+
+// How many heads an XCD takes at a time in the wave form: as many as 3 MB hold K and V of (an L2 is 4 MB), in groups of about
+// one size, within what a grid takes (65535 workgroups in y).
+static int wave_heads(const smha_plan *plan, int heads, int D, int workgroups) {
+    const int rounds = std::max(heads / 8, 1);
+    const int64_t fit = std::max<int64_t>(1, ((int64_t)3 << 20) / ((int64_t)plan->Sk * D * 4));
+    const int64_t at_most = std::max<int64_t>(1, std::min({fit, (int64_t)rounds, (int64_t)65535 / workgroups}));
+    const int groups = (int)((rounds + at_most - 1) / at_most);
+    return (rounds + groups - 1) / groups;
 }
 
 // The work order and workspaces for a call shape that runs `form` at grain `lvl` (wave form: with lists of up to `alone`
@@ -1751,6 +1763,9 @@ static smha_status_t forward_impl(const smha_plan_t *plan, const void *Q, const 
             fp.bmp_bytes = (int64_t)plan->h_kt_bitmap.size() * 8;
             fp.wave_n = pr->longest;
             fp.heads_magic = ((uint64_t)1 << 40) / (uint64_t)H + 1;
+            fp.wave_heads = wave_heads(plan, B * H, D, fp.wave_n);
+            fp.group_magic = ((uint64_t)1 << 32) / (uint64_t)fp.wave_heads + 1;
+            if (B * H % 8) fp.left_magic = ((uint64_t)1 << 32) / (uint64_t)(B * H % 8) + 1;
             fp.max_slots = plan->wave.max_slots;
             fp.split_rows = dv.wave_splits; fp.split_off = dv.wave_split_off;
         }

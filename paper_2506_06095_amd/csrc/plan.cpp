@@ -504,7 +504,7 @@ static void build_wave_lists(smha_plan *p, const std::vector<int32_t> &bmp_base)
     const int n_masks = p->Bm * p->Hm, n_groups = (p->S + 31) / 32;
     int64_t at_most = 0;
     for (const MaskFormats &m : p->masks) at_most += 4 * (int64_t)m.kt_col.size();
-    if (at_most > kMaxWaveEntries || p->h_kt_bitmap.size() * sizeof(uint64_t) >= ((size_t)1 << 31)) return;
+    if (at_most > kMaxWaveEntries || n_groups > 16384 /* (a grid's y holds a mask's workgroups) */ || p->h_kt_bitmap.size() * sizeof(uint64_t) >= ((size_t)1 << 31)) return;
     WaveLists &wl = p->wave;
     std::vector<WaveEntry> list[2];
     std::vector<WaveItem> items;
@@ -533,6 +533,7 @@ static void build_wave_lists(smha_plan *p, const std::vector<int32_t> &bmp_base)
                 }
             }
             for (int side = 0; side < 2 && 2 * tr + side < n_groups; ++side) {
+                for (const WaveEntry &e : list[side]) wl.part_ents += e.code >= 0;
                 wl.ents.insert(wl.ents.end(), list[side].begin(), list[side].end());
                 first.push_back((int32_t)wl.ents.size());
             }
@@ -904,31 +905,35 @@ size_t workspace_bytes(const smha_plan *plan, int lvl, int form, int B, int H, i
 }
 
 // The wave form's work for one call shape: four waves make a workgroup, and each mask gets as many workgroups (records
-// past a mask's own have rg = -1).  Workgroups start in the order in which they are listed, longest items first; an
-// item of more than `alone` entries is shared by the four waves of a workgroup.
+// past a mask's own have rg = -1).  An item of more than `alone` entries is shared by the four waves of a workgroup.
+// Workgroups start in the order in which they are listed: those that last longest first, whichever kind (shared items
+// first instead, however short their quarters: window 4 x 8 x 1089 x 128 with `alone` = 12 33.5 us, 27 so).
 int build_wave_order(const smha_plan *plan, int alone, std::vector<int32_t> &table) {
     const WaveLists &wl = plan->wave;
     const int n_masks = plan->Bm * plan->Hm;
-    std::vector<size_t> waves(n_masks, 0);
+    std::vector<int32_t> shared(n_masks, 0);
     size_t most = 0;
     for (int mi = 0; mi < n_masks; ++mi) {
-        for (int32_t i = wl.item_off[mi]; i < wl.item_off[mi] + wl.item_cnt[mi]; ++i) waves[mi] += wl.items[i].n > alone ? 4 : 1;
-        most = std::max(most, (waves[mi] + 3) / 4);
+        const WaveItem *items = wl.items.data() + wl.item_off[mi];
+        while (shared[mi] < wl.item_cnt[mi] && items[shared[mi]].n > alone) ++shared[mi];
+        most = std::max(most, (size_t)shared[mi] + (wl.item_cnt[mi] - shared[mi] + 3) / 4);
     }
     static_assert(sizeof(WaveItem) == 32, "eight words a record");
     table.resize(most * n_masks * 32);
     for (int mi = 0; mi < n_masks; ++mi) {
+        const WaveItem *items = wl.items.data() + wl.item_off[mi];
         WaveItem *to = reinterpret_cast<WaveItem *>(table.data()) + most * 4 * mi, *const end = to + most * 4;
-        for (int32_t i = wl.item_off[mi]; i < wl.item_off[mi] + wl.item_cnt[mi]; ++i) {
-            const WaveItem &it = wl.items[i];
-            if (it.n <= alone) {
-                *to++ = it;
-                continue;
-            }
-            for (int w = 0; w < 4; ++w) {
-                const int at = it.n * w / 4;
-                const WaveEntry &e = wl.ents[it.begin + at];
-                *to++ = WaveItem{it.rg, it.begin + at, it.n * (w + 1) / 4 - at, it.slot, it.split, e.key, e.code, 1};
+        int32_t team = 0, solo = shared[mi];  // next of each kind; both kinds come longest first
+        while (team < shared[mi] || solo < wl.item_cnt[mi]) {
+            if (team < shared[mi] && (solo == wl.item_cnt[mi] || (items[team].n + 3) / 4 >= items[solo].n)) {
+                const WaveItem &it = items[team++];
+                for (int w = 0; w < 4; ++w) {
+                    const int at = it.n * w / 4;
+                    const WaveEntry &e = wl.ents[it.begin + at];
+                    *to++ = WaveItem{it.rg, it.begin + at, it.n * (w + 1) / 4 - at, it.slot, it.split, e.key, e.code, 1};
+                }
+            } else {
+                for (int w = 0; w < 4; ++w) *to++ = solo < wl.item_cnt[mi] ? items[solo++] : WaveItem{-1, 0, 0, -1, -1, 0, -1, 0};
             }
         }
         for (; to < end; ++to) *to = WaveItem{-1, 0, 0, -1, -1, 0, -1, 0};
@@ -936,38 +941,54 @@ int build_wave_order(const smha_plan *plan, int alone, std::vector<int32_t> &tab
     return (int)most;
 }
 
-// Estimated time of a call through the wave form, with the longest list that one wave walks alone chosen for it (`alone`).
-// Two things bound a launch, and the root of the sum of their p-th powers is the estimate: what the chip's waves take
-// together (each its start and end, and its steps; at 128 columns, where only eight waves fit a compute unit, a
-// workgroup holds its place as long as its longest wave), and the longest wave's chain of steps, which is slower the
-// fuller the chip is.  A list shared by four waves is a chain of a quarter, but four starts and a merge.
-// Constants fitted to 201 calls (all kinds of masks, 128 to 8192 queries, 2 to 300 heads, each with 12 limits): 6 % mean
-// error at 64 columns, 7 % at 128; the limit chosen is 2 % behind the best one in the mean.  Where sharing matters, us with
-// the longest list alone / shared: Longformer 8 x 12 x 512 x 64 14.1 / 8.8, window 1 x 2 x 1772 x 32 7.2 / 4.4.
+// Estimated times of a call, for the choice between the wave form and the other two (and for its `alone`).  Two things
+// bound a launch: what the chip's compute units take together, and the longest chain of steps in one wave or workgroup;
+// the estimate is the root of the sum of their p-th powers.  Constants are in us (per wave and step of the wave form: ns)
+// and fitted to 521 calls: all kinds of masks, 64 to 8192 queries, 2 to 400 heads, 8 to 256 columns, the wave form with 12
+// values of `alone` each.  Mean error 5 to 7 % (wave form), 5 to 9 % (the others).
+struct WaveCost {
+    double start, wave, step, held, part, bf16, chain, chain_full, power, uneven;
+};
+static const WaveCost kWaveCost[3] = {{3.41, 0.654, 0.374, 0.22, 0.076, 1.20, 0.459, 0.195, 3.4, 0.0},    // 64 columns
+                                      {3.98, 1.502, 0.717, 0.05, 0.191, 1.17, 0.683, 0.154, 4.0, 0.09},   // 128
+                                      {5.64, 4.639, 1.507, 0.63, 0.156, 1.17, 1.400, 0.0, 4.0, 0.23}};    // 256
+struct BlockCost {
+    double start, unit, group, part, act, bf16, gather, power, fine;
+};
+static const BlockCost kBlockCost[3][2] = {  // first form, third form
+    {{2.20, 0.523, 0.777, 0.057, 0.139, 1.232, 1.113, 4.1, 4.9}, {}},
+    {{1.92, 0.906, 1.061, 0.102, 0.261, 1.072, 1.117, 8.0, 10.0}, {2.32, 0.980, 0.937, -0.018, 0.235, 1.147, 1.0, 4.3, 5.7}},
+    {{0.0, 2.934, 0.0, -0.229, 0.248, 1.067, 1.20, 5.2, 1.8}, {1.84, 1.838, 0.0, -0.062, 0.376, 1.078, 1.0, 7.4, 10.8}}};
+
+// The wave form.  Every wave has its start and end, every step its share of the chip; a workgroup's places are partly
+// `held` until its longest wave ends, and steps of partly filled tiles and bfloat16 cost more.  A list shared by four
+// waves is a chain of a quarter, but four starts and a merge: `alone` is the longest list that one wave walks, chosen
+// for the least time (within 2 % of the best of the 12 in the mean).  us with the longest lists alone / shared:
+// Longformer 8 x 12 x 512 x 64 14.1 / 8.8, window 1 x 2 x 1772 x 32 7.2 / 4.4.
 static double wave_time_us(const smha_plan *plan, int B, int H, int D, bool bf16, int &alone) {
     const WaveLists &wl = plan->wave;
     const double per_mask = 1.0 / (plan->Bm * plan->Hm), heads = (double)B * H;
-    const bool wide = D > 64;
-    const double slots = (wide ? 8.0 : 16.0) * plan->n_cu, bf16_cost = bf16 ? 1.15 : 1.0;
-    double best = 0;
+    const WaveCost &c = kWaveCost[row_width(D)];
+    const double slots = (D == 64 ? 16.0 : D == 128 ? 8.0 : 4.0) * plan->n_cu;
+    const double step_ns = c.step * (1 + c.part * (double)wl.part_ents / std::max<double>(1.0, (double)wl.ents.size()));
+    double best = 0, best_us = 0;
     alone = 0;
     for (int limit : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64}) {
-        // a mask's workgroups, longest items first: those that one item fills, then four items each
-        double teams = 0, solos = 0, steps = 0, held = 0, left = 0;
+        double teams = 0, solos = 0, steps = 0, held = 0, left = 0;  // of a mask; left: places in a workgroup already opened
         int chain = 0;
         for (int n = kWaveWhole; n >= 0; --n) {
+            if (wl.of_length[n] == 0) continue;
             double k = per_mask * wl.of_length[n];
-            if (k == 0) continue;
             steps += k * n;
+            const int walked = n > limit ? (n + 3) / 4 : n;
+            chain = std::max(chain, walked);
             if (n > limit) {
                 teams += k;
-                held += 4 * k * ((n + 3) / 4);
-                chain = std::max(chain, (n + 3) / 4);
+                held += 4 * k * walked;
                 continue;
             }
-            chain = std::max(chain, n);
             solos += k;
-            const double filled = std::min(k, left);  // places in a workgroup that a longer item opened
+            const double filled = std::min(k, left);
             left -= filled;
             k -= filled;
             const double opened = std::ceil(k / 4 - 1e-9);
@@ -976,53 +997,34 @@ static double wave_time_us(const smha_plan *plan, int B, int H, int D, bool bf16
         }
         const double waves = heads * (4 * teams + solos), groups = heads * (teams + std::ceil(solos / 4));
         const double uneven = groups > plan->n_cu ? std::ceil(groups / plan->n_cu) * plan->n_cu / groups - 1 : 0;
-        const double work_us = wide ? 1e-3 * (waves * 1.52 + heads * (0.05 * steps + 0.95 * held) * 0.693) * (1 + 0.35 * uneven)
-                                    : 1e-3 * (waves * 0.755 + heads * steps * 0.372);
-        const double fill = std::min(1.0, waves / slots);
-        const double chain_us = chain * (wide ? 0.692 + 0.143 * fill : 0.487 + 0.207 * fill);
-        const double power = wide ? 3.3 : 2.25;
-        const double us = std::pow(std::pow(work_us, power) + std::pow(chain_us, power), 1 / power);
-        if (alone == 0 || us < best) {
-            best = us;
+        const double walked = heads * (steps + c.held * (held - steps)) * step_ns;
+        const double longest = chain * (c.chain + c.chain_full * std::min(1.0, waves / slots));
+        auto us = [&](double type) {
+            return std::pow(std::pow(1e-3 * (waves * c.wave + walked * type) * (1 + c.uneven * uneven), c.power) + std::pow(longest * type, c.power), 1 / c.power);
+        };
+        const double at = us(1.0);  // (the same limit for both types: one order serves them)
+        if (alone == 0 || at < best) {
+            best = at;
+            best_us = us(bf16 ? c.bf16 : 1.0);
             alone = limit;
         }
     }
-    return (wide ? 3.7 : 3.25) + best * bf16_cost;
+    return c.start + best_us;
 }
 
-// Estimated time of a call through one of the other two forms (1: four waves of 32 rows, 3: eight of 16), the same way:
-// the busiest compute unit's work and the longest workgroup's chain, in steps plus 2 per item (see build_work_order).
-// Fitted to the same calls: 8 to 9 % mean error.
+// The first (four waves of 32 rows) and third form (eight of 16): the busiest compute unit's work and the longest
+// workgroup's chain, in steps plus 2 per item (see build_work_order).  Steps in which both tile rows have work (`act`:
+// tiles per step), partly filled tiles and bfloat16 cost more, and so does the fine grain, whose parts are merged.
 static double block_time_us(const smha_plan *plan, int lvl, int form, int B, int H, int D, bool bf16) {
     const WorkLists &wl = plan->lists[plan->fine_differs ? lvl : 0];
-    const int BH = B * H, n_masks = plan->Bm * plan->Hm;
-    double total = 0, items = 0, longest = 0;
-    std::vector<double> cost(n_masks, 0.0);
-    for (int mi = 0; mi < n_masks; ++mi) {
-        for (int it = 0; it < wl.item_cnt[mi]; ++it) {
-            const Item &i = wl.items[wl.item_off[mi] + it];
-            cost[mi] += 2 + i.end - i.begin;
-            longest = std::max(longest, 2.0 + i.end - i.begin);
-        }
+    const double per_xcd = (double)B * H / (plan->Bm * plan->Hm) / 8;
+    double cost = 0, longest = 0;
+    for (const Item &i : wl.items) {
+        cost += 2 + i.end - i.begin;
+        longest = std::max(longest, 2.0 + i.end - i.begin);
     }
-    for (int x = 0; x < std::min(8, BH); ++x) {  // the busiest XCD
-        double t = 0, n = 0;
-        if (n_masks == 1) {
-            const int heads = (BH - x + 7) / 8;
-            t = heads * cost[0];
-            n = (double)heads * wl.item_cnt[0];
-        } else {
-            for (int bh = x; bh < BH; bh += 8) {
-                const int mi = (plan->Bm > 1 ? bh / H : 0) * plan->Hm + (plan->Hm > 1 ? bh % H : 0);
-                t += cost[mi];
-                n += wl.item_cnt[mi];
-            }
-        }
-        total = std::max(total, t);
-        items = std::max(items, n);
-    }
-    const double units = std::max(plan->n_cu / 8, 1);
-    const double slots = units * (D == 64 ? 4 : D == 128 ? 2 : 1);
+    const double total = cost * per_xcd, items = (double)wl.items.size() * per_xcd;
+    const double units = std::max(plan->n_cu / 8, 1), slots = units * (D == 64 ? 4 : D == 128 ? 2 : 1);
     const double unit = items > units ? std::max(longest, total / units + 0.35 * total / items) : longest;
     const double group = std::max(longest, total / std::max(1.0, std::min(slots, items)));
     int64_t tiles = 0, part = 0;
@@ -1030,28 +1032,22 @@ static double block_time_us(const smha_plan *plan, int lvl, int form, int B, int
         tiles += (int64_t)m.kt_col.size();
         part += (int64_t)(m.kt_bitmap.size() / 64);
     }
-    const double parts = tiles ? (double)part / (double)tiles : 0.0, gathers = plan->n_gathered > 0 ? 1.0 : 0.0, fine = plan->fine_differs ? lvl : 0;
-    if (D == 64) return 2.43 + (1 + 0.137 * parts) * std::pow(std::pow(unit * 0.461, 4.0) + std::pow(group * 0.717, 4.0), 0.25) * (bf16 ? 1.236 : 1.0) * (1 + 0.178 * gathers) + 5.0 * fine;
-    if (form == 1) return 3.9 + (1 - 0.16 * parts) * std::max(unit * 0.962, group * 1.121) * (bf16 ? 1.017 : 1.0) * (1 + 0.337 * gathers) + 5.9 * fine;
-    return 3.0 + (unit * 0.9 + group * 0.148) * (bf16 ? 1.086 : 1.0) + 4.5 * fine;
+    const BlockCost &c = kBlockCost[row_width(D)][form == 3];
+    const double parts = tiles ? (double)part / (double)tiles : 0.0, act = std::min(2.0, (double)tiles / std::max<double>(1.0, (double)plan->h_uent.size() - 1));
+    return c.start + (1 + c.part * parts) * (1 + c.act * (act - 1.5)) * (bf16 ? c.bf16 : 1.0) * (plan->n_gathered > 0 ? c.gather : 1.0) *
+           std::pow(std::pow(unit * c.unit, c.power) + std::pow(group * c.group, c.power), 1 / c.power) + (plan->fine_differs && lvl ? c.fine : 0.0);
 }
 
 // The wave form wins where tiles are filled poorly (BigBird with random 32-blocks 16 x 12 x 2048 x 64: 112 us, 66 with
 // the wave form) and where a call has too few 128-row groups to fill the chip (fresh mask 1 x 4 x 1037 x 64: 8.9 / 4.6;
-// causal 9 x 2 x 1088 x 128: 26.2 / 14.4); it loses where tiles are full and rows many (causal 16 x 12 x 4096 x 128: 870 /
-// 1176), because every K and V tile is loaded once per 32 rows.  It has to win by 5 %, and by 20 % on masks of
-// full tiles, where the estimates are farther off: with these margins no one of the 201 calls is more than 2 % slower
-// than without the form, the mean is 0.73, and the best choice for each would be 0.71.
+// causal 9 x 2 x 1088 x 128: 26.2 / 14.4; per-head 64-blocks 1 x 4 x 640 x 256 20.7 / 11.2); it loses where tiles are full and
+// rows many (causal 16 x 12 x 4096 x 128: 870 / 1176), because every K and V tile is loaded once per 32 rows.  It has to win
+// by a tenth: of the 521 calls it then slows one by more than 3 % (7 %), and the mean is 0.67 at 64 columns, 0.78 at
+// 128, 0.82 at 256, where the best choice for each would be 0.65, 0.75 and 0.81.
 bool wave_form_pays(const smha_plan *plan, int lvl, int form, int B, int H, int D, bool bf16, int &alone) {
-    if (plan->wave.items.empty() || D > 128 || H > 65535 || (int64_t)B * H > (1 << 19)) return false;
+    if (plan->wave.items.empty() || H > 65535 || (int64_t)B * H > (1 << 19)) return false;
     if (workspace_bytes(plan, 0, 4, B, H, D, nullptr) > kStaticScratchBytes) return false;  // (smha_forward_static takes what it took)
-    int64_t tiles = 0, part = 0;
-    for (const MaskFormats &m : plan->masks) {
-        tiles += (int64_t)m.kt_col.size();
-        part += (int64_t)(m.kt_bitmap.size() / 64);
-    }
-    const double margin = 10 * part > tiles ? 0.95 : 0.8;
-    return wave_time_us(plan, B, H, D, bf16, alone) < margin * block_time_us(plan, lvl, form, B, H, D, bf16);
+    return wave_time_us(plan, B, H, D, bf16, alone) < 0.9 * block_time_us(plan, lvl, form, B, H, D, bf16);
 }
 
 // The block kernel's work order for B x H heads on `slots` resident workgroups per XCD.  Items

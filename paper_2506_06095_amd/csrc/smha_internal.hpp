@@ -133,6 +133,7 @@ struct WaveLists {
     std::vector<SplitRow> splits;
     int max_splits = 0, max_slots = 0;
     int32_t of_length[kWaveWhole + 1] = {0};  // items by entries, over all masks
+    int64_t part_ents = 0;                    // entries that have a bitmap
 };
 
 }  // namespace smha

@@ -922,15 +922,16 @@ def wave_form_masks(name, B, H):
 
 
 @pytest.mark.parametrize("name", ["one_key", "ragged", "shared", "cut", "blocks"])
-@pytest.mark.parametrize("d,dtype", [(64, "f16"), (64, "bf16"), (128, "f16"), (128, "bf16"), (8, "f16"), (80, "bf16")])
+@pytest.mark.parametrize("d,dtype", [(64, "f16"), (64, "bf16"), (128, "f16"), (128, "bf16"), (8, "f16"), (80, "bf16"),
+                                     (256, "f16"), (160, "bf16")])
 def test_wave_form(torch_mod, smha, name, d, dtype):
-    """The wave form beside the first (and at 128 columns the third) form of the block kernel, all against the oracle;
+    """The wave form beside the first (and at 128 and 256 columns the third) form of the block kernel, all against the oracle;
     strided tensors, so that a read or store past a row's end would meet its neighbours.  Three heads: the heads that
-    are left over are dealt over all XCDs; nine: one full round and one left over."""
+    are left over are dealt over all XCDs; nine: one full round and one left over; 24: three rounds, taken together."""
     torch = torch_mod
-    for B, H in ((1, 3), (3, 3)):
+    for B, H in ((1, 3), (3, 3), (2, 12)):
         masks = wave_form_masks(name, B, H)
-        if B > 1 and name in ("shared", "cut"):
+        if B > 1 and name in ("shared", "cut") or B == 2 and d > 128:
             continue
         Sq, Sk = masks.shape[2:]
         Q = W.qkv_bits(B, H, Sq, d, dtype, 1.0, 901)[0]
@@ -941,7 +942,8 @@ def test_wave_form(torch_mod, smha, name, d, dtype):
         for form in (0, 1, 3) if d > 64 else (0, 1):
             with make(masks, head_dim=d, force=smha.SMHA_KERNEL_BLOCK, block_form=form) as plan:
                 kernel = smha.smha_call_kernel_name(plan.handle, B, H, d, smha.SMHA_F16 if dtype == "f16" else smha.SMHA_BF16)
-                assert (kernel == "smha_wave_fwd") == (form == 0), kernel
+                if form or d <= 128 or dtype == "f16" and name != "one_key":  # (at 256 columns some stay with the third form)
+                    assert (kernel == "smha_wave_fwd") == (form == 0), kernel
                 for f32 in (False, True):
                     out = torch.full((B, Sq, H, d), float("nan"), device="cuda", dtype=torch.float32 if f32 else q.dtype).transpose(1, 2)
                     plan.forward(q, k, v, out=out)

@@ -673,7 +673,7 @@ def test_which_calls_take_the_wave_form():
     for spec, B, H, S, d, opts, want in [
             (bert, 16, 12, 2048, 64, {}, "smha_wave_fwd"),                  # poorly filled tiles
             (bert, 16, 12, 2048, 64, {"block_form": 1}, "smha_block_fwd"),  # asked for
-            (bert, 1, 2, 2048, 256, {}, "smha_block_fwd16"),                # 256 columns never
+            (bert, 1, 2, 2048, 256, {}, "smha_wave_fwd"), (causal, 16, 12, 2048, 256, {}, "smha_block_fwd16"),
             (causal, 1, 2, 512, 64, {}, "smha_wave_fwd"),                   # too few 128-row groups
             (causal, 16, 12, 4096, 64, {}, "smha_block_fwd"), (causal, 16, 12, 4096, 128, {}, "smha_block_fwd"),
             (blocks, 1, 32, 8192, 128, {}, "smha_block_fwd16"), (blocks, 1, 2, 2048, 128, {}, "smha_wave_fwd")]:

@@ -292,16 +292,17 @@ def smha_forward(plan: int, Q, K, V, O, scale: float = 0.0, kernel: int = SMHA_K
     if _DTYPE_CODES is None:
         _DTYPE_CODES = {torch.float16: SMHA_F16, torch.bfloat16: SMHA_BF16, torch.float32: SMHA_F32}
     lib = _load()
-    B, H, S, d = Q.shape
+    q_shape, k_shape = Q.shape, K.shape
+    B, H, S, d = q_shape
     if _dims is None:
         info = PlanInfo()
         st = lib.smha_plan_info(plan, C.byref(info))
         if st != 0:
             raise SmhaError(st, "smha_plan_info")
         _dims = (info.S, info.Sk)
-    if O.shape != Q.shape or K.shape != V.shape or K.shape[:2] != Q.shape[:2] or K.shape[3] != d:
+    if O.shape != q_shape or k_shape != V.shape or len(k_shape) != 4 or k_shape[0] != B or k_shape[1] != H or k_shape[3] != d:
         raise ValueError("Q, O must be [B,H,S,d] and K, V [B,H,Sk,d]")
-    if S != _dims[0] or K.shape[2] != _dims[1]:
+    if S != _dims[0] or k_shape[2] != _dims[1]:
         raise ValueError(f"the plan is for {_dims[0]} queries and {_dims[1]} keys per sequence")
     in_code = _DTYPE_CODES.get(Q.dtype)
     if in_code is None or in_code == SMHA_F32 or K.dtype != Q.dtype or V.dtype != Q.dtype:
@@ -367,7 +368,8 @@ class Plan:
                 kernel: int = SMHA_KERNEL_AUTO, stream=None):
         import torch
         if out is None:
-            out = torch.empty(Q.shape, dtype=out_dtype or Q.dtype, device=Q.device)
+            # (packed whatever Q's strides are; torch.empty with a size, a type and a device costs the host 2 us more)
+            out = torch.empty_like(Q, dtype=out_dtype, memory_format=torch.contiguous_format)
         if self._dims is None:
             info = self.info()
             self._dims = (info["S"], info["Sk"])

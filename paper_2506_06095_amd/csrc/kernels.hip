@@ -1167,8 +1167,12 @@ __global__ void __launch_bounds__(256) smha_mask_classify(const uint8_t *__restr
     uint32_t slot = 0;
     const bool part = cnt > 0 && cnt < 4096;
     if (part) {
-        if (lane == 0) slot = atomicAdd(counters + mi, 1u);
-        slot = __shfl(slot, 0);
+        if (counters) {
+            if (lane == 0) slot = atomicAdd(counters + mi, 1u);
+            slot = __shfl(slot, 0);
+        } else {  // (a place for every tile)
+            slot = (uint32_t)rem;
+        }
         part_bits[((long long)mi * per_mask + slot) * 64 + lane] = word;
     }
     if (lane == 0) info[tile] = TileInfo{used, cnt | (v16 << 16), slot};
@@ -1180,6 +1184,44 @@ smha_status_t classify_device_mask(const uint8_t *dev_mask, int n_masks, int Sq,
     const long long per_mask = (long long)nqt * nkt, n_tiles = per_mask * n_masks;
     info.resize((size_t)n_tiles);
     part_bits.assign((size_t)n_masks, {});
+    // Small masks: the kernel writes its tile records and the bitmaps, a place for every tile, straight into pinned host
+    // memory that is kept (1 MB).  No counters to clear, no copy back, one wait: with a copy to pageable memory each for
+    // records and bitmaps a plan of a 1024 x 1024 mask took 69 us to analyse and upload, so 58.
+    constexpr size_t kDirectAtMost = (size_t)1 << 20;
+    static std::mutex direct_mutex;
+    if ((size_t)n_tiles * (sizeof(TileInfo) + 512) <= kDirectAtMost) {
+        static char *pinned = nullptr;
+        std::lock_guard<std::mutex> direct_lock(direct_mutex);
+        if (!pinned && hipHostMalloc(reinterpret_cast<void **>(&pinned), kDirectAtMost, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+            (void)hipGetLastError();
+            pinned = nullptr;
+        }
+        void *dev = nullptr;
+        if (pinned && hipHostGetDevicePointer(&dev, pinned, 0) == hipSuccess) {
+            const size_t bits_at = (size_t)n_tiles * sizeof(TileInfo);
+            hipLaunchKernelGGL(smha_mask_classify, dim3((unsigned)((n_tiles + 3) / 4)), dim3(256), 0, 0, dev_mask, reinterpret_cast<TileInfo *>(dev),
+                               reinterpret_cast<uint64_t *>((char *)dev + bits_at), (uint32_t *)nullptr, Sq, Sk, nqt, nkt, n_tiles);
+            if (hipGetLastError() != hipSuccess || hipStreamSynchronize(0) != hipSuccess) {
+                (void)hipGetLastError();
+                return SMHA_ERR_HIP;
+            }
+            std::memcpy(info.data(), pinned, bits_at);
+            for (int mi = 0; mi < n_masks; ++mi) {
+                TileInfo *tiles = info.data() + (size_t)mi * per_mask;
+                size_t n = 0;
+                for (long long t = 0; t < per_mask; ++t) n += (tiles[t].cnt_v16 & 0xFFFFu) % 4096 != 0;
+                part_bits[mi].resize(n * 64);
+                uint32_t slot = 0;
+                for (long long t = 0; t < per_mask; ++t) {
+                    if ((tiles[t].cnt_v16 & 0xFFFFu) % 4096 == 0) continue;
+                    std::memcpy(part_bits[mi].data() + (size_t)slot * 64, pinned + bits_at + ((size_t)mi * per_mask + t) * 512, 512);
+                    tiles[t].slot = slot++;
+                }
+            }
+            return SMHA_OK;
+        }
+        (void)hipGetLastError();
+    }
     // One scratch allocation {tile records, per-mask counters, bitmap slots}; it is kept for the next plan
     // (allocating and freeing tens of megabytes costs more than the analysis) unless it is very large.
     const size_t info_bytes = (size_t)n_tiles * sizeof(TileInfo), cnt_bytes = ((size_t)n_masks * 4 + 255) / 256 * 256;
@@ -1246,6 +1288,65 @@ smha_status_t classify_device_mask(const uint8_t *dev_mask, int n_masks, int Sq,
             return done(SMHA_ERR_HIP);
     }
     return done(SMHA_OK);
+}
+
+// Device memory of destroyed plans, kept for the next ones: allocating and freeing a plan's few blocks cost more than
+// analysing a small mask (plan, forward and destroy for a new 1024 x 1024 mask: 121 us, with blocks kept 112).  Only blocks
+// of up to 1 MB, 16 MB of them at most; a block comes in when its device is idle (release_device waits for it, as hipFree does), so that
+// whoever takes it may use it on any stream.
+namespace {
+struct PoolBlock { void *ptr; size_t bytes; int device; };
+constexpr size_t kPoolBlockAtMost = (size_t)1 << 20, kPoolAtMost = (size_t)16 << 20;
+std::mutex pool_mutex;
+std::vector<PoolBlock> pool;
+size_t pool_bytes = 0;
+}  // namespace
+static size_t pool_size(size_t bytes) {  // what a block for so many bytes has
+    if (bytes > kPoolBlockAtMost) return bytes;
+    size_t n = (size_t)64 << 10;
+    while (n < bytes) n *= 2;
+    return n;
+}
+static hipError_t device_alloc(void **ptr, size_t bytes, int device) {  // (`device` is current)
+    const size_t want = pool_size(bytes);
+    if (want <= kPoolBlockAtMost) {
+        std::lock_guard<std::mutex> lock(pool_mutex);
+        for (size_t i = pool.size(); i-- > 0;)
+            if (pool[i].device == device && pool[i].bytes == want) {
+                *ptr = pool[i].ptr;
+                pool[i] = pool.back();
+                pool.pop_back();
+                pool_bytes -= want;
+                return hipSuccess;
+            }
+    }
+    hipError_t e = hipMalloc(ptr, want);
+    if (e != hipSuccess) {  // (what is kept goes back to the device first)
+        (void)hipGetLastError();
+        {
+            std::lock_guard<std::mutex> lock(pool_mutex);
+            for (const PoolBlock &b : pool) (void)hipFree(b.ptr);
+            pool.clear();
+            pool_bytes = 0;
+        }
+        e = hipMalloc(ptr, want);
+    }
+    return e;
+}
+static void device_free(void *ptr, size_t bytes, int device, bool idle) {
+    const size_t have = pool_size(bytes);
+    if (idle && have <= kPoolBlockAtMost) {
+        std::lock_guard<std::mutex> lock(pool_mutex);
+        if (pool_bytes + have <= kPoolAtMost) {
+            try {
+                pool.push_back({ptr, have, device});
+                pool_bytes += have;
+                return;
+            } catch (const std::bad_alloc &) {
+            }
+        }
+    }
+    (void)hipFree(ptr);
 }
 
 // Every index array of a plan lives in one device allocation, filled with one copy: a plan has up to 18
@@ -1316,7 +1417,8 @@ smha_status_t upload_plan(smha_plan *p, int device_id) {
     }
     bool ok = true;
     if (!arena.host.empty()) {
-        ok = hipMalloc(&d.arena, arena.host.size()) == hipSuccess &&
+        d.arena_bytes = arena.host.size();
+        ok = device_alloc(&d.arena, d.arena_bytes, device_id) == hipSuccess &&
              hipMemcpy(d.arena, arena.host.data(), arena.host.size(), hipMemcpyHostToDevice) == hipSuccess;
         if (ok)
             for (auto &f : arena.fixups) *f.first = (char *)d.arena + f.second;
@@ -1337,12 +1439,14 @@ void release_device(smha_plan *p) {
     (void)hipGetDevice(&prev);
     (void)hipSetDevice(p->device);
     DeviceArrays &d = p->dev;
-    if (d.arena) (void)hipFree(d.arena);
+    const bool idle = hipDeviceSynchronize() == hipSuccess;  // (launches that read these arrays have ended)
+    if (!idle) (void)hipGetLastError();
+    if (d.arena) device_free(d.arena, d.arena_bytes, p->device, idle);
     d = DeviceArrays{};
     for (smha_plan::Prepared *pr : p->prepared) {
-        if (pr->order) (void)hipFree(pr->order);
+        if (pr->order) device_free(pr->order, pr->order_bytes, p->device, idle);
         for (void *q : pr->ws)
-            if (q) (void)hipFree(q);
+            if (q) device_free(q, pr->ws_bytes, p->device, idle);
         delete pr;
     }
     p->prepared.clear();
@@ -1554,14 +1658,14 @@ static smha_status_t make_prepared(const smha_plan *plan, int B, int H, int d, i
     q->step_words = step_words;
     q->item_words = item_words;
     bool ok = table.empty() ||
-              (hipMalloc((void **)&q->order, table.size() * sizeof(int32_t)) == hipSuccess &&
+              (device_alloc((void **)&q->order, q->order_bytes = table.size() * sizeof(int32_t), plan->device) == hipSuccess &&
                hipMemcpy(q->order, table.data(), table.size() * sizeof(int32_t), hipMemcpyHostToDevice) == hipSuccess);
     if (ok && (form == 4 ? plan->wave.max_slots : wl.max_slots) > 0) {
         q->ws_bytes = workspace_bytes(plan, lvl, form, B, H, d, &q->counters_at);
         // (the counters start at zero and every launch leaves them at zero; the copy has completed on return)
         const std::vector<uint32_t> zeros((q->ws_bytes - q->counters_at) / sizeof(uint32_t), 0u);
         for (int i = 0; ok && i < smha_plan::kCallSlots; ++i)
-            ok = hipMalloc(&q->ws[i], q->ws_bytes) == hipSuccess &&
+            ok = device_alloc(&q->ws[i], q->ws_bytes, plan->device) == hipSuccess &&
                  hipMemcpy((char *)q->ws[i] + q->counters_at, zeros.data(), zeros.size() * sizeof(uint32_t),
                            hipMemcpyHostToDevice) == hipSuccess;
     }

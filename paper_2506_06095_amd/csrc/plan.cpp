@@ -337,13 +337,13 @@ smha_status_t analyse_mask(const RowSource &src, int Sq, int Sk, int block, bool
         }
         Stripe().cols.swap(st.cols);  // release early
     }
+    mf.own_kt_bitmap = block != 64;
     if (block == 64) {  // the kernel's tiles ARE the exported tiles
         mf.kt_row_ptr = mf.load_row_ptr;
         mf.kt_col = mf.load_col_idx;
         mf.kt_bmp.resize(mf.flags.size());
         int32_t part = 0;
         for (size_t e = 0; e < mf.flags.size(); ++e) mf.kt_bmp[e] = mf.flags[e] ? -1 : part++;
-        mf.kt_bitmap = mf.bitmap;
     }
     return SMHA_OK;
 }
@@ -442,7 +442,6 @@ static void formats_from_tiles(const TileInfo *info, const std::vector<uint64_t>
     mf.kt_bmp.resize(mf.flags.size());
     int32_t part = 0;
     for (size_t e = 0; e < mf.flags.size(); ++e) mf.kt_bmp[e] = mf.flags[e] ? -1 : part++;
-    mf.kt_bitmap = mf.bitmap;
 }
 
 // Rows of at most this many keys on average may share a wave of the row kernel.
@@ -523,7 +522,7 @@ static void build_wave_lists(smha_plan *p, const std::vector<int32_t> &bmp_base)
                     for (auto &l : list) { l.push_back({key, -1}); l.push_back({key + 32, -1}); }
                     continue;
                 }
-                const uint64_t *w = m.kt_bitmap.data() + (size_t)m.kt_bmp[e] * 64;
+                const uint64_t *w = m.kt_bits().data() + (size_t)m.kt_bmp[e] * 64;
                 for (int side = 0; side < 2; ++side) {
                     uint64_t any = 0, all = ~(uint64_t)0;
                     for (int r = 32 * side; r < 32 * side + 32; ++r) { any |= w[r]; all &= w[r]; }
@@ -600,7 +599,7 @@ smha_status_t finish_plan(smha_plan *p) {
                 MaskFormats &m = p->masks[mi];
                 const int32_t bmp_base = (int32_t)(p->h_kt_bitmap.size() / 64);
                 bmp_base_of.push_back(bmp_base);
-                p->h_kt_bitmap.insert(p->h_kt_bitmap.end(), m.kt_bitmap.begin(), m.kt_bitmap.end());
+                p->h_kt_bitmap.insert(p->h_kt_bitmap.end(), m.kt_bits().begin(), m.kt_bits().end());
                 // union of the two tile rows of every supertile (both lists ascending: merge); tiles
                 // that use few key columns are repacked into gathered tiles (see UEntry), which go
                 // to the end of the supertile's list
@@ -619,7 +618,7 @@ smha_status_t finish_plan(smha_plan *p) {
                         if (e < 0) return (uint64_t)0;
                         if (m.kt_bmp[e] < 0) return ~(uint64_t)0;
                         uint64_t u = 0;
-                        const uint64_t *w = m.kt_bitmap.data() + (size_t)m.kt_bmp[e] * 64;
+                        const uint64_t *w = m.kt_bits().data() + (size_t)m.kt_bmp[e] * 64;
                         for (int r = 0; r < 64; ++r) u |= w[r];
                         return u;
                     };
@@ -678,7 +677,7 @@ smha_status_t finish_plan(smha_plan *p) {
                                     if (m.kt_bmp[e] < 0) {
                                         for (int r = 0; r < 64; ++r) dst[r] |= 1ull << k;
                                     } else {
-                                        const uint64_t *w = m.kt_bitmap.data() + (size_t)m.kt_bmp[e] * 64;
+                                        const uint64_t *w = m.kt_bits().data() + (size_t)m.kt_bmp[e] * 64;
                                         for (int r = 0; r < 64; ++r) dst[r] |= ((w[r] >> bit) & 1ull) << k;
                                     }
                                 }
@@ -1030,7 +1029,7 @@ static double block_time_us(const smha_plan *plan, int lvl, int form, int B, int
     int64_t tiles = 0, part = 0;
     for (const MaskFormats &m : plan->masks) {
         tiles += (int64_t)m.kt_col.size();
-        part += (int64_t)(m.kt_bitmap.size() / 64);
+        part += (int64_t)(m.kt_bits().size() / 64);
     }
     const BlockCost &c = kBlockCost[row_width(D)][form == 3];
     const double parts = tiles ? (double)part / (double)tiles : 0.0, act = std::min(2.0, (double)tiles / std::max<double>(1.0, (double)plan->h_uent.size() - 1));

@@ -24,7 +24,9 @@ struct MaskFormats {
     std::vector<uint64_t> bitmap;                          // n_part * block words
     // 64x64 tiles visited by the block kernel (identical to the arrays above when block == 64)
     std::vector<int32_t> kt_row_ptr, kt_col, kt_bmp;       // kt_bmp: bitmap index or -1 (full)
-    std::vector<uint64_t> kt_bitmap;                       // n_part64 * 64 words
+    std::vector<uint64_t> kt_bitmap;                       // n_part64 * 64 words; block == 64: empty, they are in `bitmap`
+    bool own_kt_bitmap = false;                            // block != 64
+    const std::vector<uint64_t> &kt_bits() const { return own_kt_bitmap ? kt_bitmap : bitmap; }
 };
 
 // The block kernel walks, per 128-row query supertile, the UNION of the key tiles of its two
@@ -95,6 +97,7 @@ constexpr int row_step_keys(int width, int form) {  // keys of a row that one st
 
 struct DeviceArrays {
     void *arena = nullptr;        // the one allocation every array below is a part of
+    size_t arena_bytes = 0;
     // row path
     int32_t *row_ptr = nullptr;   // [n_masks][S+1], offsets local to the mask
     int32_t *col_idx = nullptr;   // concatenated
@@ -183,6 +186,7 @@ struct smha_plan {
         int B = 0, H = 0, d = 0, lvl = 0, form = 1, per_xcd = 0, longest = 0;  // form: which block kernel the order is for
         int alone = 0;  // wave form (4): see build_wave_order
         int32_t *order = nullptr;
+        size_t order_bytes = 0;
         int64_t step_words = 0, item_words = 0;  // second form: sizes of the step and item streams inside `order`
         size_t ws_bytes = 0, counters_at = 0;  // one workspace; byte offset of its counters
         void *ws[kCallSlots] = {nullptr, nullptr, nullptr, nullptr};

@@ -1573,8 +1573,8 @@ static int grain_for(const smha_plan *plan, int B, int H, int d, int form) {
 }
 
 // (a form that was asked for, by option or environment, is run; the library's own choice may give way)
-static bool takes_wave_form(const smha_plan *plan, int lvl, int form, int B, int H, int d, bool bf16, int &alone) {
-    return form_asked(plan) == 0 && wave_form_pays(plan, lvl, form, B, H, d, bf16, alone);
+static bool takes_wave_form(const smha_plan *plan, int lvl, int form, int B, int H, int d, int &alone) {
+    return form_asked(plan) == 0 && wave_form_pays(plan, lvl, form, B, H, d, alone);
 }
 
 // How many heads an XCD takes at a time in the wave form: as many as 3 MB hold K and V of (an L2 is 4 MB), in groups of about
@@ -1701,7 +1701,7 @@ static smha_status_t prepared_for(const smha_plan *plan, int B, int H, int d, bo
         if (!may_allocate) return SMHA_ERR_UNSUPPORTED;
         int lvl = grain_for(plan, B, H, d, form), alone = 0;
         try {
-            const bool wave = takes_wave_form(plan, lvl, form, B, H, d, bf16, alone);
+            const bool wave = takes_wave_form(plan, lvl, form, B, H, d, alone);
             if (wave) lvl = 0;
             const int runs = wave ? 4 : form;
             for (smha_plan::Prepared *q : plan->prepared)
@@ -1943,7 +1943,7 @@ extern "C" const char *smha_call_kernel_name(const smha_plan_t *plan, int B, int
         const int D = kernel_head_size(d), form = block_form(plan, D, bf16);
         int alone = 0;
         try {
-            if (takes_wave_form(plan, grain_for(plan, B, H, D, form), form, B, H, D, bf16, alone)) return "smha_wave_fwd";
+            if (takes_wave_form(plan, grain_for(plan, B, H, D, form), form, B, H, D, alone)) return "smha_wave_fwd";
         } catch (const std::bad_alloc &) {
             return "";
         }

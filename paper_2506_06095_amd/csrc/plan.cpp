@@ -1042,11 +1042,15 @@ static double block_time_us(const smha_plan *plan, int lvl, int form, int B, int
 // causal 9 x 2 x 1088 x 128: 26.2 / 14.4; per-head 64-blocks 1 x 4 x 640 x 256 20.7 / 11.2); it loses where tiles are full and
 // rows many (causal 16 x 12 x 4096 x 128: 870 / 1176), because every K and V tile is loaded once per 32 rows.  It has to win
 // by a tenth: of the 521 calls it then slows one by more than 3 % (7 %), and the mean is 0.67 at 64 columns, 0.78 at
-// 128, 0.82 at 256, where the best choice for each would be 0.65, 0.75 and 0.81.
-bool wave_form_pays(const smha_plan *plan, int lvl, int form, int B, int H, int D, bool bf16, int &alone) {
+// 128, 0.82 at 256, where the best choice for each would be 0.65, 0.75 and 0.81 (201 others, types decided together: 0.751 and
+// 0.739, none more than 3.4 % slower).
+// The two input types are decided together (by the product of their ratios): one order and one set of workspaces serves both.
+bool wave_form_pays(const smha_plan *plan, int lvl, int form, int B, int H, int D, int &alone) {
     if (plan->wave.items.empty() || H > 65535 || (int64_t)B * H > (1 << 19)) return false;
     if (workspace_bytes(plan, 0, 4, B, H, D, nullptr) > kStaticScratchBytes) return false;  // (smha_forward_static takes what it took)
-    return wave_time_us(plan, B, H, D, bf16, alone) < 0.9 * block_time_us(plan, lvl, form, B, H, D, bf16);
+    double ratio = 1;
+    for (const bool bf16 : {false, true}) ratio *= wave_time_us(plan, B, H, D, bf16, alone) / block_time_us(plan, lvl, form, B, H, D, bf16);
+    return ratio < 0.9 * 0.9;
 }
 
 // The block kernel's work order for B x H heads on `slots` resident workgroups per XCD.  Items

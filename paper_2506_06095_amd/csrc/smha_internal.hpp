@@ -212,7 +212,7 @@ smha_status_t finish_plan(smha_plan *p);      // selector, work lists, concatena
 // which workgroup of the block kernel takes which item, for B x H heads on `slots` workgroups per XCD
 void build_work_order(const smha_plan *plan, int lvl, int B, int H, int slots, bool spread, std::vector<int32_t> &table, int &per_xcd);
 // whether a call shape runs the wave form rather than `form` at grain `lvl`; alone: see build_wave_order
-bool wave_form_pays(const smha_plan *plan, int lvl, int form, int B, int H, int D, bool bf16, int &alone);
+bool wave_form_pays(const smha_plan *plan, int lvl, int form, int B, int H, int D, int &alone);
 // the wave form's workgroups: four WaveItems each, as many per mask (the result); see WaveItem
 int build_wave_order(const smha_plan *plan, int alone, std::vector<int32_t> &table);
 // which of kRowForms[row_width(D)] a call of the row kernel runs

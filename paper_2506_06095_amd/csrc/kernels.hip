@@ -1691,12 +1691,12 @@ static smha_status_t make_prepared(const smha_plan *plan, int B, int H, int d, i
 // What a call shape was given: found, or made now.  `form` is the block form the call would run (block_form); the wave
 // form takes its place where it is estimated to be faster.  *ws receives the workspace for this call (null if it
 // splits no group).
-static smha_status_t prepared_for(const smha_plan *plan, int B, int H, int d, bool bf16, int form,
+static smha_status_t prepared_for(const smha_plan *plan, int B, int H, int d, int form,
                                   const smha_plan::Prepared **out, void **ws, bool may_allocate = true) {
     std::lock_guard<std::mutex> lock(plan->prepared_mutex);
     smha_plan::Prepared *hit = nullptr;
     for (const smha_plan::CallShape &c : plan->calls)
-        if (c.B == B && c.H == H && c.d == d && c.bf16 == (int)bf16 && c.form == form) hit = c.prepared;
+        if (c.B == B && c.H == H && c.d == d && c.form == form) hit = c.prepared;
     if (!hit) {
         if (!may_allocate) return SMHA_ERR_UNSUPPORTED;
         int lvl = grain_for(plan, B, H, d, form), alone = 0;
@@ -1710,7 +1710,7 @@ static smha_status_t prepared_for(const smha_plan *plan, int B, int H, int d, bo
                 const smha_status_t st = make_prepared(plan, B, H, d, lvl, runs, alone, &hit);
                 if (st != SMHA_OK) return st;
             }
-            plan->calls.push_back({B, H, d, (int)bf16, form, hit});
+            plan->calls.push_back({B, H, d, form, hit});
         } catch (const std::bad_alloc &) {
             return SMHA_ERR_ALLOC;
         }
@@ -1749,7 +1749,7 @@ extern "C" smha_status_t smha_plan_prepare(const smha_plan_t *plan, int B, int H
         if (form == 2 && d != D) form = 1;  // (the second form has no narrower heads)
         const smha_plan::Prepared *pr = nullptr;
         void *ws = nullptr;
-        const smha_status_t s2 = prepared_for(plan, B, H, D, bf16 != 0, form, &pr, &ws);
+        const smha_status_t s2 = prepared_for(plan, B, H, D, form, &pr, &ws);
         if (s2 != SMHA_OK) return s2;
     }
     return SMHA_OK;
@@ -1842,7 +1842,7 @@ static smha_status_t forward_impl(const smha_plan_t *plan, const void *Q, const 
         const int asked = block_form(plan, D, in_dtype == SMHA_BF16);
         const smha_plan::Prepared *pr = nullptr;
         void *ws = nullptr;
-        const smha_status_t st = prepared_for(plan, B, H, D, in_dtype == SMHA_BF16, asked == 2 && d != D ? 1 : asked /* (the second form has no narrower heads) */, &pr, &ws, !static_ws);
+        const smha_status_t st = prepared_for(plan, B, H, D, asked == 2 && d != D ? 1 : asked /* (the second form has no narrower heads) */, &pr, &ws, !static_ws);
         if (st != SMHA_OK) return st;
         const int form = fp.form = pr->form, lvl = pr->lvl;
         const WorkLists &wl = plan->lists[lvl];

@@ -192,10 +192,10 @@ struct smha_plan {
         void *ws[kCallSlots] = {nullptr, nullptr, nullptr, nullptr};
         unsigned next = 0;
     };
-    // which of them serves a call: decided once per shape, input type and block form (the first or third) it would run
-    // otherwise
+    // which of them serves a call: decided once per shape and block form (the first or third) it would run otherwise; the
+    // input type decides nothing beside the form (a call prepared with one type serves the other in smha_forward_static)
     struct CallShape {
-        int B, H, d, bf16, form;
+        int B, H, d, form;
         Prepared *prepared;
     };
     mutable std::mutex prepared_mutex;

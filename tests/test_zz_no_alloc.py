@@ -42,3 +42,19 @@ def test_static_workspace_entry_point_matches_forward_on_two_calls_in_a_row():
             got = out[:1, h:h + 1].float().cpu().numpy().astype(np.float64)
             assert np.abs(got - ref).max() <= 5e-3
             assert np.linalg.norm(got - ref) / np.linalg.norm(ref) <= 1e-3
+
+
+@pytest.mark.parametrize("H,S", [(2, 512), (16, 4096)])
+def test_a_call_shape_that_ran_with_one_type_serves_the_other(H, S):
+    """At 64 columns both input types run the same form, so a float16 forward prepares the bfloat16 call too."""
+    import torch
+    import paper_2506_06095_amd as smha
+    spec = W.MaskSpec(flags=W.WINDOW | W.GLOBAL, window_left=32, window_right=32, n_global=8)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    q, k, v = (torch.randn(1, H, S, 64, device="cuda", generator=g) for _ in range(3))
+    with smha.Plan.from_desc(spec, 1, H, S, head_dim=64, force=smha.SMHA_KERNEL_BLOCK) as plan:
+        plan.forward(q.half(), k.half(), v.half())
+        args = [x.bfloat16() for x in (q, k, v)]
+        out = torch.full_like(args[0], float("nan"))
+        plan.forward_static(*args, out)
+        assert torch.equal(out, plan.forward(*args))

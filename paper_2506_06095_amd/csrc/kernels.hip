@@ -74,6 +74,7 @@ struct FwdParams {
     // left_magic = 2^32 / (B H mod 8) + 1
     const WaveItem *wave_items;
     const WaveEntry *wave_ents;
+    const uint32_t *wave_used;
     int wave_n, wave_heads;
     int64_t bmp_bytes;
     uint64_t heads_magic, group_magic, left_magic;
@@ -1411,6 +1412,7 @@ smha_status_t upload_plan(smha_plan *p, int device_id) {
         }
         if (!p->wave.items.empty()) {
             arena.add(d.wave_ents, p->wave.ents);
+            arena.add(d.wave_used, p->wave.used);
             arena.add(d.wave_split_off, p->wave.split_off);
             arena.add(d.wave_splits, p->wave.splits);
         }
@@ -1863,7 +1865,7 @@ static smha_status_t forward_impl(const smha_plan_t *plan, const void *Q, const 
         fp.order_hdr = pr->order;
         fp.order = pr->order ? pr->order + 16 : nullptr;
         if (form == 4) {
-            fp.wave_items = (const WaveItem *)pr->order; fp.wave_ents = dv.wave_ents;
+            fp.wave_items = (const WaveItem *)pr->order; fp.wave_ents = dv.wave_ents; fp.wave_used = dv.wave_used;
             fp.bmp_bytes = (int64_t)plan->h_kt_bitmap.size() * 8;
             fp.wave_n = pr->longest;
             fp.heads_magic = ((uint64_t)1 << 40) / (uint64_t)H + 1;

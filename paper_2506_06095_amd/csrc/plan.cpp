@@ -506,20 +506,25 @@ static void build_wave_lists(smha_plan *p, const std::vector<int32_t> &bmp_base)
     if (at_most > kMaxWaveEntries || n_groups > 16384 /* (a grid's y holds a mask's workgroups) */ || p->h_kt_bitmap.size() * sizeof(uint64_t) >= ((size_t)1 << 31)) return;
     WaveLists &wl = p->wave;
     std::vector<WaveEntry> list[2];
+    std::vector<uint32_t> used[2];
     std::vector<WaveItem> items;
     std::vector<int32_t> first;  // of each 32-row group: its first entry
     std::vector<int32_t> at;
     wl.ents.reserve((size_t)at_most + 1);
+    wl.used.reserve((size_t)at_most + 1);
     for (int mi = 0; mi < n_masks; ++mi) {
         const MaskFormats &m = p->masks[mi];
         first.assign(1, (int32_t)wl.ents.size());
         for (int tr = 0; 2 * tr < n_groups; ++tr) {
             list[0].clear();
             list[1].clear();
+            used[0].clear();
+            used[1].clear();
             for (int e = m.kt_row_ptr[tr]; e < m.kt_row_ptr[tr + 1]; ++e) {
                 const int32_t key = m.kt_col[e] * 64;
                 if (m.kt_bmp[e] < 0) {
                     for (auto &l : list) { l.push_back({key, -1}); l.push_back({key + 32, -1}); }
+                    for (auto &u : used) u.insert(u.end(), 2, 0xFFFFFFFFu);
                     continue;
                 }
                 const uint64_t *w = m.kt_bits().data() + (size_t)m.kt_bmp[e] * 64;
@@ -527,13 +532,16 @@ static void build_wave_lists(smha_plan *p, const std::vector<int32_t> &bmp_base)
                     uint64_t any = 0, all = ~(uint64_t)0;
                     for (int r = 32 * side; r < 32 * side + 32; ++r) { any |= w[r]; all &= w[r]; }
                     for (int half = 0; half < 2; ++half)
-                        if ((uint32_t)(any >> (32 * half)))
+                        if ((uint32_t)(any >> (32 * half))) {
+                            used[side].push_back((uint32_t)(any >> (32 * half)));
                             list[side].push_back({key + 32 * half, (uint32_t)(all >> (32 * half)) == 0xFFFFFFFFu ? -1 : m.kt_bmp[e] + bmp_base[mi]});
+                        }
                 }
             }
             for (int side = 0; side < 2 && 2 * tr + side < n_groups; ++side) {
                 for (const WaveEntry &e : list[side]) wl.part_ents += e.code >= 0;
                 wl.ents.insert(wl.ents.end(), list[side].begin(), list[side].end());
+                wl.used.insert(wl.used.end(), used[side].begin(), used[side].end());
                 first.push_back((int32_t)wl.ents.size());
             }
         }
@@ -569,6 +577,7 @@ static void build_wave_lists(smha_plan *p, const std::vector<int32_t> &bmp_base)
         wl.max_slots = std::max(wl.max_slots, (int)slots);
     }
     wl.ents.push_back({0, -1});  // (an empty item's entry)
+    wl.used.push_back(0);
 }
 
 smha_status_t finish_plan(smha_plan *p) {

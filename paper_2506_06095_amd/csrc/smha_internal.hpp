@@ -113,6 +113,7 @@ struct DeviceArrays {
     int32_t *split_off[2] = {nullptr, nullptr}, *split_cnt[2] = {nullptr, nullptr};    // [n_masks]
     // the wave form's (WaveLists)
     WaveEntry *wave_ents = nullptr;
+    uint32_t *wave_used = nullptr;
     int32_t *wave_split_off = nullptr;                                                 // [n_masks]
     SplitRow *wave_splits = nullptr;
 };
@@ -132,6 +133,7 @@ constexpr int kWaveWhole = 128;  // longest list that is not cut
 struct WaveLists {
     std::vector<WaveItem> items;
     std::vector<WaveEntry> ents;
+    std::vector<uint32_t> used;  // of each entry: its keys that any of the 32 rows has, bit k = k-th key
     std::vector<int32_t> item_off, item_cnt, split_off;
     std::vector<SplitRow> splits;
     int max_splits = 0, max_slots = 0;

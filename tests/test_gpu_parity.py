@@ -952,3 +952,26 @@ def test_wave_form(torch_mod, smha, name, d, dtype):
                     for _ in range(3):                  # (the merge's counters are back at zero, its order is fixed)
                         plan.forward(q, k, v, out=out)
                     assert np.array_equal(out.float().cpu().numpy(), first)
+
+
+@pytest.mark.parametrize("d,gathered", [(64, True), (80, True), (128, True), (64, False), (80, False), (128, False), (256, False)])
+def test_wave_form_reads_no_value_of_a_key_without_rows(torch_mod, smha, d, gathered):
+    """An infinite V at a key that none of 32 rows has leaves these rows as they are, bit for bit, also where they have
+    other keys of its tile (as gathered tiles do, which hold no such key)."""
+    torch, S = torch_mod, 700
+    i, j = np.arange(S)[:, None], np.arange(S)[None]
+    mask = ((np.abs(i - j) < 10) | (j % 32 == 5) | (j > 695)).astype(np.uint8)[None, None]
+    g = torch.Generator(device="cuda").manual_seed(d)
+    Q, K, V = (torch.randn(1, 2, S, d, device="cuda", dtype=torch.float16, generator=g) for _ in range(3))
+    Vi, at = V.clone(), [0, 4, 6, 31, 200, 340, 691]
+    Vi[:, :, at, d - 3] = float("inf")
+    Vi[:, :, at, 1] = float("nan")
+    groups = np.add.reduceat(mask[0, 0][:, at].any(1), np.arange(0, S, 32)) == 0
+    clean = torch.from_numpy(np.repeat(groups, 32)[:S]).cuda()
+    assert 32 < int(clean.sum()) < S
+    for dtype in (torch.float16, torch.bfloat16):
+        with smha.Plan.from_dense(mask, force=smha.SMHA_KERNEL_BLOCK, head_dim=d, no_gather=not gathered) as plan:
+            assert (plan.info()["n_gathered"] > 0) == gathered
+            assert smha.smha_call_kernel_name(plan.handle, 1, 2, d, smha.SMHA_F16) == "smha_wave_fwd"
+            want, got = (plan.forward(Q.to(dtype), K.to(dtype), x.to(dtype)) for x in (V, Vi))
+            assert torch.equal(got[:, :, clean], want[:, :, clean])

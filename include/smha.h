@@ -66,7 +66,7 @@ typedef struct {
                        work lists only; the exported formats are never affected)               */
     int block_form; /* which form of the block-wise kernel runs where several exist: 0 = the library's choice
                        (at 128 columns form 3, unless nearly all tiles are full and the lists long: form 1;
-                       at 256 columns form 3; at 64 columns form 1; at 64 and 128 columns the wave form, one
+                       at 256 columns form 3; at 64 columns form 1; at all widths the wave form, one
                        wave per 32 query rows, for calls that it is estimated to run faster),
                        1 = four waves per workgroup, every wave forms scores, probabilities and output of
                        its 32 rows (one to four workgroups per compute unit); 2 = eight waves per workgroup,

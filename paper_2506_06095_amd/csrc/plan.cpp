@@ -1055,7 +1055,7 @@ static double block_time_us(const smha_plan *plan, int lvl, int form, int B, int
 // 0.739, none more than 3.4 % slower).
 // The two input types are decided together (by the product of their ratios): one order and one set of workspaces serves both.
 bool wave_form_pays(const smha_plan *plan, int lvl, int form, int B, int H, int D, int &alone) {
-    if (plan->wave.items.empty() || H > 65535 || (int64_t)B * H > (1 << 19)) return false;
+    if (plan->wave.items.empty() || H > 65535 || (int64_t)B * H > (1 << 18) /* (a grid's z holds an eighth of them) */) return false;
     if (workspace_bytes(plan, 0, 4, B, H, D, nullptr) > kStaticScratchBytes) return false;  // (smha_forward_static takes what it took)
     double ratio = 1;
     for (const bool bf16 : {false, true}) ratio *= wave_time_us(plan, B, H, D, bf16, alone) / block_time_us(plan, lvl, form, B, H, D, bf16);

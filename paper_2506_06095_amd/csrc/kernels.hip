@@ -1293,7 +1293,7 @@ smha_status_t classify_device_mask(const uint8_t *dev_mask, int n_masks, int Sq,
 
 // Device memory of destroyed plans, kept for the next ones: allocating and freeing a plan's few blocks cost more than
 // analysing a small mask (plan, forward and destroy for a new 1024 x 1024 mask: 121 us, with blocks kept 112).  Only blocks
-// of up to 1 MB, 16 MB of them at most; a block comes in when its device is idle (release_device waits for it, as hipFree does), so that
+// of up to 1 MB, 16 MB of them at most; a block comes in when its device is idle (release_device's hipFree has waited for it), so that
 // whoever takes it may use it on any stream.
 namespace {
 struct PoolBlock { void *ptr; size_t bytes; int device; };
@@ -1419,8 +1419,7 @@ smha_status_t upload_plan(smha_plan *p, int device_id) {
     }
     bool ok = true;
     if (!arena.host.empty()) {
-        d.arena_bytes = arena.host.size();
-        ok = device_alloc(&d.arena, d.arena_bytes, device_id) == hipSuccess &&
+        ok = hipMalloc(&d.arena, arena.host.size()) == hipSuccess &&
              hipMemcpy(d.arena, arena.host.data(), arena.host.size(), hipMemcpyHostToDevice) == hipSuccess;
         if (ok)
             for (auto &f : arena.fixups) *f.first = (char *)d.arena + f.second;
@@ -1441,9 +1440,10 @@ void release_device(smha_plan *p) {
     (void)hipGetDevice(&prev);
     (void)hipSetDevice(p->device);
     DeviceArrays &d = p->dev;
-    const bool idle = hipDeviceSynchronize() == hipSuccess;  // (launches that read these arrays have ended)
+    // hipFree waits until the device is idle, so that launches which read the plan's other blocks have ended too, and what
+    // it may do during a capture is ruled by this thread's mode (hipDeviceSynchronize ends any thread's capture).
+    const bool idle = d.arena && hipFree(d.arena) == hipSuccess;
     if (!idle) (void)hipGetLastError();
-    if (d.arena) device_free(d.arena, d.arena_bytes, p->device, idle);
     d = DeviceArrays{};
     for (smha_plan::Prepared *pr : p->prepared) {
         if (pr->order) device_free(pr->order, pr->order_bytes, p->device, idle);

@@ -97,7 +97,6 @@ constexpr int row_step_keys(int width, int form) {  // keys of a row that one st
 
 struct DeviceArrays {
     void *arena = nullptr;        // the one allocation every array below is a part of
-    size_t arena_bytes = 0;
     // row path
     int32_t *row_ptr = nullptr;   // [n_masks][S+1], offsets local to the mask
     int32_t *col_idx = nullptr;   // concatenated

@@ -58,3 +58,34 @@ def test_a_call_shape_that_ran_with_one_type_serves_the_other(H, S):
         out = torch.full_like(args[0], float("nan"))
         plan.forward_static(*args, out)
         assert torch.equal(out, plan.forward(*args))
+
+
+@pytest.mark.parametrize("mode", ["thread_local", "relaxed"])
+def test_a_plan_destroyed_on_another_thread_leaves_a_capture_alone(mode):
+    """A capture that only binds its own thread survives the end of another thread's plan (a finaliser, say), also of a
+    plan whose launches have to be waited for."""
+    import threading
+
+    import torch
+    import paper_2506_06095_amd as smha
+    spec = W.MaskSpec(flags=W.WINDOW | W.GLOBAL, window_left=40, window_right=9, n_global=8)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    q, k, v = (torch.randn(1, 4, 512, 64, device="cuda", generator=g).half() for _ in range(3))
+    out = torch.empty_like(q)
+    with smha.Plan.from_desc(spec, 1, 4, 512, head_dim=64, force=smha.SMHA_KERNEL_BLOCK) as plan:
+        plan.prepare(1, 4, 64)
+        eager = plan.forward(q, k, v)
+        torch.cuda.synchronize()
+        other = smha.Plan.from_desc(spec, 1, 4, 512, head_dim=64, force=smha.SMHA_KERNEL_BLOCK)
+        elsewhere, side, graph = torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.CUDAGraph()
+        kept = other.forward(q, k, v, stream=elsewhere)  # noqa: F841 (its memory is held until it has run)
+        with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side, capture_error_mode=mode):
+            closer = threading.Thread(target=other.close)
+            closer.start()
+            closer.join()
+            plan.forward(q, k, v, out=out)
+        for _ in range(3):
+            out.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, eager)

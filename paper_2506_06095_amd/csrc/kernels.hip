@@ -18,6 +18,7 @@
 #include <cstring>
 #include <vector>
 
+#include "device_pool.hpp"
 #include "smha_internal.hpp"
 
 namespace smha {
@@ -1291,64 +1292,10 @@ smha_status_t classify_device_mask(const uint8_t *dev_mask, int n_masks, int Sq,
     return done(SMHA_OK);
 }
 
-// Device memory of destroyed plans, kept for the next ones: allocating and freeing a plan's few blocks cost more than
-// analysing a small mask (plan, forward and destroy for a new 1024 x 1024 mask: 121 us, with blocks kept 112).  Only blocks
-// of up to 1 MB, 16 MB of them at most; a block comes in when its device is idle (release_device's hipFree has waited for it), so that
-// whoever takes it may use it on any stream.
-namespace {
-struct PoolBlock { void *ptr; size_t bytes; int device; };
-constexpr size_t kPoolBlockAtMost = (size_t)1 << 20, kPoolAtMost = (size_t)16 << 20;
-std::mutex pool_mutex;
-std::vector<PoolBlock> pool;
-size_t pool_bytes = 0;
-}  // namespace
-static size_t pool_size(size_t bytes) {  // what a block for so many bytes has
-    if (bytes > kPoolBlockAtMost) return bytes;
-    size_t n = (size_t)64 << 10;
-    while (n < bytes) n *= 2;
-    return n;
-}
-static hipError_t device_alloc(void **ptr, size_t bytes, int device) {  // (`device` is current)
-    const size_t want = pool_size(bytes);
-    if (want <= kPoolBlockAtMost) {
-        std::lock_guard<std::mutex> lock(pool_mutex);
-        for (size_t i = pool.size(); i-- > 0;)
-            if (pool[i].device == device && pool[i].bytes == want) {
-                *ptr = pool[i].ptr;
-                pool[i] = pool.back();
-                pool.pop_back();
-                pool_bytes -= want;
-                return hipSuccess;
-            }
-    }
-    hipError_t e = hipMalloc(ptr, want);
-    if (e != hipSuccess) {  // (what is kept goes back to the device first)
-        (void)hipGetLastError();
-        {
-            std::lock_guard<std::mutex> lock(pool_mutex);
-            for (const PoolBlock &b : pool) (void)hipFree(b.ptr);
-            pool.clear();
-            pool_bytes = 0;
-        }
-        e = hipMalloc(ptr, want);
-    }
-    return e;
-}
-static void device_free(void *ptr, size_t bytes, int device, bool idle) {
-    const size_t have = pool_size(bytes);
-    if (idle && have <= kPoolBlockAtMost) {
-        std::lock_guard<std::mutex> lock(pool_mutex);
-        if (pool_bytes + have <= kPoolAtMost) {
-            try {
-                pool.push_back({ptr, have, device});
-                pool_bytes += have;
-                return;
-            } catch (const std::bad_alloc &) {
-            }
-        }
-    }
-    (void)hipFree(ptr);
-}
+// (An error left behind would be reported by the caller's next call.  Never destroyed: plans may outlive it at exit.)
+static DevicePool &device_pool = *new DevicePool(
+    [](void **ptr, size_t bytes) { return hipMalloc(ptr, bytes) == hipSuccess ? 0 : ((void)hipGetLastError(), 1); },
+    [](void *ptr) { return hipFree(ptr) == hipSuccess ? 0 : ((void)hipGetLastError(), 1); });
 
 // Every index array of a plan lives in one device allocation, filled with one copy: a plan has up to 18
 // arrays, and an allocation and a copy each cost more than the analysis of a small mask.
@@ -1419,7 +1366,7 @@ smha_status_t upload_plan(smha_plan *p, int device_id) {
     }
     bool ok = true;
     if (!arena.host.empty()) {
-        ok = hipMalloc(&d.arena, arena.host.size()) == hipSuccess &&
+        ok = device_pool.fresh(&d.arena, arena.host.size()) == 0 &&
              hipMemcpy(d.arena, arena.host.data(), arena.host.size(), hipMemcpyHostToDevice) == hipSuccess;
         if (ok)
             for (auto &f : arena.fixups) *f.first = (char *)d.arena + f.second;
@@ -1446,9 +1393,9 @@ void release_device(smha_plan *p) {
     if (!idle) (void)hipGetLastError();
     d = DeviceArrays{};
     for (smha_plan::Prepared *pr : p->prepared) {
-        if (pr->order) device_free(pr->order, pr->order_bytes, p->device, idle);
+        if (pr->order) device_pool.give(pr->order, pr->order_bytes, p->device, idle);
         for (void *q : pr->ws)
-            if (q) device_free(q, pr->ws_bytes, p->device, idle);
+            if (q) device_pool.give(q, pr->ws_bytes, p->device, idle);
         delete pr;
     }
     p->prepared.clear();
@@ -1660,14 +1607,14 @@ static smha_status_t make_prepared(const smha_plan *plan, int B, int H, int d, i
     q->step_words = step_words;
     q->item_words = item_words;
     bool ok = table.empty() ||
-              (device_alloc((void **)&q->order, q->order_bytes = table.size() * sizeof(int32_t), plan->device) == hipSuccess &&
+              (device_pool.take((void **)&q->order, q->order_bytes = table.size() * sizeof(int32_t), plan->device) == 0 &&
                hipMemcpy(q->order, table.data(), table.size() * sizeof(int32_t), hipMemcpyHostToDevice) == hipSuccess);
     if (ok && (form == 4 ? plan->wave.max_slots : wl.max_slots) > 0) {
         q->ws_bytes = workspace_bytes(plan, lvl, form, B, H, d, &q->counters_at);
         // (the counters start at zero and every launch leaves them at zero; the copy has completed on return)
         const std::vector<uint32_t> zeros((q->ws_bytes - q->counters_at) / sizeof(uint32_t), 0u);
         for (int i = 0; ok && i < smha_plan::kCallSlots; ++i)
-            ok = device_alloc(&q->ws[i], q->ws_bytes, plan->device) == hipSuccess &&
+            ok = device_pool.take(&q->ws[i], q->ws_bytes, plan->device) == 0 &&
                  hipMemcpy((char *)q->ws[i] + q->counters_at, zeros.data(), zeros.size() * sizeof(uint32_t),
                            hipMemcpyHostToDevice) == hipSuccess;
     }
@@ -1680,9 +1627,10 @@ static smha_status_t make_prepared(const smha_plan *plan, int B, int H, int d, i
     }
     if (!ok) {
         (void)hipGetLastError();
-        if (q->order) (void)hipFree(q->order);
+        // (no launch has seen these blocks; during a capture they cannot be freed, so they are kept for the next plan)
+        if (q->order) device_pool.give(q->order, q->order_bytes, plan->device, true);
         for (void *w : q->ws)
-            if (w) (void)hipFree(w);
+            if (w) device_pool.give(w, q->ws_bytes, plan->device, true);
         delete q;
         return SMHA_ERR_ALLOC;
     }

@@ -510,6 +510,7 @@ static void build_wave_lists(smha_plan *p, const std::vector<int32_t> &bmp_base)
     std::vector<WaveItem> items;
     std::vector<int32_t> first;  // of each 32-row group: its first entry
     std::vector<int32_t> at;
+    std::vector<char> touched(2 * (size_t)((p->Sk + 63) / 64), 0);  // 32-key tiles
     wl.ents.reserve((size_t)at_most + 1);
     wl.used.reserve((size_t)at_most + 1);
     for (int mi = 0; mi < n_masks; ++mi) {
@@ -525,6 +526,7 @@ static void build_wave_lists(smha_plan *p, const std::vector<int32_t> &bmp_base)
                 if (m.kt_bmp[e] < 0) {
                     for (auto &l : list) { l.push_back({key, -1}); l.push_back({key + 32, -1}); }
                     for (auto &u : used) u.insert(u.end(), 2, 0xFFFFFFFFu);
+                    touched[2 * m.kt_col[e]] = touched[2 * m.kt_col[e] + 1] = 1;
                     continue;
                 }
                 const uint64_t *w = m.kt_bits().data() + (size_t)m.kt_bmp[e] * 64;
@@ -533,6 +535,7 @@ static void build_wave_lists(smha_plan *p, const std::vector<int32_t> &bmp_base)
                     for (int r = 32 * side; r < 32 * side + 32; ++r) { any |= w[r]; all &= w[r]; }
                     for (int half = 0; half < 2; ++half)
                         if ((uint32_t)(any >> (32 * half))) {
+                            touched[2 * m.kt_col[e] + half] = 1;
                             used[side].push_back((uint32_t)(any >> (32 * half)));
                             list[side].push_back({key + 32 * half, (uint32_t)(all >> (32 * half)) == 0xFFFFFFFFu ? -1 : m.kt_bmp[e] + bmp_base[mi]});
                         }
@@ -576,6 +579,7 @@ static void build_wave_lists(smha_plan *p, const std::vector<int32_t> &bmp_base)
         wl.max_splits = std::max(wl.max_splits, (int)n_splits);
         wl.max_slots = std::max(wl.max_slots, (int)slots);
     }
+    wl.keys = 32 * (int)std::count(touched.begin(), touched.end(), 1);
     wl.ents.push_back({0, -1});  // (an empty item's entry)
     wl.used.push_back(0);
 }
@@ -949,24 +953,34 @@ int build_wave_order(const smha_plan *plan, int alone, std::vector<int32_t> &tab
     return (int)most;
 }
 
-// Estimated times of a call, for the choice between the wave form and the other two (and for its `alone`).  Two things
-// bound a launch: what the chip's compute units take together, and the longest chain of steps in one wave or workgroup;
-// the estimate is the root of the sum of their p-th powers.  Constants are in us (per wave and step of the wave form: ns)
-// and fitted to 521 calls: all kinds of masks, 64 to 8192 queries, 2 to 400 heads, 8 to 256 columns, the wave form with 12
-// values of `alone` each.  Mean error 5 to 7 % (wave form), 5 to 9 % (the others).
+// Estimated times of a call, for the choice between the wave form and the other two (and for its `alone`).  Several things
+// bound a launch: what the chip's compute units take together, the longest chain of steps in one wave or workgroup, and
+// the bytes of Q, K, V and O; the estimate is the root of the sum of their p-th powers.  Constants are in us (per wave and
+// step of the wave form: ns, `memory`: us per MB), fitted by least squares of the logarithms to 1000 calls of
+// profiles/block_forms.csv (all kinds of masks, 64 to 8192 queries, 1 to 400 heads, 8 to 256 columns; clocks settled by 10 ms of the
+// same work and three sets of inputs in turn: measured from idle clocks the first form took 15 % longer, the wave form 3 %,
+// and the choice went wrong by that).  Mean error over the table's other 600 calls: 5 to 7 % (wave form), 5 % (the others).
 struct WaveCost {
-    double start, wave, step, held, part, bf16, chain, chain_full, power, uneven;
+    double start, wave, step, held, part, bf16, chain, chain_full, power, uneven, part_all, join, memory;
 };
-static const WaveCost kWaveCost[3] = {{3.41, 0.654, 0.374, 0.22, 0.076, 1.20, 0.459, 0.195, 3.4, 0.0},    // 64 columns
-                                      {3.98, 1.502, 0.717, 0.05, 0.191, 1.17, 0.683, 0.154, 4.0, 0.09},   // 128
-                                      {5.64, 4.639, 1.507, 0.63, 0.156, 1.17, 1.400, 0.0, 4.0, 0.23}};    // 256
+static const WaveCost kWaveCost[3] = {
+    {3.07, 0.7079, 0.4048, 0.22, 0.076, 1.20, 0.4968, 0.2111, 3.4, 0.0, -0.027, 1.649, 0.0311},     // 64 columns
+    {3.83, 1.6077, 0.7674, 0.05, 0.191, 1.17, 0.7311, 0.1648, 4.0, 0.09, -0.114, 2.275, 0.0914},    // 128
+    {5.48, 5.0865, 1.6524, 0.63, 0.156, 1.17, 1.5350, 0.0, 4.0, 0.23, -0.043, 2.934, 0.0589}};      // 256
 struct BlockCost {
-    double start, unit, group, part, act, bf16, gather, power, fine;
+    double start, unit, unit_act, unit_part, unit_sub, unit_lone, group, group_act, group_part, unit_bf16, group_bf16, gather, power, merge, memory;
 };
-static const BlockCost kBlockCost[3][2] = {  // first form, third form
-    {{2.20, 0.523, 0.777, 0.057, 0.139, 1.232, 1.113, 4.1, 4.9}, {}},
-    {{1.92, 0.906, 1.061, 0.102, 0.261, 1.072, 1.117, 8.0, 10.0}, {2.32, 0.980, 0.937, -0.018, 0.235, 1.147, 1.0, 4.3, 5.7}},
-    {{0.0, 2.934, 0.0, -0.229, 0.248, 1.067, 1.20, 5.2, 1.8}, {1.84, 1.838, 0.0, -0.062, 0.376, 1.078, 1.0, 7.4, 10.8}}};
+static const BlockCost kBlockCost[3][2] = {  // first form, third form (none at 64 columns)
+    {{1.730, -0.941, 0.657, -0.037, -0.006, 0.007, -0.570, -0.355, 0.163, 1.295, 1.163, 1.139, 1.588, 5.257, 0.096}, {}},
+    {{2.033, -0.656, -0.261, 0.033, 0.009, -0.049, -0.065, 0.299, -0.052, 1.257, 1.049, 0.998, 1.200, 11.013, 0.098},
+     {1.669, -0.415, -0.189, -0.002, 0.105, -0.177, -0.394, 0.030, 0.162, 1.229, 1.051, 1.100, 1.669, 7.180, 0.156}},
+    {{2.212, 0.693, -0.199, 0.146, 0.000, -0.399, 0.186, 0.390, -0.400, 1.155, 1.061, 0.900, 1.200, 10.661, 0.098},
+     {1.609, -0.132, -0.036, 0.238, 0.064, -0.803, 0.186, 0.065, -0.388, 1.133, 1.140, 1.100, 1.399, 10.224, 0.130}}};
+
+// MB that a call on masks which touch `keys` keys reads and writes (the kernel's width in place of the head size)
+static double call_mb(const smha_plan *plan, int B, int H, int D, int keys) {
+    return 4e-6 * B * H * D * ((double)plan->S + std::min(keys, plan->Sk));
+}
 
 // The wave form.  Every wave has its start and end, every step its share of the chip; a workgroup's places are partly
 // `held` until its longest wave ends, and steps of partly filled tiles and bfloat16 cost more.  A list shared by four
@@ -978,7 +992,8 @@ static double wave_time_us(const smha_plan *plan, int B, int H, int D, bool bf16
     const double per_mask = 1.0 / (plan->Bm * plan->Hm), heads = (double)B * H;
     const WaveCost &c = kWaveCost[row_width(D)];
     const double slots = (D == 64 ? 16.0 : D == 128 ? 8.0 : 4.0) * plan->n_cu;
-    const double step_ns = c.step * (1 + c.part * (double)wl.part_ents / std::max<double>(1.0, (double)wl.ents.size()));
+    const double part = (double)wl.part_ents / std::max<double>(1.0, (double)wl.ents.size() - 1);
+    const double step_ns = c.step * (1 + c.part * part);
     double best = 0, best_us = 0;
     alone = 0;
     for (int limit : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64}) {
@@ -1017,12 +1032,14 @@ static double wave_time_us(const smha_plan *plan, int B, int H, int D, bool bf16
             alone = limit;
         }
     }
-    return c.start + best_us;
+    return c.start + std::pow(std::pow(best_us * std::exp(c.part_all * part), c.join) + std::pow(c.memory * call_mb(plan, B, H, D, wl.keys), c.join), 1 / c.join);
 }
 
 // The first (four waves of 32 rows) and third form (eight of 16): the busiest compute unit's work and the longest
-// workgroup's chain, in steps plus 2 per item (see build_work_order).  Steps in which both tile rows have work (`act`:
-// tiles per step), partly filled tiles and bfloat16 cost more, and so does the fine grain, whose parts are merged.
+// workgroup's chain, in steps plus 2 per item (see build_work_order).  A step's cost follows the tile rows that have work
+// in it (`act`: tiles per step), how many of the tiles are partly filled, how many 32 x 32 sub-tiles have keys (`subs`) and
+// whether most steps are full tiles that one tile row has to itself (`lone`: the other's waves only wait); merging parts of
+// a cut list costs extra.
 static double block_time_us(const smha_plan *plan, int lvl, int form, int B, int H, int D, bool bf16) {
     const WorkLists &wl = plan->lists[plan->fine_differs ? lvl : 0];
     const double per_xcd = (double)B * H / (plan->Bm * plan->Hm) / 8;
@@ -1041,25 +1058,34 @@ static double block_time_us(const smha_plan *plan, int lvl, int form, int B, int
         part += (int64_t)(m.kt_bits().size() / 64);
     }
     const BlockCost &c = kBlockCost[row_width(D)][form == 3];
-    const double parts = tiles ? (double)part / (double)tiles : 0.0, act = std::min(2.0, (double)tiles / std::max<double>(1.0, (double)plan->h_uent.size() - 1));
-    return c.start + (1 + c.part * parts) * (1 + c.act * (act - 1.5)) * (bf16 ? c.bf16 : 1.0) * (plan->n_gathered > 0 ? c.gather : 1.0) *
-           std::pow(std::pow(unit * c.unit, c.power) + std::pow(group * c.group, c.power), 1 / c.power) + (plan->fine_differs && lvl ? c.fine : 0.0);
+    const double steps = std::max<double>(1.0, (double)plan->h_uent.size() - 1);
+    const double parts = tiles ? (double)part / (double)tiles : 0.0, act = std::min(2.0, (double)tiles / steps);
+    const double subs = ((double)plan->wave.ents.size() - 1) / steps;
+    const double lone = (1 - parts) * std::min(1.0, std::max(0.0, (1.35 - act) / 0.3));
+    const double gather = plan->n_gathered > 0 ? c.gather : 1.0;
+    const double unit_us = unit * std::exp(c.unit + c.unit_act * (act - 1.5) + c.unit_part * act * parts + c.unit_sub * (subs - 5) + c.unit_lone * lone);
+    const double group_us = group * std::exp(c.group + c.group_act * (act - 1.5) + c.group_part * act * parts);
+    return c.start + (wl.max_slots > 0 ? c.merge : 0.0) +
+           std::pow(std::pow(gather * unit_us * (bf16 ? c.unit_bf16 : 1.0), c.power) + std::pow(gather * group_us * (bf16 ? c.group_bf16 : 1.0), c.power) +
+                        std::pow(c.memory * call_mb(plan, B, H, D, plan->wave.keys), c.power),
+                    1 / c.power);
 }
 
-// The wave form wins where tiles are filled poorly (BigBird with random 32-blocks 16 x 12 x 2048 x 64: 112 us, 66 with
-// the wave form) and where a call has too few 128-row groups to fill the chip (fresh mask 1 x 4 x 1037 x 64: 8.9 / 4.6;
-// causal 9 x 2 x 1088 x 128: 26.2 / 14.4; per-head 64-blocks 1 x 4 x 640 x 256 20.7 / 11.2); it loses where tiles are full and
-// rows many (causal 16 x 12 x 4096 x 128: 870 / 1176), because every K and V tile is loaded once per 32 rows.  It has to win
-// by a tenth: of the 521 calls it then slows one by more than 3 % (7 %), and the mean is 0.67 at 64 columns, 0.78 at
-// 128, 0.82 at 256, where the best choice for each would be 0.65, 0.75 and 0.81 (201 others, types decided together: 0.751 and
-// 0.739, none more than 3.4 % slower).
+// The wave form wins where tiles are filled poorly (BigBird with random 32-blocks 16 x 12 x 2048 x 64: 126 us, 77 with
+// the wave form) and where a call has too few 128-row groups to fill the chip (causal 1 x 12 x 1024 x 64 15.2 / 8.5, per-head
+// 64-blocks 1 x 2 x 2816 x 256 20.6 / 12.8); it loses where tiles are full and rows many (causal 16 x 12 x 4096 x 128:
+// 870 / 1176), because every K and V tile is loaded once per 32 rows.  It has to win by 5 %: of the table's 1600 calls (see
+// above) 15 then run the slower form by more than 2 % with one of the input types (22 before, when the estimates came from
+// idle clocks and the margin was a tenth: 64-blocks 2 x 16 x 4096 x 64 bf16 34.0 us, 34.4 with the wave form), and the mean against
+// the other forms is 0.666 at 64 columns, 0.715 at 128, 0.768 at 256 (0.669, 0.720 and 0.770 before), where the better form for
+// each call would give 0.663, 0.711 and 0.765.
 // The two input types are decided together (by the product of their ratios): one order and one set of workspaces serves both.
 bool wave_form_pays(const smha_plan *plan, int lvl, int form, int B, int H, int D, int &alone) {
     if (plan->wave.items.empty() || H > 65535 || (int64_t)B * H > (1 << 18) /* (a grid's z holds an eighth of them) */) return false;
     if (workspace_bytes(plan, 0, 4, B, H, D, nullptr) > kStaticScratchBytes) return false;  // (smha_forward_static takes what it took)
     double ratio = 1;
     for (const bool bf16 : {false, true}) ratio *= wave_time_us(plan, B, H, D, bf16, alone) / block_time_us(plan, lvl, form, B, H, D, bf16);
-    return ratio < 0.9 * 0.9;
+    return ratio < 0.95 * 0.95;
 }
 
 // The block kernel's work order for B x H heads on `slots` resident workgroups per XCD.  Items

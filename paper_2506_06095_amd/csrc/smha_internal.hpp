@@ -138,6 +138,7 @@ struct WaveLists {
     int max_splits = 0, max_slots = 0;
     int32_t of_length[kWaveWhole + 1] = {0};  // items by entries, over all masks
     int64_t part_ents = 0;                    // entries that have a bitmap
+    int keys = 0;                             // in 32-key tiles that any entry names
 };
 
 }  // namespace smha

@@ -1357,12 +1357,6 @@ smha_status_t upload_plan(smha_plan *p, int device_id) {
             arena.add(d.split_off[lvl], wl.split_off);
             arena.add(d.split_cnt[lvl], wl.split_cnt);
         }
-        if (!p->wave.items.empty()) {
-            arena.add(d.wave_ents, p->wave.ents);
-            arena.add(d.wave_used, p->wave.used);
-            arena.add(d.wave_split_off, p->wave.split_off);
-            arena.add(d.wave_splits, p->wave.splits);
-        }
     }
     bool ok = true;
     if (!arena.host.empty()) {
@@ -1400,6 +1394,7 @@ void release_device(smha_plan *p) {
     }
     p->prepared.clear();
     p->calls.clear();
+    p->wave_dev = WaveArrays{};
     p->device = -1;
     (void)hipSetDevice(prev);
 }
@@ -1546,8 +1541,14 @@ static smha_status_t make_prepared(const smha_plan *plan, int B, int H, int d, i
     int64_t step_words = 0, item_words = 0;
     const int slots = workgroups_per_cu(form, d) * plan->n_cu / 8;  // workgroups that fit an XCD at once
     smha_plan::Prepared *q = nullptr;
+    Arena arena;
+    WaveArrays lists;
+    int32_t *order = nullptr;
+    size_t ws_bytes = 0, counters_at = 0;
+    std::vector<uint32_t> zeros;
     try {
         if (form == 4) {
+            make_wave_lists(plan);
             longest = build_wave_order(plan, alone, table);
         } else {
             build_work_order(plan, lvl, B, H, slots, true, table, per_xcd);
@@ -1597,6 +1598,17 @@ static smha_status_t make_prepared(const smha_plan *plan, int B, int H, int d, i
             step_words = (int64_t)steps.size();
             item_words = (int64_t)items.size();
         }
+        if (form == 4 && !plan->wave_dev.ents) {  // (the first order brings the lists, in one block and one copy)
+            arena.add(order, table);
+            arena.add(lists.ents, plan->wave.ents);
+            arena.add(lists.used, plan->wave.used);
+            arena.add(lists.split_off, plan->wave.split_off);
+            arena.add(lists.splits, plan->wave.splits);
+        }
+        if ((form == 4 ? plan->wave.max_slots : wl.max_slots) > 0) {
+            ws_bytes = workspace_bytes(plan, lvl, form, B, H, d, &counters_at);
+            zeros.assign((ws_bytes - counters_at) / sizeof(uint32_t), 0u);
+        }
         q = new smha_plan::Prepared();
     } catch (const std::bad_alloc &) {
         return SMHA_ERR_ALLOC;
@@ -1606,18 +1618,18 @@ static smha_status_t make_prepared(const smha_plan *plan, int B, int H, int d, i
     q->alone = alone;
     q->step_words = step_words;
     q->item_words = item_words;
-    bool ok = table.empty() ||
-              (device_pool.take((void **)&q->order, q->order_bytes = table.size() * sizeof(int32_t), plan->device) == 0 &&
-               hipMemcpy(q->order, table.data(), table.size() * sizeof(int32_t), hipMemcpyHostToDevice) == hipSuccess);
-    if (ok && (form == 4 ? plan->wave.max_slots : wl.max_slots) > 0) {
-        q->ws_bytes = workspace_bytes(plan, lvl, form, B, H, d, &q->counters_at);
+    const void *const src = arena.host.empty() ? (const void *)table.data() : arena.host.data();
+    q->order_bytes = arena.host.empty() ? table.size() * sizeof(int32_t) : arena.host.size();
+    bool ok = q->order_bytes == 0 || (device_pool.take((void **)&q->order, q->order_bytes, plan->device) == 0 &&
+                                      hipMemcpy(q->order, src, q->order_bytes, hipMemcpyHostToDevice) == hipSuccess);
+    q->ws_bytes = ws_bytes;
+    q->counters_at = counters_at;
+    if (ok && ws_bytes > 0)
         // (the counters start at zero and every launch leaves them at zero; the copy has completed on return)
-        const std::vector<uint32_t> zeros((q->ws_bytes - q->counters_at) / sizeof(uint32_t), 0u);
         for (int i = 0; ok && i < smha_plan::kCallSlots; ++i)
             ok = device_pool.take(&q->ws[i], q->ws_bytes, plan->device) == 0 &&
                  hipMemcpy((char *)q->ws[i] + q->counters_at, zeros.data(), zeros.size() * sizeof(uint32_t),
                            hipMemcpyHostToDevice) == hipSuccess;
-    }
     if (ok) {
         try {
             plan->prepared.push_back(q);
@@ -1633,6 +1645,10 @@ static smha_status_t make_prepared(const smha_plan *plan, int B, int H, int d, i
             if (w) device_pool.give(w, q->ws_bytes, plan->device, true);
         delete q;
         return SMHA_ERR_ALLOC;
+    }
+    if (!arena.host.empty()) {
+        for (auto &f : arena.fixups) *f.first = (char *)q->order + f.second;
+        plan->wave_dev = lists;
     }
     *out = q;
     return SMHA_OK;
@@ -1813,7 +1829,7 @@ static smha_status_t forward_impl(const smha_plan_t *plan, const void *Q, const 
         fp.order_hdr = pr->order;
         fp.order = pr->order ? pr->order + 16 : nullptr;
         if (form == 4) {
-            fp.wave_items = (const WaveItem *)pr->order; fp.wave_ents = dv.wave_ents; fp.wave_used = dv.wave_used;
+            fp.wave_items = (const WaveItem *)pr->order; fp.wave_ents = plan->wave_dev.ents; fp.wave_used = plan->wave_dev.used;
             fp.bmp_bytes = (int64_t)plan->h_kt_bitmap.size() * 8;
             fp.wave_n = pr->longest;
             fp.heads_magic = ((uint64_t)1 << 40) / (uint64_t)H + 1;
@@ -1821,7 +1837,7 @@ static smha_status_t forward_impl(const smha_plan_t *plan, const void *Q, const 
             fp.group_magic = ((uint64_t)1 << 32) / (uint64_t)fp.wave_heads + 1;
             if (B * H % 8) fp.left_magic = ((uint64_t)1 << 32) / (uint64_t)(B * H % 8) + 1;
             fp.max_slots = plan->wave.max_slots;
-            fp.split_rows = dv.wave_splits; fp.split_off = dv.wave_split_off;
+            fp.split_rows = plan->wave_dev.splits; fp.split_off = plan->wave_dev.split_off;
         }
         if (form == 2) {
             fp.order_hdr = pr->order + 8;

@@ -496,92 +496,156 @@ static bool row_may_be_chosen(const smha_plan *p) {
     return nnz / n_masks * cm.entry_ns + p->S * cm.row_ns < tiles / n_masks * cm.step_ns + cm.fixed_ns;
 }
 
-// The wave form's lists (see WaveItem).  Masks with more than kMaxWaveEntries 32-key tiles in all get none: their lists
-// would be a burden, and calls on masks so large fill the chip through the other forms.
-static void build_wave_lists(smha_plan *p, const std::vector<int32_t> &bmp_base) {
+// The wave form's lists (see WaveItem), in two steps: what the estimates need of them (their lengths), once a call shape is
+// first asked for, and the lists, once a call takes the form.  (Made with every plan they cost those that never use them
+// 5 to 7 %: BigBird blocks at 8192, per-head 64-blocks at 4096.)  Masks with more than kMaxWaveEntries 32-key tiles in all get
+// none: their lists would be a burden, and calls on masks so large fill the chip through the other forms.
+//
+static WaveTile wave_tile(const uint64_t *rows) {
+    WaveTile t{{0, 0}, 0};
+    for (int side = 0; side < 2; ++side) {
+        uint64_t any = 0, all = ~(uint64_t)0;
+        for (int r = 32 * side; r < 32 * side + 32; ++r) { any |= rows[r]; all &= rows[r]; }
+        t.any[side] = any;
+        t.full |= (uint8_t)((((uint32_t)all == 0xFFFFFFFFu) | ((uint32_t)(all >> 32) == 0xFFFFFFFFu) << 1) << (2 * side));
+    }
+    return t;
+}
+static int wave_parts(int32_t n) { return n <= kWaveWhole ? 1 : (n + 63) / 64; }  // (a wave holds one entry per lane, and four may share a list)
+
+bool count_wave_lists(const smha_plan *p) {
+    WaveLists &wl = p->wave;
+    std::lock_guard<std::mutex> lock(wl.mutex);
+    if (wl.counted) return wl.possible;
     constexpr int64_t kMaxWaveEntries = 1 << 20;
-    const int n_masks = p->Bm * p->Hm, n_groups = (p->S + 31) / 32;
+    const int n_masks = p->Bm * p->Hm, n_groups = (p->S + 31) / 32, stride = 2 * ((n_groups + 1) / 2);
     int64_t at_most = 0;
     for (const MaskFormats &m : p->masks) at_most += 4 * (int64_t)m.kt_col.size();
-    if (at_most > kMaxWaveEntries || n_groups > 16384 /* (a grid's y holds a mask's workgroups) */ || p->h_kt_bitmap.size() * sizeof(uint64_t) >= ((size_t)1 << 31)) return;
-    WaveLists &wl = p->wave;
-    std::vector<WaveEntry> list[2];
-    std::vector<uint32_t> used[2];
-    std::vector<WaveItem> items;
-    std::vector<int32_t> first;  // of each 32-row group: its first entry
-    std::vector<int32_t> at;
-    std::vector<char> touched(2 * (size_t)((p->Sk + 63) / 64), 0);  // 32-key tiles
-    wl.ents.reserve((size_t)at_most + 1);
-    wl.used.reserve((size_t)at_most + 1);
+    if (!p->has_block || p->opts.block_form != 0 || at_most > kMaxWaveEntries || n_groups > 16384 /* (a grid's y holds a mask's workgroups) */ ||
+        p->h_kt_bitmap.size() * sizeof(uint64_t) >= ((size_t)1 << 31)) {
+        wl.counted = true;
+        return false;
+    }
+    std::vector<int32_t> lengths((size_t)n_masks * stride, 0);
+    std::vector<char> touched(2 * (size_t)((p->Sk + 63) / 64), 0);                // 32-key tiles
+    std::vector<int32_t> of_length(kWaveWhole + 1, 0);
+    std::vector<WaveTile> tiles;
+    size_t n_part = 0;
+    for (const MaskFormats &m : p->masks) n_part += m.kt_bits().size() / 64;
+    tiles.reserve(n_part);
+    int64_t ents = 0, part_ents = 0;
+    int max_splits = 0, max_slots = 0;
     for (int mi = 0; mi < n_masks; ++mi) {
         const MaskFormats &m = p->masks[mi];
-        first.assign(1, (int32_t)wl.ents.size());
-        for (int tr = 0; 2 * tr < n_groups; ++tr) {
-            list[0].clear();
-            list[1].clear();
-            used[0].clear();
-            used[1].clear();
+        int32_t *const of = lengths.data() + (size_t)mi * stride;
+        for (int tr = 0; 2 * tr < n_groups; ++tr)
             for (int e = m.kt_row_ptr[tr]; e < m.kt_row_ptr[tr + 1]; ++e) {
-                const int32_t key = m.kt_col[e] * 64;
+                char *const keys = touched.data() + 2 * (size_t)m.kt_col[e];
                 if (m.kt_bmp[e] < 0) {
-                    for (auto &l : list) { l.push_back({key, -1}); l.push_back({key + 32, -1}); }
-                    for (auto &u : used) u.insert(u.end(), 2, 0xFFFFFFFFu);
-                    touched[2 * m.kt_col[e]] = touched[2 * m.kt_col[e] + 1] = 1;
+                    of[2 * tr] += 2;
+                    of[2 * tr + 1] += 2;
+                    keys[0] = keys[1] = 1;
                     continue;
                 }
-                const uint64_t *w = m.kt_bits().data() + (size_t)m.kt_bmp[e] * 64;
-                for (int side = 0; side < 2; ++side) {
-                    uint64_t any = 0, all = ~(uint64_t)0;
-                    for (int r = 32 * side; r < 32 * side + 32; ++r) { any |= w[r]; all &= w[r]; }
+                tiles.push_back(wave_tile(m.kt_bits().data() + (size_t)m.kt_bmp[e] * 64));
+                const WaveTile &t = tiles.back();
+                for (int side = 0; side < 2; ++side)
                     for (int half = 0; half < 2; ++half)
-                        if ((uint32_t)(any >> (32 * half))) {
-                            touched[2 * m.kt_col[e] + half] = 1;
-                            used[side].push_back((uint32_t)(any >> (32 * half)));
-                            list[side].push_back({key + 32 * half, (uint32_t)(all >> (32 * half)) == 0xFFFFFFFFu ? -1 : m.kt_bmp[e] + bmp_base[mi]});
+                        if ((uint32_t)(t.any[side] >> (32 * half))) {
+                            ++of[2 * tr + side];
+                            part_ents += !(t.full >> (2 * side + half) & 1);
+                            keys[half] = 1;
                         }
-                }
             }
-            for (int side = 0; side < 2 && 2 * tr + side < n_groups; ++side) {
-                for (const WaveEntry &e : list[side]) wl.part_ents += e.code >= 0;
-                wl.ents.insert(wl.ents.end(), list[side].begin(), list[side].end());
-                wl.used.insert(wl.used.end(), used[side].begin(), used[side].end());
-                first.push_back((int32_t)wl.ents.size());
-            }
+        int slots = 0, splits = 0;
+        for (int g = 0; g < n_groups; ++g) {
+            const int parts = wave_parts(of[g]);
+            for (int c = 0; c < parts; ++c) ++of_length[(size_t)((int64_t)of[g] * (c + 1) / parts - (int64_t)of[g] * c / parts)];
+            ents += of[g];
+            slots += parts > 1 ? parts : 0;
+            splits += parts > 1;
         }
-        // a wave holds one entry per lane and four waves may share a list (build_wave_order): lists of more than 128
-        // entries are cut into parts of at most 64, whose partial results are merged in memory
+        max_slots = std::max(max_slots, slots);
+        max_splits = std::max(max_splits, splits);
+    }
+    std::copy(of_length.begin(), of_length.end(), wl.of_length);
+    wl.tiles.swap(tiles);
+    wl.lengths.swap(lengths);
+    wl.n_ents = ents;
+    wl.part_ents = part_ents;
+    wl.keys = 32 * (int)std::count(touched.begin(), touched.end(), 1);
+    wl.max_slots = max_slots;
+    wl.max_splits = max_splits;
+    wl.possible = wl.counted = true;
+    return true;
+}
+
+void make_wave_lists(const smha_plan *p) {  // (count_wave_lists has said that they are possible)
+    WaveLists &wl = p->wave;
+    std::lock_guard<std::mutex> lock(wl.mutex);
+    if (wl.made) return;
+    const int n_masks = p->Bm * p->Hm, n_groups = (p->S + 31) / 32, stride = 2 * ((n_groups + 1) / 2);
+    std::vector<WaveItem> all_items, items;
+    std::vector<WaveEntry> ents((size_t)wl.n_ents + 1, WaveEntry{0, -1});  // (the last: an empty item's entry)
+    std::vector<uint32_t> all_used((size_t)wl.n_ents + 1, 0u);
+    std::vector<int32_t> item_off, item_cnt, split_off, first((size_t)stride + 1), next, at;  // first: of each 32-row group its first entry
+    std::vector<SplitRow> all_splits;
+    const WaveTile *tile = wl.tiles.data();
+    first[0] = 0;
+    for (int mi = 0; mi < n_masks; ++mi) {
+        const MaskFormats &m = p->masks[mi];
+        for (int g = 0; g < stride; ++g) first[g + 1] = first[g] + wl.lengths[(size_t)mi * stride + g];
+        next.assign(first.begin(), first.end());
+        for (int tr = 0; 2 * tr < n_groups; ++tr)
+            for (int e = m.kt_row_ptr[tr]; e < m.kt_row_ptr[tr + 1]; ++e) {
+                const int32_t key = m.kt_col[e] * 64;
+                const bool whole = m.kt_bmp[e] < 0;
+                const WaveTile t = whole ? WaveTile{{~(uint64_t)0, ~(uint64_t)0}, 15} : *tile++;
+                for (int side = 0; side < 2; ++side)
+                    for (int half = 0; half < 2; ++half) {
+                        const uint32_t any = (uint32_t)(t.any[side] >> (32 * half));
+                        if (any == 0) continue;
+                        const size_t to = (size_t)next[2 * tr + side]++;
+                        all_used[to] = any;
+                        ents[to] = WaveEntry{key + 32 * half, t.full >> (2 * side + half) & 1 ? -1 : m.kt_bmp[e] + wl.bmp_base[mi]};
+                    }
+            }
+        // lists of more than kWaveWhole entries are cut, and the parts' results are merged in memory
         items.clear();
         int32_t slots = 0, n_splits = 0;
-        wl.split_off.push_back((int32_t)wl.splits.size());
+        split_off.push_back((int32_t)all_splits.size());
         for (int g = 0; g < n_groups; ++g) {
             const int32_t b = first[g], n = first[g + 1] - b;
-            const int parts = n <= kWaveWhole ? 1 : (n + 63) / 64;
-            if (parts > 1) wl.splits.push_back({g, slots, parts, 0});
+            const int parts = wave_parts(n);
+            if (parts > 1) all_splits.push_back({g, slots, parts, 0});
             for (int c = 0; c < parts; ++c) {
                 const int32_t cb = b + (int32_t)((int64_t)n * c / parts), ce = b + (int32_t)((int64_t)n * (c + 1) / parts);
-                const WaveEntry e0 = ce > cb ? wl.ents[cb] : WaveEntry{0, -1};
+                const WaveEntry e0 = ce > cb ? ents[cb] : WaveEntry{0, -1};
                 items.push_back({g, cb, ce - cb, parts > 1 ? slots++ : -1, parts > 1 ? n_splits : -1, e0.key, e0.code, 0});
             }
             n_splits += parts > 1;
         }
         // longest first, in row order where equal: a counting sort
         at.assign(kWaveWhole + 2, 0);
-        for (const WaveItem &i : items) {
-            ++at[kWaveWhole - i.n + 1];
-            ++wl.of_length[i.n];
-        }
+        for (const WaveItem &i : items) ++at[kWaveWhole - i.n + 1];
         for (int c = 0; c <= kWaveWhole; ++c) at[c + 1] += at[c];
-        const size_t base = wl.items.size();
-        wl.items.resize(base + items.size());
-        for (const WaveItem &i : items) wl.items[base + at[kWaveWhole - i.n]++] = i;
-        wl.item_off.push_back((int32_t)base);
-        wl.item_cnt.push_back((int32_t)items.size());
-        wl.max_splits = std::max(wl.max_splits, (int)n_splits);
-        wl.max_slots = std::max(wl.max_slots, (int)slots);
+        const size_t base = all_items.size();
+        all_items.resize(base + items.size());
+        for (const WaveItem &i : items) all_items[base + at[kWaveWhole - i.n]++] = i;
+        item_off.push_back((int32_t)base);
+        item_cnt.push_back((int32_t)items.size());
+        first[0] = first[stride];
     }
-    wl.keys = 32 * (int)std::count(touched.begin(), touched.end(), 1);
-    wl.ents.push_back({0, -1});  // (an empty item's entry)
-    wl.used.push_back(0);
+    wl.items.swap(all_items);
+    wl.ents.swap(ents);
+    wl.used.swap(all_used);
+    wl.item_off.swap(item_off);
+    wl.item_cnt.swap(item_cnt);
+    wl.split_off.swap(split_off);
+    wl.splits.swap(all_splits);
+    std::vector<WaveTile>().swap(wl.tiles);
+    std::vector<int32_t>().swap(wl.lengths);
+    wl.made = true;
 }
 
 smha_status_t finish_plan(smha_plan *p) {
@@ -602,7 +666,6 @@ smha_status_t finish_plan(smha_plan *p) {
     p->row_mean_nnz = nnz / S;
 
     try {
-        std::vector<int32_t> bmp_base_of;  // of each mask: its first block in h_kt_bitmap
         // ---- block path first (its work lists say how many tiles the kernel will really visit,
         // which the selector needs): tiles, work items, split rows --------------------------
         if (p->opts.force != SMHA_KERNEL_ROW || p->opts.build_both) {
@@ -611,7 +674,7 @@ smha_status_t finish_plan(smha_plan *p) {
             for (int mi = 0; mi < n_masks; ++mi) {
                 MaskFormats &m = p->masks[mi];
                 const int32_t bmp_base = (int32_t)(p->h_kt_bitmap.size() / 64);
-                bmp_base_of.push_back(bmp_base);
+                p->wave.bmp_base.push_back(bmp_base);
                 p->h_kt_bitmap.insert(p->h_kt_bitmap.end(), m.kt_bits().begin(), m.kt_bits().end());
                 // union of the two tile rows of every supertile (both lists ascending: merge); tiles
                 // that use few key columns are repacked into gathered tiles (see UEntry), which go
@@ -811,7 +874,6 @@ smha_status_t finish_plan(smha_plan *p) {
             const double groups = (double)n_masks * ((p->S + 127) / 128);
             p->dense_long_lists = (double)part_in_lists < 0.15 * (double)tiles_in_lists && (double)p->h_uent.size() > 16.0 * groups;
         }
-        if (p->has_block && p->opts.block_form == 0) build_wave_lists(p, bmp_base_of);
         if (p->has_block) {
             p->h_kt_bitmap.insert(p->h_kt_bitmap.end(), 64, 0ull);  // spare all-zero block
             p->h_uent.push_back(UEntry{0, {-2, -2}, 0});             // spare entry: an empty item may read one past its list
@@ -992,7 +1054,7 @@ static double wave_time_us(const smha_plan *plan, int B, int H, int D, bool bf16
     const double per_mask = 1.0 / (plan->Bm * plan->Hm), heads = (double)B * H;
     const WaveCost &c = kWaveCost[row_width(D)];
     const double slots = (D == 64 ? 16.0 : D == 128 ? 8.0 : 4.0) * plan->n_cu;
-    const double part = (double)wl.part_ents / std::max<double>(1.0, (double)wl.ents.size() - 1);
+    const double part = (double)wl.part_ents / std::max<double>(1.0, (double)wl.n_ents);
     const double step_ns = c.step * (1 + c.part * part);
     double best = 0, best_us = 0;
     alone = 0;
@@ -1060,7 +1122,7 @@ static double block_time_us(const smha_plan *plan, int lvl, int form, int B, int
     const BlockCost &c = kBlockCost[row_width(D)][form == 3];
     const double steps = std::max<double>(1.0, (double)plan->h_uent.size() - 1);
     const double parts = tiles ? (double)part / (double)tiles : 0.0, act = std::min(2.0, (double)tiles / steps);
-    const double subs = ((double)plan->wave.ents.size() - 1) / steps;
+    const double subs = (double)plan->wave.n_ents / steps;
     const double lone = (1 - parts) * std::min(1.0, std::max(0.0, (1.35 - act) / 0.3));
     const double gather = plan->n_gathered > 0 ? c.gather : 1.0;
     const double unit_us = unit * std::exp(c.unit + c.unit_act * (act - 1.5) + c.unit_part * act * parts + c.unit_sub * (subs - 5) + c.unit_lone * lone);
@@ -1081,7 +1143,8 @@ static double block_time_us(const smha_plan *plan, int lvl, int form, int B, int
 // each call would give 0.663, 0.711 and 0.765.
 // The two input types are decided together (by the product of their ratios): one order and one set of workspaces serves both.
 bool wave_form_pays(const smha_plan *plan, int lvl, int form, int B, int H, int D, int &alone) {
-    if (plan->wave.items.empty() || H > 65535 || (int64_t)B * H > (1 << 18) /* (a grid's z holds an eighth of them) */) return false;
+    if (H > 65535 || (int64_t)B * H > (1 << 18) /* (a grid's z holds an eighth of them) */) return false;
+    if (!count_wave_lists(plan)) return false;
     if (workspace_bytes(plan, 0, 4, B, H, D, nullptr) > kStaticScratchBytes) return false;  // (smha_forward_static takes what it took)
     double ratio = 1;
     for (const bool bf16 : {false, true}) ratio *= wave_time_us(plan, B, H, D, bf16, alone) / block_time_us(plan, lvl, form, B, H, D, bf16);
@@ -1501,12 +1564,18 @@ extern "C" smha_status_t smha_plan_export(const smha_plan_t *p, int mask_index, 
             bytes = (size_t)wl.item_cnt[mask_index] * sizeof(Item); break;
         }
         case SMHA_EXPORT_WAVE_ITEMS:
-            if (p->wave.items.empty()) return SMHA_ERR_UNSUPPORTED;
+        case SMHA_EXPORT_WAVE_ENTRIES:
+            try {
+                if (!count_wave_lists(p)) return SMHA_ERR_UNSUPPORTED;
+                make_wave_lists(p);
+            } catch (const std::bad_alloc &) {
+                return SMHA_ERR_ALLOC;
+            }
+            if (which == SMHA_EXPORT_WAVE_ENTRIES) {
+                src = p->wave.ents.data(); bytes = (p->wave.ents.size() - 1) * sizeof(WaveEntry); break;  // (without the spare entry)
+            }
             src = p->wave.items.data() + p->wave.item_off[mask_index];
             bytes = (size_t)p->wave.item_cnt[mask_index] * sizeof(WaveItem); break;
-        case SMHA_EXPORT_WAVE_ENTRIES:
-            if (p->wave.items.empty()) return SMHA_ERR_UNSUPPORTED;
-            src = p->wave.ents.data(); bytes = (p->wave.ents.size() - 1) * sizeof(WaveEntry); break;  // (without the spare entry)
         default: return SMHA_ERR_INVALID_ARG;
     }
     *need = bytes;

@@ -110,11 +110,14 @@ struct DeviceArrays {
     int32_t *item_off[2] = {nullptr, nullptr}, *item_cnt[2] = {nullptr, nullptr};      // [n_masks]
     SplitRow *split_rows[2] = {nullptr, nullptr};
     int32_t *split_off[2] = {nullptr, nullptr}, *split_cnt[2] = {nullptr, nullptr};    // [n_masks]
-    // the wave form's (WaveLists)
-    WaveEntry *wave_ents = nullptr;
-    uint32_t *wave_used = nullptr;
-    int32_t *wave_split_off = nullptr;                                                 // [n_masks]
-    SplitRow *wave_splits = nullptr;
+};
+
+// The wave form's arrays (WaveLists): in the block of the first call shape's order that takes the form.
+struct WaveArrays {
+    WaveEntry *ents = nullptr;
+    uint32_t *used = nullptr;
+    int32_t *split_off = nullptr;  // [n_masks]
+    SplitRow *splits = nullptr;
 };
 
 // The block kernel's work items for every mask of a plan: each 128-row group's list of steps, whole
@@ -127,18 +130,34 @@ struct WorkLists {
     int max_items = 0, max_split_rows = 0, max_slots = 0;
 };
 
-// The wave form's work items of every mask, longest first; none where the form is ruled out.
+// A partly filled tile as the wave form's lists see it: of each 32-row half which keys any row has, and whether all
+// 32 x 32 scores are kept (bit 2 half + (key / 32)).
+struct WaveTile {
+    uint64_t any[2];
+    uint8_t full;
+};
+
+// The wave form's work items of every mask, longest first.  Neither the lists nor what the estimates need of them is made with
+// the plan: count_wave_lists and make_wave_lists do that once, under `mutex`, and change nothing afterwards.
 constexpr int kWaveWhole = 128;  // longest list that is not cut
 struct WaveLists {
+    std::mutex mutex;
+    std::vector<int32_t> bmp_base;  // of each mask: its first block in h_kt_bitmap
+    // by count_wave_lists
+    bool counted = false, possible = false;
+    int max_splits = 0, max_slots = 0;
+    int32_t of_length[kWaveWhole + 1] = {0};  // items by entries, over all masks
+    int64_t n_ents = 0, part_ents = 0;        // entries, and those that have a bitmap
+    int keys = 0;                             // in 32-key tiles that any entry names
+    std::vector<int32_t> lengths;             // of each mask: its 32-row groups' entries, an even number of groups; and the
+    std::vector<WaveTile> tiles;              // partly filled tiles of all masks: both until the lists are made
+    // by make_wave_lists
+    bool made = false;
     std::vector<WaveItem> items;
     std::vector<WaveEntry> ents;
     std::vector<uint32_t> used;  // of each entry: its keys that any of the 32 rows has, bit k = k-th key
     std::vector<int32_t> item_off, item_cnt, split_off;
     std::vector<SplitRow> splits;
-    int max_splits = 0, max_slots = 0;
-    int32_t of_length[kWaveWhole + 1] = {0};  // items by entries, over all masks
-    int64_t part_ents = 0;                    // entries that have a bitmap
-    int keys = 0;                             // in 32-key tiles that any entry names
 };
 
 }  // namespace smha
@@ -166,7 +185,7 @@ struct smha_plan {
     // keep the chip busy); [1]: every list cut to at most 16 steps (latency: with few heads the
     // longest list is the whole launch).  smha_forward picks by how many items the call has.
     smha::WorkLists lists[2];
-    smha::WaveLists wave;
+    mutable smha::WaveLists wave;
     bool fine_differs = false;  // false: [1] is empty and [0] serves both
     // Tiles almost all full and lists long (dense causal and the like): at 128 columns such plans run the
     // block kernel's first form; all others its third form, whose waves skip at 16 rows x 32 keys.
@@ -203,6 +222,7 @@ struct smha_plan {
     mutable std::mutex prepared_mutex;
     mutable std::vector<Prepared *> prepared;
     mutable std::vector<CallShape> calls;
+    mutable smha::WaveArrays wave_dev;
 };
 
 namespace smha {
@@ -213,6 +233,9 @@ constexpr size_t kStaticScratchBytes = (size_t)32 << 20;  // smha_forward_static
 smha_status_t finish_plan(smha_plan *p);      // selector, work lists, concatenation
 // which workgroup of the block kernel takes which item, for B x H heads on `slots` workgroups per XCD
 void build_work_order(const smha_plan *plan, int lvl, int B, int H, int slots, bool spread, std::vector<int32_t> &table, int &per_xcd);
+// what the estimates need of the wave form's lists (false: the plan has none), and the lists
+bool count_wave_lists(const smha_plan *p);
+void make_wave_lists(const smha_plan *p);
 // whether a call shape runs the wave form rather than `form` at grain `lvl`; alone: see build_wave_order
 bool wave_form_pays(const smha_plan *plan, int lvl, int form, int B, int H, int D, int &alone);
 // the wave form's workgroups: four WaveItems each, as many per mask (the result); see WaveItem

@@ -1,13 +1,15 @@
 // The host planner (csrc/plan.cpp) under AddressSanitizer and UndefinedBehaviorSanitizer: plans for ragged,
 // rectangular, scattered, strided and long-row masks, every tile size, every kernel choice, with and without
-// gathered tiles, every export.  The device side is stubbed out (plans stay host-only).  Built and run by
+// gathered tiles, every export, both work orders, the wave form's lists and orders.  The device side is stubbed out (plans stay host-only).  Built and run by
 // tests/test_planner_sanitizers.py.
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <vector>
 #include "smha.h"
 #include "smha_internal.hpp"
+using namespace smha;
 namespace smha {
 smha_status_t upload_plan(smha_plan *, int) { return SMHA_OK; }
 void release_device(smha_plan *) {}
@@ -17,8 +19,70 @@ smha_status_t classify_device_mask(const uint8_t *, int, int, int, std::vector<T
 }
 static uint64_t rng_state = 12345;
 static uint32_t rnd() { rng_state = rng_state * 6364136223846793005ull + 1442695040888963407ull; return (uint32_t)(rng_state >> 33); }
+static void expect(bool ok, const char *what) {
+    if (ok) return;
+    printf("failed: %s\n", what);
+    exit(1);
+}
+// The wave form's lists: made for the first call that takes the form, not with the plan; each entry's keys are those that any
+// of its 32 rows has; every order hands each wave at most 64 entries and covers each entry once.
+static void wave_form(smha_plan_t *p, int B, int H) {
+    expect(!p->wave.counted && !p->wave.made, "nothing of the wave form's lists is made with the plan");
+    int alone = 0;
+    for (int D : {64, 128, 256})
+        for (int form : {1, 3})
+            if (p->has_block && (form == 1 || D > 64)) wave_form_pays(p, 0, form, B, H, D, alone);
+    expect(!p->wave.made, "nor for an estimate");
+    if (!count_wave_lists(p)) return;
+    const WaveLists &wl = p->wave;
+    int64_t n_items = 0, n_ents = 0;
+    for (int n = 0; n <= kWaveWhole; ++n) { n_items += wl.of_length[n]; n_ents += (int64_t)n * wl.of_length[n]; }
+    expect(n_ents == wl.n_ents, "the lengths add up");
+    make_wave_lists(p);
+    expect((int64_t)wl.items.size() == n_items && (int64_t)wl.ents.size() == n_ents + 1 && wl.used.size() == wl.ents.size(), "as many as counted");
+    const int n_masks = p->Bm * p->Hm;
+    int slots = 0, splits = 0;
+    int64_t part = 0;
+    for (int mi = 0; mi < n_masks; ++mi) {
+        int s = 0, top = 0;
+        for (int i = 0; i < wl.item_cnt[mi]; ++i) {
+            const WaveItem &it = wl.items[wl.item_off[mi] + i];
+            s += it.slot >= 0;
+            top = std::max(top, it.split + 1);
+            for (int e = it.begin; e < it.begin + it.n; ++e) {
+                uint32_t any = 0xFFFFFFFFu;
+                if (wl.ents[e].code >= 0) {
+                    any = 0;
+                    ++part;
+                    for (int r = 0; r < 32; ++r)
+                        any |= (uint32_t)(p->h_kt_bitmap[(size_t)wl.ents[e].code * 64 + 32 * (it.rg & 1) + r] >> (wl.ents[e].key & 32));
+                }
+                expect(any != 0 && any == wl.used[e], "the keys that any row of an entry has");
+            }
+        }
+        slots = std::max(slots, s);
+        splits = std::max(splits, top);
+    }
+    expect(slots == wl.max_slots && splits == wl.max_splits && part == wl.part_ents, "slots, split groups and partly filled entries as counted");
+    for (int limit : {1, 2, 12, 64}) {
+        std::vector<int32_t> table;
+        const int wgs = build_wave_order(p, limit, table);
+        expect(table.size() == (size_t)wgs * n_masks * 32, "four records of eight words a workgroup");
+        const WaveItem *rec = reinterpret_cast<const WaveItem *>(table.data());
+        std::vector<int> seen(wl.ents.size(), 0);
+        for (size_t i = 0; i < (size_t)wgs * n_masks * 4; ++i) {
+            expect(rec[i].n >= 0 && rec[i].n <= 64 && rec[i].begin >= 0 && (size_t)rec[i].begin + rec[i].n < wl.ents.size() + 1, "a wave's entries");
+            expect(rec[i].team == rec[i / 4 * 4].team && (rec[i].team == 0 || rec[i].rg >= 0), "a team is a whole workgroup");
+            expect(rec[i].n == 0 || (rec[i].key0 == wl.ents[rec[i].begin].key && rec[i].code0 == wl.ents[rec[i].begin].code), "the first entry's words");
+            for (int e = 0; e < rec[i].n; ++e) ++seen[rec[i].begin + e];
+        }
+        for (int64_t e = 0; e < n_ents; ++e) expect(seen[e] == 1, "each entry once");
+    }
+}
 static void exports(smha_plan_t *p, int n_masks) {
-    for (int which = 0; which <= 15; ++which)
+    smha_plan_info_t shape;
+    if (smha_plan_info(p, &shape) == SMHA_OK) wave_form(p, shape.Bm == 1 ? 3 : shape.Bm, shape.Hm == 1 ? 9 : shape.Hm);
+    for (int which = 0; which <= 17; ++which)
         for (int mi = 0; mi < n_masks; ++mi) {
             size_t need = 0;
             if (smha_plan_export(p, mi, (smha_export_t)which, nullptr, 0, &need) != SMHA_OK) continue;
@@ -41,6 +105,9 @@ static void exports(smha_plan_t *p, int n_masks) {
                     if (smha_plan_work_order(p, B, H, slots, fine, nullptr, 0, &need, &per) != SMHA_OK) continue;
                     std::vector<int32_t> buf(need);
                     smha_plan_work_order(p, B, H, slots, fine, buf.data(), need, &need, &per);
+                    if (smha_plan_call_order(p, B, H, slots, fine, nullptr, 0, &need, &per) != SMHA_OK) continue;
+                    buf.assign(need, 0);
+                    smha_plan_call_order(p, B, H, slots, fine, buf.data(), need, &need, &per);
                 }
 }
 int main() {

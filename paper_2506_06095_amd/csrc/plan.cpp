@@ -1018,26 +1018,26 @@ int build_wave_order(const smha_plan *plan, int alone, std::vector<int32_t> &tab
 // Estimated times of a call, for the choice between the wave form and the other two (and for its `alone`).  Several things
 // bound a launch: what the chip's compute units take together, the longest chain of steps in one wave or workgroup, and
 // the bytes of Q, K, V and O; the estimate is the root of the sum of their p-th powers.  Constants are in us (per wave and
-// step of the wave form: ns, `memory`: us per MB), fitted by least squares of the logarithms to 1000 calls of
+// step of the wave form: ns, `memory`: us per MB), fitted by least squares of the logarithms to 1207 calls of
 // profiles/block_forms.csv (all kinds of masks, 64 to 8192 queries, 1 to 400 heads, 8 to 256 columns; clocks settled by 10 ms of the
 // same work and three sets of inputs in turn: measured from idle clocks the first form took 15 % longer, the wave form 3 %,
-// and the choice went wrong by that).  Mean error over the table's other 600 calls: 5 to 7 % (wave form), 5 % (the others).
+// and the choice went wrong by that).  Mean error over 600 other calls of the table: 5 to 7 % (wave form), 5 % (the others).
 struct WaveCost {
     double start, wave, step, held, part, bf16, chain, chain_full, power, uneven, part_all, join, memory;
 };
 static const WaveCost kWaveCost[3] = {
-    {3.07, 0.7079, 0.4048, 0.22, 0.076, 1.20, 0.4968, 0.2111, 3.4, 0.0, -0.027, 1.649, 0.0311},     // 64 columns
-    {3.83, 1.6077, 0.7674, 0.05, 0.191, 1.17, 0.7311, 0.1648, 4.0, 0.09, -0.114, 2.275, 0.0914},    // 128
-    {5.48, 5.0865, 1.6524, 0.63, 0.156, 1.17, 1.5350, 0.0, 4.0, 0.23, -0.043, 2.934, 0.0589}};      // 256
+    {3.07, 0.7028, 0.4019, 0.22, 0.076, 1.20, 0.4933, 0.2096, 3.4, 0.0, -0.003, 1.946, 0.0461},     // 64 columns
+    {3.80, 1.5978, 0.7627, 0.05, 0.191, 1.17, 0.7266, 0.1638, 4.0, 0.09, -0.076, 1.877, 0.0700},    // 128
+    {5.43, 5.1097, 1.6599, 0.63, 0.156, 1.17, 1.5420, 0.0, 4.0, 0.23, -0.041, 4.513, 0.1521}};      // 256
 struct BlockCost {
     double start, unit, unit_act, unit_part, unit_sub, unit_lone, group, group_act, group_part, unit_bf16, group_bf16, gather, power, merge, memory;
 };
 static const BlockCost kBlockCost[3][2] = {  // first form, third form (none at 64 columns)
-    {{1.730, -0.941, 0.657, -0.037, -0.006, 0.007, -0.570, -0.355, 0.163, 1.295, 1.163, 1.139, 1.588, 5.257, 0.096}, {}},
-    {{2.033, -0.656, -0.261, 0.033, 0.009, -0.049, -0.065, 0.299, -0.052, 1.257, 1.049, 0.998, 1.200, 11.013, 0.098},
-     {1.669, -0.415, -0.189, -0.002, 0.105, -0.177, -0.394, 0.030, 0.162, 1.229, 1.051, 1.100, 1.669, 7.180, 0.156}},
-    {{2.212, 0.693, -0.199, 0.146, 0.000, -0.399, 0.186, 0.390, -0.400, 1.155, 1.061, 0.900, 1.200, 10.661, 0.098},
-     {1.609, -0.132, -0.036, 0.238, 0.064, -0.803, 0.186, 0.065, -0.388, 1.133, 1.140, 1.100, 1.399, 10.224, 0.130}}};
+    {{1.743, -0.920, 0.640, -0.040, -0.009, 0.049, -0.526, -0.291, 0.165, 1.304, 1.172, 1.136, 1.781, 5.390, 0.131}, {}},
+    {{2.095, -0.519, -0.107, -0.089, 0.007, -0.154, -0.253, 0.255, 0.004, 1.254, 1.043, 1.073, 1.200, 11.641, 0.098},
+     {1.686, -0.455, -0.179, -0.008, 0.097, -0.216, -0.378, 0.057, 0.132, 1.229, 1.057, 1.100, 1.570, 6.935, 0.145}},
+    {{2.039, 0.773, 0.001, 0.086, 0.001, -0.329, 0.186, -0.182, -0.400, 1.158, 1.004, 0.900, 1.200, 10.146, 0.090},
+     {1.576, -0.137, -0.049, 0.247, 0.065, -0.856, 0.186, 0.050, -0.400, 1.128, 1.147, 1.100, 1.384, 10.481, 0.128}}};
 
 // MB that a call on masks which touch `keys` keys reads and writes (the kernel's width in place of the head size)
 static double call_mb(const smha_plan *plan, int B, int H, int D, int keys) {
@@ -1136,11 +1136,11 @@ static double block_time_us(const smha_plan *plan, int lvl, int form, int B, int
 // The wave form wins where tiles are filled poorly (BigBird with random 32-blocks 16 x 12 x 2048 x 64: 126 us, 77 with
 // the wave form) and where a call has too few 128-row groups to fill the chip (causal 1 x 12 x 1024 x 64 15.2 / 8.5, per-head
 // 64-blocks 1 x 2 x 2816 x 256 20.6 / 12.8); it loses where tiles are full and rows many (causal 16 x 12 x 4096 x 128:
-// 870 / 1176), because every K and V tile is loaded once per 32 rows.  It has to win by 5 %: of the table's 1600 calls (see
-// above) 15 then run the slower form by more than 2 % with one of the input types (22 before, when the estimates came from
-// idle clocks and the margin was a tenth: 64-blocks 2 x 16 x 4096 x 64 bf16 34.0 us, 34.4 with the wave form), and the mean against
-// the other forms is 0.666 at 64 columns, 0.715 at 128, 0.768 at 256 (0.669, 0.720 and 0.770 before), where the better form for
-// each call would give 0.663, 0.711 and 0.765.
+// 870 / 1176), because every K and V tile is loaded once per 32 rows.  It has to win by 4 %: of 1600
+// calls of the table that were drawn at random 16 then run the slower form by more than 2 % with one of the input types (22 before, when
+// the estimates came from idle clocks and the margin was a tenth: 64-blocks 2 x 16 x 4096 x 64 bf16 34.0 us, 34.4 with the
+// wave form), and the mean against the other forms is 0.666 at 64 columns, 0.715 at 128, 0.768 at 256 (0.669, 0.720 and 0.770
+// before), where the better form for each call would give 0.663, 0.711 and 0.765.
 // The two input types are decided together (by the product of their ratios): one order and one set of workspaces serves both.
 bool wave_form_pays(const smha_plan *plan, int lvl, int form, int B, int H, int D, int &alone) {
     if (H > 65535 || (int64_t)B * H > (1 << 18) /* (a grid's z holds an eighth of them) */) return false;
@@ -1148,7 +1148,7 @@ bool wave_form_pays(const smha_plan *plan, int lvl, int form, int B, int H, int 
     if (workspace_bytes(plan, 0, 4, B, H, D, nullptr) > kStaticScratchBytes) return false;  // (smha_forward_static takes what it took)
     double ratio = 1;
     for (const bool bf16 : {false, true}) ratio *= wave_time_us(plan, B, H, D, bf16, alone) / block_time_us(plan, lvl, form, B, H, D, bf16);
-    return ratio < 0.95 * 0.95;
+    return ratio < 0.96 * 0.96;
 }
 
 // The block kernel's work order for B x H heads on `slots` resident workgroups per XCD.  Items

@@ -690,7 +690,7 @@ def measured_calls():
     with open(os.path.join(ROOT, "profiles", "block_forms.csv")) as f:
         for row in csv.DictReader(line for line in f if not line.startswith("#")):
             num = {k: float(v) if k == "fill" or "16" in k else int(v) for k, v in row.items() if v and k not in ("set", "kind")}
-            yield dict(num, kind=row["kind"])
+            yield dict(num, kind=row["kind"], set=row["set"])
 
 
 def plan_of_measured_call(c):
@@ -719,18 +719,20 @@ def plan_of_measured_call(c):
 
 
 def test_the_form_of_a_call_is_the_faster_one_of_the_measured_calls():
-    """1600 measured calls: at most 1 % of them run a form that is more than 2 % slower than the other with one of the input
-    types, and what the choice as a whole gives away against the faster form for each call stays under 1 %."""
-    chosen, best, slower = [], [], []
+    """Of 1600 measured calls drawn at random at most 1 % run a form that is more than 2 % slower than the other with one of the
+    input types; what the choice gives away against the faster form for each call stays under 0.7 % of these, and under 1 %
+    where 422 calls are added that two estimates disagreed on."""
+    lost, slower, drawn = [], [], []
     for c in measured_calls():
         with plan_of_measured_call(c) as plan:
             names = [smha.smha_call_kernel_name(plan.handle, c["B"], c["H"], c["d"], t) for t in (smha.SMHA_F16, smha.SMHA_BF16)]
         assert names[0] == names[1] and names[0] in ("smha_wave_fwd", "smha_block_fwd16" if c["third"] else "smha_block_fwd"), c
         ratios = [c["wave_f16"] / c["block_f16"], c["wave_bf16"] / c["block_bf16"]]
         joint = np.log(ratios).mean()
-        chosen.append(joint if names[0] == "smha_wave_fwd" else 0.0)
-        best.append(min(joint, 0.0))
-        if names[0] == "smha_wave_fwd" and max(ratios) > 1.02:
+        lost.append((joint if names[0] == "smha_wave_fwd" else 0.0) - min(joint, 0.0))
+        drawn.append(not c["set"].endswith("_near"))
+        if drawn[-1] and names[0] == "smha_wave_fwd" and max(ratios) > 1.02:
             slower.append((max(ratios), c))
-    assert len(chosen) == 1600 and len(slower) <= 0.01 * len(chosen), slower
-    assert np.exp(np.mean(chosen) - np.mean(best)) < 1.01
+    lost, drawn = np.array(lost), np.array(drawn)
+    assert drawn.sum() == 1600 and len(drawn) == 2022 and len(slower) <= 16, slower
+    assert lost[drawn].mean() < 0.007 and lost.mean() < 0.01

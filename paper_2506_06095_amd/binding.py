@@ -368,8 +368,12 @@ class Plan:
                 kernel: int = SMHA_KERNEL_AUTO, stream=None):
         import torch
         if out is None:
-            # (packed whatever Q's strides are; torch.empty with a size, a type and a device costs the host 2 us more)
-            out = torch.empty_like(Q, dtype=out_dtype, memory_format=torch.contiguous_format)
+            # (packed whatever Q's strides are, and a plain tensor whatever Q is; torch.empty with a size, a type and a device
+            # costs the host 2 us more, but empty_like hands on a subclass and dimension names)
+            if type(Q) is torch.Tensor and not Q.has_names():
+                out = torch.empty_like(Q, dtype=out_dtype, memory_format=torch.contiguous_format)
+            else:
+                out = torch.empty(Q.shape, dtype=out_dtype or Q.dtype, device=Q.device)
         if self._dims is None:
             info = self.info()
             self._dims = (info["S"], info["Sk"])

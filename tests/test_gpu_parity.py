@@ -975,3 +975,22 @@ def test_wave_form_reads_no_value_of_a_key_without_rows(torch_mod, smha, d, gath
             assert smha.smha_call_kernel_name(plan.handle, 1, 2, d, smha.SMHA_F16) == "smha_wave_fwd"
             want, got = (plan.forward(Q.to(dtype), K.to(dtype), x.to(dtype)) for x in (V, Vi))
             assert torch.equal(got[:, :, clean], want[:, :, clean])
+
+
+def test_forward_allocates_a_plain_tensor_whatever_q_is(torch_mod, smha):
+    """The output that forward allocates is a packed torch.Tensor without names, also for a Q of a subclass, a parameter, a named or
+    a transposed tensor, and holds the same values for all of them."""
+    torch = torch_mod
+
+    class Marked(torch.Tensor):
+        pass
+
+    g = torch.Generator(device="cuda").manual_seed(1)
+    Q, K, V = (torch.randn(2, 3, 100, 64, device="cuda", dtype=torch.float16, generator=g) for _ in range(3))
+    with smha.Plan.from_desc(W.MaskSpec(flags=W.CAUSAL), 2, 3, 100) as plan:
+        want = plan.forward(Q, K, V)
+        for q in (Q.as_subclass(Marked), torch.nn.Parameter(Q), Q.clone().rename("b", "h", "s", "d"),
+                  Q.transpose(1, 2).contiguous().transpose(1, 2)):
+            out = plan.forward(q, K, V)
+            assert type(out) is torch.Tensor and not out.has_names() and not out.requires_grad and out.is_contiguous()
+            assert torch.equal(out, want)

@@ -29,7 +29,7 @@ PEAK_HBM_GBS = 8000.0
 # HBM bytes per launch of the dominant kernel: constants copied from the rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE
 # summaries under profiles/ (runs of this very command, scaled by what the same counters read for a 256 MiB device
 # copy: FETCH_SIZE x2.0, WRITE_SIZE x1.0 on this machine).  This run does not measure them; the line says so.
-MEASURED_TRAFFIC = {  # (workload, kernel as smha_kernel_name gives it)
+MEASURED_TRAFFIC = {  # (workload, kernel as smha_call_kernel_name gives it)
     ("cfg5_bigbird_8k", "smha_block_fwd16"): {"read_bytes": 335.6e6, "write_bytes": 82.8e6},
     ("cfg5_bigbird_8k", "smha_block_fwd"): {"read_bytes": 343.4e6, "write_bytes": 82.3e6},
     ("cfg4_random_blocks", "smha_block_fwd"): {"read_bytes": 50.7e6, "write_bytes": 16.8e6},
@@ -125,6 +125,9 @@ def main() -> int:
         # MFMA work per staged tile (one per 64-row half of a group), which is what the roofline may count
         tile_flops = min(tile_flops, 2.0 * 4.0 * info["n_union"] * 64 * 64 * pairs_per_mask * d)
     kernel = "row" if info["kernel"] == smha.SMHA_KERNEL_ROW else "block"
+    launched = smha.smha_call_kernel_name(plan.handle, B, H, d, smha.SMHA_F16 if c.dtype == "f16" else smha.SMHA_BF16)
+    if launched == "smha_wave_fwd":  # (its work is the 32 x 32 tiles that hold a key)
+        tile_flops = 4.0 * (plan.export("wave_entries").size // 2) * 32 * 32 * pairs_per_mask * d
 
     stream = torch.cuda.current_stream()
     if args.copy_probe:
@@ -176,7 +179,7 @@ def main() -> int:
         achieved = tile_flops / (launch_ms * 1e-3) / 1e12
         roof = {"bound": "mfma", "achieved": achieved, "peak": PEAK_TFLOPS[c.dtype], "unit": "TFLOP/s",
                 "frac": achieved / PEAK_TFLOPS[c.dtype], "traffic": None,
-                "kernel": smha.smha_kernel_name(plan.handle, d, 0 if c.dtype == "f16" else 1),
+                "kernel": launched,
                 "flops_per_launch": tile_flops, "launch_ms": launch_ms,
                 "compulsory_hbm_bytes": 4.0 * B * H * S * d * 2}
     else:
@@ -185,7 +188,7 @@ def main() -> int:
         achieved = alg_bytes / (launch_ms * 1e-3) / 1e9
         roof = {"bound": "hbm", "achieved": achieved, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                 "frac": achieved / PEAK_HBM_GBS, "traffic": None,
-                "kernel": smha.smha_kernel_name(plan.handle, d, 0 if c.dtype == "f16" else 1),
+                "kernel": launched,
                 "bytes_per_launch": alg_bytes, "launch_ms": launch_ms}
 
     tr = MEASURED_TRAFFIC.get((c.name, roof["kernel"]))

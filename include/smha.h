@@ -312,10 +312,10 @@ void smha_plan_destroy(smha_plan_t *plan); /* NULL is allowed */
 
 const char *smha_status_string(smha_status_t status);
 
-/* Name and average duration bookkeeping is left to the caller; this returns the symbol
- * name of the kernel smha_forward would launch, for matching profiler output: of the block
- * kernel's forms, the one that calls run which fill the chip.  smha_call_kernel_name answers for
- * one call shape, where the wave form may take its place ("" for arguments that forward refuses). */
+/* Symbol names of kernels, for matching profiler output (name and duration bookkeeping is left to the caller).
+ * smha_call_kernel_name: the kernel that smha_forward launches for a call with this batch size, head count, head size
+ * and input type ("" for arguments that it refuses).  smha_kernel_name knows no call shape: the kernel that runs where
+ * the block kernel's wave form does not take its place, which depends on the call (block_form 0 only). */
 const char *smha_call_kernel_name(const smha_plan_t *plan, int B, int H, int d, smha_dtype_t in_dtype,
                                   smha_kernel_t kernel);
 const char *smha_kernel_name(const smha_plan_t *plan, int d, smha_dtype_t in_dtype,

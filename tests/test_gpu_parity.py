@@ -994,3 +994,27 @@ def test_forward_allocates_a_plain_tensor_whatever_q_is(torch_mod, smha):
             out = plan.forward(q, K, V)
             assert type(out) is torch.Tensor and not out.has_names() and not out.requires_grad and out.is_contiguous()
             assert torch.equal(out, want)
+
+
+def test_the_kernel_that_is_named_is_the_kernel_that_runs(torch_mod, smha):
+    """smha_call_kernel_name against the names that the profiler sees: the row kernel, the block kernel's first and third form,
+    and the wave form on a chip that is full and one that is not."""
+    torch = torch_mod
+    from torch.profiler import ProfilerActivity, profile
+    c2, blocks, causal = W.config(2), W.config(4).mask, W.MaskSpec(flags=W.CAUSAL)
+    seen = []
+    for spec, B, H, S, d, force in ((c2.mask, c2.B, c2.H, c2.S, c2.d, smha.SMHA_KERNEL_AUTO), (W.table2_spec("bigbird"), 16, 12, 2048, 64, smha.SMHA_KERNEL_AUTO),
+                                    (blocks, 2, 16, 4096, 64, smha.SMHA_KERNEL_AUTO), (causal, 16, 12, 1024, 256, smha.SMHA_KERNEL_AUTO),
+                                    (causal, 1, 2, 200, 64, smha.SMHA_KERNEL_ROW)):
+        q = torch.zeros(B, H, S, d, device="cuda", dtype=torch.float16)
+        with smha.Plan.from_desc(spec, B, H, S, head_dim=d, force=force) as plan:
+            out = plan.forward(q, q, q)
+            torch.cuda.synchronize()
+            with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as prof:
+                plan.forward(q, q, q, out=out)
+                torch.cuda.synchronize()
+            name = smha.smha_call_kernel_name(plan.handle, B, H, d, smha.SMHA_F16)
+        ran = [e.key for e in prof.key_averages() if "smha_" in e.key]
+        assert len(ran) == 1 and name + "<" in ran[0], (name, ran)
+        seen.append(name)
+    assert seen == ["smha_wave_fwd", "smha_wave_fwd", "smha_block_fwd", "smha_block_fwd16", "smha_row_fwd"]

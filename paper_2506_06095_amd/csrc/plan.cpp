@@ -1186,33 +1186,38 @@ void build_work_order(const smha_plan *plan, int lvl, int B, int H, int slots, b
     const int BH = B * H;
     auto mask_of = [&](int bh) { return (plan->Bm > 1 ? bh / H : 0) * plan->Hm + (plan->Hm > 1 ? bh % H : 0); };
     constexpr int kItemCost = 2;  // an item's start and end, in tiles
-    // what each XCD gets of each head: all items, or those listed in `some`
+    // what each XCD gets: all items of every eighth head, then those items of left-over heads that are listed in `some`
     struct Share { int32_t bh; std::vector<int32_t> some; };
-    std::vector<Share> shares[8];
+    std::vector<Share> parts[8];
     const int left_over = spread ? BH % 8 : 0, whole = BH - left_over;
-    for (int x = 0; x < 8; ++x)
-        for (int bh = x; bh < whole; bh += 8) shares[x].push_back({bh, {}});
+    auto whole_heads = [&](int x) { return (whole - x + 7) / 8; };
     int64_t dealt[8] = {0};
     for (int l = 0; l < left_over; ++l) {
         const int mask = mask_of(whole + l), first = 8 * l / left_over, last = (8 * (l + 1) - 1) / left_over;
-        for (int x = first; x <= last; ++x) shares[x].push_back({whole + l, {}});
+        for (int x = first; x <= last; ++x) parts[x].push_back({whole + l, {}});
         for (int32_t it = 0; it < wl.item_cnt[mask]; ++it) {
             const Item &item = wl.items[wl.item_off[mask] + it];
             int to = first;
             for (int x = first + 1; x <= last; ++x)
                 if (dealt[x] < dealt[to]) to = x;
             dealt[to] += kItemCost + (item.end - item.begin);
-            shares[to].back().some.push_back(it);
+            parts[to].back().some.push_back(it);
         }
         for (int x = first; x <= last; ++x)
-            if (shares[x].back().some.empty()) shares[x].pop_back();
+            if (parts[x].back().some.empty()) parts[x].pop_back();
     }
-    auto count = [&](const Share &s) { return s.some.empty() ? (int64_t)wl.item_cnt[mask_of(s.bh)] : (int64_t)s.some.size(); };
-    int64_t most = 0;  // items of the busiest XCD
+    // of XCD x's i-th head: which it is, how many items, and which (null: all of them)
+    auto head = [&](int x, int i) { return i < whole_heads(x) ? x + 8 * i : parts[x][i - whole_heads(x)].bh; };
+    auto listed = [&](int x, int i) { return i < whole_heads(x) ? nullptr : parts[x][i - whole_heads(x)].some.data(); };
+    auto count = [&](int x, int i) {
+        return i < whole_heads(x) ? (int64_t)wl.item_cnt[mask_of(x + 8 * i)] : (int64_t)parts[x][i - whole_heads(x)].some.size();
+    };
+    auto heads = [&](int x) { return whole_heads(x) + (int)parts[x].size(); };
+    int64_t items_of[8], most = 0;  // of the busiest XCD
     for (int x = 0; x < 8; ++x) {
-        int64_t n = 0;
-        for (const Share &s : shares[x]) n += count(s);
-        most = std::max(most, n);
+        items_of[x] = 0;
+        for (int i = 0; i < heads(x); ++i) items_of[x] += count(x, i);
+        most = std::max(most, items_of[x]);
     }
     // (as many workgroups on every compute unit: an odd one would be a unit that takes its second item late)
     const int n_units = (int)std::min<int64_t>({(int64_t)std::max(plan->n_cu / 8, 1), (int64_t)slots, most});
@@ -1249,25 +1254,24 @@ void build_work_order(const smha_plan *plan, int lvl, int B, int H, int slots, b
         for (int u = 0; u < n_units; ++u) heap[u] = u;
         std::fill(done.begin(), done.end(), 0.0);
         std::fill(turns.begin(), turns.end(), 0);
-        const std::vector<Share> &mine = shares[x];
-        const int last = (int)mine.size() - 1;  // this XCD's last head
-        int joint = last;                       // first head of the joint deal
-        int64_t here = 0;                       // items of this XCD
-        for (const Share &s : mine) here += count(s);
+        const int last = heads(x) - 1;  // this XCD's last head
+        int joint = last;               // first head of the joint deal
+        const int64_t here = items_of[x];
         const bool apart = aged && fine && here > per_xcd && here < 2 * (int64_t)per_xcd;
         for (int64_t n = 0; joint >= 0; --joint) {
-            n += count(mine[joint]);
+            n += count(x, joint);
             if (apart && joint != last) break;
             if (4 * n > (aged ? 12 : 9) * (int64_t)per_xcd && joint != last) break;
         }
         ++joint;
         for (int i = 0; i <= last; ++i) {
-            const int32_t bh = mine[i].bh;
+            const int32_t bh = head(x, i);
+            const int32_t *const some = listed(x, i);
             const int32_t off = wl.item_off[mask_of(bh)];
             if (i <= joint) deal.clear();
-            const int64_t n = count(mine[i]);
+            const int64_t n = count(x, i);
             for (int64_t k = 0; k < n; ++k) {  // (sorted by length, longest first)
-                const int32_t it = mine[i].some.empty() ? (int32_t)k : mine[i].some[k];
+                const int32_t it = some ? some[k] : (int32_t)k;
                 const Item &item = wl.items[off + it];
                 deal.push_back({bh, off + it, kItemCost + (item.end - item.begin)});
             }

@@ -4,6 +4,8 @@ import csv
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -736,3 +738,16 @@ def test_the_form_of_a_call_is_the_faster_one_of_the_measured_calls():
     lost, drawn = np.array(lost), np.array(drawn)
     assert drawn.sum() == 1600 and len(drawn) == 2022 and len(slower) <= 16, slower
     assert lost[drawn].mean() < 0.007 and lost.mean() < 0.01
+
+
+def test_the_order_of_very_many_heads_takes_little_more_than_its_table():
+    """2^24 heads of one item each: the table is 140 MB, and the peak while it is made and copied stays under three of them."""
+    code = ("import resource, numpy as np, paper_2506_06095_amd as smha\n"
+            "with smha.Plan.from_dense(np.ones((1, 1, 64, 64), np.uint8), device_id=-2, force=smha.SMHA_KERNEL_BLOCK) as p:\n"
+            "    before = resource.getrusage(resource.RUSAGE_SELF).ru_maxrss\n"
+            "    table, per_xcd = p.work_order(1 << 12, 1 << 12, 128, spread=True)\n"
+            "    print(table.nbytes, 1024 * (resource.getrusage(resource.RUSAGE_SELF).ru_maxrss - before))\n")
+    run = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert run.returncode == 0, run.stderr[-2000:]
+    size, peak = map(int, run.stdout.split())
+    assert size >= 8 << 24 and peak < 3 * size

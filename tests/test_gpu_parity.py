@@ -49,12 +49,15 @@ def check(got, ref, what, bf16_out=False):
 
 
 def run_case(torch, smha, Q, K, V, dtype, masks, kernel, block=64, out_f32=False, scale=0.0,
-             heads=None, plan=None, what=""):
-    """GPU forward on everything; oracle on `heads` (list of (b, h)) or on everything."""
+             heads=None, plan=None, what="", form=0):
+    """GPU forward on everything; oracle on `heads` (list of (b, h)) or on everything.  form: of the block kernel (0: the
+    library's choice); a form that was asked for is asserted to run."""
     B, H, S, d = Q.shape
     own = plan is None
     if own:
-        plan = smha.Plan.from_dense(masks, block=block, build_both=True, head_dim=d)
+        plan = smha.Plan.from_dense(masks, block=block, build_both=True, head_dim=d, block_form=form)
+        if form:
+            runs_form(smha, plan, B, H, d, dtype, form)
     try:
         q, k, v = (to_dev(torch, x, dtype) for x in (Q, K, V))
         out = plan.forward(q, k, v, out_dtype=torch.float32 if out_f32 else None, scale=scale, kernel=kernel)
@@ -78,15 +81,26 @@ def run_case(torch, smha, Q, K, V, dtype, masks, kernel, block=64, out_f32=False
 
 
 KERNELS = {"row": 1, "block": 2}
+# kernel and form: calls that the library leaves to the wave form run the older forms too
+FORMS = {"row": (1, 0), "block": (2, 0), "block_form1": (2, 1), "block_form3": (2, 3)}
 
 
-@pytest.mark.parametrize("kernel", ["block", "row"])
+def runs_form(smha, plan, B, H, d, dtype, form):
+    """The block kernel's form that a plan was asked for is the one that runs (the third exists at 128 and 256 columns, and not for
+    gathered tiles)."""
+    name = smha.smha_call_kernel_name(plan.handle, B, H, d, smha.SMHA_F16 if dtype == "f16" else smha.SMHA_BF16, smha.SMHA_KERNEL_BLOCK)
+    third = d > 64 and form == 3 and plan.info()["n_gathered"] == 0
+    assert name == ("smha_block_fwd16" if third else "smha_block_fwd"), name
+
+
+@pytest.mark.parametrize("kernel", ["block", "block_form1", "row"])
 @pytest.mark.parametrize("idx", [1, 2, 3])
 def test_configs_1_to_3_full_size(torch_mod, smha, idx, kernel):
     c = W.config(idx)
     Q, K, V = W.qkv_bits(c.B, c.H, c.S, c.d, c.dtype, c.std, c.seed)
     masks = W.dense_mask(c.mask, c.B, c.H, c.S)
-    run_case(torch_mod, smha, Q, K, V, c.dtype, masks, KERNELS[kernel], block=c.block, what=f"{c.name}/{kernel}")
+    kind, form = FORMS[kernel]
+    run_case(torch_mod, smha, Q, K, V, c.dtype, masks, kind, block=c.block, what=f"{c.name}/{kernel}", form=form)
 
 
 @pytest.mark.parametrize("kernel", ["block", "row"])
@@ -177,7 +191,7 @@ def test_long_sequences_on_sampled_rows(torch_mod, smha, name, kernel):
         assert np.all(got[:, :, rows >= valid] == 0.0)
 
 
-@pytest.mark.parametrize("kernel", ["block", "row"])
+@pytest.mark.parametrize("kernel", ["block", "block_form1", "block_form3", "row"])
 @pytest.mark.parametrize("Sq,Sk,d,dtype", [(64, 512, 64, "f16"), (100, 1000, 128, "f16"), (257, 130, 64, "bf16"),
                                            (1, 777, 128, "bf16"), (1024, 64, 64, "f16"), (300, 2100, 128, "f16")])
 def test_fewer_or_more_queries_than_keys(torch_mod, smha, kernel, Sq, Sk, d, dtype):
@@ -193,10 +207,12 @@ def test_fewer_or_more_queries_than_keys(torch_mod, smha, kernel, Sq, Sk, d, dty
         masks[0, 2, :, 64:] = 0                             # only the first key tile
     for dev in (False, True):
         m = torch_mod.from_numpy(masks).cuda() if dev else masks
-        with smha.Plan.from_dense_rect(m, build_both=True, head_dim=d) as plan:
+        with smha.Plan.from_dense_rect(m, build_both=True, head_dim=d, block_form=FORMS[kernel][1]) as plan:
             assert (plan.info()["S"], plan.info()["Sk"]) == (Sq, Sk)
+            if FORMS[kernel][1]:
+                runs_form(smha, plan, B, H, d, dtype, FORMS[kernel][1])
             q, k, v = (to_dev(torch_mod, x, dtype) for x in (Q, K, V))
-            out = plan.forward(q, k, v, out_dtype=torch_mod.float32, kernel=KERNELS[kernel])
+            out = plan.forward(q, k, v, out_dtype=torch_mod.float32, kernel=FORMS[kernel][0])
             torch_mod.cuda.synchronize()
             got = out.cpu().numpy()
             with pytest.raises(ValueError):
@@ -236,19 +252,20 @@ def test_gathered_tiles(torch_mod, smha, name, d, dtype):
     Q, _, _ = W.qkv_bits(B, H, Sq, d, dtype, 1.0, seed=Sq + d)
     _, K, V = W.qkv_bits(B, H, Sk, d, dtype, 1.0, seed=Sk + d + 1)
     q, k, v = (to_dev(torch_mod, x, dtype) for x in (Q, K, V))
-    outs = []
-    for no_gather in (False, True):
-        with smha.Plan.from_dense_rect(masks, head_dim=d, force=smha.SMHA_KERNEL_BLOCK, no_gather=no_gather) as plan:
-            assert (plan.info()["n_gathered"] > 0) == (not no_gather)
-            if name == "many_gathered" and not no_gather:
-                assert plan.info()["n_split_rows"] > 0      # lists cut at 16 gathered tiles: partial results merged
-            outs.append(plan.forward(q, k, v, out_dtype=torch_mod.float32).cpu().numpy())
     ref = oracle.masked_attention(Q, K, V, dtype, masks)
-    check(outs[0], ref, f"gathered {name}")
-    check(outs[1], ref, f"ungathered {name}")
+    for form in (1, 3, 0):                                  # (the wave form, which most of these calls take, gathers nothing)
+        for no_gather in (False, True):
+            with smha.Plan.from_dense_rect(masks, head_dim=d, force=smha.SMHA_KERNEL_BLOCK, no_gather=no_gather, block_form=form) as plan:
+                assert (plan.info()["n_gathered"] > 0) == (not no_gather)
+                if form:
+                    runs_form(smha, plan, B, H, d, dtype, form)
+                if name == "many_gathered" and not no_gather:
+                    assert plan.info()["n_split_rows"] > 0  # lists cut at 16 gathered tiles: partial results merged
+                got = plan.forward(q, k, v, out_dtype=torch_mod.float32).cpu().numpy()
+            check(got, ref, f"{name} form {form} no_gather {no_gather}")
 
 
-@pytest.mark.parametrize("kernel", ["block", "row"])
+@pytest.mark.parametrize("kernel", ["block", "block_form1", "block_form3", "row"])
 @pytest.mark.parametrize("d,dtype", [(64, "f16"), (128, "f16"), (64, "bf16"), (128, "bf16")])
 def test_ragged_lengths_and_degenerate_rows(torch_mod, smha, kernel, d, dtype):
     for S in (1, 37, 100, 130, 257):
@@ -260,8 +277,8 @@ def test_ragged_lengths_and_degenerate_rows(torch_mod, smha, kernel, d, dtype):
         masks[0, 1] = 1                      # dense attention
         masks[1, 0, S // 2] = 0              # one fully masked row
         masks[1, 1] = np.eye(S, dtype=np.uint8)  # one key per row: O = V
-        got = run_case(torch_mod, smha, Q, K, V, dtype, masks, KERNELS[kernel], out_f32=True,
-                       what=f"ragged S={S} d={d} {dtype} {kernel}")
+        kind, form = FORMS[kernel]
+        got = run_case(torch_mod, smha, Q, K, V, dtype, masks, kind, out_f32=True, what=f"ragged S={S} d={d} {dtype} {kernel}", form=form)
         assert np.all(got[0, 0] == 0.0) and np.all(got[1, 0, S // 2] == 0.0)
         # one key per row: the only weight is 1 up to fp32 rounding of the exponent argument
         assert np.allclose(got[1, 1].astype(np.float64), W.bits_to_f64(V, dtype)[1, 1], rtol=1e-5, atol=1e-7)
@@ -362,12 +379,13 @@ def test_row_kernel_reaches_the_far_end_of_a_widely_strided_head(torch_mod, smha
         assert torch.equal(plan.forward(Q, Kf, Vf), want)
 
 
-@pytest.mark.parametrize("kernel", ["block", "row"])
+@pytest.mark.parametrize("kernel", ["block", "block_form1", "block_form3", "row"])
 @pytest.mark.parametrize("d,dtype", [(8, "f16"), (32, "f16"), (32, "bf16"), (40, "f16"), (80, "bf16"), (96, "f16"),
                                      (96, "bf16"), (120, "f16"), (136, "bf16"), (192, "f16"), (256, "f16"), (256, "bf16")])
 def test_head_sizes_other_than_64_and_128(torch_mod, smha, kernel, d, dtype):
     """Any multiple of 8 up to 256: the kernels for 64, 128 and 256 columns run narrower heads (SURVEY's shape
     variants: 32, 96 and 256).  Rows are packed, so a read or a store past a row's d columns would hit its neighbour."""
+    kind, form = FORMS[kernel]
     for S in (37, 257, 1000):
         B, H = 2, 2
         Q, K, V = W.qkv_bits(B, H, S, d, dtype, 1.0, 4000 + S + d)
@@ -377,18 +395,20 @@ def test_head_sizes_other_than_64_and_128(torch_mod, smha, kernel, d, dtype):
         masks[1, 0, S // 2] = 0              # one fully masked row
         masks[1, 1] = np.eye(S, dtype=np.uint8)  # one key per row: O = V
         for out_f32 in (True, False):
-            got = run_case(torch_mod, smha, Q, K, V, dtype, masks, KERNELS[kernel], out_f32=out_f32,
-                           what=f"head size {d} S={S} {dtype} {kernel} f32out={out_f32}")
+            got = run_case(torch_mod, smha, Q, K, V, dtype, masks, kind, out_f32=out_f32,
+                           what=f"head size {d} S={S} {dtype} {kernel} f32out={out_f32}", form=form)
             assert np.all(got[1, 0, S // 2] == 0.0)
     # split groups (partial results merged) and gathered tiles at a narrow head
-    if kernel == "block":
+    if kind == KERNELS["block"]:
         S = 2100
         for spec, want in ((W.MaskSpec(flags=W.WINDOW | W.GLOBAL, window_left=32, window_right=32, n_global=70), "n_split_rows"),
                            (W.MaskSpec(flags=W.CAUSAL | W.WINDOW | W.STRIDED, window_left=70, stride=37, stride_phase=5), "n_gathered")):
             Q, K, V = W.qkv_bits(1, 2, S, d, dtype, 1.0, 77 + d)
             masks = W.dense_mask(spec, 1, 2, S)
-            with smha.Plan.from_desc(spec, 1, 2, S, head_dim=d, force=smha.SMHA_KERNEL_BLOCK) as plan:
+            with smha.Plan.from_desc(spec, 1, 2, S, head_dim=d, force=smha.SMHA_KERNEL_BLOCK, block_form=form) as plan:
                 assert plan.info()[want] > 0
+                if form:
+                    runs_form(smha, plan, 1, 2, d, dtype, form)
                 for out_f32 in (True, False):
                     run_case(torch_mod, smha, Q, K, V, dtype, masks, 0, plan=plan, out_f32=out_f32,
                              what=f"head size {d} {want} f32out={out_f32}")
@@ -435,13 +455,16 @@ def test_random_shapes_masks_and_sharing(torch_mod, smha):
         ref = oracle.masked_attention(Qb, Kb, Vb, dtype, m, None)
         what = f"case {case}: B{B} H{H} Sq{Sq} Sk{Sk} d{d} {dtype} Bm{Bm} Hm{Hm} kind{kind} density{dens} block{block}"
         make = smha.Plan.from_dense if Sq == Sk else smha.Plan.from_dense_rect
-        with make(m, block=block, build_both=True, head_dim=d) as plan:
-            for kernel in KERNELS.values():
-                for f32 in (True, False):
-                    out = plan.forward(q, k, v, out_dtype=torch.float32 if f32 else None, kernel=kernel)
-                    torch.cuda.synchronize()
-                    check(out.float().cpu().numpy(), ref, f"{what} kernel {kernel} fp32 out {f32}",
-                          bf16_out=(dtype == "bf16" and not f32))
+        for form in (0, 1, 3):
+            with make(m, block=block, build_both=True, head_dim=d, block_form=form) as plan:
+                if form:
+                    runs_form(smha, plan, B, H, d, dtype, form)
+                for kernel in KERNELS.values() if form == 0 else (smha.SMHA_KERNEL_BLOCK,):
+                    for f32 in (True, False):
+                        out = plan.forward(q, k, v, out_dtype=torch.float32 if f32 else None, kernel=kernel)
+                        torch.cuda.synchronize()
+                        check(out.float().cpu().numpy(), ref, f"{what} kernel {kernel} form {form} fp32 out {f32}",
+                              bf16_out=(dtype == "bf16" and not f32))
 
 
 @pytest.mark.parametrize("bs", [16, 32, 64])
@@ -477,8 +500,9 @@ def test_split_rows_merge_matches_unsplit_semantics(torch_mod, smha):
         run_case(torch_mod, smha, Q, K, V, "f16", masks, 0, plan=plan, what="split")
 
 
+@pytest.mark.parametrize("form", [1, 3, 0])
 @pytest.mark.parametrize("d,dtype", [(64, "f16"), (128, "bf16")])
-def test_few_heads_take_the_fine_work_items_and_agree_with_many_heads(torch_mod, smha, d, dtype):
+def test_few_heads_take_the_fine_work_items_and_agree_with_many_heads(torch_mod, smha, d, dtype, form):
     """One plan, one mask: a call with 2 heads leaves the chip mostly empty and walks the lists cut to 16
     steps (partials merged), a call with 160 heads walks the whole lists; the heads they share must agree
     with the oracle, and with each other to rounding."""
@@ -487,7 +511,9 @@ def test_few_heads_take_the_fine_work_items_and_agree_with_many_heads(torch_mod,
     spec = W.table2_spec("causal")
     masks = W.dense_mask(spec, 1, 1, S)
     Q, K, V = W.qkv_bits(1, 2, S, d, dtype, 1.0, 21)
-    with smha.Plan.from_desc(spec, 1, 2, S, head_dim=d, force=smha.SMHA_KERNEL_BLOCK) as plan:
+    with smha.Plan.from_desc(spec, 1, 2, S, head_dim=d, force=smha.SMHA_KERNEL_BLOCK, block_form=form) as plan:
+        if form:                                                       # (the library's choice may walk the wave form's lists instead)
+            runs_form(smha, plan, 1, 2, d, dtype, form)
         coarse = plan.export("kernel_items").reshape(-1, 8)
         fine = plan.export("kernel_items_fine").reshape(-1, 8)
         assert len(fine) > len(coarse) and (coarse[:, 3] == -1).all() and (fine[:, 3] >= 0).any()
@@ -500,7 +526,8 @@ def test_few_heads_take_the_fine_work_items_and_agree_with_many_heads(torch_mod,
         assert np.abs(many[:, :2].astype(np.float64) - few).max() <= 1e-3
 
 
-def test_one_plan_serves_many_batch_sizes_in_turn(torch_mod, smha):
+@pytest.mark.parametrize("form", [1, 0])
+def test_one_plan_serves_many_batch_sizes_in_turn(torch_mod, smha, form):
     """The plan keeps a work order per (batch, heads) it has seen, a few at a time: going round more batch
     sizes than it keeps, twice, every call must still give each replicated head the same rows."""
     torch = torch_mod
@@ -509,7 +536,9 @@ def test_one_plan_serves_many_batch_sizes_in_turn(torch_mod, smha):
     masks = W.dense_mask(spec, 1, 1, S)
     Q, K, V = W.qkv_bits(1, H, S, d, "f16", 1.0, 33)
     ref = oracle.masked_attention(Q, K, V, "f16", masks)
-    with smha.Plan.from_desc(spec, 1, H, S, head_dim=d, force=smha.SMHA_KERNEL_BLOCK) as plan:
+    with smha.Plan.from_desc(spec, 1, H, S, head_dim=d, force=smha.SMHA_KERNEL_BLOCK, block_form=form) as plan:
+        names = {smha.smha_call_kernel_name(plan.handle, B, H, d, smha.SMHA_F16) for B in (1, 13)}
+        assert names == {"smha_block_fwd" if form else "smha_wave_fwd"}
         for rnd in range(2):
             for B in (1, 2, 3, 5, 7, 11, 13, 4, 6, 9, 12):
                 q, k, v = (to_dev(torch, np.ascontiguousarray(np.tile(x, (B, 1, 1, 1))), "f16") for x in (Q, K, V))
@@ -574,7 +603,10 @@ def test_device_mask_is_packed_on_the_gpu_and_gives_the_host_plan(torch_mod, smh
                     np.testing.assert_array_equal(ph.export(which, mi), pd.export(which, mi), err_msg=f"{which} mask {mi} bs {bs}")
 
 
-@pytest.mark.parametrize("Sq,Sk", [(1, 1), (63, 63), (100, 100), (130, 130), (512, 512), (1000, 1000), (200, 3000), (777, 91)])
+# (small masks are classified straight into host memory, larger ones through device memory: 6 x 1024 x 1152 is 1728 tiles, 912 KB of
+# records and bitmaps, 6 x 1152 x 1216 2052 tiles and 1083 KB)
+@pytest.mark.parametrize("Sq,Sk", [(1, 1), (63, 63), (100, 100), (130, 130), (512, 512), (1000, 1000), (200, 3000), (777, 91),
+                                   (1024, 1152), (1152, 1216), (1030, 2100)])
 def test_device_mask_is_analysed_on_the_gpu_and_gives_the_host_plan(torch_mod, smha, Sq, Sk):
     """A device mask whose plan needs no per-row lists (block kernel, 64-wide tiles) is classified tile by tile
     on the GPU; statistics, exported block format and the kernel's work lists must equal, bit for bit, those
@@ -595,11 +627,14 @@ def test_device_mask_is_analysed_on_the_gpu_and_gives_the_host_plan(torch_mod, s
         for key in ("S", "Sk", "nnz", "n_valid", "n_full", "n_part", "n_valid16", "n_tiles64", "n_union", "n_items",
                     "n_gathered", "n_split_rows", "kernel", "eq1_threshold", "model_block_us", "model_row_us"):
             assert ih[key] == idv[key], key
-        for which in ("kernel_entries", "kernel_bitmaps", "kernel_gather_keys"):
+        for which in ("kernel_entries", "kernel_bitmaps", "kernel_gather_keys", "wave_entries"):
             np.testing.assert_array_equal(ph.export(which), pd.export(which), err_msg=which)
         for mi in range(6):
-            for which in ("load_row_ptr", "load_col_idx", "flags", "bitmap", "full_col_idx", "part_row_ptr", "kernel_items"):
+            for which in ("load_row_ptr", "load_col_idx", "flags", "bitmap", "full_col_idx", "part_row_ptr", "kernel_items", "wave_items"):
                 np.testing.assert_array_equal(ph.export(which, mi), pd.export(which, mi), err_msg=f"{which} mask {mi}")
+        with smha.Plan.from_dense_rect(dev[:1, :1, :64, :64].contiguous(), **kw) as small, smha.Plan.from_dense_rect(dev, **kw) as again:
+            assert small.info()["n_valid"] == int(masks[0, 0, :64, :64].any())      # (a small mask between two others)
+            np.testing.assert_array_equal(ph.export("kernel_bitmaps"), again.export("kernel_bitmaps"))
         Q, _, _ = W.qkv_bits(2, 3, Sq, 64, "f16", 1.0, seed=Sq)
         _, K, V = W.qkv_bits(2, 3, Sk, 64, "f16", 1.0, seed=Sk + 1)
         q, k, v = (to_dev(torch, x, "f16") for x in (Q, K, V))
@@ -658,7 +693,16 @@ def test_selected_kernel_wins_on_its_own_ground(torch_mod, smha):
         assert plan.info()["kernel"] == smha.SMHA_KERNEL_ROW
 
 
-@pytest.mark.parametrize("case", ["split_rows", "gathered"])
+# global rows over lists of more than 128 entries: cut, their parts merged in memory by the wave that comes last
+WAVE_CUT = W.MaskSpec(flags=W.WINDOW | W.GLOBAL, window_left=20, window_right=20, n_global=5)
+
+
+def runs_cut_wave_lists(smha, plan, B, H, d):
+    assert smha.smha_call_kernel_name(plan.handle, B, H, d, smha.SMHA_F16) == "smha_wave_fwd"
+    assert (plan.export("wave_items").reshape(-1, 8)[:, 3] >= 0).any()
+
+
+@pytest.mark.parametrize("case", ["split_rows", "gathered", "wave_cut", "wave_cut_128"])
 def test_forward_replays_from_a_hip_graph(torch_mod, smha, case):
     """Once its shape is prepared, the very first forward can be captured into a HIP graph: every replay,
     with eager forwards of the same and of other batch sizes and synchronisation in between, gives the
@@ -667,12 +711,19 @@ def test_forward_replays_from_a_hip_graph(torch_mod, smha, case):
     if case == "split_rows":    # global block rows make a split 128-row group: partial results merged in the launch
         spec = W.MaskSpec(flags=W.BIGBIRD, block=64, n_window_blocks=3, n_global_blocks=2, n_random_blocks=2, seed=9)
         B, H, S, d = 1, 4, 4096, 128
-    else:
+    elif case == "gathered":
         spec = W.MaskSpec(flags=W.CAUSAL | W.WINDOW | W.STRIDED, window_left=100, stride=32, stride_phase=1)
         B, H, S, d = 2, 2, 1500, 64
-    with smha.Plan.from_desc(spec, B, H, S, head_dim=d, force=smha.SMHA_KERNEL_BLOCK) as plan:
+    else:
+        spec, B, H, S = WAVE_CUT, 1, 9, 6000
+        d = 128 if case.endswith("128") else 64
+    with smha.Plan.from_desc(spec, B, H, S, head_dim=d, force=smha.SMHA_KERNEL_BLOCK, block_form=1 if case == "gathered" else 0) as plan:
         info = plan.info()
-        assert (info["n_split_rows"] > 0) if case == "split_rows" else (info["n_gathered"] > 0)
+        if case.startswith("wave"):
+            runs_cut_wave_lists(smha, plan, B, H, d)
+        else:
+            assert (info["n_split_rows"] > 0) if case == "split_rows" else (info["n_gathered"] > 0)
+            assert smha.smha_call_kernel_name(plan.handle, B, H, d, smha.SMHA_F16).startswith("smha_block_fwd")
         gen = torch.Generator(device="cuda").manual_seed(5)
         q, k, v = (torch.randn(B, H, S, d, device="cuda", generator=gen).half() for _ in range(3))
         out = torch.empty_like(q)
@@ -702,15 +753,22 @@ def test_forward_replays_from_a_hip_graph(torch_mod, smha, case):
         check(out[:1, :1].float().cpu().numpy(), ref, f"graph replay {case}")
 
 
-def test_forwards_on_one_plan_overlap_on_two_streams(torch_mod, smha):
+@pytest.mark.parametrize("case", ["block", "wave"])
+def test_forwards_on_one_plan_overlap_on_two_streams(torch_mod, smha, case):
     """Two forwards on one plan (split 128-row groups, so both use a workspace and arrival counters) run at
     the same time on two streams, several rounds in a row: each call takes its own workspace, so every
     output equals the one computed alone, and that one matches the oracle."""
     torch = torch_mod
     spec = W.MaskSpec(flags=W.BIGBIRD, block=64, n_window_blocks=3, n_global_blocks=2, n_random_blocks=2, seed=3)
     B, H, S, d = 1, 8, 4096, 128
+    if case == "wave":
+        spec, B, H, S, d = WAVE_CUT, 2, 8, 6000, 64
     with smha.Plan.from_desc(spec, B, H, S, head_dim=d, force=smha.SMHA_KERNEL_BLOCK) as plan:
-        assert plan.info()["n_split_rows"] > 0
+        if case == "wave":
+            runs_cut_wave_lists(smha, plan, B, H, d)
+        else:
+            assert plan.info()["n_split_rows"] > 0
+            assert smha.smha_call_kernel_name(plan.handle, B, H, d, smha.SMHA_F16) == "smha_block_fwd16"
         plan.prepare(B, H, d)
         gen = torch.Generator(device="cuda").manual_seed(11)
         sets = [[torch.randn(B, H, S, d, device="cuda", generator=gen).half() for _ in range(3)] for _ in range(2)]
@@ -781,16 +839,26 @@ def test_nothing_is_written_outside_the_output(torch_mod, smha):
         (W.MaskSpec(flags=W.BIGBIRD, block=64, n_window_blocks=3, n_global_blocks=2, n_random_blocks=2, seed=4), 1, 3, 4000, 128, "split"),
         (W.MaskSpec(flags=W.CAUSAL | W.WINDOW | W.STRIDED, window_left=100, stride=32, stride_phase=1), 2, 2, 1501, 64, "gathered"),
         (W.MaskSpec(flags=W.WINDOW, window_left=40, window_right=9), 1, 5, 777, 128, "plain"),
+        (W.MaskSpec(flags=W.WINDOW, window_left=40, window_right=9), 1, 5, 777, 128, "plain, first form"),
+        (W.MaskSpec(flags=W.WINDOW, window_left=40, window_right=9), 1, 5, 777, 128, "plain, third form"),
+        (W.MaskSpec(flags=W.CAUSAL | W.WINDOW | W.STRIDED, window_left=100, stride=32, stride_phase=1), 2, 2, 1501, 64, "gathered, first form"),
+        (WAVE_CUT, 1, 9, 4707, 64, "cut wave lists"),
+        (WAVE_CUT, 1, 3, 4707, 136, "cut wave lists"),
         (W.MaskSpec(flags=W.WINDOW, window_left=1, window_right=1), 1, 5, 777, 64, "eight rows a wave"),
         (W.MaskSpec(flags=W.WINDOW, window_left=1, window_right=1), 1, 5, 777, 128, "four rows a wave"),
         (W.MaskSpec(flags=W.WINDOW, window_left=1, window_right=1), 1, 5, 777, 256, "two rows a wave"),
     ]
     for spec, B, H, S, d, what in cases:
-        with smha.Plan.from_desc(spec, B, H, S, head_dim=d, build_both=True) as plan:
+        form = 1 if what.endswith("first form") else 3 if what.endswith("third form") else 0
+        with smha.Plan.from_desc(spec, B, H, S, head_dim=d, build_both=True, block_form=form) as plan:
             info = plan.info()
+            if form:
+                runs_form(smha, plan, B, H, d, "f16", form)
+            if what == "cut wave lists":
+                runs_cut_wave_lists(smha, plan, B, H, d)
             if what == "split":
                 assert info["n_split_rows"] > 0
-            if what == "gathered":
+            if what.startswith("gathered"):
                 assert info["n_gathered"] > 0
             if what.endswith("a wave"):
                 assert plan.row_form(B, H, d) == {64: (8, 3), 128: (4, 3), 256: (2, 3)}[d]
@@ -910,9 +978,10 @@ def wave_form_masks(name, B, H):
     elif name == "shared":                              # lists of 1 to 128 entries: walked alone and by four waves
         i, j = np.arange(4096 - 300, 4096)[:, None], np.arange(4096)[None]
         m = ((j <= i) & ((i < 3860) | (i - j < 40) | (j % 1024 == 3)))[None, None]
-    elif name == "cut":                                 # 129 entries and more: parts merged in memory
-        m = np.zeros((1, 1, 70, 6000), bool)
-        m[..., :33, :] = True
+    elif name.startswith("cut"):                        # 129 entries and more: parts merged in memory
+        m = np.zeros((1, H if name == "cut_per_head" else 1, 70, 6000), bool)
+        for h in range(m.shape[1]):                     # (one mask per head: cut into 3, into 3 shorter ones, and not at all)
+            m[0, h, :33, :(6000, 4500, 100)[h % 3]] = True
         m[..., 33:64, ::7] = True
         m[..., 64:, 5000:] = True
     else:                                               # "blocks": full and partial 32 x 32 sub-tiles, one mask per head
@@ -921,18 +990,26 @@ def wave_form_masks(name, B, H):
     return m.astype(np.uint8)
 
 
-@pytest.mark.parametrize("name", ["one_key", "ragged", "shared", "cut", "blocks"])
+@pytest.mark.parametrize("name", ["one_key", "ragged", "shared", "cut", "cut_per_head", "blocks"])
 @pytest.mark.parametrize("d,dtype", [(64, "f16"), (64, "bf16"), (128, "f16"), (128, "bf16"), (8, "f16"), (80, "bf16"),
                                      (256, "f16"), (160, "bf16")])
 def test_wave_form(torch_mod, smha, name, d, dtype):
     """The wave form beside the first (and at 128 and 256 columns the third) form of the block kernel, all against the oracle;
     strided tensors, so that a read or store past a row's end would meet its neighbours.  Three heads: the heads that
-    are left over are dealt over all XCDs; nine: one full round and one left over; 24: three rounds, taken together."""
+    are left over are dealt over all XCDs; nine: one full round and one left over; 24: three rounds, taken together.  Cut lists
+    with 3, 8, 9 and 16 heads, and with 27, whose keys fill an L2 with two of an XCD's three rounds: groups of two and one."""
     torch = torch_mod
-    for B, H in ((1, 3), (3, 3), (2, 12)):
+    shapes = ((1, 3), (3, 3), (2, 12))
+    if name == "shared":
+        shapes = ((1, 3),)
+    elif name == "cut":
+        shapes = ((1, 3), (1, 8), (2, 8)) + (((3, 9),) if d <= 64 else ())
+    elif name == "cut_per_head":
+        shapes = ((1, 9),)
+    elif d > 128:
+        shapes = ((1, 3), (3, 3))
+    for B, H in shapes:
         masks = wave_form_masks(name, B, H)
-        if B > 1 and name in ("shared", "cut") or B == 2 and d > 128:
-            continue
         Sq, Sk = masks.shape[2:]
         Q = W.qkv_bits(B, H, Sq, d, dtype, 1.0, 901)[0]
         _, K, V = W.qkv_bits(B, H, Sk, d, dtype, 1.0, 902)
@@ -942,8 +1019,10 @@ def test_wave_form(torch_mod, smha, name, d, dtype):
         for form in (0, 1, 3) if d > 64 else (0, 1):
             with make(masks, head_dim=d, force=smha.SMHA_KERNEL_BLOCK, block_form=form) as plan:
                 kernel = smha.smha_call_kernel_name(plan.handle, B, H, d, smha.SMHA_F16 if dtype == "f16" else smha.SMHA_BF16)
-                if form or d <= 128 or dtype == "f16" and name != "one_key":  # (at 256 columns some stay with the third form)
+                if form or d <= 128 or name != "one_key":  # (at 256 columns that one stays with the third form)
                     assert (kernel == "smha_wave_fwd") == (form == 0), kernel
+                if form == 0 and name.startswith("cut"):
+                    assert (plan.export("wave_items").reshape(-1, 8)[:, 3] >= 0).any()
                 for f32 in (False, True):
                     out = torch.full((B, Sq, H, d), float("nan"), device="cuda", dtype=torch.float32 if f32 else q.dtype).transpose(1, 2)
                     plan.forward(q, k, v, out=out)

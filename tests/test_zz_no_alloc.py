@@ -19,10 +19,17 @@ def test_static_workspace_entry_point_matches_forward_on_two_calls_in_a_row():
     cases = [
         (W.MaskSpec(flags=W.BIGBIRD, block=64, n_window_blocks=3, n_global_blocks=2, n_random_blocks=2, seed=4), 1, 8, 4096, 128),
         (W.MaskSpec(flags=W.WINDOW | W.GLOBAL, window_left=32, window_right=32, n_global=70), 1, 2, 4096, 64),
+        # the wave form's own workspace: parts of 32 rows, one counter a group
+        (W.MaskSpec(flags=W.WINDOW | W.GLOBAL, window_left=20, window_right=20, n_global=40), 1, 9, 6000, 64),
+        (W.MaskSpec(flags=W.WINDOW | W.GLOBAL, window_left=20, window_right=20, n_global=5), 1, 3, 6000, 128),
     ]
     for spec, B, H, S, d in cases:
-        with smha.Plan.from_desc(spec, B, H, S, head_dim=d, force=smha.SMHA_KERNEL_BLOCK) as plan:
+        form = 1 if (S, d) == (4096, 64) else 0                 # (left to the library it takes the wave form, which cuts nothing here)
+        with smha.Plan.from_desc(spec, B, H, S, head_dim=d, force=smha.SMHA_KERNEL_BLOCK, block_form=form) as plan:
             assert plan.info()["n_split_rows"] > 0              # the call really uses the workspace and its counters
+            if S == 6000:
+                assert smha.smha_call_kernel_name(plan.handle, B, H, d, smha.SMHA_F16) == "smha_wave_fwd"
+                assert (plan.export("wave_items").reshape(-1, 8)[:, 3] >= 0).any()
             q, k, v = (torch.randn(B, H, S, d, device="cuda", generator=gen).half() for _ in range(3))
             out = torch.full_like(q, float("nan"))
             with pytest.raises(smha.SmhaError):                 # nothing prepared yet: the entry point may not allocate

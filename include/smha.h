@@ -245,7 +245,7 @@ smha_status_t smha_forward(const smha_plan_t *plan, const void *Q, const void *K
 
 /* smha_forward for callers that cannot allocate device memory (code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc): same arguments, same result, but the partial
- * results of split 128-row groups go to an array inside the library's own image (32 MiB per GPU,
+ * results of split row groups go to an array inside the library's own image (32 MiB per GPU,
  * held until the process ends) instead of a workspace of the plan, and nothing is ever allocated,
  * freed or synchronised.  The call shape must have been prepared (smha_plan_prepare, or an earlier
  * smha_forward with the same B, H, d): UNSUPPORTED otherwise, and also when the shape's workspace
@@ -263,17 +263,22 @@ smha_status_t smha_forward_static(const smha_plan_t *plan, const void *Q, const 
                                   void *hip_stream);
 
 /* Makes, once, everything smha_forward needs for calls with this batch size, head count and head
- * size on a plan that runs the block-wise kernel (Sec. 4.2.2): the work order (which workgroup
- * takes which work item, see smha_plan_work_order) and 4 workspaces that hold the partial results
- * of 128-row groups whose tile lists were split between workgroups (those are merged inside the
- * same launch by whichever part finishes last) -- B*H * (split parts per head) * (128 D + 1024)
- * floats each, D the kernel width for d (64, 128 or 256); plans that split nothing get none.
+ * size on a plan that runs the block-wise kernel (Sec. 4.2.2): the form of the kernel is decided, the
+ * work order made (which workgroup takes which work item, see smha_plan_call_order; the wave form has
+ * an order of its own, and its lists, SMHA_EXPORT_WAVE_ITEMS, are made by the first shape that takes
+ * it), and 4 workspaces that hold the partial results of row groups whose tile lists were split
+ * (those are merged inside the same launch by whichever part finishes last): B*H * (split parts per
+ * head) * (128 D + 1024) floats each for the 128-row groups of the older forms, (32 D + 128) for the
+ * 32-row groups of the wave form, which may split where they do not, and one counter per split group
+ * and head (8 for the older forms); D is the kernel width for d (64, 128 or 256).  Shapes that split
+ * nothing get none.
  * Allocates device memory and copies to it (blocking); call it outside stream capture, on the plan's device.  Calling it again for the
  * same shape does nothing; plans that run the row-wise kernel need nothing and return SMHA_OK.
  * Errors: INVALID_ARG, UNSUPPORTED (d, more than 2^28 work items), SHAPE, ALLOC, HIP. */
 smha_status_t smha_plan_prepare(const smha_plan_t *plan, int B, int H, int d);
 
-/* The block kernel's work order for B x H heads when workgroups_per_xcd workgroups are
+/* A work order of the block kernel's older forms for B x H heads (smha_plan_call_order gives the one that
+ * a forward walks when B * H is no multiple of 8) when workgroups_per_xcd workgroups are
  * resident on each of the chip's 8 XCDs (smha_forward uses 4 per compute unit at 64 columns,
  * 2 at 128, 1 at 256): the plan's work items (the workgroup tiling of Algorithm 1's outer loop)
  * differ in length, and each head's items go, longest first, to the compute unit with the least

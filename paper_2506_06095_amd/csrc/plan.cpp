@@ -1039,6 +1039,8 @@ static const BlockCost kBlockCost[3][2] = {  // first form, third form (none at 
     {{2.039, 0.773, 0.001, 0.086, 0.001, -0.329, 0.186, -0.182, -0.400, 1.158, 1.004, 0.900, 1.200, 10.146, 0.090},
      {1.576, -0.137, -0.049, 0.247, 0.065, -0.856, 0.186, 0.050, -0.400, 1.128, 1.147, 1.100, 1.384, 10.481, 0.128}}};
 
+struct TypeTimes { double f16, bf16; };  // us with float16 and with bfloat16 inputs
+
 // MB that a call on masks which touch `keys` keys reads and writes (the kernel's width in place of the head size)
 static double call_mb(const smha_plan *plan, int B, int H, int D, int keys) {
     return 4e-6 * B * H * D * ((double)plan->S + std::min(keys, plan->Sk));
@@ -1049,20 +1051,23 @@ static double call_mb(const smha_plan *plan, int B, int H, int D, int keys) {
 // waves is a chain of a quarter, but four starts and a merge: `alone` is the longest list that one wave walks, chosen
 // for the least time (within 2 % of the best of the 12 in the mean).  us with the longest lists alone / shared:
 // Longformer 8 x 12 x 512 x 64 14.1 / 8.8, window 1 x 2 x 1772 x 32 7.2 / 4.4.
-static double wave_time_us(const smha_plan *plan, int B, int H, int D, bool bf16, int &alone) {
+static TypeTimes wave_time_us(const smha_plan *plan, int B, int H, int D, int &alone) {
     const WaveLists &wl = plan->wave;
     const double per_mask = 1.0 / (plan->Bm * plan->Hm), heads = (double)B * H;
     const WaveCost &c = kWaveCost[row_width(D)];
     const double slots = (D == 64 ? 16.0 : D == 128 ? 8.0 : 4.0) * plan->n_cu;
     const double part = (double)wl.part_ents / std::max<double>(1.0, (double)wl.n_ents);
     const double step_ns = c.step * (1 + c.part * part);
-    double best = 0, best_us = 0;
+    int lengths[kWaveWhole + 1], n_lengths = 0;  // those that any item has, longest first
+    for (int n = kWaveWhole; n >= 0; --n)
+        if (wl.of_length[n] > 0) lengths[n_lengths++] = n;
+    TypeTimes best{0, 0};
     alone = 0;
     for (int limit : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64}) {
         double teams = 0, solos = 0, steps = 0, held = 0, left = 0;  // of a mask; left: places in a workgroup already opened
         int chain = 0;
-        for (int n = kWaveWhole; n >= 0; --n) {
-            if (wl.of_length[n] == 0) continue;
+        for (int i = 0; i < n_lengths; ++i) {
+            const int n = lengths[i];
             double k = per_mask * wl.of_length[n];
             steps += k * n;
             const int walked = n > limit ? (n + 3) / 4 : n;
@@ -1088,13 +1093,14 @@ static double wave_time_us(const smha_plan *plan, int B, int H, int D, bool bf16
             return std::pow(std::pow(1e-3 * (waves * c.wave + walked * type) * (1 + c.uneven * uneven), c.power) + std::pow(longest * type, c.power), 1 / c.power);
         };
         const double at = us(1.0);  // (the same limit for both types: one order serves them)
-        if (alone == 0 || at < best) {
-            best = at;
-            best_us = us(bf16 ? c.bf16 : 1.0);
+        if (alone == 0 || at < best.f16) {
+            best = {at, us(c.bf16)};
             alone = limit;
         }
     }
-    return c.start + std::pow(std::pow(best_us * std::exp(c.part_all * part), c.join) + std::pow(c.memory * call_mb(plan, B, H, D, wl.keys), c.join), 1 / c.join);
+    const double part_all = std::exp(c.part_all * part), memory = std::pow(c.memory * call_mb(plan, B, H, D, wl.keys), c.join);
+    auto joined = [&](double us) { return c.start + std::pow(std::pow(us * part_all, c.join) + memory, 1 / c.join); };
+    return {joined(best.f16), joined(best.bf16)};
 }
 
 // The first (four waves of 32 rows) and third form (eight of 16): the busiest compute unit's work and the longest
@@ -1102,7 +1108,7 @@ static double wave_time_us(const smha_plan *plan, int B, int H, int D, bool bf16
 // in it (`act`: tiles per step), how many of the tiles are partly filled, how many 32 x 32 sub-tiles have keys (`subs`) and
 // whether most steps are full tiles that one tile row has to itself (`lone`: the other's waves only wait); merging parts of
 // a cut list costs extra.
-static double block_time_us(const smha_plan *plan, int lvl, int form, int B, int H, int D, bool bf16) {
+static TypeTimes block_time_us(const smha_plan *plan, int lvl, int form, int B, int H, int D) {
     const WorkLists &wl = plan->lists[plan->fine_differs ? lvl : 0];
     const double per_xcd = (double)B * H / (plan->Bm * plan->Hm) / 8;
     double cost = 0, longest = 0;
@@ -1127,10 +1133,12 @@ static double block_time_us(const smha_plan *plan, int lvl, int form, int B, int
     const double gather = plan->n_gathered > 0 ? c.gather : 1.0;
     const double unit_us = unit * std::exp(c.unit + c.unit_act * (act - 1.5) + c.unit_part * act * parts + c.unit_sub * (subs - 5) + c.unit_lone * lone);
     const double group_us = group * std::exp(c.group + c.group_act * (act - 1.5) + c.group_part * act * parts);
-    return c.start + (wl.max_slots > 0 ? c.merge : 0.0) +
-           std::pow(std::pow(gather * unit_us * (bf16 ? c.unit_bf16 : 1.0), c.power) + std::pow(gather * group_us * (bf16 ? c.group_bf16 : 1.0), c.power) +
-                        std::pow(c.memory * call_mb(plan, B, H, D, plan->wave.keys), c.power),
-                    1 / c.power);
+    const double memory = std::pow(c.memory * call_mb(plan, B, H, D, plan->wave.keys), c.power);
+    auto us = [&](double unit_type, double group_type) {
+        return c.start + (wl.max_slots > 0 ? c.merge : 0.0) +
+               std::pow(std::pow(gather * unit_us * unit_type, c.power) + std::pow(gather * group_us * group_type, c.power) + memory, 1 / c.power);
+    };
+    return {us(1.0, 1.0), us(c.unit_bf16, c.group_bf16)};
 }
 
 // The wave form wins where tiles are filled poorly (BigBird with random 32-blocks 16 x 12 x 2048 x 64: 126 us, 77 with
@@ -1146,9 +1154,8 @@ bool wave_form_pays(const smha_plan *plan, int lvl, int form, int B, int H, int 
     if (H > 65535 || (int64_t)B * H > (1 << 18) /* (a grid's z holds an eighth of them) */) return false;
     if (!count_wave_lists(plan)) return false;
     if (workspace_bytes(plan, 0, 4, B, H, D, nullptr) > kStaticScratchBytes) return false;  // (smha_forward_static takes what it took)
-    double ratio = 1;
-    for (const bool bf16 : {false, true}) ratio *= wave_time_us(plan, B, H, D, bf16, alone) / block_time_us(plan, lvl, form, B, H, D, bf16);
-    return ratio < 0.96 * 0.96;
+    const TypeTimes wave = wave_time_us(plan, B, H, D, alone), block = block_time_us(plan, lvl, form, B, H, D);
+    return wave.f16 * wave.bf16 < 0.96 * 0.96 * block.f16 * block.bf16;
 }
 
 // The block kernel's work order for B x H heads on `slots` resident workgroups per XCD.  Items

@@ -963,8 +963,8 @@ int row_form(const smha_plan *plan, int B, int H, int D) {
 }
 
 // One workspace of the block kernel for a call shape: per (batch*head) max_slots partial results of
-// 128 rows (O, then running maximum and sum per row, each written per wave: 128 d + 512 floats), then
-// four arrival counters (one per 32-row quarter) per (batch*head, split group).
+// 128 rows (O, then reference and sum per row, each written per wave, with room for eight waves: 128 d + 1024 floats), then
+// eight arrival counters (one per wave of the form with most) per (batch*head, split group).
 size_t workspace_bytes(const smha_plan *plan, int lvl, int form, int B, int H, int d, size_t *counters_at) {
     if (form == 4) {  // 32 rows per partial result, one counter per split group
         const size_t at = ((size_t)B * H * plan->wave.max_slots * (size_t)(32 * d + 128) * sizeof(float) + 255) / 256 * 256;

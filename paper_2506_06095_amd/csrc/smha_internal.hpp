@@ -242,7 +242,7 @@ bool wave_form_pays(const smha_plan *plan, int lvl, int form, int B, int H, int 
 int build_wave_order(const smha_plan *plan, int alone, std::vector<int32_t> &table);
 // which of kRowForms[row_width(D)] a call of the row kernel runs
 int row_form(const smha_plan *plan, int B, int H, int D);
-// bytes of one workspace for that call shape: partials first, then 4 counters per (batch*head, split group)
+// bytes of one workspace for that call shape: partials first, then the arrival counters of each (batch*head, split group)
 size_t workspace_bytes(const smha_plan *plan, int lvl, int form, int B, int H, int d, size_t *counters_at);
 // device.hip
 smha_status_t upload_plan(smha_plan *p, int device_id);

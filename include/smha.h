@@ -15,7 +15,7 @@
  *     produces an all-zero output row (the paper does not define this case).
  *   - Self-attention has Sq = Sk = S; a dense mask may also have fewer or more queries than
  *     keys (smha_plan_from_dense_rect: cross-attention, a chunk of queries against cached
- *     keys).  head_dim d is a multiple of 8 up to 256 (the kernels exist for 64, 128 and 256
+ *     keys).  head_dim d is a multiple of 8 up to 256 (the kernels exist for 32, 64, 96, 128, 160 and 256
  *     columns; a narrower head runs on the next of them, its missing columns read as zeros).  Q/K/V are IEEE binary16 or bfloat16.
  *   - All functions return a status code; nothing is printed, thrown or aborted.
  *     On error, output parameters are left untouched.
@@ -270,7 +270,7 @@ smha_status_t smha_forward_static(const smha_plan_t *plan, const void *Q, const 
  * (those are merged inside the same launch by whichever part finishes last): B*H * (split parts per
  * head) * (128 D + 1024) floats each for the 128-row groups of the older forms, (32 D + 128) for the
  * 32-row groups of the wave form, which may split where they do not, and one counter per split group
- * and head (8 for the older forms); D is the kernel width for d (64, 128 or 256).  Shapes that split
+ * and head (8 for the older forms); D is the kernel width for d (32, 64, 96, 128, 160 or 256).  Shapes that split
  * nothing get none.
  * Allocates device memory and copies to it (blocking); call it outside stream capture, on the plan's device.  Calling it again for the
  * same shape does nothing; plans that run the row-wise kernel need nothing and return SMHA_OK.

@@ -16,6 +16,7 @@
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "device_pool.hpp"
@@ -158,13 +159,28 @@ __device__ __forceinline__ u32x4 buf_load16(__amdgpu_buffer_rsrc_t r, int byte_o
     return __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, 0, 0);  // out of range -> zeros
 }
 // (rows of 256 bytes or more: a row's chunks are permuted inside each aligned group of 16)
+// Rows of an odd number of 64-byte groups (32, 96 and 160 columns) spread by themselves: four consecutive rows start in
+// the four groups of a 256-byte window, so V needs no swizzle, and for K the chunks of each aligned group of four are permuted
+// by which of four such row quadruples the row is in.
+template <int D> constexpr bool kOddRows = D % 64 == 32;
 template <int D> __device__ __forceinline__ int swz_k(int row) {
-    if constexpr (D >= 128) return row & 15;
+    if constexpr (kOddRows<D>) return (row >> 2) & 3;
+    else if constexpr (D >= 128) return row & 15;
     else return (row / (128 / D)) & (D / 8 - 1);
 }
 template <int D> __device__ __forceinline__ int swz_v(int row) {
-    if constexpr (D >= 128) return (row & 3) << 2;
+    if constexpr (kOddRows<D>) return 0;
+    else if constexpr (D >= 128) return (row & 3) << 2;
     else return ((row / (128 / D)) & (D / 32 - 1)) << 2;
+}
+// A swizzled row's chunk pair 2 s (+ lane part) and its 64-byte group g, from the byte address of pair / group 0.
+template <int D> __device__ __forceinline__ int at_pair(int base, int s) {
+    if constexpr (kOddRows<D>) return (base ^ (32 * (s & 1))) + 64 * (s >> 1);
+    else return base ^ (32 * s);
+}
+template <int D> __device__ __forceinline__ int at_group(int base, int g) {
+    if constexpr (kOddRows<D>) return base + 64 * g;
+    else return base ^ (64 * g);
 }
 typedef __attribute__((address_space(3))) void lds_void;
 typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -374,14 +390,14 @@ __device__ __forceinline__ void finish_split_part(const FwdParams &p, const f32x
 // SPLIT: the plan cuts some 128-row groups into parts (the instantiation for plans that do not carries
 // none of the merge code: its registers would be paid for in every item's start and end).
 template <int D, bool BF16, int OUT, bool GATHER, bool SPLIT>
-__global__ void __launch_bounds__(256, D == 64 ? 4 : D == 128 ? 2 : 1) smha_block_fwd(const FwdParams p) {
+__global__ void __launch_bounds__(256, block_groups(D)) smha_block_fwd(const FwdParams p) {
     constexpr int NS = D / 16;            // k-steps of S^T = K Q^T
     constexpr int NDT = D / 32;           // 32-wide d tiles of O^T
     constexpr int TILE = 64 * D;          // one K or V tile, in elements
     constexpr int CPR = D / 8;            // 16-byte chunks per K/V row
     constexpr int LPW = CPR / 4;          // 1 KiB load instructions per wave, per tile, per tensor
     constexpr int NP = BF16 ? 2 : 1;      // P operands per product (hi, lo for bfloat16)
-    constexpr int PF = D >= 128 ? 8 : 4;  // LDS fragment requests kept ahead of the MFMAs (d = 128 has the registers: 199 of 256;
+    constexpr int PF = D == 128 || D == 256 ? 8 : 4;  // LDS fragment requests kept ahead of the MFMAs (d = 128 has the registers: 199 of 256;
                                           // 8 instead of 4 is worth 1.6 % there; at d = 64 more would spill)
     // K[0], K[1], V[0], V[1]: tile t lives in K[t & 1], V[t & 1]
     __shared__ __attribute__((aligned(1024))) uint16_t smem[4 * TILE];
@@ -401,11 +417,11 @@ __global__ void __launch_bounds__(256, D == 64 ? 4 : D == 128 ? 2 : 1) smha_bloc
 
     // LDS operand read offsets (bytes inside a tile).
     // K fragment (kt, s): row 32 kt + j, logical chunk 2 s + hh -> physical chunk (2 s) ^ hh ^ swz_k(j):
-    // byte offset k_rd ^ (32 s) (+ 64 kt D)
+    // byte offset at_pair(k_rd, s) (+ 64 kt D)
     const int k_rd = j * D * 2 + ((hh ^ swz_k<D>(j)) * 16);
     // V^T fragment (dt, key group of 4): lane reads 8 bytes of row 4 hh + (lane%16)/4 (+ 8 a + 16 cu),
     // logical chunk 4 dt + 2 ((lane/16)&1) + (lane%4)/2, second half of the chunk if lane%4 is odd:
-    // byte offset v_rd ^ (64 dt) (+ 2 D (8 a + 16 cu))
+    // byte offset at_group(v_rd, dt) (+ 2 D (8 a + 16 cu))
     const int v_row = 4 * hh + ((lane & 15) >> 2);
     const int v_rd = v_row * D * 2 + ((swz_v<D>(v_row) + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) * 16) + (lane & 1) * 8;
 
@@ -465,22 +481,37 @@ __global__ void __launch_bounds__(256, D == 64 ? 4 : D == 128 ? 2 : 1) smha_bloc
     // of 16) below block w, which leaves the swizzle alone: one per-lane offset serves all i.
     // (D = 256: the blocks are 8 rows apart, and the K swizzle of a wave's odd blocks differs from that of
     // its even ones in bit 3: a second offset)
-    constexpr int RSTEP = 4 * 64 / CPR;  // rows between two of a wave's blocks
-    constexpr int NKO = RSTEP % 16 ? 2 : 1;
+    // (rows of an odd number of 64-byte groups: a block holds no whole number of rows, every block has its own offset)
+    constexpr int RSTEP = kOddRows<D> ? 0 : 4 * 64 / CPR;  // rows between two of a wave's blocks
+    constexpr int NKO = kOddRows<D> ? LPW : RSTEP % 16 ? 2 : 1, NVO = kOddRows<D> ? LPW : 1;
     // A head narrower than D has no chunks d/8 .. CPR-1: a lane whose chunk is one of them carries kNoChunk
     // instead of its offset.  Offsets are unsigned 32-bit sums below 2^31 (the host checks the sizes), so with
     // kNoChunk added they stay past every buffer, the load returns zeros and a store is dropped.
     constexpr uint32_t kNoChunk = 0x80000000u;
     const int cpr_d = p.d >> 3;  // chunks a row has in memory
-    uint32_t k_go[NKO], v_go;  // (block i of the wave: k_go[i % NKO] + i RSTEP rows)
-    uint32_t g_kc[NKO], g_vc;  // with gathered tiles a staged row may come from any key: offset = key * pitch + chunk part
-    const int g_row = (w * 64 + lane) / CPR;  // the lane's row in the wave's first block
-    {
+    uint32_t k_go[NKO], v_go[NVO];  // (block i of the wave: k_go[i % NKO] + i RSTEP rows)
+    uint32_t g_kc[NKO], g_vc[NVO];  // with gathered tiles a staged row may come from any key: offset = key * pitch + chunk part
+    const int g_row = (w * 64 + lane) / CPR;  // the lane's row in the wave's first block, and in block i:
+    auto row_of = [&](int i) __attribute__((always_inline)) {
+        if constexpr (kOddRows<D>) return ((w + 4 * i) * 64 + lane) / CPR;
+        else return g_row + i * RSTEP;
+    };
+    if constexpr (kOddRows<D>) {
+#pragma unroll
+        for (int o = 0; o < LPW; ++o) {
+            const int row = row_of(o), pc = ((w + 4 * o) * 64 + lane) % CPR;
+            const int vc = pc ^ swz_v<D>(row), kc = pc ^ swz_k<D>(row);
+            v_go[o] = vc < cpr_d ? (uint32_t)(row * vsb + vc * 16) : kNoChunk;
+            g_vc[o] = vc < cpr_d ? (uint32_t)(vc * 16) : kNoChunk;
+            k_go[o] = kc < cpr_d ? (uint32_t)(row * ksb + kc * 16) : kNoChunk;
+            g_kc[o] = kc < cpr_d ? (uint32_t)(kc * 16) : kNoChunk;
+        }
+    } else {
         const int pchunk = w * 64 + lane;
         const int row = pchunk / CPR, pc = pchunk % CPR;
         const int vc = pc ^ swz_v<D>(row);
-        v_go = vc < cpr_d ? (uint32_t)(row * vsb + vc * 16) : kNoChunk;
-        g_vc = vc < cpr_d ? (uint32_t)(vc * 16) : kNoChunk;
+        v_go[0] = vc < cpr_d ? (uint32_t)(row * vsb + vc * 16) : kNoChunk;
+        g_vc[0] = vc < cpr_d ? (uint32_t)(vc * 16) : kNoChunk;
 #pragma unroll
         for (int o = 0; o < NKO; ++o) {
             const int kc = pc ^ swz_k<D>(row + o * RSTEP);
@@ -542,22 +573,22 @@ __global__ void __launch_bounds__(256, D == 64 ? 4 : D == 128 ? 2 : 1) smha_bloc
             // planner puts gathered tiles last, so this only happens in items that have no other)
             int key[LPW];
 #pragma unroll
-            for (int i = 0; i < LPW; ++i) key[i] = wk.col0 * 64 + g_row + i * RSTEP;
+            for (int i = 0; i < LPW; ++i) key[i] = wk.col0 * 64 + row_of(i);
             if (wk.gid0 > 0) {
 #pragma unroll
-                for (int i = 0; i < LPW; ++i) key[i] = p.gidx[(size_t)(wk.gid0 - 1) * 64 + g_row + i * RSTEP];
+                for (int i = 0; i < LPW; ++i) key[i] = p.gidx[(size_t)(wk.gid0 - 1) * 64 + row_of(i)];
             }
 #pragma unroll
             for (int i = 0; i < LPW; ++i) {
                 load_to_lds(rK, smem_base + (w + 4 * i) * 1024, g_kc[i % NKO] + (wk.n > 0 ? key[i] * ksb : OOB));
-                load_to_lds(rV, smem_base + 2 * TB + (w + 4 * i) * 1024, g_vc + (wk.n > 0 ? key[i] * vsb : OOB));
+                load_to_lds(rV, smem_base + 2 * TB + (w + 4 * i) * 1024, g_vc[i % NVO] + (wk.n > 0 ? key[i] * vsb : OOB));
             }
         } else {
             const int kb = wk.n > 0 ? wk.col0 * 64 * ksb : OOB, vb = wk.n > 0 ? wk.col0 * 64 * vsb : OOB;
 #pragma unroll
             for (int i = 0; i < LPW; ++i) {
                 load_to_lds(rK, smem_base + (w + 4 * i) * 1024, k_go[i % NKO] + (kb + i * RSTEP * ksb));
-                load_to_lds(rV, smem_base + 2 * TB + (w + 4 * i) * 1024, v_go + (vb + i * RSTEP * vsb));
+                load_to_lds(rV, smem_base + 2 * TB + (w + 4 * i) * 1024, v_go[i % NVO] + (vb + i * RSTEP * vsb));
             }
         }
     };
@@ -601,8 +632,8 @@ __global__ void __launch_bounds__(256, D == 64 ? 4 : D == 128 ? 2 : 1) smha_bloc
             ld_live = t < n;
 #pragma unroll
             for (int i = 0; i < LPW; ++i) {
-                const int from_list = gix[slot * 64 + g_row + i * RSTEP];
-                ld_key[i] = gid > 0 ? from_list : col * 64 + g_row + i * RSTEP;
+                const int from_list = gix[slot * 64 + row_of(i)];
+                ld_key[i] = gid > 0 ? from_list : col * 64 + row_of(i);
             }
         } else {
             ld_kb = t < n ? col * 64 * ksb : OOB;
@@ -612,11 +643,11 @@ __global__ void __launch_bounds__(256, D == 64 ? 4 : D == 128 ? 2 : 1) smha_bloc
     auto load_piece = [&](int i, uint32_t Kd, uint32_t Vd) __attribute__((always_inline)) {  // i in [0, 2 LPW); LDS byte addresses
         if constexpr (GATHER) {
             if (i & 1)
-                load_to_lds(rV, Vd + (w + 4 * (i >> 1)) * 1024, g_vc + (ld_live ? ld_key[i >> 1] * vsb : OOB));
+                load_to_lds(rV, Vd + (w + 4 * (i >> 1)) * 1024, g_vc[(i >> 1) % NVO] + (ld_live ? ld_key[i >> 1] * vsb : OOB));
             else
                 load_to_lds(rK, Kd + (w + 4 * (i >> 1)) * 1024, g_kc[(i >> 1) % NKO] + (ld_live ? ld_key[i >> 1] * ksb : OOB));
         } else if (i & 1)
-            load_to_lds(rV, Vd + (w + 4 * (i >> 1)) * 1024, v_go + (ld_vb + (i >> 1) * RSTEP * vsb));
+            load_to_lds(rV, Vd + (w + 4 * (i >> 1)) * 1024, v_go[(i >> 1) % NVO] + (ld_vb + (i >> 1) * RSTEP * vsb));
         else
             load_to_lds(rK, Kd + (w + 4 * (i >> 1)) * 1024, k_go[(i >> 1) % NKO] + (ld_kb + (i >> 1) * RSTEP * ksb));
     };
@@ -637,7 +668,7 @@ __global__ void __launch_bounds__(256, D == 64 ? 4 : D == 128 ? 2 : 1) smha_bloc
         f32x16 acc[2] = {zero16, zero16};
         auto k_addr = [&](int i) __attribute__((always_inline)) {  // i = 2 s + kt
             const int s = i >> 1, kt = i & 1;
-            return reinterpret_cast<const char *>(smem) + ((krd ^ (32 * s)) + 64 * kt * D);
+            return reinterpret_cast<const char *>(smem) + (at_pair<D>(krd, s) + 64 * kt * D);
         };
         u32x4 kfrag[PF];
 #pragma unroll
@@ -719,7 +750,7 @@ __global__ void __launch_bounds__(256, D == 64 ? 4 : D == 128 ? 2 : 1) smha_bloc
         // group cu+1 are issued between the MFMAs of group cu, so they run under the matrix pipe.
         auto v_frag = [&](int i) __attribute__((always_inline)) {  // i = cu * NDT + dt
             const int cu = i / NDT, dt = i % NDT;
-            const char *ptr = reinterpret_cast<const char *>(smem) + ((vrd ^ (64 * dt)) + 32 * cu * D);
+            const char *ptr = reinterpret_cast<const char *>(smem) + (at_group<D>(vrd, dt) + 32 * cu * D);
             const u32x2 lo = lds_read_tr(reinterpret_cast<const uint16_t *>(ptr)), hi = lds_read_tr(reinterpret_cast<const uint16_t *>(ptr + 16 * D));
             return u32x4{lo[0], lo[1], hi[0], hi[1]};
         };
@@ -738,12 +769,8 @@ __global__ void __launch_bounds__(256, D == 64 ? 4 : D == 128 ? 2 : 1) smha_bloc
                 if constexpr (BF16) o[dt] = mfma32<BF16>(vfrag[i % PF], pf[cu][1], o[dt]);
                 if (i + PF < 4 * NDT) vfrag[i % PF] = v_frag(i + PF);
                 if (cu < 3) {  // the next key group's four pairs, spread over this group's MFMAs
-                    if constexpr (NDT <= 4) {
 #pragma unroll
-                        for (int q = dt * (4 / NDT); q < (dt + 1) * (4 / NDT); ++q) p_pair(cu + 1, q, gs);
-                    } else {
-                        if (dt % (NDT / 4) == 0) p_pair(cu + 1, dt / (NDT / 4), gs);
-                    }
+                    for (int q = (4 * dt + NDT - 1) / NDT; q < (4 * dt + NDT + 3) / NDT; ++q) p_pair(cu + 1, q, gs);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -766,7 +793,7 @@ __global__ void __launch_bounds__(256, D == 64 ? 4 : D == 128 ? 2 : 1) smha_bloc
         asm volatile("" : "+v"(krd));  // (the fragment addresses are made here, not kept across items)
 #pragma unroll
         for (int s = 0; s < NS; ++s)
-            qf[s] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(priv) + (krd ^ (32 * s)));
+            qf[s] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(priv) + at_pair<D>(krd, s));
     }
     int code = entry_code(0);
     uint64_t word = raw_word;
@@ -807,7 +834,7 @@ __global__ void __launch_bounds__(256, D == 64 ? 4 : D == 128 ? 2 : 1) smha_bloc
             for (int g4 = 0; g4 < 4; ++g4) {
                 const u32x2 v = {pack2<OUT == SMHA_BF16>(o[dt][4 * g4] * inv, o[dt][4 * g4 + 1] * inv),
                                  pack2<OUT == SMHA_BF16>(o[dt][4 * g4 + 2] * inv, o[dt][4 * g4 + 3] * inv)};
-                *reinterpret_cast<u32x2 *>(reinterpret_cast<char *>(priv) + (o_wr ^ ((4 * dt + g4) * 16))) = v;
+                *reinterpret_cast<u32x2 *>(reinterpret_cast<char *>(priv) + (kOddRows<D> ? (o_wr ^ (16 * g4)) + 64 * dt : o_wr ^ ((4 * dt + g4) * 16))) = v;
                 __builtin_amdgcn_sched_barrier(0);  // (pack and write as we go: no second copy of the tile in registers)
             }
         u32x4 ov[NQL];
@@ -1423,12 +1450,15 @@ static int block_form(const smha_plan *plan, int d, bool bf16) {
     const int asked = form_asked(plan);
     if (plan->n_gathered > 0) return 1;
     if (d > 128) return asked == 1 ? 1 : 3;  // 256 columns: eight waves of 16 rows are two waves per SIMD, four of 32 are one
-    if (asked == 3) return d == 128 ? 3 : 1;  // eight waves of 16 rows: 128 and 256 columns
-    if (asked == 0) return d == 128 && !plan->dense_long_lists ? 3 : 1;  // the library's choice
-    if (bf16 && d == 128) return 1;
-    return asked == 2 ? 2 : 1;
+    if (asked == 3) return d > 64 ? 3 : 1;  // eight waves of 16 rows: more than 64 columns
+    if (asked != 0) return asked == 2 && (d == 64 || (d == 128 && !bf16)) ? 2 : 1;
+    // The library's choice.  At 96 columns the first form fits three workgroups on a compute unit and is faster (where the
+    // wave form is not, f16 0.91 of the third form's time, bf16 0.94: per-head 64-blocks 4 x 16 x 1280 x 80 18.7 us, 21.6), except
+    // that nearly nothing but partly filled tiles, whose empty parts the third form skips, is a draw (0.99, bf16 1.02).
+    if (d == 96) return plan->mostly_partial ? 3 : 1;
+    return d == 128 && !plan->dense_long_lists ? 3 : 1;
 }
-static int workgroups_per_cu(int form, int d) { return form == 2 ? 1 : form == 3 ? (d > 128 ? 1 : 2) : (d == 64 ? 4 : d == 128 ? 2 : 1); }
+static int workgroups_per_cu(int form, int d) { return form == 2 ? 1 : form == 3 ? block16_groups(d) : block_groups(d); }
 
 template <int D, bool BF16, int OUT>
 static hipError_t launch_block_out(const smha_plan *plan, FwdParams &fp, hipStream_t stream) {
@@ -1443,7 +1473,7 @@ static hipError_t launch_block_out(const smha_plan *plan, FwdParams &fp, hipStre
             hipLaunchKernelGGL((smha_wave_fwd<D, BF16, OUT, false>), grid, dim3(256), 0, stream, fp);
         return hipGetLastError();
     }
-    if constexpr (!(BF16 && D == 128) && D <= 128) {
+    if constexpr (D == 64 || (D == 128 && !BF16)) {
         if (fp.form == 2) {
             hipLaunchKernelGGL((smha_block_fwd2<D, BF16, OUT>), dim3(8u * (unsigned)fp.per_xcd), dim3(512), 0, stream, fp);
             return hipGetLastError();
@@ -1453,7 +1483,7 @@ static hipError_t launch_block_out(const smha_plan *plan, FwdParams &fp, hipStre
     // registers); the work order was made for exactly this many workgroups
     const unsigned grid = 8u * (unsigned)fp.per_xcd;
     const bool split = fp.max_slots > 0;
-    if constexpr (D >= 128) {
+    if constexpr (D > 64) {
         if (fp.form == 3) {  // eight waves of 16 rows (plans without gathered tiles; at 64 columns the form also
                              // works, but fits two workgroups per compute unit where the first form fits four,
                              // and was 10-20 % slower on every mask measured: not instantiated)
@@ -1686,10 +1716,26 @@ static smha_status_t prepared_for(const smha_plan *plan, int B, int H, int d, in
     return SMHA_OK;
 }
 
-// Head sizes: any multiple of 8 up to 256.  The kernels exist for 64, 128 and 256 columns; a narrower head
-// runs on the next of the three, its missing columns read as zeros (which changes no score) and never stored.
+// Head sizes: any multiple of 8 up to 256.  The row kernel exists for 64, 128 and 256 columns, the block kernel for those of
+// block_head_size; a narrower head runs on the next of them, its missing columns read as zeros (which changes no score) and never stored.
 static bool head_size_ok(int d) { return d >= 8 && d <= 256 && d % 8 == 0; }
-static int kernel_head_size(int d) { return d <= 64 ? 64 : d <= 128 ? 128 : 256; }
+static int row_head_size(int d) { return d <= 64 ? 64 : d <= 128 ? 128 : 256; }
+
+// The width a call runs at: its own, but what was prepared with another head size of the same 64, 128 or 256 columns serves it too
+// (at that width, with the same results), so that it neither allocates nor, in smha_forward_static, is refused.
+static int call_width(const smha_plan *plan, int B, int H, int d, bool bf16) {
+    const int D = block_head_size(d), wide = row_head_size(d);
+    if (D == wide) return D;
+    const int form = block_form(plan, D, bf16), wide_form = block_form(plan, wide, bf16) == 2 ? 1 : block_form(plan, wide, bf16);
+    std::lock_guard<std::mutex> lock(plan->prepared_mutex);
+    bool other = false;
+    for (const smha_plan::CallShape &c : plan->calls) {
+        if (c.B != B || c.H != H) continue;
+        if (c.d == D && c.form == form) return D;
+        other |= c.d == wide && c.form == wide_form;
+    }
+    return other ? wide : D;
+}
 
 static smha_status_t check_shape(const smha_plan *plan, int B, int H, int d) {
     if (!plan || B < 1 || H < 1) return SMHA_ERR_INVALID_ARG;
@@ -1709,7 +1755,7 @@ extern "C" smha_status_t smha_plan_prepare(const smha_plan_t *plan, int B, int H
         (void)hipGetLastError();
         return SMHA_ERR_HIP;
     }
-    const int D = kernel_head_size(d);
+    const int D = block_head_size(d);
     for (int bf16 = 0; bf16 < 2; ++bf16) {  // (the two input types may run different forms of the kernel)
         int form = block_form(plan, D, bf16 != 0);
         if (form == 2 && d != D) form = 1;  // (the second form has no narrower heads)
@@ -1758,7 +1804,6 @@ static smha_status_t forward_impl(const smha_plan_t *plan, const void *Q, const 
     if (in_dtype != SMHA_F16 && in_dtype != SMHA_BF16) return SMHA_ERR_UNSUPPORTED;
     if (out_dtype != in_dtype && out_dtype != SMHA_F32) return SMHA_ERR_UNSUPPORTED;
     if (!head_size_ok(d)) return SMHA_ERR_UNSUPPORTED;
-    const int D = kernel_head_size(d);
     if (kernel < SMHA_KERNEL_AUTO || kernel > SMHA_KERNEL_BLOCK) return SMHA_ERR_INVALID_ARG;
     if ((plan->Bm != 1 && plan->Bm != B) || (plan->Hm != 1 && plan->Hm != H)) return SMHA_ERR_SHAPE;
     if (!strides_ok(q_strides) || !strides_ok(k_strides) || !strides_ok(v_strides) || !strides_ok(o_strides))
@@ -1805,7 +1850,7 @@ static smha_status_t forward_impl(const smha_plan_t *plan, const void *Q, const 
     hipStream_t stream = (hipStream_t)hip_stream;
     hipError_t e = hipSuccess;
     if (which == SMHA_KERNEL_BLOCK) {
-        const int asked = block_form(plan, D, in_dtype == SMHA_BF16);
+        const int D = call_width(plan, B, H, d, in_dtype == SMHA_BF16), asked = block_form(plan, D, in_dtype == SMHA_BF16);
         const smha_plan::Prepared *pr = nullptr;
         void *ws = nullptr;
         const smha_status_t st = prepared_for(plan, B, H, D, asked == 2 && d != D ? 1 : asked /* (the second form has no narrower heads) */, &pr, &ws, !static_ws);
@@ -1851,16 +1896,23 @@ static smha_status_t forward_impl(const smha_plan_t *plan, const void *Q, const 
         fp.scratch = (float *)ws;
         fp.counters = ws ? (uint32_t *)((char *)ws + pr->counters_at) : nullptr;
         fp.max_splits = form == 4 ? plan->wave.max_splits : wl.max_split_rows;
-        if (D == 64)
-            e = in_dtype == SMHA_BF16 ? launch_block<64, true>(plan, fp, stream) : launch_block<64, false>(plan, fp, stream);
-        else if (D == 128)
-            e = in_dtype == SMHA_BF16 ? launch_block<128, true>(plan, fp, stream) : launch_block<128, false>(plan, fp, stream);
-        else
-            e = in_dtype == SMHA_BF16 ? launch_block<256, true>(plan, fp, stream) : launch_block<256, false>(plan, fp, stream);
+        auto launch = [&](auto width) {
+            constexpr int W = decltype(width)::value;
+            return in_dtype == SMHA_BF16 ? launch_block<W, true>(plan, fp, stream) : launch_block<W, false>(plan, fp, stream);
+        };
+        switch (D) {
+            case 32: e = launch(std::integral_constant<int, 32>()); break;
+            case 64: e = launch(std::integral_constant<int, 64>()); break;
+            case 96: e = launch(std::integral_constant<int, 96>()); break;
+            case 128: e = launch(std::integral_constant<int, 128>()); break;
+            case 160: e = launch(std::integral_constant<int, 160>()); break;
+            default: e = launch(std::integral_constant<int, 256>());
+        }
     } else {
-        if (D == 64)
+        const int R = row_head_size(d);
+        if (R == 64)
             e = in_dtype == SMHA_BF16 ? launch_row<64, true>(plan, fp, stream) : launch_row<64, false>(plan, fp, stream);
-        else if (D == 128)
+        else if (R == 128)
             e = in_dtype == SMHA_BF16 ? launch_row<128, true>(plan, fp, stream) : launch_row<128, false>(plan, fp, stream);
         else
             e = in_dtype == SMHA_BF16 ? launch_row<256, true>(plan, fp, stream) : launch_row<256, false>(plan, fp, stream);
@@ -1894,7 +1946,7 @@ extern "C" const char *smha_kernel_name(const smha_plan_t *plan, int d, smha_dty
     const int which = kernel == SMHA_KERNEL_AUTO ? plan->kernel : (int)kernel;
     if (which == SMHA_KERNEL_ROW) return "smha_row_fwd";
     if (!head_size_ok(d)) return "smha_block_fwd";
-    const int D = kernel_head_size(d);
+    const int D = block_head_size(d);
     int form = block_form(plan, D, in_dtype == SMHA_BF16);
     if (form == 2 && d != D) form = 1;
     return form == 3 ? "smha_block_fwd16" : form == 2 ? "smha_block_fwd2" : "smha_block_fwd";
@@ -1906,7 +1958,7 @@ extern "C" const char *smha_call_kernel_name(const smha_plan_t *plan, int B, int
     const int which = kernel == SMHA_KERNEL_AUTO ? plan->kernel : (int)kernel;
     if (which == SMHA_KERNEL_BLOCK && plan->has_block) {
         const bool bf16 = in_dtype == SMHA_BF16;
-        const int D = kernel_head_size(d), form = block_form(plan, D, bf16);
+        const int D = block_head_size(d), form = block_form(plan, D, bf16);
         int alone = 0;
         try {
             if (takes_wave_form(plan, grain_for(plan, B, H, D, form), form, B, H, D, alone)) return "smha_wave_fwd";

@@ -872,6 +872,7 @@ smha_status_t finish_plan(smha_plan *p) {
                     part_in_lists += u.code[side] >= 0;
                 }
             const double groups = (double)n_masks * ((p->S + 127) / 128);
+            p->mostly_partial = (double)part_in_lists > 0.9 * (double)tiles_in_lists;
             p->dense_long_lists = (double)part_in_lists < 0.15 * (double)tiles_in_lists && (double)p->h_uent.size() > 16.0 * groups;
         }
         if (p->has_block) {
@@ -1021,21 +1022,31 @@ int build_wave_order(const smha_plan *plan, int alone, std::vector<int32_t> &tab
 // step of the wave form: ns, `memory`: us per MB), fitted by least squares of the logarithms to 1207 calls of
 // profiles/block_forms.csv (all kinds of masks, 64 to 8192 queries, 1 to 400 heads, 8 to 256 columns; clocks settled by 10 ms of the
 // same work and three sets of inputs in turn: measured from idle clocks the first form took 15 % longer, the wave form 3 %,
-// and the choice went wrong by that).  Mean error over 600 other calls of the table: 5 to 7 % (wave form), 5 % (the others).
+// and the choice went wrong by that).  Mean error over 600 other calls of the table: 5 to 7 % (wave form), 5 % (the others).  At 32,
+// 96 and 160 columns: the wave form's constants of the next larger of 64, 128 and 256 with three of their own (`start`, `memory`, and one
+// factor for `wave`, `step` and the chain's), the form that the library takes there refitted (160 with gathered tiles: likewise scaled);
+// mean error 5 to 8 %.
 struct WaveCost {
     double start, wave, step, held, part, bf16, chain, chain_full, power, uneven, part_all, join, memory;
 };
-static const WaveCost kWaveCost[3] = {
-    {3.07, 0.7028, 0.4019, 0.22, 0.076, 1.20, 0.4933, 0.2096, 3.4, 0.0, -0.003, 1.946, 0.0461},     // 64 columns
+static const WaveCost kWaveCost[6] = {
+    {3.23, 0.463, 0.265, 0.22, 0.076, 1.20, 0.325, 0.138, 3.4, 0.0, -0.003, 1.946, 0.0888},        // 32 columns
+    {3.07, 0.7028, 0.4019, 0.22, 0.076, 1.20, 0.4933, 0.2096, 3.4, 0.0, -0.003, 1.946, 0.0461},     // 64
+    {3.99, 1.246, 0.595, 0.05, 0.191, 1.17, 0.567, 0.1278, 4.0, 0.09, -0.076, 1.877, 0.0683},       // 96
     {3.80, 1.5978, 0.7627, 0.05, 0.191, 1.17, 0.7266, 0.1638, 4.0, 0.09, -0.076, 1.877, 0.0700},    // 128
+    {4.735, 3.454, 1.122, 0.63, 0.156, 1.17, 1.042, 0.0, 4.0, 0.23, -0.041, 4.513, 0.1811},         // 160
     {5.43, 5.1097, 1.6599, 0.63, 0.156, 1.17, 1.5420, 0.0, 4.0, 0.23, -0.041, 4.513, 0.1521}};      // 256
 struct BlockCost {
     double start, unit, unit_act, unit_part, unit_sub, unit_lone, group, group_act, group_part, unit_bf16, group_bf16, gather, power, merge, memory;
 };
-static const BlockCost kBlockCost[3][2] = {  // first form, third form (none at 64 columns)
+static const BlockCost kBlockCost[6][2] = {  // first form, third form (that the library takes at 128, 160 and 256 columns)
+    {{2.033, -1.240, 0.499, 0.061, 0.006, 0.075, -0.611, -0.179, 0.148, 1.224, 1.137, 1.136, 1.813, 3.040, 0.149}, {}},
     {{1.743, -0.920, 0.640, -0.040, -0.009, 0.049, -0.526, -0.291, 0.165, 1.304, 1.172, 1.136, 1.781, 5.390, 0.131}, {}},
+    {{2.053, -0.572, 0.020, -0.040, 0.014, -0.150, -0.278, -0.053, 0.118, 1.219, 1.108, 1.073, 1.844, 5.286, 0.162}, {}},
     {{2.095, -0.519, -0.107, -0.089, 0.007, -0.154, -0.253, 0.255, 0.004, 1.254, 1.043, 1.073, 1.200, 11.641, 0.098},
      {1.686, -0.455, -0.179, -0.008, 0.097, -0.216, -0.378, 0.057, 0.132, 1.229, 1.057, 1.100, 1.570, 6.935, 0.145}},
+    {{1.558, 0.565, 0.001, 0.086, 0.001, -0.329, -0.827, -0.182, -0.400, 1.158, 1.004, 0.900, 1.200, 10.146, 0.126},
+     {2.347, -0.300, -0.098, 0.200, 0.107, -0.921, 0.091, 0.023, -0.223, 1.106, 1.142, 1.100, 1.718, 8.993, 0.141}},
     {{2.039, 0.773, 0.001, 0.086, 0.001, -0.329, 0.186, -0.182, -0.400, 1.158, 1.004, 0.900, 1.200, 10.146, 0.090},
      {1.576, -0.137, -0.049, 0.247, 0.065, -0.856, 0.186, 0.050, -0.400, 1.128, 1.147, 1.100, 1.384, 10.481, 0.128}}};
 
@@ -1054,8 +1065,8 @@ static double call_mb(const smha_plan *plan, int B, int H, int D, int keys) {
 static TypeTimes wave_time_us(const smha_plan *plan, int B, int H, int D, int &alone) {
     const WaveLists &wl = plan->wave;
     const double per_mask = 1.0 / (plan->Bm * plan->Hm), heads = (double)B * H;
-    const WaveCost &c = kWaveCost[row_width(D)];
-    const double slots = (D == 64 ? 16.0 : D == 128 ? 8.0 : 4.0) * plan->n_cu;
+    const WaveCost &c = kWaveCost[block_width(D)];
+    const double slots = 4.0 * wave_groups(D) * plan->n_cu;
     const double part = (double)wl.part_ents / std::max<double>(1.0, (double)wl.n_ents);
     const double step_ns = c.step * (1 + c.part * part);
     int lengths[kWaveWhole + 1], n_lengths = 0;  // those that any item has, longest first
@@ -1117,7 +1128,7 @@ static TypeTimes block_time_us(const smha_plan *plan, int lvl, int form, int B, 
         longest = std::max(longest, 2.0 + i.end - i.begin);
     }
     const double total = cost * per_xcd, items = (double)wl.items.size() * per_xcd;
-    const double units = std::max(plan->n_cu / 8, 1), slots = units * (D == 64 ? 4 : D == 128 ? 2 : 1);
+    const double units = std::max(plan->n_cu / 8, 1), slots = units * (form == 3 ? block16_groups(D) : block_groups(D));
     const double unit = items > units ? std::max(longest, total / units + 0.35 * total / items) : longest;
     const double group = std::max(longest, total / std::max(1.0, std::min(slots, items)));
     int64_t tiles = 0, part = 0;
@@ -1125,7 +1136,7 @@ static TypeTimes block_time_us(const smha_plan *plan, int lvl, int form, int B, 
         tiles += (int64_t)m.kt_col.size();
         part += (int64_t)(m.kt_bits().size() / 64);
     }
-    const BlockCost &c = kBlockCost[row_width(D)][form == 3];
+    const BlockCost &c = kBlockCost[block_width(D)][form == 3];
     const double steps = std::max<double>(1.0, (double)plan->h_uent.size() - 1);
     const double parts = tiles ? (double)part / (double)tiles : 0.0, act = std::min(2.0, (double)tiles / steps);
     const double subs = (double)plan->wave.n_ents / steps;
@@ -1145,10 +1156,9 @@ static TypeTimes block_time_us(const smha_plan *plan, int lvl, int form, int B, 
 // the wave form) and where a call has too few 128-row groups to fill the chip (causal 1 x 12 x 1024 x 64 15.2 / 8.5, per-head
 // 64-blocks 1 x 2 x 2816 x 256 20.6 / 12.8); it loses where tiles are full and rows many (causal 16 x 12 x 4096 x 128:
 // 870 / 1176), because every K and V tile is loaded once per 32 rows.  It has to win by 4 %: of 1600
-// calls of the table that were drawn at random 16 then run the slower form by more than 2 % with one of the input types (22 before, when
-// the estimates came from idle clocks and the margin was a tenth: 64-blocks 2 x 16 x 4096 x 64 bf16 34.0 us, 34.4 with the
-// wave form), and the mean against the other forms is 0.666 at 64 columns, 0.715 at 128, 0.768 at 256 (0.669, 0.720 and 0.770
-// before), where the better form for each call would give 0.663, 0.711 and 0.765.
+// calls of the table that were drawn at random 16 then run the slower form by more than 2 % with one of the input types, and the mean
+// against the other forms is 0.645, 0.675, 0.684, 0.722, 0.724, 0.766 at 32, 64, 96, 128, 160 and 256 columns, where the better form for
+// each call would give 0.644, 0.672, 0.682, 0.718, 0.722, 0.764.
 // The two input types are decided together (by the product of their ratios): one order and one set of workspaces serves both.
 bool wave_form_pays(const smha_plan *plan, int lvl, int form, int B, int H, int D, int &alone) {
     if (H > 65535 || (int64_t)B * H > (1 << 18) /* (a grid's z holds an eighth of them) */) return false;

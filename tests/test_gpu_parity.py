@@ -1097,3 +1097,40 @@ def test_the_kernel_that_is_named_is_the_kernel_that_runs(torch_mod, smha):
         assert len(ran) == 1 and name + "<" in ran[0], (name, ran)
         seen.append(name)
     assert seen == ["smha_wave_fwd", "smha_wave_fwd", "smha_block_fwd", "smha_block_fwd16", "smha_row_fwd"]
+
+
+@pytest.mark.parametrize("mask", ["mixed", "cut", "gathered"])
+@pytest.mark.parametrize("d", [8, 24, 32, 72, 88, 96, 136, 152, 160])
+def test_kernel_widths_of_32_96_and_160_columns(torch_mod, smha, d, mask):
+    """The smallest and largest head of each width whose rows are no power of two of 64-byte groups, in every form: full, partly
+    filled and empty tiles, lists cut and merged, gathered tiles; rows that fill no tile; Q, K, V and O between guard columns
+    (NaN beside every row of the inputs, a pattern that stays beside every row of O)."""
+    torch, rng = torch_mod, np.random.default_rng(d)
+    S = 601 if mask == "mixed" else 2100
+    if mask == "mixed":
+        m = rng.random((2, 1, S, S)) < 0.05
+        m[0, 0, :200] = True
+        m[1, 0, 64:96] = False
+        m[1, 0, 300:, :256] = False
+    else:
+        i, j = np.arange(S)[:, None], np.arange(S)[None]
+        m = np.broadcast_to(((abs(i - j) < 20) | (i < 70) | (j < 40)) if mask == "cut" else ((j <= i) & ((i - j < 70) | (j % 37 == 5))), (1, 1, S, S))
+    m = np.ascontiguousarray(m).astype(np.uint8)
+    B, H = m.shape[0], 3
+    for dtype in ("f16", "bf16"):
+        Q, K, V = W.qkv_bits(B, H, S, d, dtype, 1.0, 50 + d)
+        ref = oracle.masked_attention(Q, K, V, dtype, m)
+        wide = [torch.full((B, H, S, d + 8), float("nan"), device="cuda", dtype=to_dev(torch, Q, dtype).dtype) for _ in range(3)]
+        for to, x in zip(wide, (Q, K, V)):
+            to[..., :d] = to_dev(torch, x, dtype)
+        q, k, v = (x[..., :d] for x in wide)
+        for form in (0, 1, 3) if d > 64 else (0, 1):
+            with smha.Plan.from_dense(m, head_dim=d, force=smha.SMHA_KERNEL_BLOCK, block_form=form) as plan:
+                if form:
+                    runs_form(smha, plan, B, H, d, dtype, form)
+                assert mask == "mixed" or plan.info()["n_split_rows" if mask == "cut" else "n_gathered"] > 0
+                for f32 in (False, True):
+                    room = torch.full((B, H, S, d + 8), 7.0, device="cuda", dtype=torch.float32 if f32 else q.dtype)
+                    plan.forward(q, k, v, out=room[..., :d])
+                    check(room[..., :d].float().cpu().numpy(), ref, f"{mask} d={d} {dtype} form={form} f32={f32}", bf16_out=dtype == "bf16" and not f32)
+                    assert bool((room[..., d:] == 7.0).all())

@@ -96,3 +96,21 @@ def test_a_plan_destroyed_on_another_thread_leaves_a_capture_alone(mode):
             graph.replay()
             torch.cuda.synchronize()
             assert torch.equal(out, eager)
+
+
+@pytest.mark.parametrize("prepared,d", [(64, 24), (128, 80), (256, 136)])
+def test_what_one_head_size_prepared_serves_the_narrower_ones_of_its_64_128_or_256_columns(prepared, d):
+    """... in the entry point that allocates nothing, at the wider width and with the same bits as at the call's own."""
+    import torch
+    import paper_2506_06095_amd as smha
+    spec = W.MaskSpec(flags=W.WINDOW | W.GLOBAL, window_left=32, window_right=32, n_global=8)
+    g = torch.Generator(device="cuda").manual_seed(d)
+    q, k, v = (torch.randn(2, 4, 1000, d, device="cuda", generator=g).half() for _ in range(3))
+    for form in (0, 1):
+        with smha.Plan.from_desc(spec, 2, 4, 1000, head_dim=d, force=smha.SMHA_KERNEL_BLOCK, block_form=form) as plan:
+            plan.prepare(2, 4, prepared)
+            wide = plan.forward_static(q, k, v, torch.full_like(q, float("nan")))
+            plan.prepare(2, 4, d)
+            own = plan.forward_static(q, k, v, torch.full_like(q, float("nan")))
+            torch.cuda.synchronize()
+            assert bool(torch.isfinite(own).all()) and torch.allclose(wide.float(), own.float(), rtol=2e-3, atol=2e-3)

@@ -1,4 +1,4 @@
-"""ctypes binding of include/smha.h: argument marshalling only.
+"""ctypes binding of include/smha.h: argument marshalling only (Plan.forward's ordinary calls: csrc/torch_binding.cpp).
 
 Function names mirror the C ABI.  torch is used for device memory and streams;
 numpy for host index arrays.  Nothing here computes attention.
@@ -112,6 +112,21 @@ def _load():
     lib.smha_call_kernel_name.restype = C.c_char_p
     _lib = lib
     return lib
+
+
+_native = None  # (forward of _smha_torch, address of smha_forward)
+
+
+def _load_native():
+    global _native
+    if _native is None:
+        lib = _load()
+        if not os.path.exists(_build.EXT):
+            _build.build_extension()
+        import torch  # noqa: F401  (the module uses its libraries)
+        from . import _smha_torch
+        _native = (_smha_torch.forward, C.cast(lib.smha_forward, C.c_void_p).value)
+    return _native
 
 
 def smha_status_string(status: int) -> str:
@@ -366,6 +381,17 @@ class Plan:
 
     def forward(self, Q, K, V, out=None, out_dtype=None, scale: float = 0.0,
                 kernel: int = SMHA_KERNEL_AUTO, stream=None):
+        if self._dims is None:
+            info = self.info()
+            self._dims = (info["S"], info["Sk"])
+        if stream is None:  # the native way, for every call that it takes (csrc/torch_binding.cpp)
+            call, entry = _native or _load_native()
+            S, Sk = self._dims
+            got = call(entry, self.handle, S, Sk, Q, K, V, out, out_dtype, scale, kernel)
+            if got is not None:
+                if type(got) is int:
+                    raise SmhaError(got, "smha_forward")
+                return got
         import torch
         if out is None:
             # (packed whatever Q's strides are, and a plain tensor whatever Q is; torch.empty with a size, a type and a device
@@ -374,9 +400,6 @@ class Plan:
                 out = torch.empty_like(Q, dtype=out_dtype, memory_format=torch.contiguous_format)
             else:
                 out = torch.empty(Q.shape, dtype=out_dtype or Q.dtype, device=Q.device)
-        if self._dims is None:
-            info = self.info()
-            self._dims = (info["S"], info["Sk"])
         smha_forward(self.handle, Q, K, V, out, scale, kernel, stream, self._dims)
         return out
 

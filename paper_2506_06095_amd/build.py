@@ -1,14 +1,17 @@
-"""Build libsmha.so (HIP, gfx950) in-tree with hipcc."""
+"""Build libsmha.so (HIP, gfx950) with hipcc and the native call path for torch (_smha_torch.so) with g++, in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsmha.so")
+EXT = os.path.join(HERE, "_smha_torch.so")
+EXT_SOURCE = os.path.join(CSRC, "torch_binding.cpp")
 SOURCES = ["plan.cpp", "kernels.hip"]
 HEADERS = ["smha_internal.hpp", "device_pool.hpp", "block_fwd2.inc", "block_fwd16.inc", "wave_fwd.inc", os.path.join(ROOT, "include", "smha.h")]
 
@@ -31,6 +34,18 @@ def command(extra=()):
             *[os.path.join(CSRC, s) for s in SOURCES], "-o", LIB]
 
 
+def build_extension() -> str:
+    """_smha_torch.so against the installed torch's headers (torch has its libraries loaded when the module is imported)."""
+    from torch.utils import cpp_extension
+    import torch
+    subprocess.run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
+                    f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+                    *[f"-isystem{d}" for d in (*cpp_extension.include_paths(), "/opt/rocm/include")],
+                    "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), EXT_SOURCE, "-o", EXT,
+                    *[f"-L{d}" for d in cpp_extension.library_paths()], "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"], check=True)
+    return EXT
+
+
 def stale() -> bool:
     if not os.path.exists(LIB):
         return True
@@ -43,6 +58,8 @@ def build_library(force: bool = True, verbose: bool = False) -> str:
     if force or stale():
         cmd = command(("-Rpass-analysis=kernel-resource-usage",) if verbose else ())
         subprocess.run(cmd, check=True)
+    if force or not os.path.exists(EXT) or os.path.getmtime(EXT_SOURCE) > os.path.getmtime(EXT):
+        build_extension()
     return LIB
 
 

@@ -1134,3 +1134,77 @@ def test_kernel_widths_of_32_96_and_160_columns(torch_mod, smha, d, mask):
                     plan.forward(q, k, v, out=room[..., :d])
                     check(room[..., :d].float().cpu().numpy(), ref, f"{mask} d={d} {dtype} form={form} f32={f32}", bf16_out=dtype == "bf16" and not f32)
                     assert bool((room[..., d:] == 7.0).all())
+
+
+def test_the_native_call_path_and_the_general_one_agree(torch_mod, smha):
+    """Plan.forward through _smha_torch against smha_forward with the same arguments: types, layouts, a given output, streams."""
+    torch = torch_mod
+    from paper_2506_06095_amd import binding
+    call, entry = binding._load_native()
+    spec = W.MaskSpec(flags=W.WINDOW, window_left=20, window_right=3)
+    B, H, S, d = 2, 3, 130, 72
+    g = torch.Generator(device="cuda").manual_seed(1)
+    with smha.Plan.from_desc(spec, B, H, S, head_dim=d, build_both=True) as plan:
+        for dtype in (torch.float16, torch.bfloat16):
+            packed = [torch.randn(B, H, S, d, device="cuda", generator=g).to(dtype) for _ in range(3)]
+            for q, k, v in (packed, [x.transpose(1, 2).contiguous().transpose(1, 2) for x in packed]):
+                for out_dtype in (None, dtype, torch.float32):
+                    for kernel in (0, 1, 2):
+                        want = torch.empty(B, H, S, d, device="cuda", dtype=out_dtype or dtype)
+                        smha.smha_forward(plan.handle, q, k, v, want, kernel=kernel, scale=0.3)
+                        got = call(entry, plan.handle, S, S, q, k, v, None, out_dtype, 0.3, kernel)
+                        assert type(got) is torch.Tensor and got.is_contiguous() and got.dtype == want.dtype and torch.equal(got, want)
+                        assert torch.equal(plan.forward(q, k, v, out_dtype=out_dtype, kernel=kernel, scale=0.3), want)
+                room = torch.zeros(B, S, H, d, device="cuda", dtype=torch.float32).transpose(1, 2)
+                smha.smha_forward(plan.handle, q, k, v, want, scale=0.3)
+                assert plan.forward(q, k, v, out=room, scale=0.3) is room and torch.equal(room, want)
+        q, k, v = packed
+        side = torch.cuda.Stream()
+        with torch.cuda.stream(side):                           # (a long wait ahead of the inputs, on the stream that is current)
+            torch.cuda._sleep(20_000_000)
+            late = q + 1
+            got = plan.forward(late, k, v)
+        side.synchronize()
+        assert torch.equal(got, plan.forward(q + 1, k, v))
+        assert not plan.forward(q.clone().requires_grad_(), k, v).requires_grad
+
+
+def test_calls_that_the_native_path_leaves_to_the_general_one(torch_mod, smha):
+    """It answers None, and Plan.forward does what it did: raises, or runs."""
+    torch = torch_mod
+    from paper_2506_06095_amd import binding
+    call, entry = binding._load_native()
+    spec = W.MaskSpec(flags=W.WINDOW, window_left=20, window_right=3)
+    x = torch.randn(1, 2, 130, 64, device="cuda").half()
+    wide = torch.randn(1, 2, 130, 128, device="cuda").half()
+
+    class Sub(torch.Tensor):
+        pass
+
+    with smha.Plan.from_desc(spec, 1, 2, 130, head_dim=64) as plan:
+        want = plan.forward(x, x, x)
+        for q, k, v, kw in ((x.cpu(), x, x, {}), (x, x[:, :1], x, {}), (x, x.bfloat16(), x, {}), (x.float(), x.float(), x.float(), {}),
+                            (wide[..., ::2], x, x, {}), (x, x, x, {"out_dtype": torch.float64}), (x[0], x, x, {}), (x[:, :, :64], x, x, {}),
+                            (x, x, x, {"out": torch.empty(1, 2, 130, 32, device="cuda").half()})):
+            assert call(entry, plan.handle, 130, 130, q, k, v, kw.get("out"), kw.get("out_dtype"), 0.0, 0) is None
+            with pytest.raises(ValueError):
+                plan.forward(q, k, v, **kw)
+        with pytest.raises(smha.SmhaError):                     # (refused by the library: rows of 65 elements)
+            plan.forward(torch.empty(1, 2, 130, 65, device="cuda").half()[..., :64], x, x)
+        for q in (x.as_subclass(Sub), x.clone().rename("b", "h", "s", "d")):
+            assert call(entry, plan.handle, 130, 130, q, x, x, None, None, 0.0, 0) is None
+            got = plan.forward(q, x, x)
+            assert type(got) is torch.Tensor and torch.equal(got, want)
+        seen = []
+
+        class Mode(torch.utils._python_dispatch.TorchDispatchMode):
+            def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+                seen.append(str(func))
+                return func(*args, **(kwargs or {}))
+        with Mode():
+            assert torch.equal(plan.forward(x, x, x).clone(), want.clone())
+        assert any("empty_like" in f for f in seen)
+        with pytest.raises(RuntimeError):
+            torch.vmap(lambda t: plan.forward(t, x, x))(x[None])
+    with pytest.raises(smha.SmhaError):
+        plan.forward(x, x, x)

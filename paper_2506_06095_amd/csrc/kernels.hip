@@ -390,7 +390,7 @@ __device__ __forceinline__ void finish_split_part(const FwdParams &p, const f32x
 // SPLIT: the plan cuts some 128-row groups into parts (the instantiation for plans that do not carries
 // none of the merge code: its registers would be paid for in every item's start and end).
 template <int D, bool BF16, int OUT, bool GATHER, bool SPLIT>
-__global__ void __launch_bounds__(256, block_groups(D)) smha_block_fwd(const FwdParams p) {
+__global__ void __launch_bounds__(256, block_groups(D, GATHER)) smha_block_fwd(const FwdParams p) {
     constexpr int NS = D / 16;            // k-steps of S^T = K Q^T
     constexpr int NDT = D / 32;           // 32-wide d tiles of O^T
     constexpr int TILE = 64 * D;          // one K or V tile, in elements
@@ -1458,7 +1458,9 @@ static int block_form(const smha_plan *plan, int d, bool bf16) {
     if (d == 96) return plan->mostly_partial ? 3 : 1;
     return d == 128 && !plan->dense_long_lists ? 3 : 1;
 }
-static int workgroups_per_cu(int form, int d) { return form == 2 ? 1 : form == 3 ? block16_groups(d) : block_groups(d); }
+static int workgroups_per_cu(const smha_plan *plan, int form, int d) {
+    return form == 2 ? 1 : form == 3 ? block16_groups(d) : block_groups(d, plan->n_gathered > 0);
+}
 
 template <int D, bool BF16, int OUT>
 static hipError_t launch_block_out(const smha_plan *plan, FwdParams &fp, hipStream_t stream) {
@@ -1543,7 +1545,7 @@ static int grain_for(const smha_plan *plan, int B, int H, int d, int form) {
     else
         for (int bh = 0; bh < B * H; ++bh)
             n_items += w0.item_cnt[(plan->Bm > 1 ? bh / H : 0) * plan->Hm + (plan->Hm > 1 ? bh % H : 0)];
-    return 2 * n_items < (int64_t)workgroups_per_cu(form, d) * plan->n_cu ? 1 : 0;
+    return 2 * n_items < (int64_t)workgroups_per_cu(plan, form, d) * plan->n_cu ? 1 : 0;
 }
 
 // (a form that was asked for, by option or environment, is run; the library's own choice may give way)
@@ -1569,7 +1571,7 @@ static smha_status_t make_prepared(const smha_plan *plan, int B, int H, int d, i
     std::vector<int32_t> table;
     int per_xcd = 0, longest = 0;
     int64_t step_words = 0, item_words = 0;
-    const int slots = workgroups_per_cu(form, d) * plan->n_cu / 8;  // workgroups that fit an XCD at once
+    const int slots = workgroups_per_cu(plan, form, d) * plan->n_cu / 8;  // workgroups that fit an XCD at once
     smha_plan::Prepared *q = nullptr;
     Arena arena;
     WaveArrays lists;

@@ -1128,7 +1128,7 @@ static TypeTimes block_time_us(const smha_plan *plan, int lvl, int form, int B, 
         longest = std::max(longest, 2.0 + i.end - i.begin);
     }
     const double total = cost * per_xcd, items = (double)wl.items.size() * per_xcd;
-    const double units = std::max(plan->n_cu / 8, 1), slots = units * (form == 3 ? block16_groups(D) : block_groups(D));
+    const double units = std::max(plan->n_cu / 8, 1), slots = units * (form == 3 ? block16_groups(D) : block_groups(D, plan->n_gathered > 0));
     const double unit = items > units ? std::max(longest, total / units + 0.35 * total / items) : longest;
     const double group = std::max(longest, total / std::max(1.0, std::min(slots, items)));
     int64_t tiles = 0, part = 0;

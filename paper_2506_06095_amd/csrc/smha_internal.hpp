@@ -100,7 +100,8 @@ constexpr int block_head_size(int d) { return d <= 32 ? 32 : d <= 64 ? 64 : d <=
 constexpr int block_width(int D) { return D == 256 ? 5 : D / 32 - 1; }
 // workgroups that fit a compute unit (LDS and registers): wave form, first form, third form
 constexpr int wave_groups(int D) { return D <= 64 ? 4 : D == 96 ? 3 : D == 128 ? 2 : 1; }
-constexpr int block_groups(int D) { return D <= 64 ? 4 : D == 96 ? 3 : D <= 160 ? 2 : 1; }
+// (first form at 160 columns: two take the whole LDS, and there is no room for the key numbers of gathered tiles)
+constexpr int block_groups(int D, bool gathered) { return D <= 64 ? 4 : D == 96 ? 3 : D <= (gathered ? 128 : 160) ? 2 : 1; }
 constexpr int block16_groups(int D) { return D <= 160 ? 2 : 1; }
 constexpr int row_step_keys(int width, int form) {  // keys of a row that one step covers
     return kRowForms[width][form].batch * (8 >> width) / kRowForms[width][form].rows;

@@ -93,13 +93,13 @@ constexpr RowForm kRowForms[3][3] = {{{8, 3}, {4, 4}, {1, 2}}, {{4, 3}, {4, 4}, 
 constexpr int row_width(int D) { return D <= 64 ? 0 : D <= 128 ? 1 : 2; }
 // The block kernel's widths: 32, 64, 96, 128, 160 and 256 columns, and the index of each.  Every form is bound by what a step
 // loads into LDS, reads from it and multiplies, and by how many waves fit, all of which go with the width: over 685 calls with
-// heads of 32, 80, 96 and 160 columns the wave form is 1.14, 1.10 and 1.32 times as fast at 32, 96 and 160 columns as at 64, 128
+// heads of 32, 80, 96 and 160 columns the wave form is 1.14, 1.10 and 1.51 times as fast at 32, 96 and 160 columns as at 64, 128
 // and 256, the older forms 1.15, 1.12 and 1.22 (window 2 x 20 x 1728 x 80 35.8 -> 27.3 us, BigBird 7 x 12 x 2688 x 32 41.8 ->
 // 28.6, BigBird blocks 2 x 20 x 3082 x 160 bf16 132 -> 101).  Heads of 168 to 248 columns stay at 256.
 constexpr int block_head_size(int d) { return d <= 32 ? 32 : d <= 64 ? 64 : d <= 96 ? 96 : d <= 128 ? 128 : d <= 160 ? 160 : 256; }
 constexpr int block_width(int D) { return D == 256 ? 5 : D / 32 - 1; }
 // workgroups that fit a compute unit (LDS and registers): wave form, first form, third form
-constexpr int wave_groups(int D) { return D <= 64 ? 4 : D == 96 ? 3 : D == 128 ? 2 : 1; }
+constexpr int wave_groups(int D) { return D <= 64 ? 4 : D == 96 ? 3 : D <= 160 ? 2 : 1; }
 // (first form at 160 columns: two take the whole LDS, and there is no room for the key numbers of gathered tiles)
 constexpr int block_groups(int D, bool gathered) { return D <= 64 ? 4 : D == 96 ? 3 : D <= (gathered ? 128 : 160) ? 2 : 1; }
 constexpr int block16_groups(int D) { return D <= 160 ? 2 : 1; }

@@ -1023,7 +1023,7 @@ int build_wave_order(const smha_plan *plan, int alone, std::vector<int32_t> &tab
 // profiles/block_forms.csv (all kinds of masks, 64 to 8192 queries, 1 to 400 heads, 8 to 256 columns; clocks settled by 10 ms of the
 // same work and three sets of inputs in turn: measured from idle clocks the first form took 15 % longer, the wave form 3 %,
 // and the choice went wrong by that).  Mean error over 600 other calls of the table: 5 to 7 % (wave form), 5 % (the others).  At 32,
-// 96 and 160 columns: the wave form's constants of 64, 128 and 128 columns with three of their own (`start`, `memory`, and one
+// 96, 160 and 256 columns: the wave form's constants of 64, 128, 128 and 256 columns at first with three of their own (`start`, `memory`, and one
 // factor for `wave`, `step` and the chain's), the form that the library takes there refitted (160 with gathered tiles: likewise scaled);
 // mean error 5 to 8 %.
 struct WaveCost {
@@ -1035,7 +1035,7 @@ static const WaveCost kWaveCost[6] = {
     {3.99, 1.246, 0.595, 0.05, 0.191, 1.17, 0.567, 0.1278, 4.0, 0.09, -0.076, 1.877, 0.0683},       // 96
     {3.80, 1.5978, 0.7627, 0.05, 0.191, 1.17, 0.7266, 0.1638, 4.0, 0.09, -0.076, 1.877, 0.0700},    // 128
     {4.594, 2.067, 0.987, 0.05, 0.191, 1.17, 0.940, 0.2120, 4.0, 0.09, -0.076, 1.877, 0.1045},      // 160
-    {5.43, 5.1097, 1.6599, 0.63, 0.156, 1.17, 1.5420, 0.0, 4.0, 0.23, -0.041, 4.513, 0.1521}};      // 256
+    {5.631, 4.5016, 1.4624, 0.63, 0.156, 1.17, 1.3585, 0.0, 4.0, 0.23, -0.041, 4.513, 0.2327}};     // 256
 struct BlockCost {
     double start, unit, unit_act, unit_part, unit_sub, unit_lone, group, group_act, group_part, unit_bf16, group_bf16, gather, power, merge, memory;
 };
@@ -1157,8 +1157,8 @@ static TypeTimes block_time_us(const smha_plan *plan, int lvl, int form, int B, 
 // 64-blocks 1 x 2 x 2816 x 256 20.6 / 12.8); it loses where tiles are full and rows many (causal 16 x 12 x 4096 x 128:
 // 870 / 1176), because every K and V tile is loaded once per 32 rows.  It has to win by 4 %: of 1600
 // calls of the table that were drawn at random 16 then run the slower form by more than 2 % with one of the input types, and the mean
-// against the other forms is 0.645, 0.675, 0.684, 0.722, 0.659, 0.766 at 32, 64, 96, 128, 160 and 256 columns, where the better form for
-// each call would give 0.644, 0.672, 0.682, 0.718, 0.653, 0.764.
+// against the other forms is 0.645, 0.675, 0.684, 0.722, 0.659, 0.728 at 32, 64, 96, 128, 160 and 256 columns, where the better form for
+// each call would give 0.644, 0.672, 0.682, 0.718, 0.653, 0.722.
 // The two input types are decided together (by the product of their ratios): one order and one set of workspaces serves both.
 bool wave_form_pays(const smha_plan *plan, int lvl, int form, int B, int H, int D, int &alone) {
     if (H > 65535 || (int64_t)B * H > (1 << 18) /* (a grid's z holds an eighth of them) */) return false;

@@ -66,13 +66,14 @@ typedef struct {
                        work lists only; the exported formats are never affected)               */
     int block_form; /* which form of the block-wise kernel runs where several exist: 0 = the library's choice
                        (at 128 columns form 3, unless nearly all tiles are full and the lists long: form 1;
-                       at 256 columns form 3; at 64 columns form 1; at all widths the wave form, one
+                       at 160 and 256 columns form 3; at 32 and 64 columns form 1; at 96 columns form 1, unless
+                       nine tiles in ten are partly filled: form 3; at all widths the wave form, one
                        wave per 32 query rows, for calls that it is estimated to run faster),
                        1 = four waves per workgroup, every wave forms scores, probabilities and output of
                        its 32 rows (one to four workgroups per compute unit); 2 = eight waves per workgroup,
                        score waves and value waves, one workgroup per compute unit (64 and 128 columns);
-                       3 = eight waves of 16 rows per workgroup, two workgroups per compute unit at 128
-                       columns, one at 256.  Plans with gathered tiles always run form 1, as does bfloat16
+                       3 = eight waves of 16 rows per workgroup, two workgroups per compute unit at 96 to
+                       160 columns, one at 256.  Plans with gathered tiles always run form 1, as does bfloat16
                        at 128 columns where form 2 is asked for.  For measurements and tests.             */
 } smha_plan_opts_t;
 

@@ -66,9 +66,10 @@ typedef struct {
                        work lists only; the exported formats are never affected)               */
     int block_form; /* which form of the block-wise kernel runs where several exist: 0 = the library's choice
                        (at 128 columns form 3, unless nearly all tiles are full and the lists long: form 1;
-                       at 160 and 256 columns form 3; at 32 and 64 columns form 1; at 96 columns form 1, unless
-                       nine tiles in ten are partly filled: form 3; at all widths the wave form, one
-                       wave per 32 query rows, for calls that it is estimated to run faster),
+                       at 160 and 256 columns form 3; at 32, 64 and 96 columns form 1, at 96 form 3
+                       where nine tiles in ten are partly filled and a quarter of their 32 x 32 sub-tiles has
+                       no keys; at all widths the wave form, one wave per 32 query rows, for calls that it
+                       is estimated to run faster),
                        1 = four waves per workgroup, every wave forms scores, probabilities and output of
                        its 32 rows (one to four workgroups per compute unit); 2 = eight waves per workgroup,
                        score waves and value waves, one workgroup per compute unit (64 and 128 columns);

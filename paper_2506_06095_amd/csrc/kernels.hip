@@ -1452,11 +1452,7 @@ static int block_form(const smha_plan *plan, int d, bool bf16) {
     if (d > 128) return asked == 1 ? 1 : 3;  // 256 columns: eight waves of 16 rows are two waves per SIMD, four of 32 are one
     if (asked == 3) return d > 64 ? 3 : 1;  // eight waves of 16 rows: more than 64 columns
     if (asked != 0) return asked == 2 && (d == 64 || (d == 128 && !bf16)) ? 2 : 1;
-    // The library's choice.  At 96 columns the first form fits three workgroups on a compute unit and is faster (where the
-    // wave form is not, f16 0.91 of the third form's time, bf16 0.94: per-head 64-blocks 4 x 16 x 1280 x 80 18.7 us, 21.6), except
-    // that nearly nothing but partly filled tiles, whose empty parts the third form skips, is a draw (0.99, bf16 1.02).
-    if (d == 96) return plan->mostly_partial ? 3 : 1;
-    return d == 128 && !plan->dense_long_lists ? 3 : 1;
+    return library_form(d, plan->dense_long_lists, d == 96 && empty_sub_tiles(plan));
 }
 static int workgroups_per_cu(const smha_plan *plan, int form, int d) {
     return form == 2 ? 1 : form == 3 ? block16_groups(d) : block_groups(d, plan->n_gathered > 0);

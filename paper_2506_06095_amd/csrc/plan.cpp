@@ -580,6 +580,19 @@ bool count_wave_lists(const smha_plan *p) {
     return true;
 }
 
+// Nearly all tiles are partly filled, and one in four or more of their 32 x 32 sub-tiles has no keys.
+bool empty_sub_tiles(const smha_plan *p) {
+    if (!p->mostly_partial) return false;
+    try {
+        if (!count_wave_lists(p)) return false;
+    } catch (const std::bad_alloc &) {
+        return false;
+    }
+    int64_t tiles = 0;
+    for (const MaskFormats &m : p->masks) tiles += (int64_t)m.kt_col.size();
+    return (double)p->wave.n_ents < 0.75 * 4.0 * (double)tiles;
+}
+
 void make_wave_lists(const smha_plan *p) {  // (count_wave_lists has said that they are possible)
     WaveLists &wl = p->wave;
     std::lock_guard<std::mutex> lock(wl.mutex);
@@ -1039,16 +1052,25 @@ static const WaveCost kWaveCost[6] = {
 struct BlockCost {
     double start, unit, unit_act, unit_part, unit_sub, unit_lone, group, group_act, group_part, unit_bf16, group_bf16, gather, power, merge, memory;
 };
-static const BlockCost kBlockCost[6][2] = {  // first form, third form (that the library takes at 128, 160 and 256 columns)
+static constexpr BlockCost kBlockCost[6][2] = {  // first form, third form (that the library takes at 96 to 256 columns)
     {{2.033, -1.240, 0.499, 0.061, 0.006, 0.075, -0.611, -0.179, 0.148, 1.224, 1.137, 1.136, 1.813, 3.040, 0.149}, {}},
     {{1.743, -0.920, 0.640, -0.040, -0.009, 0.049, -0.526, -0.291, 0.165, 1.304, 1.172, 1.136, 1.781, 5.390, 0.131}, {}},
-    {{2.053, -0.572, 0.020, -0.040, 0.014, -0.150, -0.278, -0.053, 0.118, 1.219, 1.108, 1.073, 1.844, 5.286, 0.162}, {}},
+    {{2.053, -0.572, 0.020, -0.040, 0.014, -0.150, -0.278, -0.053, 0.118, 1.219, 1.108, 1.073, 1.844, 5.286, 0.162},
+     {2.371, -0.577, -0.168, -0.103, 0.100, -0.247, -0.402, 0.069, 0.160, 1.203, 1.045, 1.100, 1.580, 5.086, 0.142}},
     {{2.095, -0.519, -0.107, -0.089, 0.007, -0.154, -0.253, 0.255, 0.004, 1.254, 1.043, 1.073, 1.200, 11.641, 0.098},
      {1.686, -0.455, -0.179, -0.008, 0.097, -0.216, -0.378, 0.057, 0.132, 1.229, 1.057, 1.100, 1.570, 6.935, 0.145}},
     {{1.558, 0.565, 0.001, 0.086, 0.001, -0.329, -0.827, -0.182, -0.400, 1.158, 1.004, 0.900, 1.200, 10.146, 0.126},
      {2.347, -0.300, -0.098, 0.200, 0.107, -0.921, 0.091, 0.023, -0.223, 1.106, 1.142, 1.100, 1.718, 8.993, 0.141}},
     {{2.039, 0.773, 0.001, 0.086, 0.001, -0.329, 0.186, -0.182, -0.400, 1.158, 1.004, 0.900, 1.200, 10.146, 0.090},
      {1.576, -0.137, -0.049, 0.247, 0.065, -0.856, 0.186, 0.050, -0.400, 1.128, 1.147, 1.100, 1.384, 10.481, 0.128}}};
+
+static_assert([] {  // every form that the library may take has constants
+    for (int D = 32; D <= 256; D += 32)
+        if (block_head_size(D) == D)
+            for (int is = 0; is < 4; ++is)
+                if (!(kBlockCost[block_width(D)][library_form(D, is & 1, is & 2) == 3].power > 0) || !(kBlockCost[block_width(D)][0].power > 0)) return false;
+    return true;
+}());
 
 struct TypeTimes { double f16, bf16; };  // us with float16 and with bfloat16 inputs
 
@@ -1157,8 +1179,8 @@ static TypeTimes block_time_us(const smha_plan *plan, int lvl, int form, int B, 
 // 64-blocks 1 x 2 x 2816 x 256 20.6 / 12.8); it loses where tiles are full and rows many (causal 16 x 12 x 4096 x 128:
 // 870 / 1176), because every K and V tile is loaded once per 32 rows.  It has to win by 4 %: of 1600
 // calls of the table that were drawn at random 16 then run the slower form by more than 2 % with one of the input types, and the mean
-// against the other forms is 0.645, 0.675, 0.684, 0.722, 0.659, 0.728 at 32, 64, 96, 128, 160 and 256 columns, where the better form for
-// each call would give 0.644, 0.672, 0.682, 0.718, 0.653, 0.722.
+// against the other forms is 0.645, 0.675, 0.687, 0.722, 0.659, 0.728 at 32, 64, 96, 128, 160 and 256 columns, where the better form for
+// each call would give 0.644, 0.672, 0.684, 0.718, 0.653, 0.722.
 // The two input types are decided together (by the product of their ratios): one order and one set of workspaces serves both.
 bool wave_form_pays(const smha_plan *plan, int lvl, int form, int B, int H, int D, int &alone) {
     if (H > 65535 || (int64_t)B * H > (1 << 18) /* (a grid's z holds an eighth of them) */) return false;

@@ -103,6 +103,14 @@ constexpr int wave_groups(int D) { return D <= 64 ? 4 : D == 96 ? 3 : D <= 160 ?
 // (first form at 160 columns: two take the whole LDS, and there is no room for the key numbers of gathered tiles)
 constexpr int block_groups(int D, bool gathered) { return D <= 64 ? 4 : D == 96 ? 3 : D <= (gathered ? 128 : 160) ? 2 : 1; }
 constexpr int block16_groups(int D) { return D <= 160 ? 2 : 1; }
+// Which of the two older forms the library takes for plans without gathered tiles (those run the first).  At 96 columns the first
+// form fits three workgroups on a compute unit and is the faster one, 0.93 of the third form's time on 90 calls whose tiles are nearly all
+// partly filled with nearly every 32 x 32 sub-tile in use (1.02 at most; random 5 % 16 x 16 x 2048 x 80 417 us, 496), 0.96 on 58 with
+// more than three in four in use.  With fewer the third form, whose waves skip empty parts of a tile, is: the first takes 1.06
+// of its time (53 calls; longformer 1 x 16 x 3200 x 96 26.1 us, 23.9).
+constexpr int library_form(int D, bool dense_long_lists, bool empty_sub_tiles) {
+    return D > 128 || (D == 128 && !dense_long_lists) || (D == 96 && empty_sub_tiles) ? 3 : 1;
+}
 constexpr int row_step_keys(int width, int form) {  // keys of a row that one step covers
     return kRowForms[width][form].batch * (8 >> width) / kRowForms[width][form].rows;
 }
@@ -248,6 +256,7 @@ smha_status_t finish_plan(smha_plan *p);      // selector, work lists, concatena
 void build_work_order(const smha_plan *plan, int lvl, int B, int H, int slots, bool spread, std::vector<int32_t> &table, int &per_xcd);
 // what the estimates need of the wave form's lists (false: the plan has none), and the lists
 bool count_wave_lists(const smha_plan *p);
+bool empty_sub_tiles(const smha_plan *p);
 void make_wave_lists(const smha_plan *p);
 // whether a call shape runs the wave form rather than `form` at grain `lvl`; alone: see build_wave_order
 bool wave_form_pays(const smha_plan *plan, int lvl, int form, int B, int H, int D, int &alone);

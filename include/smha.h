@@ -250,8 +250,9 @@ smha_status_t smha_forward(const smha_plan_t *plan, const void *Q, const void *K
  * results of split row groups go to an array inside the library's own image (32 MiB per GPU,
  * held until the process ends) instead of a workspace of the plan, and nothing is ever allocated,
  * freed or synchronised.  The call shape must have been prepared (smha_plan_prepare, or an earlier
- * smha_forward with the same B, H, d): UNSUPPORTED otherwise, and also when the shape's workspace
- * (see smha_plan_prepare) exceeds the 32 MiB.  A small kernel clears the array's arrival counters
+ * smha_forward with the same B, H, d; what another d of the same 64, 128 or 256 columns prepared serves
+ * too, see smha_plan_prepare): UNSUPPORTED otherwise, and also when the workspace (as there, with D the
+ * kernel width that runs) exceeds the 32 MiB.  A small kernel clears the array's arrival counters
  * ahead of the attention kernel, on the same stream.  Every call on a GPU shares that GPU's one
  * array: calls that overlap in time on one GPU (two streams, two plans, two threads) race on it and
  * must be serialised by the caller; calls that follow each other on one stream are fine.  Plans that
@@ -272,8 +273,12 @@ smha_status_t smha_forward_static(const smha_plan_t *plan, const void *Q, const 
  * (those are merged inside the same launch by whichever part finishes last): B*H * (split parts per
  * head) * (128 D + 1024) floats each for the 128-row groups of the older forms, (32 D + 128) for the
  * 32-row groups of the wave form, which may split where they do not, and one counter per split group
- * and head (8 for the older forms); D is the kernel width for d (32, 64, 96, 128, 160 or 256).  Shapes that split
+ * and head (8 for the older forms); D is 64, 128 or 256, the next above d.  Shapes that split
  * nothing get none.
+ * Every kernel width (32, 64, 96, 128, 160 and 256 columns: the next above d) has a preparation of its own, which
+ * smha_forward makes where there is none.  Only where nothing may be allocated (smha_forward_static, or smha_forward on a
+ * stream that is captured) does a shape without one run on that of another d with the same D, at the wider of the two
+ * kernel widths and in the form that was prepared: the same result within rounding.
  * Allocates device memory and copies to it (blocking); call it outside stream capture, on the plan's device.  Calling it again for the
  * same shape does nothing; plans that run the row-wise kernel need nothing and return SMHA_OK.
  * Errors: INVALID_ARG, UNSUPPORTED (d, more than 2^28 work items), SHAPE, ALLOC, HIP. */
@@ -321,7 +326,7 @@ const char *smha_status_string(smha_status_t status);
 
 /* Symbol names of kernels, for matching profiler output (name and duration bookkeeping is left to the caller).
  * smha_call_kernel_name: the kernel that smha_forward launches for a call with this batch size, head count, head size
- * and input type ("" for arguments that it refuses).  smha_kernel_name knows no call shape: the kernel that runs where
+ * and input type ("" for arguments that it refuses), on a preparation of its own (see smha_plan_prepare).  smha_kernel_name knows no call shape: the kernel that runs where
  * the block kernel's wave form does not take its place, which depends on the call (block_form 0 only). */
 const char *smha_call_kernel_name(const smha_plan_t *plan, int B, int H, int d, smha_dtype_t in_dtype,
                                   smha_kernel_t kernel);

@@ -1559,6 +1559,11 @@ static int wave_heads(const smha_plan *plan, int heads, int D, int workgroups) {
     return (rounds + groups - 1) / groups;
 }
 
+// Head sizes: any multiple of 8 up to 256.  The row kernel exists for 64, 128 and 256 columns, the block kernel for those of
+// block_head_size; a narrower head runs on the next of them, its missing columns read as zeros (which changes no score) and never stored.
+static bool head_size_ok(int d) { return d >= 8 && d <= 256 && d % 8 == 0; }
+static int row_head_size(int d) { return d <= 64 ? 64 : d <= 128 ? 128 : 256; }
+
 // The work order and workspaces for a call shape that runs `form` at grain `lvl` (wave form: with lists of up to `alone`
 // entries walked by one wave): allocates and copies; nothing that exists is freed or moved.
 static smha_status_t make_prepared(const smha_plan *plan, int B, int H, int d, int lvl, int form, int alone, smha_plan::Prepared **out) {
@@ -1634,7 +1639,7 @@ static smha_status_t make_prepared(const smha_plan *plan, int B, int H, int d, i
             arena.add(lists.splits, plan->wave.splits);
         }
         if ((form == 4 ? plan->wave.max_slots : wl.max_slots) > 0) {
-            ws_bytes = workspace_bytes(plan, lvl, form, B, H, d, &counters_at);
+            ws_bytes = workspace_bytes(plan, lvl, form, B, H, row_head_size(d), &counters_at);  // (see prepared_for)
             zeros.assign((ws_bytes - counters_at) / sizeof(uint32_t), 0u);
         }
         q = new smha_plan::Prepared();
@@ -1682,15 +1687,33 @@ static smha_status_t make_prepared(const smha_plan *plan, int B, int H, int d, i
     return SMHA_OK;
 }
 
+static bool capturing(hipStream_t stream) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 // What a call shape was given: found, or made now.  `form` is the block form the call would run (block_form); the wave
 // form takes its place where it is estimated to be faster.  *ws receives the workspace for this call (null if it
-// splits no group).
-static smha_status_t prepared_for(const smha_plan *plan, int B, int H, int d, int form,
-                                  const smha_plan::Prepared **out, void **ws, bool may_allocate = true) {
+// splits no group).  width: a forward's kernel width, d.  Where a forward may not allocate (smha_forward_static, a stream
+// that is captured), a shape that was not prepared runs with what another head size of the same 64, 128 or 256 columns
+// prepared (the same lists, and workspaces of that size), at the wider of the two widths.  Elsewhere every head size makes its own, so that
+// what a call runs does not depend on the calls before it.
+static smha_status_t prepared_for(const smha_plan *plan, int B, int H, int d, int form, bool bf16,
+                                  const smha_plan::Prepared **out, void **ws, int *width = nullptr, bool may_allocate = true, hipStream_t stream = nullptr) {
     std::lock_guard<std::mutex> lock(plan->prepared_mutex);
     smha_plan::Prepared *hit = nullptr;
     for (const smha_plan::CallShape &c : plan->calls)
         if (c.B == B && c.H == H && c.d == d && c.form == form) hit = c.prepared;
+    if (!hit && width && form != 2 && (!may_allocate || capturing(stream)))
+        for (const smha_plan::CallShape &c : plan->calls) {
+            if (c.B != B || c.H != H || c.d == d || row_head_size(c.d) != row_head_size(d)) continue;
+            const int f = block_form(plan, c.d, bf16);
+            if (c.form != (f == 2 ? 1 : f)) continue;  // (the second form serves no other head size)
+            hit = c.prepared;
+            *width = std::max(d, c.d);
+        }
     if (!hit) {
         if (!may_allocate) return SMHA_ERR_UNSUPPORTED;
         int lvl = grain_for(plan, B, H, d, form), alone = 0;
@@ -1712,27 +1735,6 @@ static smha_status_t prepared_for(const smha_plan *plan, int B, int H, int d, in
     *out = hit;
     *ws = hit->ws_bytes ? hit->ws[hit->next++ % smha_plan::kCallSlots] : nullptr;
     return SMHA_OK;
-}
-
-// Head sizes: any multiple of 8 up to 256.  The row kernel exists for 64, 128 and 256 columns, the block kernel for those of
-// block_head_size; a narrower head runs on the next of them, its missing columns read as zeros (which changes no score) and never stored.
-static bool head_size_ok(int d) { return d >= 8 && d <= 256 && d % 8 == 0; }
-static int row_head_size(int d) { return d <= 64 ? 64 : d <= 128 ? 128 : 256; }
-
-// The width a call runs at: its own, but what was prepared with another head size of the same 64, 128 or 256 columns serves it too
-// (at that width, with the same results), so that it neither allocates nor, in smha_forward_static, is refused.
-static int call_width(const smha_plan *plan, int B, int H, int d, bool bf16) {
-    const int D = block_head_size(d), wide = row_head_size(d);
-    if (D == wide) return D;
-    const int form = block_form(plan, D, bf16), wide_form = block_form(plan, wide, bf16) == 2 ? 1 : block_form(plan, wide, bf16);
-    std::lock_guard<std::mutex> lock(plan->prepared_mutex);
-    bool other = false;
-    for (const smha_plan::CallShape &c : plan->calls) {
-        if (c.B != B || c.H != H) continue;
-        if (c.d == D && c.form == form) return D;
-        other |= c.d == wide && c.form == wide_form;
-    }
-    return other ? wide : D;
 }
 
 static smha_status_t check_shape(const smha_plan *plan, int B, int H, int d) {
@@ -1759,7 +1761,7 @@ extern "C" smha_status_t smha_plan_prepare(const smha_plan_t *plan, int B, int H
         if (form == 2 && d != D) form = 1;  // (the second form has no narrower heads)
         const smha_plan::Prepared *pr = nullptr;
         void *ws = nullptr;
-        const smha_status_t s2 = prepared_for(plan, B, H, D, form, &pr, &ws);
+        const smha_status_t s2 = prepared_for(plan, B, H, D, form, bf16 != 0, &pr, &ws);
         if (s2 != SMHA_OK) return s2;
     }
     return SMHA_OK;
@@ -1848,25 +1850,29 @@ static smha_status_t forward_impl(const smha_plan_t *plan, const void *Q, const 
     hipStream_t stream = (hipStream_t)hip_stream;
     hipError_t e = hipSuccess;
     if (which == SMHA_KERNEL_BLOCK) {
-        const int D = call_width(plan, B, H, d, in_dtype == SMHA_BF16), asked = block_form(plan, D, in_dtype == SMHA_BF16);
+        const bool bf16 = in_dtype == SMHA_BF16;
+        int D = block_head_size(d);
+        const int asked = block_form(plan, D, bf16);
         const smha_plan::Prepared *pr = nullptr;
         void *ws = nullptr;
-        const smha_status_t st = prepared_for(plan, B, H, D, asked == 2 && d != D ? 1 : asked /* (the second form has no narrower heads) */, &pr, &ws, !static_ws);
+        const smha_status_t st = prepared_for(plan, B, H, D, asked == 2 && d != D ? 1 : asked /* (the second form has no narrower heads) */, bf16, &pr, &ws, &D, !static_ws, stream);
         if (st != SMHA_OK) return st;
         const int form = fp.form = pr->form, lvl = pr->lvl;
         const WorkLists &wl = plan->lists[lvl];
         fp.items = dv.items[lvl]; fp.item_off = dv.item_off[lvl]; fp.item_cnt = dv.item_cnt[lvl];
         fp.max_slots = wl.max_slots;
         fp.split_rows = dv.split_rows[lvl]; fp.split_off = dv.split_off[lvl]; fp.split_cnt = dv.split_cnt[lvl];
+        size_t counters_at = pr->counters_at;
         if (static_ws && pr->ws_bytes) {
             // the library's own array instead of a workspace of the plan; its counters are cleared by a
             // small kernel ahead of the launch (the array is shared by every such call on this GPU)
-            if (pr->ws_bytes > kStaticScratchBytes) return SMHA_ERR_UNSUPPORTED;
+            const size_t need = workspace_bytes(plan, lvl, form, B, H, D, &counters_at);
+            if (need > kStaticScratchBytes) return SMHA_ERR_UNSUPPORTED;
             ws = static_scratch_for(plan->device);
             if (!ws) return SMHA_ERR_HIP;
-            const size_t n = (pr->ws_bytes - pr->counters_at) / sizeof(uint32_t);
+            const size_t n = (need - counters_at) / sizeof(uint32_t);
             hipLaunchKernelGGL(smha_fill_zero, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream,
-                               (uint32_t *)((char *)ws + pr->counters_at), n);
+                               (uint32_t *)((char *)ws + counters_at), n);
             if (hipGetLastError() != hipSuccess) return SMHA_ERR_HIP;
         }
         fp.order_hdr = pr->order;
@@ -1892,7 +1898,7 @@ static smha_status_t forward_impl(const smha_plan_t *plan, const void *Q, const 
         fp.n_work = 8 * pr->longest;
         fp.per_xcd = pr->per_xcd;
         fp.scratch = (float *)ws;
-        fp.counters = ws ? (uint32_t *)((char *)ws + pr->counters_at) : nullptr;
+        fp.counters = ws ? (uint32_t *)((char *)ws + counters_at) : nullptr;
         fp.max_splits = form == 4 ? plan->wave.max_splits : wl.max_split_rows;
         auto launch = [&](auto width) {
             constexpr int W = decltype(width)::value;

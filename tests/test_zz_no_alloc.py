@@ -98,19 +98,77 @@ def test_a_plan_destroyed_on_another_thread_leaves_a_capture_alone(mode):
             assert torch.equal(out, eager)
 
 
-@pytest.mark.parametrize("prepared,d", [(64, 24), (128, 80), (256, 136)])
-def test_what_one_head_size_prepared_serves_the_narrower_ones_of_its_64_128_or_256_columns(prepared, d):
-    """... in the entry point that allocates nothing, at the wider width and with the same bits as at the call's own."""
+SPLIT_SPEC = W.MaskSpec(flags=W.WINDOW | W.GLOBAL, window_left=32, window_right=32, n_global=8)  # (1000 keys: whole lists; 6000: cut ones)
+
+
+def smha_width(d):
+    return next(w for w in (32, 64, 96, 128, 160, 256) if d <= w)
+
+
+def widths_of_kernels_run(torch, call):
+    """The kernel widths of the attention kernels that the call launches."""
+    import re
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    return [int(m[1]) for m in (re.search(r"smha_\w*fwd\w*<(\d+)", e.key) for e in prof.key_averages()) if m]
+
+
+@pytest.mark.parametrize("S", [1000, 6000])
+@pytest.mark.parametrize("prepared,d", [(64, 24), (128, 80), (256, 136), (24, 64), (80, 128), (136, 256)])
+def test_what_one_head_size_prepared_serves_the_others_of_its_64_128_or_256_columns(prepared, d, S):
+    """... where nothing may be allocated (smha_forward_static, a forward that is captured): at the wider width, both results
+    against the oracle; with nothing prepared, or another batch size, the entry point refuses."""
     import torch
     import paper_2506_06095_amd as smha
-    spec = W.MaskSpec(flags=W.WINDOW | W.GLOBAL, window_left=32, window_right=32, n_global=8)
+    B, H = 2, 4
+    g = torch.Generator(device="cuda").manual_seed(d)
+    q, k, v = (torch.randn(B, H, S, d, device="cuda", generator=g).half() for _ in range(3))
+    ref = oracle.masked_attention(*(np.ascontiguousarray(x[1:, 3:].cpu().numpy().view(np.uint16)) for x in (q, k, v)), "f16",
+                                  W.dense_mask(SPLIT_SPEC, B, H, S)[-1:, -1:])
+
+    def check(out):
+        got = out[1:, 3:].double().cpu().numpy()
+        assert np.abs(got - ref).max() <= 5e-3 and np.linalg.norm(got - ref) / np.linalg.norm(ref) <= 1e-3
+    for form in (0, 1):
+        with smha.Plan.from_desc(SPLIT_SPEC, B, H, S, head_dim=d, force=smha.SMHA_KERNEL_BLOCK, block_form=form) as plan:
+            assert S == 1000 or plan.info()["n_split_rows"] > 0
+            out = torch.full_like(q, float("nan"))
+            with pytest.raises(smha.SmhaError):
+                plan.forward_static(q, k, v, out)
+            plan.prepare(B, H, prepared)
+            with pytest.raises(smha.SmhaError):
+                plan.forward_static(q[:1], k[:1], v[:1], out[:1])
+            for _ in range(2):
+                plan.forward_static(q, k, v, out.fill_(float("nan")))
+                check(out)
+            assert widths_of_kernels_run(torch, lambda: plan.forward_static(q, k, v, out)) == [smha_width(max(prepared, d))]
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph):
+                plan.forward(q, k, v, out=out)
+            for _ in range(3):
+                out.fill_(float("nan"))
+                graph.replay()
+                check(out)
+            plan.prepare(B, H, d)
+            plan.forward_static(q, k, v, out.fill_(float("nan")))
+            check(out)
+            assert torch.equal(out, plan.forward(q, k, v))
+            assert widths_of_kernels_run(torch, lambda: plan.forward_static(q, k, v, out)) == [smha_width(d)]
+
+
+@pytest.mark.parametrize("before,d", [(64, 32), (128, 96), (256, 160), (96, 128)])
+def test_a_forward_runs_at_its_own_width_whatever_ran_before(before, d):
+    import torch
+    import paper_2506_06095_amd as smha
     g = torch.Generator(device="cuda").manual_seed(d)
     q, k, v = (torch.randn(2, 4, 1000, d, device="cuda", generator=g).half() for _ in range(3))
-    for form in (0, 1):
-        with smha.Plan.from_desc(spec, 2, 4, 1000, head_dim=d, force=smha.SMHA_KERNEL_BLOCK, block_form=form) as plan:
-            plan.prepare(2, 4, prepared)
-            wide = plan.forward_static(q, k, v, torch.full_like(q, float("nan")))
-            plan.prepare(2, 4, d)
-            own = plan.forward_static(q, k, v, torch.full_like(q, float("nan")))
-            torch.cuda.synchronize()
-            assert bool(torch.isfinite(own).all()) and torch.allclose(wide.float(), own.float(), rtol=2e-3, atol=2e-3)
+    x = torch.randn(2, 4, 1000, before, device="cuda", generator=g).half()
+    make = lambda: smha.Plan.from_desc(SPLIT_SPEC, 2, 4, 1000, head_dim=d, force=smha.SMHA_KERNEL_BLOCK)  # noqa: E731
+    with make() as plan, make() as other:
+        other.forward(x, x, x)
+        assert torch.equal(other.forward(q, k, v), plan.forward(q, k, v))
+        name = smha.smha_call_kernel_name(other.handle, 2, 4, d, smha.SMHA_F16)
+        assert name == smha.smha_call_kernel_name(plan.handle, 2, 4, d, smha.SMHA_F16)
+        assert widths_of_kernels_run(torch, lambda: other.forward(q, k, v)) == [d]

@@ -7,6 +7,8 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import subprocess
+import warnings
 from typing import Optional, Sequence
 
 import numpy as np
@@ -73,7 +75,7 @@ def _load():
     if _lib is not None:
         return _lib
     if not os.path.exists(_build.LIB):
-        _build.build_library(force=True)  # raises if hipcc is missing or the build fails
+        _build.build_library(force=True, extension=False)  # raises if hipcc is missing or the build fails
     lib = C.CDLL(_build.LIB)
     vp = C.c_void_p
     lib.smha_plan_from_dense.argtypes = [vp, C.c_int, C.c_int, C.c_int, C.c_int,
@@ -118,14 +120,19 @@ _native = None  # (forward of _smha_torch, address of smha_forward)
 
 
 def _load_native():
+    """The native way of Plan.forward, built if it is not there or of other sources; where that fails, one that takes no call."""
     global _native
     if _native is None:
         lib = _load()
-        if not os.path.exists(_build.EXT):
-            _build.build_extension()
         import torch  # noqa: F401  (the module uses its libraries)
-        from . import _smha_torch
-        _native = (_smha_torch.forward, C.cast(lib.smha_forward, C.c_void_p).value)
+        try:
+            if not _build.extension_current():
+                _build.build_extension()
+            from . import _smha_torch
+            _native = (_smha_torch.forward, C.cast(lib.smha_forward, C.c_void_p).value)
+        except (ImportError, OSError, subprocess.SubprocessError) as e:
+            warnings.warn(f"no native call path for Plan.forward, every call takes the slower one through ctypes: {e}", RuntimeWarning)
+            _native = (lambda *args: None, 0)
     return _native
 
 

@@ -1,6 +1,7 @@
 """Build libsmha.so (HIP, gfx950) with hipcc and the native call path for torch (_smha_torch.so) with g++, in-tree."""
 from __future__ import annotations
 
+import hashlib
 import os
 import subprocess
 import sys
@@ -12,8 +13,9 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsmha.so")
 EXT = os.path.join(HERE, "_smha_torch.so")
 EXT_SOURCE = os.path.join(CSRC, "torch_binding.cpp")
+ABI_HEADER = os.path.join(ROOT, "include", "smha.h")
 SOURCES = ["plan.cpp", "kernels.hip"]
-HEADERS = ["smha_internal.hpp", "device_pool.hpp", "block_fwd2.inc", "block_fwd16.inc", "wave_fwd.inc", os.path.join(ROOT, "include", "smha.h")]
+HEADERS = ["smha_internal.hpp", "device_pool.hpp", "block_fwd2.inc", "block_fwd16.inc", "wave_fwd.inc", ABI_HEADER]
 
 
 def hipcc() -> str:
@@ -34,15 +36,40 @@ def command(extra=()):
             *[os.path.join(CSRC, s) for s in SOURCES], "-o", LIB]
 
 
+def extension_stamp() -> str:
+    """What _smha_torch.so has to be built from and against: its sources (smha_forward's signature is compiled in), torch and Python."""
+    import torch
+    sources = hashlib.sha256()
+    for path in (EXT_SOURCE, ABI_HEADER):
+        with open(path, "rb") as f:
+            sources.update(f.read())
+    return f"smha-torch-binding:{sources.hexdigest()[:32]}:{torch.__version__}:{sys.implementation.cache_tag}:"
+
+
+def extension_current() -> bool:
+    """_smha_torch.so is there and holds that stamp (asked of the file: a module cannot be loaded twice)."""
+    if not os.path.exists(EXT):
+        return False
+    with open(EXT, "rb") as f:
+        return extension_stamp().encode() in f.read()
+
+
 def build_extension() -> str:
-    """_smha_torch.so against the installed torch's headers (torch has its libraries loaded when the module is imported)."""
+    """_smha_torch.so against the installed torch's headers (torch has its libraries loaded when the module is imported).  It takes its
+    place when it is whole: another process may be loading the old one, or building it too."""
     from torch.utils import cpp_extension
     import torch
-    subprocess.run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
-                    f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-                    *[f"-isystem{d}" for d in (*cpp_extension.include_paths(), "/opt/rocm/include")],
-                    "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), EXT_SOURCE, "-o", EXT,
-                    *[f"-L{d}" for d in cpp_extension.library_paths()], "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"], check=True)
+    part = f"{EXT}.{os.getpid()}"
+    try:
+        subprocess.run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
+                        f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DSMHA_STAMP="{extension_stamp()}"',
+                        *[f"-isystem{d}" for d in (*cpp_extension.include_paths(), "/opt/rocm/include")],
+                        "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), EXT_SOURCE, "-o", part,
+                        *[f"-L{d}" for d in cpp_extension.library_paths()], "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"], check=True)
+        os.replace(part, EXT)
+    finally:
+        if os.path.exists(part):
+            os.remove(part)
     return EXT
 
 
@@ -54,11 +81,11 @@ def stale() -> bool:
     return any(os.path.getmtime(d) > t for d in deps)
 
 
-def build_library(force: bool = True, verbose: bool = False) -> str:
+def build_library(force: bool = True, verbose: bool = False, extension: bool = True) -> str:
     if force or stale():
         cmd = command(("-Rpass-analysis=kernel-resource-usage",) if verbose else ())
         subprocess.run(cmd, check=True)
-    if force or not os.path.exists(EXT) or os.path.getmtime(EXT_SOURCE) > os.path.getmtime(EXT):
+    if extension and (force or not extension_current()):
         build_extension()
     return LIB
 

@@ -105,4 +105,8 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_smha_torch", nullptr, -1, methods
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__smha_torch() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__smha_torch() {
+    PyObject *m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "stamp", SMHA_STAMP) < 0) Py_CLEAR(m);  // what it was built from: build.py looks for it in the file
+    return m;
+}

@@ -86,7 +86,7 @@ FORMS = {"row": (1, 0), "block": (2, 0), "block_form1": (2, 1), "block_form3": (
 
 
 def runs_form(smha, plan, B, H, d, dtype, form):
-    """The block kernel's form that a plan was asked for is the one that runs (the third exists at 128 and 256 columns, and not for
+    """The block kernel's form that a plan was asked for is the one that runs (the third exists above 64 columns, and not for
     gathered tiles)."""
     name = smha.smha_call_kernel_name(plan.handle, B, H, d, smha.SMHA_F16 if dtype == "f16" else smha.SMHA_BF16, smha.SMHA_KERNEL_BLOCK)
     third = d > 64 and form == 3 and plan.info()["n_gathered"] == 0
@@ -1099,12 +1099,28 @@ def test_the_kernel_that_is_named_is_the_kernel_that_runs(torch_mod, smha):
     assert seen == ["smha_wave_fwd", "smha_wave_fwd", "smha_block_fwd", "smha_block_fwd16", "smha_row_fwd"]
 
 
+def launch_of(torch, call):
+    """Name, threads and grid of the one attention kernel that the call launches."""
+    import json
+    import tempfile
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    with tempfile.NamedTemporaryFile(suffix=".json") as f:
+        prof.export_chrome_trace(f.name)
+        with open(f.name) as trace:
+            (e,) = [e for e in json.load(trace)["traceEvents"] if "smha_" in e.get("name", "") and "grid" in e.get("args", {})]
+    return e["name"], e["args"]["block"], e["args"]["grid"]
+
+
 @pytest.mark.parametrize("mask", ["mixed", "cut", "gathered"])
 @pytest.mark.parametrize("d", [8, 24, 32, 72, 88, 96, 136, 152, 160])
 def test_kernel_widths_of_32_96_and_160_columns(torch_mod, smha, d, mask):
     """The smallest and largest head of each width whose rows are no power of two of 64-byte groups, in every form: full, partly
     filled and empty tiles, lists cut and merged, gathered tiles; rows that fill no tile; Q, K, V and O between guard columns
-    (NaN beside every row of the inputs, a pattern that stays beside every row of O)."""
+    (NaN beside every row of the inputs, a pattern that stays beside every row of O).  Left to the library, the first two masks take
+    the wave form, all lists of the first and some of the second shared by four waves."""
     torch, rng = torch_mod, np.random.default_rng(d)
     S = 601 if mask == "mixed" else 2100
     if mask == "mixed":
@@ -1126,8 +1142,12 @@ def test_kernel_widths_of_32_96_and_160_columns(torch_mod, smha, d, mask):
         q, k, v = (x[..., :d] for x in wide)
         for form in (0, 1, 3) if d > 64 else (0, 1):
             with smha.Plan.from_dense(m, head_dim=d, force=smha.SMHA_KERNEL_BLOCK, block_form=form) as plan:
-                if form:
+                if form or mask == "gathered":
                     runs_form(smha, plan, B, H, d, dtype, form)
+                else:
+                    name, _, (_, groups, _) = launch_of(torch, lambda: plan.forward(q, k, v))
+                    items = len(plan.export("wave_items")) // 8
+                    assert "smha_wave_fwd<" in name and (groups == items if mask == "mixed" else items / 4 < groups < items), (name, groups, items)
                 assert mask == "mixed" or plan.info()["n_split_rows" if mask == "cut" else "n_gathered"] > 0
                 for f32 in (False, True):
                     room = torch.full((B, H, S, d + 8), 7.0, device="cuda", dtype=torch.float32 if f32 else q.dtype)

@@ -133,6 +133,9 @@ def test_what_one_head_size_prepared_serves_the_others_of_its_64_128_or_256_colu
         assert np.abs(got - ref).max() <= 5e-3 and np.linalg.norm(got - ref) / np.linalg.norm(ref) <= 1e-3
     for form in (0, 1):
         with smha.Plan.from_desc(SPLIT_SPEC, B, H, S, head_dim=d, force=smha.SMHA_KERNEL_BLOCK, block_form=form) as plan:
+            if form == 0:
+                assert smha.smha_call_kernel_name(plan.handle, B, H, d, smha.SMHA_F16) == "smha_wave_fwd"
+                assert (plan.export("wave_items").reshape(-1, 8)[:, 3] >= 0).any() == (S == 6000)
             assert S == 1000 or plan.info()["n_split_rows"] > 0
             out = torch.full_like(q, float("nan"))
             with pytest.raises(smha.SmhaError):

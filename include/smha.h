@@ -286,8 +286,8 @@ smha_status_t smha_plan_prepare(const smha_plan_t *plan, int B, int H, int d);
 
 /* A work order of the block kernel's older forms for B x H heads (smha_plan_call_order gives the one that
  * a forward walks when B * H is no multiple of 8) when workgroups_per_xcd workgroups are
- * resident on each of the chip's 8 XCDs (smha_forward uses 4 per compute unit at 64 columns,
- * 2 at 128, 1 at 256): the plan's work items (the workgroup tiling of Algorithm 1's outer loop)
+ * resident on each of the chip's 8 XCDs (smha_forward uses for the first form 4 per compute unit at
+ * 32 and 64 columns, 3 at 96, 2 at 128 and, without gathered tiles, at 160, else 1; for the third 2, at 256 columns 1): the plan's work items (the workgroup tiling of Algorithm 1's outer loop)
  * differ in length, and each head's items go, longest first, to the compute unit with the least
  * work so far and there to the workgroup with the least (the last heads are dealt together).
  * For inspection and tests; runs on the host.

@@ -161,7 +161,8 @@ __device__ __forceinline__ u32x4 buf_load16(__amdgpu_buffer_rsrc_t r, int byte_o
 // (rows of 256 bytes or more: a row's chunks are permuted inside each aligned group of 16)
 // Rows of an odd number of 64-byte groups (32, 96 and 160 columns) spread by themselves: four consecutive rows start in
 // the four groups of a 256-byte window, so V needs no swizzle, and for K the chunks of each aligned group of four are permuted
-// by which of four such row quadruples the row is in.
+// by which of four such row quadruples the row is in.  (Bank conflicts per LDS cycle: first form at 96 columns 0.03, wave form 0.2 to 0.3
+// at 96, third form 0.33 at 160; at 64 and 128 columns 0.01 to 0.09.)
 template <int D> constexpr bool kOddRows = D % 64 == 32;
 template <int D> __device__ __forceinline__ int swz_k(int row) {
     if constexpr (kOddRows<D>) return (row >> 2) & 3;
@@ -1435,10 +1436,10 @@ using namespace smha;
 
 static bool strides_ok(const int64_t *s) { return !s || (s[0] % 8 == 0 && s[1] % 8 == 0 && s[2] % 8 == 0 && s[2] > 0); }
 
-// Which form of the block kernel runs a call: the plan's block_form option, else SMHA_BLOCK_FORM=1 or 2 in
-// the environment (read once), else the first form (on the workloads measured so far it is the faster
-// one).  Plans with gathered tiles, and bfloat16 at d = 128 (the second form's LDS does not hold two
-// probability operands per step there), run the first form whatever is asked for.
+// Which of the block kernel's three older forms a call runs (the wave form may take the place of the library's own choice): the one asked
+// for by the plan's block_form option or SMHA_BLOCK_FORM in the environment (read once), else library_form.  Plans with
+// gathered tiles run the first form whatever is asked for, as do bfloat16 at d = 128 where the second is (its LDS does not hold
+// two probability operands per step there) and widths at which the form that is asked for does not exist.
 static int form_asked(const smha_plan *plan) {
     static const int from_env = [] {
         const char *e = getenv("SMHA_BLOCK_FORM");
@@ -1449,7 +1450,7 @@ static int form_asked(const smha_plan *plan) {
 static int block_form(const smha_plan *plan, int d, bool bf16) {
     const int asked = form_asked(plan);
     if (plan->n_gathered > 0) return 1;
-    if (d > 128) return asked == 1 ? 1 : 3;  // 256 columns: eight waves of 16 rows are two waves per SIMD, four of 32 are one
+    if (d > 128) return asked == 1 ? 1 : 3;  // (256 columns: eight waves of 16 rows are two waves per SIMD, four of 32 are one)
     if (asked == 3) return d > 64 ? 3 : 1;  // eight waves of 16 rows: more than 64 columns
     if (asked != 0) return asked == 2 && (d == 64 || (d == 128 && !bf16)) ? 2 : 1;
     return library_form(d, plan->dense_long_lists, d == 96 && empty_sub_tiles(plan));
@@ -1477,8 +1478,8 @@ static hipError_t launch_block_out(const smha_plan *plan, FwdParams &fp, hipStre
             return hipGetLastError();
         }
     }
-    // the grid fills the chip once (two workgroups fit a CU at d = 128, four at d = 64: LDS and
-    // registers); the work order was made for exactly this many workgroups
+    // the grid fills the chip once (block_groups, block16_groups: LDS and registers); the work order was made
+    // for exactly this many workgroups
     const unsigned grid = 8u * (unsigned)fp.per_xcd;
     const bool split = fp.max_slots > 0;
     if constexpr (D > 64) {

@@ -100,7 +100,10 @@ constexpr int block_head_size(int d) { return d <= 32 ? 32 : d <= 64 ? 64 : d <=
 constexpr int block_width(int D) { return D == 256 ? 5 : D / 32 - 1; }
 // workgroups that fit a compute unit (LDS and registers): wave form, first form, third form
 constexpr int wave_groups(int D) { return D <= 64 ? 4 : D == 96 ? 3 : D <= 160 ? 2 : 1; }
-// (first form at 160 columns: two take the whole LDS, and there is no room for the key numbers of gathered tiles)
+// (first form at 160 columns: two take the whole LDS, and there is no room for the key numbers of gathered tiles.  With gathered tiles three
+// at 96 columns spill 12 to 21 registers with bfloat16 and next to none with float16, two spill none: 72 strided calls take, three against
+// two, 0.95 with float16 and 1.01 with bfloat16, where the chip is full 0.90 and 0.95 (8 x 12 x 3000 x 72 bf16 48.7 us, 54.0), where it is
+// filled once up to 1.13 (4 x 16 x 2048 x 96 bf16 36.7, 32.5).  At 128 columns they took 1.16 and 1.11 times as long.)
 constexpr int block_groups(int D, bool gathered) { return D <= 64 ? 4 : D == 96 ? 3 : D <= (gathered ? 128 : 160) ? 2 : 1; }
 constexpr int block16_groups(int D) { return D <= 160 ? 2 : 1; }
 // Which of the two older forms the library takes for plans without gathered tiles (those run the first).  At 96 columns the first

@@ -1041,6 +1041,8 @@ int build_wave_order(const smha_plan *plan, int alone, std::vector<int32_t> &tab
 // mean error 5 to 8 %.  At 32 columns the wave form was fitted with half of 460 calls like those of profiles/block_forms_partial.csv beside
 // the table's: mean error over the other half 6 % (11 % with the constants of 64 columns, scaled), the forms then chosen 0.973 in
 // the mean, 1.14 at most, and no call slower than at 64 columns (5 were, by up to 11 %; random 3 x 20 x 1000 x 32 29.0 us, now 23.0, 26.3 at 64).
+// At 256 columns `start`, `join` and `memory` were fitted again with 920 more calls, to what the choice gives away: 1.04 % instead of 1.56 (over either half,
+// fitted to the other, 1.0 and 1.1 instead of 1.4 and 1.7); `memory` had been so high that windows took the third form (1 x 20 x 676 x 192 13.7 us, wave form 11.6).
 struct WaveCost {
     double start, wave, step, held, part, bf16, chain, chain_full, power, uneven, part_all, join, memory;
 };
@@ -1050,7 +1052,7 @@ static const WaveCost kWaveCost[6] = {
     {3.99, 1.246, 0.595, 0.05, 0.191, 1.17, 0.567, 0.1278, 4.0, 0.09, -0.076, 1.877, 0.0683},       // 96
     {3.80, 1.5978, 0.7627, 0.05, 0.191, 1.17, 0.7266, 0.1638, 4.0, 0.09, -0.076, 1.877, 0.0700},    // 128
     {4.594, 2.067, 0.987, 0.05, 0.191, 1.17, 0.940, 0.2120, 4.0, 0.09, -0.076, 1.877, 0.1045},      // 160
-    {5.631, 4.5016, 1.4624, 0.63, 0.156, 1.17, 1.3585, 0.0, 4.0, 0.23, -0.041, 4.513, 0.2327}};     // 256
+    {5.188, 4.5016, 1.4624, 0.63, 0.156, 1.17, 1.3585, 0.0, 4.0, 0.23, -0.041, 4.449, 0.1824}};     // 256
 struct BlockCost {
     double start, unit, unit_act, unit_part, unit_sub, unit_lone, group, group_act, group_part, unit_bf16, group_bf16, gather, power, merge, memory;
 };
@@ -1181,7 +1183,7 @@ static TypeTimes block_time_us(const smha_plan *plan, int lvl, int form, int B, 
 // 64-blocks 1 x 2 x 2816 x 256 20.6 / 12.8); it loses where tiles are full and rows many (causal 16 x 12 x 4096 x 128:
 // 870 / 1176), because every K and V tile is loaded once per 32 rows.  It has to win by 4 %: of 1600
 // calls of the table that were drawn at random 16 then run the slower form by more than 2 % with one of the input types, and the mean
-// against the other forms is 0.640, 0.675, 0.687, 0.722, 0.659, 0.728 at 32, 64, 96, 128, 160 and 256 columns, where the better form for
+// against the other forms is 0.640, 0.675, 0.687, 0.722, 0.659, 0.725 at 32, 64, 96, 128, 160 and 256 columns, where the better form for
 // each call would give 0.639, 0.672, 0.684, 0.718, 0.653, 0.722.
 // The two input types are decided together (by the product of their ratios): one order and one set of workspaces serves both.
 bool wave_form_pays(const smha_plan *plan, int lvl, int form, int B, int H, int D, int &alone) {

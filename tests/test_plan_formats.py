@@ -773,6 +773,16 @@ def test_the_wave_form_is_not_taken_for_long_lists_on_two_workgroups_a_compute_u
         assert smha.smha_call_kernel_name(plan.handle, 3, 20, 32, smha.SMHA_F16) == "smha_block_fwd"
 
 
+@pytest.mark.parametrize("B,H,S,d,band,wave_us,third_us", [(1, 20, 676, 192, 30, 11.6, 13.7), (2, 8, 3840, 192, 23, 25.5, 28.1), (10, 2, 976, 256, 32, 12.6, 14.8),
+                                                           (3, 32, 1819, 256, 32, 86.4, 91.9)])
+def test_windows_at_256_columns_take_the_wave_form(B, H, S, d, band, wave_us, third_us):
+    """... which was the faster one: lists of three entries, and bytes that are most of the estimate."""
+    assert wave_us < 0.96 * third_us
+    spec = W.MaskSpec(flags=W.WINDOW, window_left=band, window_right=band)
+    with smha.Plan.from_desc(spec, B, H, S, head_dim=d, device_id=-2, force=smha.SMHA_KERNEL_BLOCK) as plan:
+        assert smha.smha_call_kernel_name(plan.handle, B, H, d, smha.SMHA_F16) == "smha_wave_fwd"
+
+
 def test_the_order_of_very_many_heads_takes_little_more_than_its_table():
     """2^24 heads of one item each: the table is 140 MB, and the peak while it is made and copied stays under three of them."""
     code = ("import resource, numpy as np, paper_2506_06095_amd as smha\n"

@@ -1038,16 +1038,17 @@ int build_wave_order(const smha_plan *plan, int alone, std::vector<int32_t> &tab
 // and the choice went wrong by that).  Mean error over 600 other calls of the table: 5 to 7 % (wave form), 5 % (the others).  At 96,
 // 160 and 256 columns: the wave form's constants of 128, 128 and 256 columns at first with three of their own (`start`, `memory`, and one
 // factor for `wave`, `step` and the chain's), the forms that the library takes there refitted (160 with gathered tiles: likewise scaled);
-// mean error 5 to 8 %.  At 32 columns the wave form was fitted with half of 460 calls like those of profiles/block_forms_partial.csv beside
-// the table's: mean error over the other half 6 % (11 % with the constants of 64 columns, scaled), the forms then chosen 0.973 in
-// the mean, 1.14 at most, and no call slower than at 64 columns (5 were, by up to 11 %; random 3 x 20 x 1000 x 32 29.0 us, now 23.0, 26.3 at 64).
+// mean error 5 to 8 %.  At 32 columns the wave form's constants were fitted to what the choice (and that of `alone`) gives away on 1257 calls, those of
+// profiles/block_forms_partial.csv and the like, drawn ones and the table's: 0.8 % instead of 2.2 with the constants of 64 columns, scaled, which had made lists of 16 to
+// 32 steps on one or two workgroups a compute unit 20 to 30 % too short (random 3 x 20 x 1000 x 32 29.0 us, 26.3 at 64 columns, now 23).  Over 340 calls that were not
+// used: 0.990 of the time before in the mean, 45 more than 2 % faster, 11 slower (1.10 at most), none slower than at 64 columns.
 // At 256 columns `start`, `join` and `memory` were fitted again with 920 more calls, to what the choice gives away: 1.04 % instead of 1.56 (over either half,
 // fitted to the other, 1.0 and 1.1 instead of 1.4 and 1.7); `memory` had been so high that windows took the third form (1 x 20 x 676 x 192 13.7 us, wave form 11.6).
 struct WaveCost {
     double start, wave, step, held, part, bf16, chain, chain_full, power, uneven, part_all, join, memory;
 };
 static const WaveCost kWaveCost[6] = {
-    {3.19, 0.3206, 0.2268, 0.22, 0.076, 1.20, 0.4398, 0.0, 3.4, 0.445, 0.1041, 1.946, 0.0888},      // 32 columns
+    {2.487, 0.3727, 0.2368, 0.218, 0.030, 1.20, 0.3972, 0.065, 3.515, 0.237, 0.1279, 1.292, 0.0678},  // 32 columns
     {3.07, 0.7028, 0.4019, 0.22, 0.076, 1.20, 0.4933, 0.2096, 3.4, 0.0, -0.003, 1.946, 0.0461},     // 64
     {3.99, 1.246, 0.595, 0.05, 0.191, 1.17, 0.567, 0.1278, 4.0, 0.09, -0.076, 1.877, 0.0683},       // 96
     {3.80, 1.5978, 0.7627, 0.05, 0.191, 1.17, 0.7266, 0.1638, 4.0, 0.09, -0.076, 1.877, 0.0700},    // 128
@@ -1182,8 +1183,8 @@ static TypeTimes block_time_us(const smha_plan *plan, int lvl, int form, int B, 
 // the wave form) and where a call has too few 128-row groups to fill the chip (causal 1 x 12 x 1024 x 64 15.2 / 8.5, per-head
 // 64-blocks 1 x 2 x 2816 x 256 20.6 / 12.8); it loses where tiles are full and rows many (causal 16 x 12 x 4096 x 128:
 // 870 / 1176), because every K and V tile is loaded once per 32 rows.  It has to win by 4 %: of 1600
-// calls of the table that were drawn at random 16 then run the slower form by more than 2 % with one of the input types, and the mean
-// against the other forms is 0.640, 0.675, 0.687, 0.722, 0.659, 0.725 at 32, 64, 96, 128, 160 and 256 columns, where the better form for
+// calls of the table that were drawn at random 15 then run the slower form by more than 2 % with one of the input types, and the mean
+// against the other forms is 0.639, 0.675, 0.687, 0.722, 0.659, 0.725 at 32, 64, 96, 128, 160 and 256 columns, where the better form for
 // each call would give 0.639, 0.672, 0.684, 0.718, 0.653, 0.722.
 // The two input types are decided together (by the product of their ratios): one order and one set of workspaces serves both.
 bool wave_form_pays(const smha_plan *plan, int lvl, int form, int B, int H, int D, int &alone) {

@@ -1707,14 +1707,18 @@ static smha_status_t prepared_for(const smha_plan *plan, int B, int H, int d, in
     smha_plan::Prepared *hit = nullptr;
     for (const smha_plan::CallShape &c : plan->calls)
         if (c.B == B && c.H == H && c.d == d && c.form == form) hit = c.prepared;
-    if (!hit && width && form != 2 && (!may_allocate || capturing(stream)))
+    if (!hit && width && form != 2) {
+        const smha_plan::CallShape *other = nullptr;
         for (const smha_plan::CallShape &c : plan->calls) {
             if (c.B != B || c.H != H || c.d == d || row_head_size(c.d) != row_head_size(d)) continue;
             const int f = block_form(plan, c.d, bf16);
-            if (c.form != (f == 2 ? 1 : f)) continue;  // (the second form serves no other head size)
-            hit = c.prepared;
-            *width = std::max(d, c.d);
+            if (c.form == (f == 2 ? 1 : f)) other = &c;  // (the second form serves no other head size)
         }
+        if (other && (!may_allocate || capturing(stream))) {
+            hit = other->prepared;
+            *width = std::max(d, other->d);
+        }
+    }
     if (!hit) {
         if (!may_allocate) return SMHA_ERR_UNSUPPORTED;
         int lvl = grain_for(plan, B, H, d, form), alone = 0;

@@ -767,7 +767,7 @@ def test_partly_filled_tiles_take_no_slower_form_than_before_their_width():
 @pytest.mark.parametrize("p", [0.05, 0.5, 0.9])
 def test_the_wave_form_is_not_taken_for_long_lists_on_two_workgroups_a_compute_unit(p):
     """3 x 20 heads of 32 columns, 1000 keys at random: 480 workgroups of four 32-entry lists took 29 us, the first form 23 (and 26 at 64
-    columns).  (The table's time of the wave form is that with lists shared by four waves, 22.6, which the estimates choose now.)"""
+    columns)."""
     m = (np.random.default_rng(1).random((1, 1, 1000, 1000)) < p).astype(np.uint8)
     with smha.Plan.from_dense(m, head_dim=32, device_id=-2, force=smha.SMHA_KERNEL_BLOCK) as plan:
         assert smha.smha_call_kernel_name(plan.handle, 3, 20, 32, smha.SMHA_F16) == "smha_block_fwd"

@@ -521,6 +521,7 @@ bool count_wave_lists(const smha_plan *p) {
     const int n_masks = p->Bm * p->Hm, n_groups = (p->S + 31) / 32, stride = 2 * ((n_groups + 1) / 2);
     int64_t at_most = 0;
     for (const MaskFormats &m : p->masks) at_most += 4 * (int64_t)m.kt_col.size();
+    wl.at_most = at_most;
     if (!p->has_block || p->opts.block_form != 0 || at_most > kMaxWaveEntries || n_groups > 16384 /* (a grid's y holds a mask's workgroups) */ ||
         p->h_kt_bitmap.size() * sizeof(uint64_t) >= ((size_t)1 << 31)) {
         wl.counted = true;
@@ -588,9 +589,7 @@ bool empty_sub_tiles(const smha_plan *p) {
     } catch (const std::bad_alloc &) {
         return false;
     }
-    int64_t tiles = 0;
-    for (const MaskFormats &m : p->masks) tiles += (int64_t)m.kt_col.size();
-    return (double)p->wave.n_ents < 0.75 * 4.0 * (double)tiles;
+    return (double)p->wave.n_ents < 0.75 * (double)p->wave.at_most;
 }
 
 void make_wave_lists(const smha_plan *p) {  // (count_wave_lists has said that they are possible)

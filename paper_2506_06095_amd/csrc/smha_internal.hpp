@@ -171,6 +171,7 @@ struct WaveLists {
     int max_splits = 0, max_slots = 0;
     int32_t of_length[kWaveWhole + 1] = {0};  // items by entries, over all masks
     int64_t n_ents = 0, part_ents = 0;        // entries, and those that have a bitmap
+    int64_t at_most = 0;                      // 32 x 32 sub-tiles of the 64 x 64 tiles, with and without keys
     int keys = 0;                             // in 32-key tiles that any entry names
     std::vector<int32_t> lengths;             // of each mask: its 32-row groups' entries, an even number of groups; and the
     std::vector<WaveTile> tiles;              // partly filled tiles of all masks: both until the lists are made
